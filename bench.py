@@ -117,7 +117,7 @@ def kernel_sources_digest():
     sources and of the launcher."""
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_1910_04940_amd", "csrc")
-    for name in ("kernel.hpp", "stream.hpp", "exec.hip", "schedule.hpp"):
+    for name in ("kernel.hpp", "fold.hpp", "fold_plan.hpp", "exec.hip", "schedule.hpp"):
         with open(os.path.join(csrc, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
@@ -405,7 +405,7 @@ def main():
                                "node": "per-node: one pass per fan-in and per fan-out",
                                "tree": "staged minimum: every rank buffer read once and written once, 8k B/elt "
                                        "(broadcast: the root read once, the others written once, 4k)"}[args.fusion],
-                "kernel": "blink_stream / blink_consume", "avg_kernel_ms": avg_kernel_ms,
+                "kernel": "blink_fold / blink_consume", "avg_kernel_ms": avg_kernel_ms,
                 "median_kernel_ms": sorted(kernel_ms)[len(kernel_ms) // 2],
                 "min_kernel_ms": min(kernel_ms)}
     if traffic is not None:   # the counters' bytes over this run's kernel time

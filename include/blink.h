@@ -3,7 +3,7 @@
  *
  * The k "ranks" of a collective are k separate device (HBM) buffers on the
  * current HIP device.  A collective is prepared in two host-side steps and then
- * executed by one persistent gfx950 kernel:
+ * executed by one gfx950 kernel launch:
  *
  *   blink_pack_trees     topology graph -> weighted spanning trees
  *                        (paper sections 3.1, 3.2, 3.2.1, 3.5)
@@ -263,11 +263,12 @@ blink_status_t blink_schedule_get_stages(const blink_schedule_t* s, blink_stage_
  * longest one).  Wavefronts take tickets in ascending order.  Where the order
  * is free (no stage waits for another) the tickets walk tile by tile across the
  * trees (section 4.2.2: trees sharing the machine take turns) unless a stage
- * reads more than 8 ranks (the library may also serve a schedule chunk by chunk
- * where it measured that to be faster, see blink_schedule_set_kernel), calls may
- * go through this list in alternating
- * directions (blink_schedule_set_sweep), and for rank buffers that all start the
- * same distance past a 1 KiB boundary the blocks are counted from that boundary.
+ * reads more than 8 ranks.  There the list states the turns, not the very tiles: the
+ * library may also serve such a schedule in another order where it measured that to
+ * be faster (blink_schedule_set_kernel), in alternating directions
+ * (blink_schedule_set_sweep), it pays no heed to chunk boundaries inside a tree's
+ * share, and tiles start on 1 KiB boundaries of the rank buffers where all of these
+ * start the same distance past one.
  * *n_tickets receives the count; stage and tile (host, caller-allocated, that
  * many entries) may both be null to ask for the count. */
 blink_status_t blink_schedule_get_tickets(const blink_schedule_t* s, uint32_t tile_elems, uint64_t* n_tickets,
@@ -350,23 +351,26 @@ blink_status_t blink_gather(void* const* bufs, int k, size_t n_elems, blink_dtyp
 blink_status_t blink_allreduce_noalloc(void* const* bufs, int k, size_t n_elems, blink_dtype_t dtype,
                                        blink_schedule_t* s, void* stream);
 
-/* Launch shape override for tuning: waves per compute unit (0 = automatic) and
- * elements per tile, the unit of work a wave draws at a time (0 = automatic;
- * else a power of two in [256, 65536]).  Changing the tile size waits for the
- * device and restarts the schedule's progress counters.  Applies to later
+/* Launch shape override for tuning: workgroups per compute unit (0 = automatic;
+ * a workgroup is one wavefront where stages wait for one another, four where they do
+ * not) and elements per tile, the unit of work a workgroup draws at a time (0 =
+ * automatic; else a power of two in [256, 65536]).  Changing the tile size waits for
+ * the device and restarts the schedule's progress counters.  Applies to later
  * calls on this schedule. */
 blink_status_t blink_schedule_set_launch(blink_schedule_t* s, int wg_per_cu, int tile_elems);
 /* A schedule whose stages do not wait for one another (whole-tree fusion) can
  * be served in up to three ways at streaming sizes; they give the same bits.
- * 1 = the ticket-drawing kernel with loads staged through registers; 2 = the
- * streaming kernel with loads straight into LDS (sums only, stages within its
- * limits); 3 = the ticket-drawing kernel with the trees taking turns chunk by
+ * 1 = tile by tile across the trees (chunk by chunk where a stage reads more than 8
+ * ranks); 2 = one front through the payload, results written past the GPU's
+ * memory-side cache where they do not fit it (sums only, stages whose partial sums
+ * need at most four accumulators); 3 = the trees taking turns chunk by
  * chunk (section 4.2.2 at the paper's own granularity) instead of tile by tile
  * (several trees only).  kernel: 0 = automatic: the first calls of at least
  * 64 MiB of traffic go round the ways the schedule has, four times each (eight
  * or twelve calls), timed with events on the caller's stream; the call after
- * them waits for them, and the fastest way serves from then on
- * (blink_allreduce_noalloc takes no part in the timing and uses way 1);
+ * them waits for them, and the fastest way serves from then on, whatever the operator
+ * (blink_allreduce_noalloc takes no part in the timing and uses way 1; so do payloads
+ * of a few tiles per compute unit);
  * 1, 2, 3 = that way, or way 1 where the schedule does not have it.
  * blink_schedule_last_kernel: the way the latest call ran (0 before the first
  * call). */
@@ -376,7 +380,8 @@ int blink_schedule_last_kernel(const blink_schedule_t* s);
  * waits for another (whole-tree fusion).  alternate = 1 (the default): the
  * second, fourth, ... call on such a schedule goes through the tiles backwards
  * and results are written with a policy that lets them stay in the GPU's
- * 256 MiB memory-side cache, so a call on the buffers of the call before it
+ * 256 MiB memory-side cache (way 2 of blink_schedule_set_kernel: only where they fit
+ * it), so a call on the buffers of the call before it
  * (training iterations without much else in between, benchmark loops) starts
  * on data that is still there.  alternate = 0: every call goes forwards and
  * streams its stores past the cache.  Same bits either way; schedules with

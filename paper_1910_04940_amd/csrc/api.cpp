@@ -319,13 +319,7 @@ int blink_schedule_last_kernel(const blink_schedule_t* s) { return s ? s->last_k
 
 blink_status_t blink_schedule_set_sweep(blink_schedule_t* s, int alternate) {
     if (!s || (alternate != 0 && alternate != 1)) return BLINK_EINVAL;
-    if (s->sweep_alternates != (alternate == 1)) {
-        s->sweep_alternates = alternate == 1;
-        // the cache policy, hence the kernel instantiation, follows the mode;
-        // tile size and counters do not
-        s->plan.made = false;
-        for (auto& per_dtype : s->occupancy) per_dtype[0] = per_dtype[1] = 0;
-    }
+    s->sweep_alternates = alternate == 1;   // order and cache policy follow it, call by call
     return BLINK_OK;
 }
 

@@ -1,7 +1,7 @@
-// The launcher of the persistent kernel (see kernel.hpp): the device block of a
-// schedule (status record, progress counters, tables), the launch plan (tile
-// size, kernel flavour), the launch and its bookkeeping.
-#include "stream.hpp"
+// The launcher of the two kernels (kernel.hpp: stages that wait for one another;
+// fold.hpp: the others): the device block of a schedule (status record, progress
+// counters, tables), the launch plan, the launch and its bookkeeping.
+#include "fold.hpp"
 
 #include <atomic>
 #include <mutex>
@@ -54,9 +54,9 @@ void drop_trial_events(blink_schedule* h);  // below, with the choice among the 
         }                                                                                 \
     } while (0)
 
-KernelFn pick_kernel(blink_dtype_t dtype, int flavour, bool many_waves, bool direct) {
-    if (dtype == BLINK_FP32) return many_waves ? kernel_f32_many(flavour) : kernel_f32_stream(flavour, direct);
-    return many_waves ? kernel_i32_many(flavour) : kernel_i32_stream(flavour, direct);
+KernelFn pick_kernel(blink_dtype_t dtype, bool many_waves) {
+    if (dtype == BLINK_FP32) return many_waves ? kernel_f32_many() : kernel_f32_stream();
+    return many_waves ? kernel_i32_many() : kernel_i32_stream();
 }
 
 size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -70,38 +70,65 @@ BlockLayout layout_of(const Schedule& s) {
     l.tmpl = round_up(l.counters_end, 256);
     l.inst = round_up(l.tmpl + s.tmpl.size() * sizeof(StageTmpl), 256);
     l.bytes = round_up(l.inst + s.inst.size() * sizeof(StageInst), 256);
+    l.words = l.done;   // a flow has an instance at least, hence kLine bytes
+    l.levels = l.words + s.inst.size() * kFlowWords * sizeof(uint32_t);
+    static_assert(kLine >= kFlowWords * sizeof(uint32_t) + sizeof(FoldLevel), "the tables fit the space of the counters");
     return l;
 }
 
-// Fill a block that lives at `block` on the current device: zero the status
-// record and the counters, copy the tables.  Synchronous.
-blink_status_t fill_block(const Schedule& s, const BlockLayout& l, char* block) {
-    BLINK_HIP(hipMemset(block, 0, l.counters_end));
-    BLINK_HIP(hipMemcpy(block + l.tmpl, s.tmpl.data(), s.tmpl.size() * sizeof(StageTmpl), hipMemcpyHostToDevice));
-    BLINK_HIP(hipMemcpy(block + l.inst, s.inst.data(), s.inst.size() * sizeof(StageInst), hipMemcpyHostToDevice));
-    BLINK_HIP(hipDeviceSynchronize());
+// Bytes at the head of a block that are zero when a schedule is new.
+size_t cleared_bytes(const LaunchPlan& pl, const BlockLayout& l) { return pl.fold ? l.done : l.counters_end; }
+
+// Copy a schedule's tables into a block on the current device.  Synchronous.
+blink_status_t copy_tables(const blink_schedule& h, const BlockLayout& l, char* block) {
+    const LaunchPlan& pl = h.plan;
+    const Schedule& s = h.s;
+    if (!pl.fold) {
+        BLINK_HIP(hipMemcpy(block + l.tmpl, s.tmpl.data(), s.tmpl.size() * sizeof(StageTmpl), hipMemcpyHostToDevice));
+        BLINK_HIP(hipMemcpy(block + l.inst, s.inst.data(), s.inst.size() * sizeof(StageInst), hipMemcpyHostToDevice));
+    } else if (!pl.tables_inline) {
+        std::vector<uint32_t> words(kFlowWords * pl.flows.size());
+        fold_words(pl.flows, static_cast<uint32_t>(pl.flows.size()), words.data());
+        BLINK_HIP(hipMemcpy(block + l.words, words.data(), words.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
+        BLINK_HIP(hipMemcpy(block + l.levels, pl.levels.data(), pl.levels.size() * sizeof(FoldLevel), hipMemcpyHostToDevice));
+    }
     return BLINK_OK;
 }
 
-// The schedule's own block: one allocation, made at the first call on a device.
-// Nothing is left behind when a step fails.
-blink_status_t upload(blink_schedule* h) {
+// A schedule belongs to the device of its first call.
+blink_status_t bind_device(blink_schedule* h) {
     int dev = -1;
     BLINK_HIP(hipGetDevice(&dev));
-    if (h->device == dev) return BLINK_OK;
-    if (h->device >= 0) return BLINK_EMISMATCH;  // the block lives on another device
-    const BlockLayout l = layout_of(h->s);
-    void* block = nullptr;
-    BLINK_HIP(hipMalloc(&block, l.bytes));
-    const blink_status_t st = fill_block(h->s, l, static_cast<char*>(block));
+    if (h->device >= 0 && h->device != dev) return BLINK_EMISMATCH;
+    h->device = dev;
+    return BLINK_OK;
+}
+
+// The schedule's own block: one allocation, made at the first call that needs it,
+// zeroed and filled synchronously.  Nothing is left behind when a step fails.
+blink_status_t upload(blink_schedule* h, const BlockLayout& l) {
+    if (h->d_block && !h->tables_stale) return BLINK_OK;
+    void* block = h->d_block;
+    if (!block) {
+        BLINK_HIP(hipMalloc(&block, l.bytes));
+        hipError_t zeroed = hipMemset(block, 0, cleared_bytes(h->plan, l));
+        if (zeroed == hipSuccess) zeroed = hipDeviceSynchronize();
+        if (zeroed != hipSuccess) {
+            (void)hipFree(block);
+            BLINK_HIP(zeroed);
+        }
+    }
+    const blink_status_t st = copy_tables(*h, l, static_cast<char*>(block));
     if (st != BLINK_OK) {
-        (void)hipFree(block);
+        if (!h->d_block) (void)hipFree(block);
         return st;
     }
-    h->d_block = block;
-    h->device = dev;
-    h->epoch = 0;
-    for (uint64_t& b : h->ticket_base) b = 0;
+    if (!h->d_block) {
+        h->d_block = block;
+        h->epoch = 0;
+        for (uint64_t& b : h->ticket_base) b = 0;
+    }
+    h->tables_stale = false;
     return BLINK_OK;
 }
 
@@ -138,8 +165,7 @@ blink_status_t claim_static_block(blink_schedule* h, const BlockLayout& l, hipSt
         }
         sb.owner = 0;
         BLINK_HIP(hipStreamSynchronize(stream));
-        BLINK_HIP(hipMemcpy(sb.ptr + l.tmpl, h->s.tmpl.data(), h->s.tmpl.size() * sizeof(StageTmpl), hipMemcpyHostToDevice));
-        BLINK_HIP(hipMemcpy(sb.ptr + l.inst, h->s.inst.data(), h->s.inst.size() * sizeof(StageInst), hipMemcpyHostToDevice));
+        if (const blink_status_t st = copy_tables(*h, l, sb.ptr)) return st;
         sb.owner = h->id;
     }
     h->last_static_device = dev;
@@ -147,28 +173,71 @@ blink_status_t claim_static_block(blink_schedule* h, const BlockLayout& l, hipSt
     return BLINK_OK;
 }
 
-// Tickets of a schedule whose tile grid is moved down by grid_shift elements.
-void count_tickets(blink_schedule* h, uint32_t grid_shift) {
+// The plan of a schedule whose stages wait for one another.  Tickets move about
+// kTicketBytesHandOver bytes.  A payload too small to give the machine 16 such
+// tickets per CU is latency-bound instead ("wide"): then all the waves that fit
+// are used and the tile shrinks until a time slot, the part of the work that can
+// run at a time, has about 64 tiles; waves beyond what a slot can use do nothing
+// but poll.
+void plan_hand_over(blink_schedule* h) {
     LaunchPlan& pl = h->plan;
-    pl.n_items = ticket_count(h->s, ticket_group(h->s), pl.tile_shift, grid_shift, &pl.tiles_per_chunk);
-    pl.n_items_turns = ticket_count(h->s, 1, pl.tile_shift, grid_shift, &pl.tiles_per_chunk);
-    pl.grid_shift = grid_shift;
+    const Schedule& s = h->s;
+    uint64_t work = 0;  // elements x stages
+    for (const StageInst& in : s.inst) work += in.len;
+    const uint64_t bytes_per_elem = std::max<uint64_t>(1, s.traffic_bytes / std::max<uint64_t>(1, work));
+    // the power of two nearest (in ratio) to ticket bytes / bytes_per_elem
+    const uint64_t ticket_bytes = kTicketBytesHandOver;
+    unsigned tile = kMinTile;
+    while (tile < kMaxTile && 2ull * tile * tile * bytes_per_elem * bytes_per_elem < ticket_bytes * ticket_bytes)
+        tile *= 2;
+    pl.wide = work / tile < 16ull * h->n_cu;
+    if (pl.wide)
+        while (tile > kMinTile && work / s.n_slots / tile < 64) tile /= 2;
+    if (h->tile_override) tile = h->tile_override;
+    pl.tile_elems = tile;
+    pl.tile_shift = 0;
+    while ((1u << pl.tile_shift) < tile) ++pl.tile_shift;
+    pl.n_items = ticket_count(s, 1, pl.tile_shift, 0, &pl.tiles_per_chunk);
 }
 
-// Tile size, kernel flavour and ticket count of a schedule on this device.
-//
-// The tile is large enough that a ticket moves about kTicketBytes.  A payload
-// too small to give a streaming grid 16 such tickets per CU is latency-bound
-// instead ("wide"): then all the waves that fit are used and the tile shrinks
-// (see below).  (Measured on 8 ranks, 4 trees, when the threshold was set, with
-// one wave per SIMD: at 11 tickets per CU the wide launch took 52 us and the
-// streaming one 72, at 16 they tied at 79, at 18 it was 157 against 130.  With
-// two waves per SIMD the wide launch wins by more below the threshold and still
-// loses above it: 10 M elements per rank 132 us against 121.)
-blink_status_t make_plan(blink_schedule* h, blink_dtype_t dtype) {
+// The plan of a schedule without dependencies.  A ticket is one sub-tile of the
+// kernel, or as many as make it move 96 KiB: the one ticket counter then has to
+// serve about 65 draws per microsecond at most.
+// A payload of at most five tiles per CU gets a workgroup for every tile: they are
+// all resident at once or nearly so, and no ticket has to be drawn (probe, 8 ranks,
+// workgroup per tile against 224 that draw: 2 MiB per rank 5.1 / 7.2 us, 4 MiB 9.6 /
+// 10.8, 7 MiB (3.5 tiles per CU) 14.4 / 16.2, 10.4 MiB (5.2) 25 / 25, 16 MiB 51 / 47).
+constexpr unsigned kFoldTicketBytes = 96 * 1024;
+constexpr unsigned kFoldSmallTilesPerCu = 5;
+constexpr unsigned kFoldHalfTilesPerCu = 2;   // up to here half tiles are faster (see fold_columns)
+
+void plan_fold(blink_schedule* h) {
+    LaunchPlan& pl = h->plan;
+    const Schedule& s = h->s;
+    pl.n_load = s.tmpl[s.inst[0].tmpl].n_load;
+    uint32_t n_store = s.tmpl[s.inst[0].tmpl].n_store;
+    pl.all = pl.n_load > 1 && n_store == pl.n_load;
+    const int n = static_cast<int>(pl.n_load);
+    const unsigned sub = fold_sub_elems(n, pl.all, false);
+    unsigned tile = sub;
+    while (tile * 4 * (pl.n_load + n_store) < kFoldTicketBytes) tile += sub;
+    uint64_t tiles = 0;
+    for (const FoldFlow& f : pl.flows) tiles += (f.len + sub - 1) / sub;
+    const uint64_t cus = static_cast<uint64_t>(h->n_cu);
+    pl.small = tiles <= kFoldSmallTilesPerCu * cus;
+    // a tile per flow more than that: shares need not be whole tiles
+    pl.half = tiles <= kFoldHalfTilesPerCu * cus + pl.flows.size() && fold_has_half(n, pl.all);
+    if (pl.small) tile = fold_sub_elems(n, pl.all, pl.half);
+    if (h->tile_override) tile = h->tile_override;
+    pl.tile_elems = tile;
+    pl.tables_inline = pl.flows.size() <= kInlineFlows;
+    pl.grid_shift = 0;
+    pl.n_items = fold_levels(pl.flows, tile, 0, !pl.tables_inline, &pl.levels);
+}
+
+blink_status_t make_plan(blink_schedule* h) {
     LaunchPlan& pl = h->plan;
     if (pl.made) return BLINK_OK;
-    const Schedule& s = h->s;
     if (h->n_cu == 0) {
         int dev = -1, n_cu = 0;
         BLINK_HIP(hipGetDevice(&dev));
@@ -176,89 +245,12 @@ blink_status_t make_plan(blink_schedule* h, blink_dtype_t dtype) {
         if (n_cu < 1) return BLINK_EHIP;
         h->n_cu = n_cu;
     }
-    uint64_t work = 0;  // elements x stages
-    for (const StageInst& in : s.inst) work += in.len;
-    const uint64_t bytes_per_elem = std::max<uint64_t>(1, s.traffic_bytes / std::max<uint64_t>(1, work));
-    // the power of two nearest (in ratio) to ticket bytes / bytes_per_elem
-    const uint64_t ticket_bytes = s.has_deps ? kTicketBytesHandOver : kTicketBytes;
-    unsigned tile = kMinTile;
-    while (tile < kMaxTile && 2ull * tile * tile * bytes_per_elem * bytes_per_elem < ticket_bytes * ticket_bytes)
-        tile *= 2;
-    pl.wide = work / tile < 16ull * h->n_cu;
-
-    const uint64_t write_bytes = s.traffic_bytes - s.read_bytes;
-    pl.read_heavy = s.read_bytes >= 2 * write_bytes;
-    const bool write_heavy = write_bytes >= 2 * s.read_bytes;
-    // Rank buffers that together fit the memory-side cache (256 MiB) are written
-    // without the streaming hint: whoever reads the result next (here: the next
-    // call) finds it there (8 x 16 MiB: 62 -> 45 us per call).  That is the
-    // read-heavy policy.  Larger buffers get it too where calls alternate their
-    // direction: a call then starts on the last 256 MiB that the call before it
-    // wrote (standalone probe, same kernel structure, repeated in place: 3 ranks x
-    // 128 MiB 0.75 -> 0.83 of the HBM peak, 8 x 64 MiB 0.72 -> 0.81, 8 x 256 MiB
-    // 0.774 -> 0.787; without the alternation the two policies tie).
-    const bool fits_cache = static_cast<uint64_t>(s.k) * s.n * 4 <= kMemorySideCacheBytes;
-    pl.flavour = s.has_deps   ? kHandOver
-                 : write_heavy ? kWriteHeavy
-                 : (pl.read_heavy || fits_cache || h->sweep_alternates) ? kReadHeavy
-                                                                        : kBalanced;
-    if (pl.wide) {
-        int& occ = h->occupancy[dtype == BLINK_FP32][0];
-        if (occ == 0) {
-            BLINK_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, pick_kernel(dtype, pl.flavour, true, false), kLanes, 0));
-            if (occ < 1) {
-                occ = 0;
-                return BLINK_EHIP;
-            }
-        }
-        // Where stages wait for one another only one time slot's worth of the
-        // work can run at a time: the tile shrinks until a slot has about 64
-        // tiles, not until half the machine has one (waves beyond what a slot
-        // can use do nothing but poll: 4 ranks x 64 Ki elements per edge,
-        // 42 -> see the measurements).
-        if (s.has_deps)
-            while (tile > kMinTile && work / s.n_slots / tile < 64) tile /= 2;
-        else {
-            // Without dependencies the tickets of such a payload are dealt out in
-            // rounds over the waves that fit (drawn, so many small ones would queue
-            // at the counter; see execute), and the call lasts as long as the wave
-            // with most of them: a tile size costs its rounds times the tile plus
-            // what a ticket costs besides its elements (about 2.5 us of latencies,
-            // the time in which a wave among a thousand moves 15 KB).
-            // Measured, 8 ranks x 4 trees on 1,024 waves, 2,048 -> 1,024-element
-            // tiles: 2.7 M elements per rank (1.3 -> 2.6 tickets per wave) 43.8 ->
-            // 38.4 us, 4.2 M (2.0 -> 4.0) 59.7 -> 52.7 us, but 3.2 M (1.5 -> 3.05)
-            // 42.9 -> 43.3 us: the last round counts whole.
-            const uint64_t waves = static_cast<uint64_t>(occ) * h->n_cu;
-            unsigned best = tile;
-            uint64_t best_cost = ~0ull;
-            for (unsigned cand = tile; cand >= kMinTile; cand /= 2) {
-                unsigned shift = 0;
-                while ((1u << shift) < cand) ++shift;
-                uint32_t most = 0;
-                const uint64_t tickets = ticket_count(s, ticket_group(s), shift, 0, &most);
-                if (tickets / std::min(waves, tickets) > 4) break;  // these would be drawn
-                const uint64_t rounds = (tickets + waves - 1) / waves;
-                const uint64_t cost = rounds * (cand + 15360 / bytes_per_elem);
-                if (cost < best_cost) {
-                    best = cand;
-                    best_cost = cost;
-                }
-            }
-            tile = best;
-        }
-    }
-    // The streaming kernel (stream.hpp) takes schedules without dependencies all
-    // of whose stages have a stack program within its limits.
-    pl.direct = !pl.wide && !s.has_deps;
-    for (const StageTmpl& st : s.tmpl)
-        if (st.seq_depth < 1 || st.seq_depth > stream_stack_limit(st.n_load)) pl.direct = false;
-    if (h->tile_override) tile = h->tile_override;
-    pl.tile_elems = tile;
-    pl.tile_shift = 0;
-    while ((1u << pl.tile_shift) < tile) ++pl.tile_shift;
+    pl.fold = fold_flows(h->s, &pl.flows);
+    if (pl.fold)
+        plan_fold(h);
+    else
+        plan_hand_over(h);
     pl.made = true;
-    count_tickets(h, 0);
     return BLINK_OK;
 }
 
@@ -271,14 +263,18 @@ blink_status_t make_plan(blink_schedule* h, blink_dtype_t dtype) {
 blink_status_t reset_progress(blink_schedule* h) {
     h->epoch = 0;
     for (uint64_t& b : h->ticket_base) b = 0;
+    const size_t cleared = cleared_bytes(h->plan, layout_of(h->s));
     h->plan = LaunchPlan();
-    for (auto& per_dtype : h->occupancy) per_dtype[0] = per_dtype[1] = 0;
+    h->tables_stale = true;       // the next plan may have others
+    h->id = next_schedule_id();   // in a static block, too
+    h->occupancy[0] = h->occupancy[1] = 0;
     drop_trial_events(h);
     h->picked = 0;
     h->trial_calls = 0;
     if (h->device < 0) return BLINK_OK;
     BLINK_HIP(hipDeviceSynchronize());
-    BLINK_HIP(hipMemset(h->d_block, 0, layout_of(h->s).counters_end));
+    if (!h->d_block) return BLINK_OK;
+    BLINK_HIP(hipMemset(h->d_block, 0, cleared));
     BLINK_HIP(hipDeviceSynchronize());
     return BLINK_OK;
 }
@@ -299,6 +295,7 @@ blink_status_t read_status(blink_schedule* h, blink_progress_t* out) {
     }
     unsigned long long rec[kStatusWords] = {};
     BLINK_HIP(hipDeviceSynchronize());
+    if (!block || h->plan.fold) return BLINK_OK;  // no stage waits for another: nothing can have gone wrong
     BLINK_HIP(hipMemcpy(rec, block, sizeof rec, hipMemcpyDeviceToHost));
     out->state = static_cast<int32_t>(rec[kStatusState]);
     if (rec[kStatusState] == 0) return BLINK_OK;
@@ -310,20 +307,21 @@ blink_status_t read_status(blink_schedule* h, blink_progress_t* out) {
     return BLINK_ESTUCK;
 }
 
-// Picking how a schedule is served.  A schedule without dependencies at
-// streaming size can run in up to three ways: on blink_consume (1), on
-// blink_stream where the operator is the sum and the stages fit it (2), and,
-// with several trees, on blink_consume with the trees taking turns chunk by
-// chunk instead of tile by tile (3).  Which is fastest depends on where the
-// buffers lie in HBM and how far apart the trees' shares are, in ways addresses
-// do not reveal: 1 wins on most placements and by far where the shares are a
-// power of two apart (8 x 256 MiB: 0.79 of the HBM peak against 0.73 for 3),
-// 2 is steadier where rank buffers are badly placed, 3 where the shares are
-// (8 x 117 MiB: 0.66 for 1, 0.73 for 3; sixteen gradient buckets of 64 KiB to
-// 400 MiB: 0.665 -> 0.69 overall).  So the first calls on such a schedule go
-// round the candidates, kTrialSamples times each, each call timed with a pair
-// of events on the caller's stream; the next call waits for the last of them
-// (the one time a call waits for the device, besides a schedule's first) and
+// Picking the way a schedule without dependencies is served at streaming size: the
+// order in which the fold kernel goes through the payload, and with it whether
+// results stream past the memory-side cache.
+//   1  tile by tile across the trees (section 4.2.2; chunk by chunk where a stage
+//      reads more than 8 ranks: 16 x 16 streams at a time are too many)
+//   2  one front through the payload, one tree's share after the other
+//   3  chunk by chunk across the trees (several trees, at most 8 ranks)
+// Which is fastest depends on where the buffers lie in HBM and how far apart the
+// trees' shares are, in ways addresses do not reveal.  With the standalone probe
+// (8 ranks, 4 trees, buffers in allocations of their own, three sets in turn; us for
+// ways 1 / 2): 64 MiB per rank 182 / 163, 114 MiB 324 / 294, 400 MiB 1119 / 1042, but
+// 256 MiB, where the shares are a power of two apart, 658 / 691.  So the first calls on
+// such a schedule go round the candidates, kTrialSamples times each, each call timed
+// with a pair of events on the caller's stream; the next call waits for the last of
+// them (the one time a call waits for the device, besides a schedule's first) and
 // the candidate with the smallest minimum serves the rest.  All give the same
 // bits.
 constexpr int kTrialSamples = 4;
@@ -339,20 +337,21 @@ void drop_trial_events(blink_schedule* h) {
 }
 
 // How this call is served (1, 2 or 3, see above); *timed: index of the event
-// pair to put around it, or -1.  streams: the schedule can run on blink_stream;
-// can_stream: this call can (its operator is the sum); can_turns: way 3 exists.
-int choose_kernel(blink_schedule* h, bool static_block, bool streams, bool can_stream, bool can_turns, int* timed) {
+// pair to put around it, or -1.  can_front, can_turns: the schedule has ways 2, 3.
+// A caller who asks for way 2 gets it for sums only, as the interface says; picked by
+// the trial it serves every operator.
+int choose_way(blink_schedule* h, bool static_block, bool sum, bool can_front, bool can_turns, int* timed) {
     *timed = -1;
-    auto allowed = [&](int way) { return way == 1 || (way == 2 && can_stream) || (way == 3 && can_turns); };
-    if (h->kernel_choice) return allowed(h->kernel_choice) ? h->kernel_choice : 1;
-    if (h->picked) return allowed(h->picked) ? h->picked : 1;
+    if (h->kernel_choice == 2) return can_front && sum ? 2 : 1;
+    if (h->kernel_choice == 3) return can_turns ? 3 : 1;
+    if (h->kernel_choice) return 1;
+    if (h->picked) return h->picked;
     int ways[3], n_ways = 0;
     ways[n_ways++] = 1;
-    if (streams) ways[n_ways++] = 2;
+    if (can_front) ways[n_ways++] = 2;
     if (can_turns) ways[n_ways++] = 3;
-    // no trial: one way only / nothing may be created here / too short / a call
-    // with another operator than the schedule's trial is held with
-    if (n_ways == 1 || static_block || h->s.traffic_bytes < kTrialMinBytes || (streams && !can_stream)) return 1;
+    // no trial: one way only / nothing may be created here / too short
+    if (n_ways == 1 || static_block || h->s.traffic_bytes < kTrialMinBytes) return 1;
     const int trial_calls = n_ways * kTrialSamples;
     if (h->trial_calls < trial_calls) {
         if (!h->trial_events_made) {
@@ -403,11 +402,230 @@ int choose_kernel(blink_schedule* h, bool static_block, bool streams, bool can_s
 
 void release_device_state(blink_schedule* h) {
     drop_trial_events(h);
-    if (h->device < 0) return;
-    (void)hipFree(h->d_block);
+    if (h->d_block) (void)hipFree(h->d_block);
     h->d_block = nullptr;
     h->device = -1;
 }
+
+namespace {
+
+// One launch on `stream`.  Its own status decides whether the call counts: an error
+// some earlier HIP call of this thread left behind is not this launch's, and a
+// launch that failed must not consume a call number or move the ticket bases
+// (the next call would wait for tiles that nobody ever counted).  timed: index of
+// the event pair to record around it, or -1.
+blink_status_t launch(blink_schedule* h, const void* fn, unsigned grid, unsigned threads, void* params, hipStream_t stream,
+                      int timed) {
+    if (timed >= 0 && hipEventRecord(static_cast<hipEvent_t>(h->trial_event[2 * timed]), stream) != hipSuccess) {
+        (void)hipGetLastError();  // e.g. a capturing stream: give the trial up
+        drop_trial_events(h);
+        h->picked = 1;
+        timed = -1;
+    }
+    void* args[] = {params};
+    const hipError_t launched = hipLaunchKernel(fn, dim3(grid), dim3(threads), args, 0, stream);
+    if (launched != hipSuccess) {
+        std::fprintf(stderr, "blink: kernel launch failed: %s\n", hipGetErrorString(launched));
+        (void)hipGetLastError();  // the failed launch's error is reported here, not left for later calls
+        return BLINK_EHIP;
+    }
+    if (timed >= 0) {
+        if (hipEventRecord(static_cast<hipEvent_t>(h->trial_event[2 * timed + 1]), stream) == hipSuccess) {
+            h->trial_calls += 1;
+        } else {
+            (void)hipGetLastError();
+            drop_trial_events(h);
+            h->picked = 1;
+        }
+    }
+    h->last_grid = grid;
+    return BLINK_OK;
+}
+
+// Clears the head of the static block before a call on it.
+blink_status_t launch_clear(char* block, size_t bytes, hipStream_t stream) {
+    unsigned long long* words = reinterpret_cast<unsigned long long*>(block);
+    unsigned long long n_words = bytes / sizeof(unsigned long long);
+    void* args[] = {&words, &n_words};
+    const unsigned grid = static_cast<unsigned>(std::min<unsigned long long>((n_words + 255) / 256, 1024));
+    const hipError_t cleared = hipLaunchKernel(reinterpret_cast<const void*>(blink_clear), dim3(grid), dim3(256), args, 0, stream);
+    if (cleared != hipSuccess) {
+        std::fprintf(stderr, "blink: kernel launch failed: %s\n", hipGetErrorString(cleared));
+        (void)hipGetLastError();
+        return BLINK_EHIP;
+    }
+    return BLINK_OK;
+}
+
+FoldFn pick_fold(blink_dtype_t dtype, bool sum, const LaunchPlan& pl, int policy) {
+    const int n = static_cast<int>(pl.n_load);
+    const bool stream = policy == kFoldStream;
+    if (n == 1) return fold_copy(policy);
+    if (dtype == BLINK_FP32) return sum ? fold_f32_sum(n, pl.all, stream, pl.half) : fold_f32_other(n, pl.all, pl.half);
+    return sum ? fold_i32_sum(n, pl.all, stream, pl.half) : fold_i32_other(n, pl.all, pl.half);
+}
+
+// A schedule without dependencies.  block: the static block, or null for the
+// schedule's own, which is only made where tickets are drawn or the tables
+// do not travel with the launch.
+blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtype, blink_redop_t redop, hipStream_t stream,
+                        const BlockLayout& l, char* block) {
+    const Schedule& s = h->s;
+    LaunchPlan& pl = h->plan;
+    const bool static_block = block != nullptr;
+    // Rank buffers that all start the same distance past a 1 KiB boundary (views
+    // into larger buffers, allocations at 512-byte granularity): the tile grid
+    // is moved down by that distance, so that tiles, and with them the 1 KiB
+    // accesses of a wave, start on such boundaries in memory.
+    uint32_t grid_shift = 0;
+    const uintptr_t past = reinterpret_cast<uintptr_t>(bufs[0]) & 1023u;
+    bool common = true;
+    for (int i = 1; i < s.k; ++i) common = common && (reinterpret_cast<uintptr_t>(bufs[i]) & 1023u) == past;
+    if (common) grid_shift = static_cast<uint32_t>(past / 4);
+    if (pl.tables_inline && grid_shift != pl.grid_shift) {
+        pl.n_items = fold_levels(pl.flows, pl.tile_elems, grid_shift, false, &pl.levels);
+        pl.grid_shift = grid_shift;
+    }
+
+    const bool sum = redop == BLINK_SUM;
+    const bool by_tile = s.max_slots <= 8 && pl.flows.size() <= 64;
+    int timed = -1;
+    const int way = choose_way(h, static_block, sum, !pl.small && s.max_stack <= 4, !pl.small && by_tile && pl.flows.size() > 1, &timed);
+    const uint64_t chunk_tiles = std::max<uint64_t>(1, s.chunk / pl.tile_elems);
+    const uint32_t chunk_turn = static_cast<uint32_t>(std::min<uint64_t>(chunk_tiles, kTurnPayload));
+
+    // Rank buffers that together fit the memory-side cache (256 MiB) are written
+    // so that results may stay there: whoever reads them next (here: the next call)
+    // finds them.  Larger ones too where calls alternate their direction: a call
+    // then starts on the last 256 MiB that the call before it wrote (3 ranks x
+    // 128 MiB, repeated in place: 0.75 -> 0.83 of the HBM peak, 8 x 256 MiB 0.774 ->
+    // 0.787).  Way 2 streams such results, which is 1 to 2 % faster where the next call
+    // works on other buffers; the trial decides.
+    const bool fits_cache = static_cast<uint64_t>(s.k) * s.n * 4 <= kMemorySideCacheBytes;
+    int policy = kFoldKeep;
+    if (pl.n_load == 1 && s.traffic_bytes >= 3 * s.read_bytes)
+        policy = kFoldSpread;
+    else if (!fits_cache && (way == 2 || !h->sweep_alternates))
+        policy = kFoldStream;
+    const FoldFn fn = pick_fold(dtype, sum, pl, policy);
+    if (!fn) return BLINK_EINVAL;
+
+    // Workgroups: all tiles of a small payload; otherwise 7 on 8 CUs (see fold.hpp), where
+    // one rank is read and others written 6 on 8 (Broadcast to 7 ranks, probe, 64 MiB:
+    // 128 / 192 / 256 workgroups 76.8 / 69.0 / 74.0 us).
+    const uint64_t cus = static_cast<uint64_t>(h->n_cu);
+    uint64_t most = pl.small ? pl.n_items : cus * (pl.n_load == 1 ? 6 : 7) / 8;
+    if (h->wg_per_cu > 0) most = h->wg_per_cu * cus;
+    const unsigned grid = static_cast<unsigned>(std::max<uint64_t>(1, std::min(most, pl.n_items)));
+    const bool dealt = pl.small || grid == pl.n_items;
+
+    if (static_block) {
+        if (!dealt)
+            if (blink_status_t st = launch_clear(block, l.done, stream)) return st;
+    } else if (!dealt || !pl.tables_inline) {
+        if (blink_status_t st = upload(h, l)) return st;
+        block = static_cast<char*>(h->d_block);
+    }
+    FoldParams p;   // every field that is read is set
+    for (int i = 0; i < BLINK_MAX_RANKS; ++i) p.buf[i] = i < s.k ? bufs[i] : nullptr;
+    p.words = nullptr;
+    p.levels = nullptr;
+    if (pl.tables_inline) {
+        fold_words(pl.flows, kInlineFlows, p.inline_words);
+        std::copy(pl.levels.begin(), pl.levels.end(), p.inline_levels);
+    } else {
+        p.words = reinterpret_cast<const unsigned*>(block + l.words);
+        p.levels = reinterpret_cast<const FoldLevel*>(block + l.levels);
+    }
+    p.ticket = block ? reinterpret_cast<unsigned long long*>(block + l.ticket) : nullptr;
+    p.ticket_base = static_block ? 0 : h->ticket_base[0];
+    p.n_items = static_cast<unsigned>(pl.n_items);
+    p.n_flows = static_cast<unsigned>(pl.flows.size());
+    p.n_levels = static_cast<unsigned>(pl.levels.size());
+    p.turn = way == 2 ? kTurnPayload : (way == 3 || !by_tile) ? chunk_turn : 1u;
+    p.tile_elems = pl.tile_elems;
+    p.grid_shift = grid_shift;
+    p.redop = static_cast<unsigned>(redop);
+    // Calls sweep the payload in alternating directions (the second, fourth, ... call
+    // backwards), unless switched off.
+    p.reverse = !static_block && h->sweep_alternates && (h->epoch & 1) != 0;
+    p.dealt = dealt;
+    if (blink_status_t st = launch(h, reinterpret_cast<const void*>(fn), grid, kFoldThreads, &p, stream, timed)) return st;
+    h->last_kernel = way;
+    if (static_block) return BLINK_OK;
+    h->epoch += 1;
+    if (!dealt) h->ticket_base[0] += pl.n_items;   // every ticket is followed by one draw
+    return BLINK_OK;
+}
+
+// A schedule whose stages wait for one another.
+blink_status_t run_hand_over(blink_schedule* h, void* const* bufs, blink_dtype_t dtype, blink_redop_t redop, hipStream_t stream,
+                             const BlockLayout& l, char* block) {
+    const Schedule& s = h->s;
+    const LaunchPlan& pl = h->plan;
+    const bool static_block = block != nullptr;
+    if (!static_block) {
+        if (blink_status_t st = upload(h, l)) return st;
+        block = static_cast<char*>(h->d_block);
+    }
+    KernelFn fn = pick_kernel(dtype, pl.wide);
+    int& occ = h->occupancy[dtype == BLINK_FP32];
+    if (occ == 0) {
+        BLINK_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, kLanes, 0));
+        if (occ < 1) {
+            occ = 0;
+            return BLINK_EHIP;
+        }
+    }
+    // Waves per CU: 4, some waves always wait (8 x 256 MiB per node 1.088 -> 1.023 ms
+    // against 3, per edge 1.242 -> 1.230); all that fit for small payloads.
+    int per_cu = std::min(occ, 4);
+    if (h->wg_per_cu > 0) per_cu = std::min(occ, h->wg_per_cu);
+    if (pl.wide && h->wg_per_cu == 0) per_cu = occ;
+    unsigned long long max_grid = static_cast<unsigned long long>(per_cu) * h->n_cu;
+    const unsigned long long n_items = pl.n_items;
+    // no more waves than three time slots' worth of tickets can be busy
+    max_grid = std::min(max_grid, std::max<unsigned long long>(64, 3 * (n_items / s.n_slots + 1)));
+    const unsigned long long grid = std::min<unsigned long long>(max_grid, n_items);
+
+    KParams p{};
+    for (int i = 0; i < s.k; ++i) p.buf[i] = bufs[i];
+    p.tmpl = reinterpret_cast<const StageTmpl*>(block + l.tmpl);
+    p.inst = reinterpret_cast<const StageInst*>(block + l.inst);
+    p.done = reinterpret_cast<unsigned long long*>(block + l.done);
+    p.ticket = reinterpret_cast<unsigned long long*>(block + l.ticket);
+    p.status = reinterpret_cast<unsigned long long*>(block);
+    p.wait_ticks = (h->wait_limit_us ? h->wait_limit_us : kDefaultWaitMicroseconds) * kTicksPerMicrosecond;
+    const unsigned n_queues = static_cast<unsigned>(std::min<unsigned long long>(kQueuesHandOver, grid));
+    p.n_queues = n_queues;
+    // A static block is shared by every schedule used on the GPU and keeps the
+    // last call's contents: each call on it starts from cleared counters, as
+    // call number 1.  The schedule's own block counts on from call to call.
+    for (unsigned q = 0; q < n_queues; ++q) p.ticket_base[q] = static_block ? 0 : h->ticket_base[q];
+    p.n_items = n_items;
+    p.epoch = static_block ? 1 : h->epoch + 1;
+    p.tiles_per_chunk = pl.tiles_per_chunk;
+    p.tile_shift = pl.tile_shift;
+    p.redop = static_cast<unsigned>(redop);
+    p.n_inst = static_cast<unsigned>(s.inst.size());
+    // Waiting waves look at their dependency every ~0.2 us in small schedules,
+    // where a hand-over is most of the time (16 one-hop trees, 256 elements,
+    // per-edge: 47 -> 36 us), and back off to ~0.8 us in large ones.
+    p.max_naps = pl.wide ? 1 : 4;
+
+    if (static_block)
+        if (blink_status_t st = launch_clear(block, l.counters_end, stream)) return st;
+    if (blink_status_t st = launch(h, reinterpret_cast<const void*>(fn), static_cast<unsigned>(grid), kLanes, &p, stream, -1)) return st;
+    h->last_kernel = 1;
+    if (static_block) return BLINK_OK;
+    h->epoch += 1;
+    // queue q holds the tickets q, q + n_queues, ...; every wave draws exactly one
+    // ticket past the end of every queue
+    for (unsigned q = 0; q < n_queues; ++q) h->ticket_base[q] += (n_items + n_queues - 1 - q) / n_queues + grid;
+    return BLINK_OK;
+}
+
+}  // namespace
 
 blink_status_t execute(blink_schedule* h, void* const* bufs, int k, size_t n, blink_dtype_t dtype,
                        blink_op_t op, blink_redop_t redop, void* stream, bool static_block) {
@@ -426,8 +644,9 @@ blink_status_t execute(blink_schedule* h, void* const* bufs, int k, size_t n, bl
         }
     }
     if (s.inst.empty()) return BLINK_OK;
+    if (blink_status_t st = make_plan(h)) return st;
     const BlockLayout l = layout_of(s);
-    char* block = nullptr;
+    char* block = nullptr;   // the static block, or null: the schedule's own
     if (static_block) {
         if (blink_status_t st = claim_static_block(h, l, static_cast<hipStream_t>(stream), &block)) return st;
     } else {
@@ -442,159 +661,11 @@ blink_status_t execute(blink_schedule* h, void* const* bufs, int k, size_t n, bl
             std::fprintf(stderr, "blink: the stream is capturing; only blink_allreduce_noalloc can be recorded into a HIP graph\n");
             return BLINK_EINVAL;
         }
-        if (blink_status_t st = upload(h)) return st;
-        block = static_cast<char*>(h->d_block);
+        if (blink_status_t st = bind_device(h)) return st;
         h->last_static_device = -1;
     }
-    if (blink_status_t st = make_plan(h, dtype)) return st;
-    // Rank buffers that all start the same distance past a 1 KiB boundary (views
-    // into larger buffers, allocations at 512-byte granularity): the tile grid
-    // is moved down by that distance, so that tiles, and with them the 1 KiB
-    // accesses of a wave, start on such boundaries in memory.  Only where no
-    // stage waits for another: there a tile is nothing but a range of elements;
-    // with dependencies finished tiles are counted, per call number, and the
-    // count of an instance must not change from call to call.
-    uint32_t grid_shift = 0;
-    if (!s.has_deps) {
-        const uintptr_t past = reinterpret_cast<uintptr_t>(bufs[0]) & 1023u;
-        bool common = true;
-        for (int i = 1; i < k; ++i) common = common && (reinterpret_cast<uintptr_t>(bufs[i]) & 1023u) == past;
-        if (common) grid_shift = static_cast<uint32_t>(past / 4);
-    }
-    if (grid_shift != h->plan.grid_shift) count_tickets(h, grid_shift);
-    const LaunchPlan& pl = h->plan;
-
-    int timed = -1;
-    const unsigned full_group = ticket_group(s);
-    const int way = choose_kernel(h, static_block, pl.direct, pl.direct && redop == BLINK_SUM,
-                                  !pl.wide && !s.has_deps && full_group > 1, &timed);
-    const bool direct = way == 2;
-    KernelFn fn = pick_kernel(dtype, pl.flavour, pl.wide, direct);
-    int& occ = h->occupancy[dtype == BLINK_FP32][direct];
-    if (occ == 0) {
-        BLINK_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, kLanes, 0));
-        if (occ < 1) {
-            occ = 0;
-            return BLINK_EHIP;
-        }
-    }
-    // Waves per CU.  blink_stream: 2, each with 64 KiB of loads in flight (all
-    // that fit).  blink_consume: 2 waves with 32 KiB each; 3 where reads dominate
-    // or where a stage reads more than 8 ranks (only 2 columns per rank fit
-    // then); 4 where stages wait for one another (some waves always wait; 8 x
-    // 256 MiB per node 1.088 -> 1.023 ms, per edge 1.242 -> 1.230); 1 where writes dominate (Broadcast,
-    // AllGather: a wave's sub-tile is then one read and seven writes of 16 KiB
-    // each, and a second wave per CU only adds to the queue of stores; 8 ranks,
-    // Broadcast: 8 x 64 MiB 83 -> 71 us, 8 x 256 MiB 300 -> 271 us; AllGather
-    // 81 -> 73 us and 312 -> 302 us).
-    const bool write_heavy = pl.flavour == kWriteHeavy;
-    int per_cu = std::min(occ, direct ? 2 : write_heavy ? 1 : s.has_deps ? 4 : (pl.read_heavy || s.max_slots > 8 ? 3 : 2));
-    if (h->wg_per_cu > 0) per_cu = std::min(occ, h->wg_per_cu);
-    if (pl.wide && h->wg_per_cu == 0) per_cu = occ;
-    unsigned long long max_grid = static_cast<unsigned long long>(per_cu) * h->n_cu;
-    const unsigned long long n_items = way == 3 ? pl.n_items_turns : pl.n_items;
-    // with dependencies no more waves than three time slots' worth of tickets can be busy
-    if (s.has_deps) max_grid = std::min(max_grid, std::max<unsigned long long>(64, 3 * (n_items / s.n_slots + 1)));
-    const unsigned long long grid = std::min<unsigned long long>(max_grid, n_items);
-
-    KParams p{};
-    for (int i = 0; i < k; ++i) p.buf[i] = bufs[i];
-    p.tmpl = reinterpret_cast<const StageTmpl*>(block + l.tmpl);
-    p.inst = reinterpret_cast<const StageInst*>(block + l.inst);
-    p.done = reinterpret_cast<unsigned long long*>(block + l.done);
-    p.ticket = reinterpret_cast<unsigned long long*>(block + l.ticket);
-    p.status = reinterpret_cast<unsigned long long*>(block);
-    p.wait_ticks = (h->wait_limit_us ? h->wait_limit_us : kDefaultWaitMicroseconds) * kTicksPerMicrosecond;
-    const unsigned n_queues =
-        static_cast<unsigned>(std::min<unsigned long long>(s.has_deps ? kQueuesHandOver : 1, grid));
-    p.n_queues = n_queues;
-    // A static block is shared by every schedule used on the GPU and keeps the
-    // last call's contents: each call on it starts from cleared counters, as
-    // call number 1.  The schedule's own block counts on from call to call.
-    for (unsigned q = 0; q < n_queues; ++q) p.ticket_base[q] = static_block ? 0 : h->ticket_base[q];
-    p.n_items = n_items;
-    // A dependency-free schedule with at most four tickets per wave is dealt out
-    // statically, without the counter (see the kernel).  Larger ones draw their
-    // tickets: waves then advance as one compact front through memory, which
-    // DRAM likes better (measured: 0.71 ms against 0.79 ms on the 256 MiB case);
-    // but every wave's first ticket is its own number: drawn, the first tickets
-    // of 512 waves queue at the counter for up to 8 us (4.4 us on average, seen
-    // with a clock in every wave), which is 2 % of a 200 us call.  blink_stream
-    // knows all or nothing.  With dependencies every ticket must come from the
-    // counter: only then is a ticket's holder known to be running.
-    const unsigned long long static_items =
-        s.has_deps ? 0 : (n_items / grid <= 4 ? n_items : (direct ? 0 : grid));
-    p.static_items = static_items;
-    p.epoch = static_block ? 1 : h->epoch + 1;
-    p.tiles_per_chunk = pl.tiles_per_chunk;
-    p.tile_shift = pl.tile_shift;
-    p.redop = static_cast<unsigned>(redop);
-    p.group = way == 3 ? 1u : full_group;
-    p.grid_shift = pl.grid_shift;
-    p.n_inst = static_cast<unsigned>(s.inst.size());
-    // Calls on a schedule without dependencies sweep the payload in alternating
-    // directions (the second, fourth, ... call backwards), unless switched off.
-    p.reverse = !s.has_deps && !static_block && h->sweep_alternates && (p.epoch & 1) == 0;
-    // Waiting waves look at their dependency every ~0.2 us in small schedules,
-    // where a hand-over is most of the time (16 one-hop trees, 256 elements,
-    // per-edge: 47 -> 36 us), and back off to ~0.8 us in large ones.
-    p.max_naps = pl.wide ? 1 : 4;
-
-    // The launch's own status decides whether the call counts: an error some
-    // earlier HIP call of this thread left behind is not this launch's, and a
-    // launch that failed must not consume a call number or move the ticket
-    // bases (the next call would wait for tiles that nobody ever counted).
-    if (static_block) {
-        unsigned long long* words = reinterpret_cast<unsigned long long*>(block);
-        unsigned long long n_words = l.counters_end / sizeof(unsigned long long);
-        void* clear_args[] = {&words, &n_words};
-        const unsigned clear_grid = static_cast<unsigned>(std::min<unsigned long long>((n_words + 255) / 256, 1024));
-        const hipError_t cleared = hipLaunchKernel(reinterpret_cast<const void*>(blink_clear), dim3(clear_grid), dim3(256),
-                                                   clear_args, 0, static_cast<hipStream_t>(stream));
-        if (cleared != hipSuccess) {
-            std::fprintf(stderr, "blink: kernel launch failed: %s\n", hipGetErrorString(cleared));
-            (void)hipGetLastError();
-            return BLINK_EHIP;
-        }
-    }
-    void* args[] = {&p};
-    if (timed >= 0 && hipEventRecord(static_cast<hipEvent_t>(h->trial_event[2 * timed]),
-                                     static_cast<hipStream_t>(stream)) != hipSuccess) {
-        (void)hipGetLastError();  // e.g. a capturing stream: give the trial up
-        drop_trial_events(h);
-        h->picked = 1;
-        timed = -1;
-    }
-    const hipError_t launched = hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3(static_cast<unsigned>(grid)),
-                                                dim3(kLanes), args, 0, static_cast<hipStream_t>(stream));
-    if (launched != hipSuccess) {
-        std::fprintf(stderr, "blink: kernel launch failed: %s\n", hipGetErrorString(launched));
-        (void)hipGetLastError();  // the failed launch's error is reported here, not left for later calls
-        return BLINK_EHIP;
-    }
-    if (timed >= 0) {
-        if (hipEventRecord(static_cast<hipEvent_t>(h->trial_event[2 * timed + 1]), static_cast<hipStream_t>(stream)) ==
-            hipSuccess) {
-            h->trial_calls += 1;
-        } else {
-            (void)hipGetLastError();
-            drop_trial_events(h);
-            h->picked = 1;
-        }
-    }
-    h->last_grid = static_cast<unsigned>(grid);
-    h->last_kernel = way;
-    if (static_block) return BLINK_OK;
-    h->epoch += 1;
-    if (static_items < n_items) {
-        // queue q holds the drawn tickets q, q + n_queues, ...; every wave
-        // draws exactly one ticket past the end of every queue
-        const unsigned long long drawn = n_items - static_items;
-        for (unsigned q = 0; q < n_queues; ++q)
-            h->ticket_base[q] += (drawn + n_queues - 1 - q) / n_queues + grid;
-    }
-    h->last_grid = static_cast<unsigned>(grid);
-    return BLINK_OK;
+    return h->plan.fold ? run_fold(h, bufs, dtype, redop, static_cast<hipStream_t>(stream), l, block)
+                        : run_hand_over(h, bufs, dtype, redop, static_cast<hipStream_t>(stream), l, block);
 }
 
 }  // namespace blink

@@ -1,0 +1,426 @@
+// The fold kernel: schedules in which no stage waits for another (whole-tree
+// fusion; paper sections 3.3, 4.1, 4.2.2).  Every rank buffer is read once and
+// written once, so the kernel is bound by HBM at large payloads and by the
+// latency of one pass (arguments -> rank data -> stores) at small ones.
+//
+// How a workgroup works, and why:
+//
+//   * Four waves share one tile; a wave owns U columns of 1 KiB per rank, so a
+//     tile is 4 * U KiB of every rank, and about 64 KiB of loads per workgroup are in
+//     flight whatever the number of ranks (fold_columns).  One such workgroup on
+//     seven of eight CUs is what HBM likes best.  Measured with a standalone probe
+//     (8 ranks, three sets of buffers in turn, 64 MiB per rank): 128 / 160 / 192 /
+//     224 / 256 workgroups 211 / 180 / 168 / 165 / 169 us; twice the bytes per
+//     workgroup on 112 of them 213 us; two single waves of 32 KiB per CU, 4 KiB of
+//     every rank at a time, 208 us.
+//   * The number of ranks a stage reads, and whether it writes them all, are
+//     template parameters: all stages of such a schedule agree on them, so the
+//     launcher picks the kernel.  Loads land in registers in the order in which the
+//     stack program consumes the ranks (StageTmpl), the top accumulator is in
+//     registers and the others are parked in LDS.  Nothing else is staged.
+//   * A tile's loads are issued before the stores of the tile in front of it
+//     (its registers are free by then): vector memory operations complete in
+//     order, so loads issued after stores would wait for them (probe as above,
+//     35.5 MiB per rank 102.8 -> 96.5 us, 114 MiB 322 -> 292 us).
+//   * Tiles are dealt out by one counter, a ticket ahead; a small payload has a
+//     workgroup for every tile and no counter (see the launcher).
+#pragma once
+#include "fold_plan.hpp"
+#include "kernel.hpp"
+
+namespace blink {
+
+constexpr int kFoldWaves = 4;
+constexpr int kFoldThreads = kFoldWaves * kLanes;
+// Tables of at most this many flows (and no more levels) travel in the kernel's
+// arguments: a schedule that fits needs no block on the device for small payloads.
+// (Copying arguments costs the host: room for 16 flows made a call 0.2 us longer.)
+constexpr int kInlineFlows = 8;
+// Up to this many flows a wave keeps the tables in vector registers, lane f holding
+// flow f's words and lane l level l's: they are fetched beside the arguments, not
+// after them, and a ticket is resolved without touching memory.  (With scalar loads
+// that depended on one another a payload of one tile per workgroup spent more than
+// a microsecond before its first load.)
+constexpr unsigned kLaneFlows = kLanes;
+
+struct FoldParams {
+    void* buf[BLINK_MAX_RANKS];
+    const unsigned* words;           // flow words (see fold_words); null: the inline ones
+    const FoldLevel* levels;         // null: the inline ones
+    unsigned long long* ticket;
+    unsigned long long ticket_base;  // the counter's value when this call starts
+    unsigned n_items;                // tickets
+    unsigned n_flows, n_levels;
+    unsigned turn;                   // see fold_ticket
+    unsigned tile_elems;             // elements per ticket
+    unsigned grid_shift;             // see fold_range
+    unsigned redop;                  // blink_redop_t
+    unsigned reverse;                // tickets walk from the last to the first
+    unsigned dealt;                  // workgroup w takes tickets w, w + grid, ...; the counter is not used
+    FoldLevel inline_levels[kInlineFlows];
+    unsigned inline_words[kFlowWords * kInlineFlows];
+};
+static_assert(sizeof(FoldParams) <= 4096, "kernel arguments");
+
+// Columns per wave and rank for stages that read n ranks: n * U of about 16 where all
+// ranks are written, twice that where one is (a tile is then hardly more than its loads;
+// 8 ranks, Reduce, 64 MiB: 118 -> 86 us), and never so many that one counter would
+// have to serve more than about 60 tickets per microsecond (it sustains 80).
+constexpr int fold_columns(int n, bool all) {
+    return n == 1 ? 4 : n == 2 ? 8 : n == 3 ? 6 : n == 4 ? 4 : n <= 6 ? 3 : n <= 8 ? (all ? 2 : 4) : n <= 10 ? 2 : 1;
+}
+// A payload of about two tiles per CU or less is latency-bound; there tiles of half the
+// size are faster (us, 4 MiB per rank, full / half: 8 ranks 13.3 / 11.4, 5 ranks 8.2 / 7.6, 4
+// ranks 7.7 / 7.2; with three tiles per CU, 8 ranks x 6 MiB, 16.1 / 17.8).  Only where all
+// ranks are written (Reduce, 8 x 4 MiB: 7.6 / 8.6; Broadcast 6.5 / 9.4).
+constexpr bool fold_has_half(int n, bool all) { return all && fold_columns(n, all) > 1; }
+constexpr int fold_columns(int n, bool all, bool half) {
+    return half && fold_has_half(n, all) ? (fold_columns(n, all) + 1) / 2 : fold_columns(n, all);
+}
+constexpr unsigned fold_sub_elems(int n, bool all, bool half) {
+    return static_cast<unsigned>(fold_columns(n, all, half)) * kFoldWaves * 256u;
+}
+
+// Cache policies of the rank buffers' loads and stores.  Measured with the probe
+// (us; 8 ranks, three sets of buffers in turn; loads always nt):
+//   MiB per rank       7    16    35.5   64     114
+//   stores sc1       16.2  47.4   96.5  164.7  291.9
+//   stores nt sc1    22.6  48.2   94.9  162.0  289.0
+//   stores nt        23.2  48.6   97.9  169.4  304.9
+enum FoldPolicy : int {
+    kFoldKeep = 0,    // results may stay in the memory-side cache: whoever reads them next finds them there
+    kFoldStream = 1,  // results stream past it
+    kFoldSpread = 2,  // one rank read, many written: loads by default policy, stores stream
+};
+template <int POLICY>
+struct FoldPolicyBits {
+    static constexpr int kLoad = POLICY == kFoldSpread ? kPolicyDefault : kPolicyStream;
+    static constexpr int kStore = POLICY == kFoldKeep ? kPolicyThrough : (kPolicyStream | kPolicyThrough);
+};
+
+template <typename T>
+__device__ __forceinline__ const BLINK_CONST T* as_const(const void* p) {
+    return reinterpret_cast<const BLINK_CONST T*>(reinterpret_cast<unsigned long long>(p));
+}
+
+// A sub-tile: the elements a workgroup moves at a time, [org + from, org + to) of the
+// payload (none where from >= to), and its flow's stage.  All wave-uniform.
+template <int N>
+struct FoldPiece {
+    long long org;              // a multiple of 4
+    unsigned from, to;
+    unsigned seq[(N + 3) / 4];  // FoldFlow::seq, four to a word
+    unsigned stores;
+    __device__ __forceinline__ unsigned rank(int i) const { return (seq[i / 4] >> ((i & 3) * 8)) & 15u; }
+    __device__ __forceinline__ bool push(int i) const { return (seq[i / 4] >> ((i & 3) * 8)) & 16u; }
+    __device__ __forceinline__ unsigned folds(int i) const { return (seq[i / 4] >> ((i & 3) * 8 + 5)) & 7u; }
+};
+
+template <typename T, bool SUM, int U>
+__device__ __forceinline__ void fold_in(unsigned redop, U4 (&acc)[U], const U4 (&in)[U]) {
+    if constexpr (SUM) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[u] = combine4<T>(BLINK_SUM, acc[u], in[u]);
+    } else if (redop == BLINK_MAX) {   // wave-uniform: one branch per operand, not per element
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[u] = combine4<T>(BLINK_MAX, acc[u], in[u]);
+    } else if (redop == BLINK_MIN) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[u] = combine4<T>(BLINK_MIN, acc[u], in[u]);
+    } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[u] = combine4<T>(BLINK_PROD, acc[u], in[u]);
+    }
+}
+
+// Up to three elements at either end of a flow that do not fill a 16-byte column,
+// one per lane.
+template <typename T, int N, bool SUM, int LD, int ST>
+__device__ __forceinline__ void fold_edges(RankTable ranks, const FoldPiece<N>& pc, unsigned redop, unsigned* park, int lane) {
+    const unsigned head_end = min((pc.from + 3) & ~3u, pc.to);
+    const unsigned tail = max(pc.to & ~3u, head_end);
+    const unsigned e = lane < 4 ? pc.from + lane : tail + (lane - 4);
+    const bool mine = lane < 4 ? e < head_end : (lane < 8 && e < pc.to);
+    const unsigned long long byte_off = static_cast<unsigned long long>(pc.org + pc.from) * 4ull;
+    const unsigned bytes = (pc.to - pc.from) * 4u;
+    const unsigned at = mine ? (e - pc.from) * 4u : 0x7ffffff0u;  // outside the window: nothing happens
+    unsigned acc = 0, depth = 0;
+    constexpr int kWords = (N + 3) / 4;
+    unsigned seq[kWords];
+#pragma unroll
+    for (int q = 0; q < kWords; ++q) seq[q] = pc.seq[q];
+    // not unrolled: rarely run, and every load's answer is read in the iteration that asks for it
+#pragma unroll 1
+    for (int i = 0; i < N; ++i) {
+        const unsigned code = seq[0] & 0xffu;
+#pragma unroll
+        for (int q = 0; q < kWords; ++q) seq[q] = (seq[q] >> 8) | (q + 1 < kWords ? seq[(q + 1) % kWords] << 24 : 0u);
+        const __amdgpu_buffer_rsrc_t win = rank_window(ranks, code & 15u, byte_off, bytes);
+        const unsigned x = __builtin_amdgcn_raw_buffer_load_b32(win, at, 0, LD);
+        if (code & 16u) {
+            if (i) park[depth++ * kLanes + lane] = acc;
+            acc = x;
+        } else {
+            acc = combine1<T>(SUM ? static_cast<unsigned>(BLINK_SUM) : redop, acc, x);
+        }
+#pragma unroll 1
+        for (unsigned f = code >> 5; f; --f)
+            acc = combine1<T>(SUM ? static_cast<unsigned>(BLINK_SUM) : redop, acc, park[--depth * kLanes + lane]);
+    }
+#pragma unroll 1
+    for (unsigned left = pc.stores; left; left &= left - 1) {
+        const __amdgpu_buffer_rsrc_t win = rank_window(ranks, __builtin_ctz(left), byte_off, bytes);
+        __builtin_amdgcn_raw_buffer_store_b32(acc, win, at, 0, ST);
+    }
+}
+
+// T: element type (float, or unsigned for wrap-around int32).  N: ranks a stage
+// reads.  ALL: it writes the same ranks, else one; stages that read one write those in
+// the flow's `stores`.  SUM: the operator is the sum, else params' redop (PROD, MIN or MAX).  HALF: tiles of half the size.
+template <typename T, int N, bool ALL, bool SUM, int POLICY, bool HALF>
+__global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) {
+    constexpr int U = fold_columns(N, ALL, HALF);
+    constexpr int LD = FoldPolicyBits<POLICY>::kLoad, ST = FoldPolicyBits<POLICY>::kStore;
+    constexpr unsigned kSub = fold_sub_elems(N, ALL, HALF);
+    constexpr int kStores = ALL ? N : 1;   // N == 1: those in the flow's `stores` instead
+    constexpr int kParked = N < 4 ? 1 : N / 2 - 1;   // a stack program over N ranks needs at most N / 2 accumulators
+    __shared__ U4 parked[N < 4 ? 1 : kParked * U * kFoldThreads];
+    __shared__ unsigned drawn[2];
+    __shared__ unsigned edge_parked[N < 4 ? 1 : kParked * kLanes];
+    const BLINK_CONST FoldParams* p = (const BLINK_CONST FoldParams*)__builtin_amdgcn_kernarg_segment_ptr();
+    const int lane = threadIdx.x & (kLanes - 1);
+    const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+    const unsigned long long mine = reinterpret_cast<unsigned long long>(p->buf[lane & (BLINK_MAX_RANKS - 1)]);
+    const RankTable ranks = {static_cast<unsigned>(mine), static_cast<unsigned>(mine >> 32)};
+    const unsigned n_items = p->n_items, n_levels = p->n_levels, turn = p->turn, tile_elems = p->tile_elems;
+    const unsigned grid_shift = p->grid_shift, redop = p->redop;
+    const bool reverse = p->reverse != 0, dealt = p->dealt != 0;
+    const BLINK_CONST unsigned* const words = p->words ? as_const<unsigned>(p->words) : p->inline_words;
+    const BLINK_CONST FoldLevel* const levels = p->levels ? as_const<FoldLevel>(p->levels) : p->inline_levels;
+    const unsigned n_flows = p->n_flows;
+    const unsigned stride = p->words ? n_flows : static_cast<unsigned>(kInlineFlows);
+    const bool in_lanes = n_flows <= kLaneFlows;   // and with them the levels
+    unsigned flow_word[kFlowWords], level_word[4];
+    {
+        const unsigned f = min(static_cast<unsigned>(lane), min(n_flows, kLaneFlows) - 1);
+        const unsigned l = min(static_cast<unsigned>(lane), min(n_levels, kLaneFlows) - 1);
+#pragma unroll
+        for (unsigned w = 0; w < kFlowWords; ++w) flow_word[w] = words[w * stride + f];
+        level_word[0] = levels[l].first, level_word[1] = levels[l].base;
+        level_word[2] = levels[l].tiles, level_word[3] = levels[l].members;
+    }
+
+    // Ticket -> its flow and elements; then its sub-tiles one after the other.
+    long long org = 0;
+    unsigned lo = 0, hi = 0;   // the ticket's elements, from org
+    unsigned sub = 0;          // where its next sub-tile starts, from org
+    unsigned seq[(N + 3) / 4], stores = 0;
+    auto resolve = [&](unsigned t) {
+        if (reverse) t = n_items - 1 - t;
+        unsigned l = 0, f, tile;
+        unsigned word[kFlowWords];
+        if (in_lanes) {
+            for (unsigned above = n_levels; above - l > 1;) {
+                const unsigned mid = (l + above) / 2;
+                if (__builtin_amdgcn_readlane(level_word[0], mid) <= t) l = mid; else above = mid;
+            }
+            fold_ticket(t - __builtin_amdgcn_readlane(level_word[0], l), __builtin_amdgcn_readlane(level_word[1], l),
+                        __builtin_amdgcn_readlane(level_word[2], l), __builtin_amdgcn_readlane(level_word[3], l), turn, &f, &tile);
+#pragma unroll
+            for (unsigned w = 0; w < kFlowWords; ++w) word[w] = __builtin_amdgcn_readlane(flow_word[w], f);
+        } else {
+            for (unsigned above = n_levels; above - l > 1;) {
+                const unsigned mid = (l + above) / 2;
+                if (levels[mid].first <= t) l = mid; else above = mid;
+            }
+            fold_ticket(t - levels[l].first, levels[l].base, levels[l].tiles, levels[l].members, turn, &f, &tile);
+#pragma unroll
+            for (unsigned w = 0; w < kFlowWords; ++w) word[w] = words[w * stride + f];
+        }
+        auto wide = [&](unsigned w) { return (static_cast<unsigned long long>(word[w + 1]) << 32) | word[w]; };
+        int64_t start;
+        fold_range(wide(kFlowOff), wide(kFlowLen), tile, tile_elems, grid_shift, &start, &lo, &hi);
+        org = start;
+        sub = 0;
+#pragma unroll
+        for (int q = 0; q < (N + 3) / 4; ++q) seq[q] = word[kFlowSeq + q];
+        stores = word[kFlowStores];
+    };
+    auto piece = [&]() {
+        FoldPiece<N> pc;
+        pc.org = org;
+        pc.from = max(sub, lo);
+        sub += kSub;
+        pc.to = min(sub, hi);
+#pragma unroll
+        for (int q = 0; q < (N + 3) / 4; ++q) pc.seq[q] = seq[q];
+        pc.stores = stores;
+        return pc;
+    };
+    U4 r[N][U];
+    const unsigned column = (wave * U * kLanes + lane) * 16u;
+    // whole 16-byte columns of a sub-tile: where they start in every rank, and bytes
+    auto vector_bytes = [&](const FoldPiece<N>& pc, unsigned long long* byte_off) {
+        const unsigned a = (pc.from + 3) & ~3u, b = pc.to & ~3u;
+        *byte_off = static_cast<unsigned long long>(pc.org + a) * 4ull;
+        return a < b ? (b - a) * 4u : 0u;
+    };
+    auto load = [&](const FoldPiece<N>& pc) {
+        unsigned long long byte_off;
+        const unsigned bytes = vector_bytes(pc, &byte_off);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const __amdgpu_buffer_rsrc_t win = rank_window(ranks, pc.rank(i), byte_off, bytes);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                r[i][u] = __builtin_amdgcn_raw_buffer_load_b128(win, column + u * kLanes * 16, 0, LD);
+        }
+    };
+
+    auto store = [&](const U4 (&v)[U], unsigned rank, unsigned long long byte_off, unsigned bytes) {
+        const __amdgpu_buffer_rsrc_t win = rank_window(ranks, rank, byte_off, bytes);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            __builtin_amdgcn_raw_buffer_store_b128(v[u], win, column + u * kLanes * 16, 0, ST);
+    };
+    // A ticket is drawn ahead: when the loads of the last sub-tile of the one in front
+    // have been issued, and before any stores, so that the counter's answer waits for
+    // neither.  Every ticket is followed by one draw: a call advances the counter by
+    // n_items.  The answer is read by whole waves on every path (readfirstlane below):
+    // a register that may still be awaited on some path costs a wait for all memory
+    // operations wherever the compiler uses it again.
+    auto draw = [&]() {
+        unsigned raw = 0;
+        if (!dealt && sub >= hi && threadIdx.x == 0)
+            raw = static_cast<unsigned>(__hip_atomic_fetch_add(p->ticket, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        return raw;
+    };
+    unsigned t = blockIdx.x;   // the grid has at most n_items workgroups
+    unsigned slot = 0;
+    resolve(t);
+    FoldPiece<N> cur = piece();
+    load(cur);
+    unsigned raw = draw();
+    // In the loop a tile's loads are followed by the stores of the tile in front of it.
+    // Stores into an empty window (dropped) give the first tile the same, and the
+    // compiler the same number of operations to leave outstanding on both ways in:
+    // otherwise it waits for the stores wherever it waits for a load.
+    if constexpr (N > 1) {
+        const U4 nothing[U] = {};
+#pragma unroll
+        for (int j = 0; j < kStores; ++j) store(nothing, 0, 0, 0);
+    }
+    for (;;) {
+        U4 acc[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[u] = r[0][u];
+        if constexpr (N > 1) {
+            unsigned depth = 0;   // accumulators parked in LDS, the oldest at the bottom
+#pragma unroll
+            for (int i = 1; i < N; ++i) {
+                if (N >= 4 && cur.push(i)) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) parked[(depth * U + u) * kFoldThreads + threadIdx.x] = acc[u];
+                    ++depth;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) acc[u] = r[i][u];
+                } else {
+                    fold_in<T, SUM, U>(redop, acc, r[i]);
+                }
+                if (N >= 4)
+#pragma unroll 1
+                    for (unsigned f = cur.folds(i); f; --f) {
+                        --depth;
+                        U4 below[U];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) below[u] = parked[(depth * U + u) * kFoldThreads + threadIdx.x];
+                        fold_in<T, SUM, U>(redop, acc, below);
+                    }
+            }
+        }
+
+        // the next sub-tile: of this ticket, or of the next one
+        const unsigned answer = __builtin_amdgcn_readfirstlane(raw);
+        bool more = true;
+        if (sub >= hi) {
+            if (dealt) {
+                t += gridDim.x;
+            } else {
+                if (wave == 0) drawn[slot] = answer - static_cast<unsigned>(p->ticket_base) + gridDim.x;
+                __syncthreads();
+                t = __builtin_amdgcn_readfirstlane(drawn[slot]);
+                slot ^= 1;   // the other word: a wave may still be reading this one
+            }
+            more = t < n_items;
+            if (more) resolve(t);
+        }
+        FoldPiece<N> next = cur;
+        raw = 0;
+        if (more) {
+            next = piece();
+            load(next);
+            raw = draw();
+        }
+
+        unsigned long long byte_off;
+        const unsigned bytes = vector_bytes(cur, &byte_off);
+        if constexpr (N > 1) {
+#pragma unroll
+            for (int j = 0; j < kStores; ++j) store(acc, ALL ? j : __builtin_ctz(cur.stores), byte_off, bytes);
+        } else {
+            for (unsigned left = cur.stores; left; left &= left - 1) store(acc, __builtin_ctz(left), byte_off, bytes);
+        }
+        if (((cur.from | cur.to) & 3u) && cur.from < cur.to && wave == 0)
+            fold_edges<T, N, SUM, LD, ST>(ranks, cur, redop, edge_parked, lane);
+        if (!more) break;
+        cur = next;
+    }
+}
+
+using FoldFn = void (*)(const FoldParams);
+
+#define BLINK_FOLD_CASES                                                                                            \
+    BLINK_CASE(2) BLINK_CASE(3) BLINK_CASE(4) BLINK_CASE(5) BLINK_CASE(6) BLINK_CASE(7) BLINK_CASE(8) BLINK_CASE(9) \
+    BLINK_CASE(10) BLINK_CASE(11) BLINK_CASE(12) BLINK_CASE(13) BLINK_CASE(14) BLINK_CASE(15) BLINK_CASE(16)
+
+// The kernel for stages that read n ranks and write them all (pick_fold_all) or one
+// (pick_fold_one); null where there is none.
+template <typename T, bool SUM, int POLICY>
+FoldFn pick_fold_all(int n) {
+    switch (n) {
+#define BLINK_CASE(N) case N: return blink_fold<T, N, true, SUM, POLICY, false>;
+        BLINK_FOLD_CASES
+#undef BLINK_CASE
+        default: return nullptr;
+    }
+}
+template <typename T, bool SUM>
+FoldFn pick_fold_half(int n) {
+    switch (n) {
+#define BLINK_CASE(N) case N: return blink_fold<T, N, true, SUM, kFoldKeep, fold_has_half(N, true)>;
+        BLINK_FOLD_CASES
+#undef BLINK_CASE
+        default: return nullptr;
+    }
+}
+template <typename T, bool SUM>
+FoldFn pick_fold_one(int n) {
+    switch (n) {
+#define BLINK_CASE(N) case N: return blink_fold<T, N, false, SUM, kFoldKeep, false>;
+        BLINK_FOLD_CASES
+#undef BLINK_CASE
+        default: return nullptr;
+    }
+}
+
+// Per element type and operator class, each in a translation unit of its own so
+// that they compile side by side.  all: a stage writes the ranks it reads, else one;
+// stream, half: the kernels for sums that stream their results, and with tiles of half the
+// size (sums and others).
+FoldFn fold_f32_sum(int n, bool all, bool stream, bool half);
+FoldFn fold_f32_other(int n, bool all, bool half);
+FoldFn fold_i32_sum(int n, bool all, bool stream, bool half);
+FoldFn fold_i32_other(int n, bool all, bool half);
+FoldFn fold_copy(int policy);   // one rank read: nothing is combined
+
+}  // namespace blink

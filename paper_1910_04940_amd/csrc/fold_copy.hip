@@ -1,0 +1,12 @@
+// Instantiations of the fold kernel: one rank read and copied to others.  See fold.hpp.
+#include "fold.hpp"
+
+namespace blink {
+
+FoldFn fold_copy(int policy) {
+    return policy == kFoldSpread   ? blink_fold<unsigned, 1, false, true, kFoldSpread, false>
+           : policy == kFoldStream ? blink_fold<unsigned, 1, false, true, kFoldStream, false>
+                                   : blink_fold<unsigned, 1, false, true, kFoldKeep, false>;
+}
+
+}  // namespace blink

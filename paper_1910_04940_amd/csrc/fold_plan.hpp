@@ -1,0 +1,149 @@
+// The work of a schedule in which no stage waits for another (whole-tree fusion)
+// as the fold kernel (fold.hpp) sees it: flows (one tree carrying one contiguous
+// range, chunk boundaries mean nothing there) cut into tiles, and the order in
+// which tiles are handed out.  Plain data and the one mapping that host and device
+// share; no HIP in here.
+#pragma once
+#include <algorithm>
+#include <cstdint>
+#include <vector>
+
+#include "schedule.hpp"
+
+namespace blink {
+
+// One flow: its range and its stage.
+struct FoldFlow {
+    uint64_t off, len;                // elements
+    uint8_t seq[BLINK_MAX_RANKS];     // the stack program of StageTmpl: the ranks in the order in which they
+                                      // are consumed, rank | push << 4 | folds << 5
+    uint32_t stores;                  // bit r: the result goes to rank r
+};
+// What the kernel reads of a flow, 32-bit words: word w of flow f lies at
+// words[w * stride + f], so that one load per word fetches it for all flows.
+enum : uint32_t { kFlowOff = 0, kFlowLen = 2, kFlowSeq = 4, kFlowStores = 8, kFlowWords = 9 };
+inline void fold_words(const std::vector<FoldFlow>& flows, uint32_t stride, uint32_t* words) {
+    for (size_t f = 0; f < flows.size(); ++f) {
+        const FoldFlow& fl = flows[f];
+        auto put = [&](uint32_t w, uint64_t v) { words[w * static_cast<size_t>(stride) + f] = static_cast<uint32_t>(v); };
+        put(kFlowOff, fl.off), put(kFlowOff + 1, fl.off >> 32);
+        put(kFlowLen, fl.len), put(kFlowLen + 1, fl.len >> 32);
+        for (uint32_t q = 0; q < 4; ++q)
+            put(kFlowSeq + q, fl.seq[4 * q] | fl.seq[4 * q + 1] << 8 | fl.seq[4 * q + 2] << 16 |
+                                  static_cast<uint32_t>(fl.seq[4 * q + 3]) << 24);
+        put(kFlowStores, fl.stores);
+    }
+}
+
+// Flows are kept longest first.  A level is a stretch of `tiles` tile positions at
+// which the first `members` flows, and only they, still have tiles: handing out
+// a level's tiles in turns over its members leaves no ticket without a tile,
+// however different the trees' weights are.
+struct FoldLevel {
+    uint32_t first;    // ticket number of the level's first tile
+    uint32_t base;     // tile position at which the level starts
+    uint32_t tiles;    // tile positions
+    uint32_t members;  // flows
+};
+
+constexpr uint32_t kTurnPayload = 0xffffffffu;  // a flow's tiles of a level one after another
+
+// Ticket -> (flow, tile of the flow).  `turn`: how many neighbouring tiles of a
+// flow are handed out before the next flow has its turn (section 4.2.2): 1 = tile
+// by tile across the trees, a chunk's worth = chunk by chunk, kTurnPayload = one
+// front through the payload.
+BLINK_HOST_DEVICE inline void fold_ticket(uint32_t w, uint32_t base, uint32_t tiles, uint32_t members, uint32_t turn,
+                                          uint32_t* flow, uint32_t* tile) {
+    if (turn == 1) {
+        *flow = w % members;
+        *tile = base + w / members;
+    } else if (turn >= tiles) {
+        *flow = w / tiles;
+        *tile = base + w % tiles;
+    } else {
+        const uint32_t round = members * turn;
+        const uint32_t done = w / round * turn;                               // positions of earlier rounds
+        const uint32_t mine = turn < tiles - done ? turn : tiles - done;      // the last round may be shorter
+        const uint32_t in_round = w - done * members;
+        *flow = in_round / mine;
+        *tile = base + done + in_round % mine;
+    }
+}
+
+// Tile `tile` of a flow: elements [*org + *a, *org + *b), none where *a >= *b.  *org is
+// where the tile would start if the flow's own start did not cut it (sub-tiles are
+// counted from there; it may lie up to 255 elements before the payload).  Tiles start
+// where a rank buffer whose first byte is 4 * grid_shift bytes past a 1 KiB boundary
+// has such a boundary (grid_shift: a multiple of 4 in [0, 256)), so *org is a multiple of 4.
+BLINK_HOST_DEVICE inline void fold_range(uint64_t off, uint64_t len, uint32_t tile, uint32_t tile_elems, uint32_t grid_shift,
+                                         int64_t* org, uint32_t* a, uint32_t* b) {
+    const uint32_t head = static_cast<uint32_t>(off + grid_shift) & 255u;
+    const uint64_t before = static_cast<uint64_t>(tile) * tile_elems;
+    const int64_t left = static_cast<int64_t>(head + len - before);   // from *org to the end of the flow
+    *org = static_cast<int64_t>(off - head + before);
+    *a = tile == 0 ? head : 0;
+    const int32_t high = static_cast<int32_t>(left >> 32);
+    const uint32_t low = static_cast<uint32_t>(left);
+    *b = high < 0 ? 0 : (high > 0 || low > tile_elems) ? tile_elems : low;
+}
+
+inline uint32_t fold_tiles(uint64_t off, uint64_t len, uint32_t tile_elems, uint32_t grid_shift) {
+    return static_cast<uint32_t>((((off + grid_shift) & 255u) + len + tile_elems - 1) / tile_elems);
+}
+
+// The flows of a schedule without dependencies: one stage each (the chunks of a
+// flow share their stage).  False where the fold kernel cannot run the schedule (no
+// whole-tree program is like that): stages that read different numbers of ranks, that
+// read several and write neither one nor as many, or whose stack program is missing or
+// deeper than the kernel's parking space (N / 2 accumulators always suffice).
+inline bool fold_flows(const Schedule& s, std::vector<FoldFlow>* out) {
+    out->clear();
+    if (s.has_deps || s.inst.empty()) return false;
+    const uint32_t n_load = s.tmpl[s.inst[0].tmpl].n_load, n_store0 = s.tmpl[s.inst[0].tmpl].n_store;
+    if (n_load > 1 && n_store0 != n_load && n_store0 != 1) return false;
+    std::vector<int> at(s.n_flows, -1);
+    for (size_t i = 0; i < s.inst.size(); ++i) {
+        const StageInst& in = s.inst[i];
+        const StageTmpl& st = s.tmpl[in.tmpl];
+        if (st.n_load != n_load || (n_load > 1 && st.n_store != n_store0) || st.seq_depth < 1 || st.seq_depth > (n_load < 4 ? 1u : n_load / 2)) return false;
+        int& f = at[static_cast<size_t>(s.inst_where[i].flow)];
+        if (f < 0) {
+            f = static_cast<int>(out->size());
+            FoldFlow fl{};
+            fl.off = in.off;
+            for (uint32_t i = 0; i < n_load; ++i)   // at most n_load / 2 - 1 folds: three bits
+                fl.seq[i] = static_cast<uint8_t>(st.seq_rank[i] | (st.seq_code[i] & 1) << 4 | (st.seq_code[i] >> 1) << 5);
+            for (int j = 0; j < st.n_store; ++j) fl.stores |= 1u << st.store_rank[j];
+            out->push_back(fl);
+        }
+        (*out)[static_cast<size_t>(f)].len += in.len;
+    }
+    std::stable_sort(out->begin(), out->end(), [](const FoldFlow& a, const FoldFlow& b) { return a.len > b.len; });
+    return true;
+}
+
+// The levels of flows that are sorted longest first; returns the ticket count.
+// every_shift: tile counts that suffice for any grid_shift (a flow may then get a
+// ticket that stands for no element).
+inline uint64_t fold_levels(const std::vector<FoldFlow>& flows, uint32_t tile_elems, uint32_t grid_shift, bool every_shift,
+                            std::vector<FoldLevel>* out) {
+    out->clear();
+    std::vector<uint32_t> count(flows.size());
+    for (size_t f = 0; f < flows.size(); ++f)
+        count[f] = every_shift ? static_cast<uint32_t>((flows[f].len + 255 + tile_elems - 1) / tile_elems)
+                               : fold_tiles(flows[f].off, flows[f].len, tile_elems, grid_shift);
+    // a flow that is no longer than the one before it may still touch one tile more
+    for (size_t f = flows.size(); f-- > 1;) count[f - 1] = std::max(count[f - 1], count[f]);
+    uint64_t tickets = 0;
+    uint32_t base = 0;
+    for (size_t m = flows.size(); m > 0; --m) {
+        if (count[m - 1] == base) continue;
+        const uint32_t tiles = count[m - 1] - base;
+        out->push_back({static_cast<uint32_t>(tickets), base, tiles, static_cast<uint32_t>(m)});
+        tickets += static_cast<uint64_t>(tiles) * m;
+        base = count[m - 1];
+    }
+    return tickets;
+}
+
+}  // namespace blink

@@ -1,8 +1,9 @@
-// The device side: one persistent gfx950 kernel that consumes the stage list of
-// all trees concurrently (paper sections 3.3, 4.1, 4.2.1, 4.2.2).  The kernel is a
-// template; kernel_{f32,i32}_{many,stream}.hip instantiate it for the two element
-// types and the two column budgets (four translation units, so that they compile
-// side by side), exec.hip holds the launcher.
+// The device side of schedules whose stages wait for one another (per-edge and
+// per-node programs; fold.hpp has the others): one persistent gfx950 kernel that
+// consumes the stage list of all trees concurrently (paper sections 3.3, 4.1, 4.2.1,
+// 4.2.2).  The kernel is a template; kernel_{f32,i32}_{many,stream}.hip instantiate it
+// for the two element types and the two column budgets (four translation units, so
+// that they compile side by side), exec.hip holds the launcher.
 //
 // A workgroup is ONE 64-lane wavefront: nothing in the kernel needs a
 // workgroup barrier, and a wave that waits for a dependency holds up nobody
@@ -48,31 +49,23 @@ constexpr int kLanes = 64;        // one wavefront per workgroup
 // 128-bit columns a lane holds in registers (and LDS slots) at once = ranks
 // read x U: 32 (32 KiB of LDS per wave) for payloads large enough to stream,
 // which run fastest with few waves that each keep many bytes in flight
-// (measured on 8 x 256 MiB, against 16 columns and one more wave per CU:
-// whole-tree stages 0.690 -> 0.680 ms, per-node stages 1.35 -> 1.19 ms,
-// per-edge stages 1.52 -> 1.41 ms); 16 where every wave that fits is wanted
-// (small payloads).
+// (measured on 8 x 256 MiB, against 16 columns and one more wave per CU: per-node
+// stages 1.35 -> 1.19 ms, per-edge stages 1.52 -> 1.41 ms); 16 where every wave that
+// fits is wanted (small payloads).
 constexpr int kColumnsMany = 16;
 constexpr int kColumnsStream = 32;
 constexpr unsigned kMinTile = kLanes * 4;   // elements: one column per lane
 constexpr unsigned kMaxTile = 65536;        // elements
-// One ticket counter sustains roughly 80 draws per microsecond.  A ticket of a
-// dependency-free schedule, which draws from one counter, should therefore move
-// about this many bytes (6 TB/s are then 47 draws per microsecond).
-constexpr unsigned kTicketBytes = 128 * 1024;
 // Progress counters sit 256 bytes apart: the few counters that are hot at any
 // moment then live in different cache lines and memory channels, so thousands
 // of polling waves do not pile up on one of them.
 constexpr int kCounterStride = 32;  // in 8-byte words
-// Tickets can be dealt from several counters ("queues"), ticket t from queue
+// Tickets are dealt from several counters ("queues"), ticket t from queue
 // t mod n: one counter sustains ~83 fetch-adds per microsecond however many
 // waves ask, n counters in different memory channels n times that (measured:
-// 540 per microsecond with 8, 1040 with 16).  Schedules whose stages wait for
-// one another use 4 queues and half-size tickets (per-edge AllReduce on
-// 8 x 256 MiB: 1.336 -> 1.277 ms, per-node 1.169 -> 1.125 ms).  Dependency-free
-// streaming keeps ONE queue: there the single counter is no bottleneck at
-// kTicketBytes per ticket, and strictly ordered tickets are as fast as anything
-// tried with more queues and smaller tiles (0.6826 vs 0.6824 ms).
+// 540 per microsecond with 8, 1040 with 16).  4 queues and 64 KiB tickets, against one
+// queue and 128 KiB: per-edge AllReduce on 8 x 256 MiB 1.336 -> 1.277 ms, per-node
+// 1.169 -> 1.125 ms.
 constexpr int kMaxQueues = 16;
 constexpr unsigned kQueuesHandOver = 4;
 constexpr unsigned kTicketBytesHandOver = 64 * 1024;
@@ -105,16 +98,12 @@ struct KParams {
     unsigned long long ticket_base[kMaxQueues];  // value of each queue's counter when this call starts
     unsigned n_queues;
     unsigned long long n_items;
-    unsigned long long static_items;  // tickets below this are dealt round-robin, without the counter
     unsigned long long epoch;
     unsigned tiles_per_chunk;
     unsigned tile_shift;  // a tile is 2^tile_shift elements
     unsigned redop;       // blink_redop_t
-    unsigned group;  // consecutive instances whose tiles are handed out in turn (1 = instance by instance)
     unsigned max_naps;  // longest pause between two looks at a dependency, in units of ~0.2 us
-    unsigned reverse;   // tickets walk the tiles from the last to the first (schedules without dependencies only)
-    unsigned grid_shift;  // elements by which the tile grid is moved down (schedules without dependencies only)
-    unsigned n_inst;      // stage instances (n_items is less than n_inst * tiles_per_chunk where the last group has fewer tiles)
+    unsigned n_inst;    // stage instances
 };
 
 // Address spaces: the kernel arguments and the schedule tables are never
@@ -188,27 +177,12 @@ constexpr int kPolicyStream = 2;        // nt: streamed once, do not keep in cac
 constexpr int kPolicyThrough = 16;      // sc1: agent scope, stores written through
 constexpr int kPolicySystem = 17;       // sc0 sc1: bypass / write through every cache level
 
-// Kernel flavours: the cache policy of rank-buffer loads and stores.
-enum Flavour : int {
-    kHandOver = 0,    // stages hand chunks over to one another (see blink_consume)
-    kBalanced = 1,    // streaming, about as many bytes read as written
-    kWriteHeavy = 2,  // streaming, at least twice as many bytes written as read
-    kReadHeavy = 3,   // streaming, at least twice as many bytes read as written
-};
-// Measured on 8 x 256 MiB, fp32 (load policy, store policy -> ms):
-//   AllReduce  (nt, nt) 0.676  (nt, nt sc1) 0.668  (default, nt sc1) 0.688  (nt, sc1) 0.676
-//   Reduce     (nt, nt) 0.411  (nt, sc1) 0.383     (default, any) 0.44-0.46
-//   Broadcast  (nt, nt) 0.383  (default, nt sc1) 0.297  (default, nt) 0.304
-//   per-edge AllReduce  (sc0 sc1, sc0 sc1) 1.417  (sc0 sc1 nt, sc0 sc1) 1.337  nt on stores 1.65-1.72
-template <int FLAVOUR>
-struct Policy {
-    static constexpr int kLoad = FLAVOUR == kHandOver ? (kPolicySystem | kPolicyStream)
-                                 : (FLAVOUR == kWriteHeavy ? kPolicyDefault : kPolicyStream);
-    static constexpr int kStore = FLAVOUR == kHandOver     ? kPolicySystem
-                                  : FLAVOUR == kWriteHeavy ? (kPolicyStream | kPolicyThrough)
-                                  : FLAVOUR == kReadHeavy  ? kPolicyThrough
-                                                           : kPolicyStream;
-};
+// Where stages hand chunks over to one another loads and stores bypass the caches
+// (see blink_consume); the loads also carry the streaming hint, which changes no
+// scope.  Per-edge AllReduce, 8 x 256 MiB (load policy, store policy -> ms): (sc0 sc1,
+// sc0 sc1) 1.417, (sc0 sc1 nt, sc0 sc1) 1.337, nt on stores 1.65-1.72.
+constexpr int kPolicyLoadHandOver = kPolicySystem | kPolicyStream;
+constexpr int kPolicyStoreHandOver = kPolicySystem;
 
 // The rank buffers' addresses live in a vector register pair, lane r holding rank
 // r's (loaded once per wave): a rank's pointer is then one readlane away instead
@@ -291,7 +265,7 @@ __device__ __forceinline__ void run_program(U4* __restrict__ slots, const unsign
 // peak; 5 ranks: 0.72 -> 0.78; buffers exactly their size apart: 0.80 -> 0.79).
 // Columns past the end of a ragged tile fall outside the window: such loads
 // return zeros and such stores are dropped.
-template <typename T, int N, int U, int LD, int ST>
+template <typename T, int N, int U>
 __device__ __forceinline__ void run_vec(U4* __restrict__ slots, ConstParams p, RankTable ranks, ConstTmpl st,
                                         unsigned long long byte_off, unsigned bytes, int lane) {
     constexpr unsigned kSubBytes = kLanes * U * 16;
@@ -315,7 +289,7 @@ __device__ __forceinline__ void run_vec(U4* __restrict__ slots, ConstParams p, R
             const __amdgpu_buffer_rsrc_t win = rank_window(ranks, BLINK_TMPL(st, load_rank, i), byte_off, bytes);
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                r[i][u] = __builtin_amdgcn_raw_buffer_load_b128(win, ((u * n_sub + sub) * kLanes + lane) * 16, 0, LD);
+                r[i][u] = __builtin_amdgcn_raw_buffer_load_b128(win, ((u * n_sub + sub) * kLanes + lane) * 16, 0, kPolicyLoadHandOver);
         }
 #pragma unroll
         for (int i = 0; i < N; ++i)
@@ -332,34 +306,34 @@ __device__ __forceinline__ void run_vec(U4* __restrict__ slots, ConstParams p, R
             const __amdgpu_buffer_rsrc_t win = rank_window(ranks, BLINK_TMPL(st, store_rank, j), byte_off, bytes);
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                __builtin_amdgcn_raw_buffer_store_b128(acc[u], win, ((u * n_sub + sub) * kLanes + lane) * 16, 0, ST);
+                __builtin_amdgcn_raw_buffer_store_b128(acc[u], win, ((u * n_sub + sub) * kLanes + lane) * 16, 0, kPolicyStoreHandOver);
         }
     }
 }
 
 // Pick U for a stage that reads N ranks: the largest power of two (at most 16)
 // with N * U <= COLS that does not exceed the tile (cols = tile columns per lane).
-template <typename T, int N, int COLS, int LD, int ST>
+template <typename T, int N, int COLS>
 __device__ __forceinline__ void run_vec_n(U4* __restrict__ slots, ConstParams p, RankTable ranks, ConstTmpl st,
                                           unsigned long long byte_off, unsigned bytes, unsigned cols, int lane) {
     constexpr int kFit = COLS / N;
     constexpr int kBudget = kFit >= 16 ? 16 : (kFit >= 8 ? 8 : (kFit >= 4 ? 4 : (kFit >= 2 ? 2 : 1)));
     if constexpr (kBudget >= 16)
-        if (cols >= 16) return run_vec<T, N, 16, LD, ST>(slots, p, ranks, st, byte_off, bytes, lane);
+        if (cols >= 16) return run_vec<T, N, 16>(slots, p, ranks, st, byte_off, bytes, lane);
     if constexpr (kBudget >= 8)
-        if (cols >= 8) return run_vec<T, N, 8, LD, ST>(slots, p, ranks, st, byte_off, bytes, lane);
+        if (cols >= 8) return run_vec<T, N, 8>(slots, p, ranks, st, byte_off, bytes, lane);
     if constexpr (kBudget >= 4)
-        if (cols >= 4) return run_vec<T, N, 4, LD, ST>(slots, p, ranks, st, byte_off, bytes, lane);
+        if (cols >= 4) return run_vec<T, N, 4>(slots, p, ranks, st, byte_off, bytes, lane);
     if constexpr (kBudget >= 2)
-        if (cols >= 2) return run_vec<T, N, 2, LD, ST>(slots, p, ranks, st, byte_off, bytes, lane);
-    run_vec<T, N, 1, LD, ST>(slots, p, ranks, st, byte_off, bytes, lane);
+        if (cols >= 2) return run_vec<T, N, 2>(slots, p, ranks, st, byte_off, bytes, lane);
+    run_vec<T, N, 1>(slots, p, ranks, st, byte_off, bytes, lane);
 }
 
-template <typename T, int COLS, int LD, int ST>
+template <typename T, int COLS>
 __device__ __forceinline__ void run_vec_any(U4* __restrict__ slots, ConstParams p, RankTable ranks, ConstTmpl st,
                                             unsigned long long byte_off, unsigned bytes, unsigned cols, int lane) {
     switch (BLINK_TMPL(st, n_load, 0)) {
-#define BLINK_CASE(N) case N: run_vec_n<T, N, COLS, LD, ST>(slots, p, ranks, st, byte_off, bytes, cols, lane); break;
+#define BLINK_CASE(N) case N: run_vec_n<T, N, COLS>(slots, p, ranks, st, byte_off, bytes, cols, lane); break;
         BLINK_CASE(1) BLINK_CASE(2) BLINK_CASE(3) BLINK_CASE(4) BLINK_CASE(5) BLINK_CASE(6)
         BLINK_CASE(7) BLINK_CASE(8) BLINK_CASE(9) BLINK_CASE(10) BLINK_CASE(11) BLINK_CASE(12)
         BLINK_CASE(13) BLINK_CASE(14) BLINK_CASE(15) BLINK_CASE(16)
@@ -371,13 +345,13 @@ __device__ __forceinline__ void run_vec_any(U4* __restrict__ slots, ConstParams 
 // The same for up to kLanes single 4-byte elements: the ragged end of a payload
 // whose length is not a multiple of 4 elements, and chunks that do not start on
 // a 16-byte boundary.  Slow path; one element per lane.
-template <typename T, int LD, int ST>
+template <typename T>
 __device__ __forceinline__ void run_scalar(unsigned* __restrict__ slots, ConstParams p, RankTable ranks, ConstTmpl st,
                                            unsigned long long byte_off, unsigned bytes, int lane) {
     const int n_load = BLINK_TMPL(st, n_load, 0);
     for (int i = 0; i < n_load; ++i) {
         const __amdgpu_buffer_rsrc_t win = rank_window(ranks, BLINK_TMPL(st, load_rank, i), byte_off, bytes);
-        slots[i * kLanes + lane] = __builtin_amdgcn_raw_buffer_load_b32(win, lane * 4, 0, LD);
+        slots[i * kLanes + lane] = __builtin_amdgcn_raw_buffer_load_b32(win, lane * 4, 0, kPolicyLoadHandOver);
     }
     unsigned acc = 0;
     const unsigned redop = p->redop;
@@ -396,38 +370,25 @@ __device__ __forceinline__ void run_scalar(unsigned* __restrict__ slots, ConstPa
     const int n_store = BLINK_TMPL(st, n_store, 0);
     for (int j = 0; j < n_store; ++j) {
         const __amdgpu_buffer_rsrc_t win = rank_window(ranks, BLINK_TMPL(st, store_rank, j), byte_off, bytes);
-        __builtin_amdgcn_raw_buffer_store_b32(acc, win, lane * 4, 0, ST);
+        __builtin_amdgcn_raw_buffer_store_b32(acc, win, lane * 4, 0, kPolicyStoreHandOver);
     }
 }
 
-// T: element type (float, or unsigned for wrap-around int32).  FLAVOUR selects
-// how data is exchanged between stages:
-//   streaming flavours: the schedule has no stage that waits for another (TREE
-//          fusion): streaming accesses with the policy measured best for the
-//          schedule's mix of reads and writes, no fences;
-//   kHandOver: stages hand chunks over to each other, possibly across XCDs whose
-//          L2 caches are not coherent with one another: all rank-buffer accesses
-//          use system-scope cache policy (loads bypass, stores write through;
-//          the loads also carry the streaming hint, which changes no scope),
-//          so the hand-over needs no L2 write-back or invalidate, only "my
-//          stores have completed" before the counter is bumped.
-// COLS: the column budget (LDS slots per lane).
+// T: element type (float, or unsigned for wrap-around int32).  COLS: the column
+// budget (LDS slots per lane).  Stages hand chunks over to each other, possibly across
+// XCDs whose L2 caches are not coherent with one another: all rank-buffer accesses
+// use system-scope cache policy (loads bypass, stores write through; the loads also
+// carry the streaming hint, which changes no scope), so the hand-over needs no L2
+// write-back or invalidate, only "my stores have completed" before the counter is
+// bumped.
 // The kernel takes all 256 vector registers and 96 accumulation registers, so
-// one wave per SIMD fits (4 per CU).  The 16-column variant, for payloads too
-// small to keep the memory system busy with that, is held to half the register
-// file (the second launch bound: two waves per SIMD; about 160 registers then
-// live in per-lane scratch memory): twice the waves hide more latency than the
-// spills cost (8 ranks x 4 trees, 1 M elements per rank 17.9 -> 15.4 us, 4.2 M
-// 52.0 -> 45.7 us); three per SIMD lose again (4.2 M: 52.1 us), and where
-// stages wait for one another the spills cost more than the waves bring.
+// one wave per SIMD fits (4 per CU); two, with spills, lose (per node, 8 x 256 MiB,
+// 1.054 -> 1.207 ms).
 // The by-value argument is only there to size the kernel-argument segment; it is
 // read through the constant address space (see ConstParams).
-template <typename T, int FLAVOUR, int COLS>
-__global__ __launch_bounds__(kLanes, COLS == kColumnsMany && FLAVOUR != kHandOver ? 2 : 1) void blink_consume(
-    const KParams) {
+template <typename T, int COLS>
+__global__ __launch_bounds__(kLanes, 1) void blink_consume(const KParams) {
     __shared__ U4 slots[COLS * kLanes];  // 16 or 32 KiB: COLS columns per lane
-    constexpr int LD = Policy<FLAVOUR>::kLoad;
-    constexpr int ST = Policy<FLAVOUR>::kStore;
     const int lane = threadIdx.x;
     ConstParams p = (ConstParams)__builtin_amdgcn_kernarg_segment_ptr();
     const RankTable ranks = load_rank_table(p, lane);
@@ -441,8 +402,6 @@ __global__ __launch_bounds__(kLanes, COLS == kColumnsMany && FLAVOUR != kHandOve
     const unsigned tile_shift = p->tile_shift;
     const unsigned tile_elems = 1u << tile_shift;
     const unsigned cols = min(tile_elems / kMinTile, static_cast<unsigned>(COLS));
-    const unsigned group = p->group;
-    const unsigned long long grid_shift = p->grid_shift;
     const unsigned n_inst = p->n_inst;
 
     // Lane-dependent regions.  readfirstlane needs lane 0 present, so the
@@ -460,16 +419,11 @@ __global__ __launch_bounds__(kLanes, COLS == kColumnsMany && FLAVOUR != kHandOve
     // wait), and the wait ends in a ballot over all lanes, which the lanes can
     // only reach together.  All other branches are wave-uniform.
     //
-    // Small schedules without dependencies are dealt round-robin instead (wave w
-    // takes tickets w, w + grid, ...; static_items == n_items): even several
-    // counters are too slow when thousands of waves each want one small tile.
-    //
-    // Drawn tickets: ticket static_items + j * n_queues + q is the j-th of queue
-    // q.  A wave starts on queue (its number mod n_queues), stays with it until
-    // it is empty and then goes round the others, so every wave draws exactly
-    // one ticket past the end of every queue.  The grid has at least n_queues
-    // waves, so each queue has waves of its own; with dependencies this keeps
-    // the schedule free of deadlock: take the first unfinished ticket t in
+    // Ticket j * n_queues + q is the j-th of queue q.  A wave starts on queue (its
+    // number mod n_queues), stays with it until it is empty and then goes round the
+    // others, so every wave draws exactly one ticket past the end of every queue.
+    // The grid has at least n_queues waves, so each queue has waves of its own; this
+    // keeps the schedule free of deadlock: take the first unfinished ticket t in
     // schedule order.  Everything it waits for is finished.  If t is drawn its
     // holder runs; if not, its queue is not empty, the queue's own waves hold
     // only earlier tickets of that queue, which are finished, so one of them
@@ -479,62 +433,39 @@ __global__ __launch_bounds__(kLanes, COLS == kColumnsMany && FLAVOUR != kHandOve
     // counters no longer mean anything) is left alone.
     unsigned long long* const status = p->status;
     if (__hip_atomic_load(status + kStatusState, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
-    const unsigned long long static_items = p->static_items;
-    unsigned long long next_static = blockIdx.x;
     unsigned queue = blockIdx.x % n_queues, empty_queues = 0;
     long long pending = -1;  // instance whose finished tile still has to be counted
     for (;;) {
-        unsigned long long t;
-        if (next_static < static_items) {
-            t = next_static;
-            next_static += gridDim.x;
-        } else {
-            if (static_items == n_items) break;  // fully dealt out: nothing left to draw
-            unsigned long long raw = 0;
-            if (lane == 0) {
-                if (pending >= 0)
-                    __hip_atomic_fetch_add(done + pending * kCounterStride, 1ull, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-                raw = __hip_atomic_fetch_add(ticket + queue * kCounterStride, 1ull, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-            }
-            pending = -1;
-            const unsigned lo = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(raw));
-            const unsigned hi = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(raw >> 32));
-            const unsigned long long nth = ((static_cast<unsigned long long>(hi) << 32) | lo) - p->ticket_base[queue];
-            t = static_items + nth * n_queues + queue;
-            if (t >= n_items) {  // this queue is empty: on to the next, or done
-                if (++empty_queues == n_queues) break;
-                queue = queue + 1 == n_queues ? 0 : queue + 1;
-                continue;
-            }
+        unsigned long long raw = 0;
+        if (lane == 0) {
+            if (pending >= 0)
+                __hip_atomic_fetch_add(done + pending * kCounterStride, 1ull, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+            raw = __hip_atomic_fetch_add(ticket + queue * kCounterStride, 1ull, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
         }
-        if (t >= n_items) break;
-        // Every other call on a schedule whose stages do not wait for one
-        // another walks the tiles backwards: it starts where the call before it
-        // ended, on what that call left in the memory-side cache.
-        if (p->reverse) t = n_items - 1 - t;
-        // ticket -> (instance, tile).  Within a group of `group` consecutive
-        // instances (the trees' turns at one chunk position) tickets walk tile
-        // by tile across the instances, so neighbouring waves work on all trees
-        // at once (section 4.2.2); group == 1 keeps an instance's tiles together.
+        pending = -1;
+        const unsigned lo = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(raw));
+        const unsigned hi = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(raw >> 32));
+        const unsigned long long nth = ((static_cast<unsigned long long>(hi) << 32) | lo) - p->ticket_base[queue];
+        const unsigned long long t = nth * n_queues + queue;
+        if (t >= n_items) {  // this queue is empty: on to the next, or done
+            if (++empty_queues == n_queues) break;
+            queue = queue + 1 == n_queues ? 0 : queue + 1;
+            continue;
+        }
+        // ticket -> (instance, tile), instance by instance
         unsigned ii, tile;
-        ticket_to_tile(t, group, tiles_per_chunk, n_inst, &ii, &tile);
+        ticket_to_tile(t, 1, tiles_per_chunk, n_inst, &ii, &tile);
         ConstInst in = inst + ii;
         // Tiles lie on the absolute grid of tile_elems-element blocks of the
         // payload, so tile starts are 128-byte (indeed tile-size) aligned even
         // when a tree's share starts at an odd multiple of 16 bytes; the first
-        // and last tile of an instance are the ragged ones.  Where the rank
-        // buffers themselves all start the same distance past a 1 KiB boundary
-        // the launcher moves the grid down by that distance (grid_shift
-        // elements): tiles then start on such boundaries in memory, which is
-        // what the 1 KiB accesses of a wave want (buffers 16 bytes past one:
-        // 0.61 of the HBM peak against 0.77, 512 bytes: 0.77 against 0.81).
+        // and last tile of an instance are the ragged ones.
         const unsigned long long off = in->off, end = off + in->len;
-        const unsigned long long block = ((off + grid_shift) >> tile_shift) + tile;
-        const unsigned long long block_lo = block << tile_shift;  // on the moved grid
-        const unsigned long long lo_e = block_lo > grid_shift ? max(off, block_lo - grid_shift) : off;
-        const unsigned long long hi_e = min(end, block_lo + tile_elems - grid_shift);
+        const unsigned long long block_lo = ((off >> tile_shift) + tile) << tile_shift;
+        const unsigned long long lo_e = max(off, block_lo);
+        const unsigned long long hi_e = min(end, block_lo + tile_elems);
         if (lo_e < hi_e) {  // instances have at most tiles_per_chunk tiles, some fewer
             const unsigned tlen = static_cast<unsigned>(hi_e - lo_e);
             ConstTmpl st = tmpl + in->tmpl;
@@ -585,15 +516,15 @@ __global__ __launch_bounds__(kLanes, COLS == kColumnsMany && FLAVOUR != kHandOve
             const unsigned long long e0 = lo_e;  // first element of the tile
             if ((e0 & 3ull) == 0) {
                 const unsigned vec_bytes = (tlen >> 2) * 16u;
-                if (vec_bytes) run_vec_any<T, COLS, LD, ST>(slots, p, ranks, st, e0 * 4ull, vec_bytes, cols, lane);
+                if (vec_bytes) run_vec_any<T, COLS>(slots, p, ranks, st, e0 * 4ull, vec_bytes, cols, lane);
                 const unsigned rem = tlen & 3u;  // only where the payload itself ends off a 16-byte boundary
                 if (rem)
-                    run_scalar<T, LD, ST>(reinterpret_cast<unsigned*>(slots), p, ranks, st, e0 * 4ull + vec_bytes,
+                    run_scalar<T>(reinterpret_cast<unsigned*>(slots), p, ranks, st, e0 * 4ull + vec_bytes,
                                           rem * 4u, lane);
             } else {
                 // chunk size not a multiple of 4 elements: element-wise, slow but correct
                 for (unsigned b = 0; b < tlen * 4u; b += kLanes * 4u)
-                    run_scalar<T, LD, ST>(reinterpret_cast<unsigned*>(slots), p, ranks, st, e0 * 4ull + b,
+                    run_scalar<T>(reinterpret_cast<unsigned*>(slots), p, ranks, st, e0 * 4ull + b,
                                           min(static_cast<unsigned>(kLanes) * 4u, tlen * 4u - b), lane);
             }
 
@@ -610,23 +541,11 @@ __global__ __launch_bounds__(kLanes, COLS == kColumnsMany && FLAVOUR != kHandOve
 // ---- what the launcher sees ---------------------------------------------------------
 using KernelFn = void (*)(const KParams);
 
-template <typename T, int COLS>
-KernelFn pick_kernel_of(int flavour) {
-    switch (flavour) {
-        case kHandOver: return blink_consume<T, kHandOver, COLS>;
-        case kWriteHeavy: return blink_consume<T, kWriteHeavy, COLS>;
-        case kReadHeavy: return blink_consume<T, kReadHeavy, COLS>;
-        default: return blink_consume<T, kBalanced, COLS>;
-    }
-}
-
-// The kernel for a flavour, per element type (float; wrap-around int32 added as
-// unsigned) and column budget (many: kColumnsMany, stream: kColumnsStream).
-// Each is defined in a translation unit of its own, so that the four compile
-// side by side.
-KernelFn kernel_f32_many(int flavour);
-KernelFn kernel_f32_stream(int flavour, bool direct);
-KernelFn kernel_i32_many(int flavour);
-KernelFn kernel_i32_stream(int flavour, bool direct);
+// Per element type and column budget (many: kColumnsMany, stream: kColumnsStream),
+// each in a translation unit of its own, so that the four compile side by side.
+KernelFn kernel_f32_many();
+KernelFn kernel_f32_stream();
+KernelFn kernel_i32_many();
+KernelFn kernel_i32_stream();
 
 }  // namespace blink

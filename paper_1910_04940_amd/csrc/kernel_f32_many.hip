@@ -1,8 +1,9 @@
-// Instantiations of the kernel: fp32 elements, 16 columns per lane.  See kernel.hpp.
+// Instantiation of the kernel for stages that wait for one another: fp32 elements,
+// 16 columns per lane.  See kernel.hpp.
 #include "kernel.hpp"
 
 namespace blink {
 
-KernelFn kernel_f32_many(int flavour) { return pick_kernel_of<float, kColumnsMany>(flavour); }
+KernelFn kernel_f32_many() { return blink_consume<float, kColumnsMany>; }
 
 }  // namespace blink

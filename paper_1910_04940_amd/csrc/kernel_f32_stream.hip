@@ -1,8 +1,9 @@
-// Instantiations of the kernels for payloads that stream: fp32 elements.  See stream.hpp.
-#include "stream.hpp"
+// Instantiation of the kernel for stages that wait for one another: fp32 elements,
+// 32 columns per lane.  See kernel.hpp.
+#include "kernel.hpp"
 
 namespace blink {
 
-KernelFn kernel_f32_stream(int flavour, bool direct) { return pick_stream_kernel_of<float>(flavour, direct); }
+KernelFn kernel_f32_stream() { return blink_consume<float, kColumnsStream>; }
 
 }  // namespace blink

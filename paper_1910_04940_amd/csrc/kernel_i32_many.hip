@@ -1,8 +1,9 @@
-// Instantiations of the kernel: int32 elements (added as unsigned: wrap-around), 16 columns per lane.  See kernel.hpp.
+// Instantiation of the kernel for stages that wait for one another: int32 elements,
+// 16 columns per lane.  See kernel.hpp.
 #include "kernel.hpp"
 
 namespace blink {
 
-KernelFn kernel_i32_many(int flavour) { return pick_kernel_of<unsigned, kColumnsMany>(flavour); }
+KernelFn kernel_i32_many() { return blink_consume<unsigned, kColumnsMany>; }
 
 }  // namespace blink

@@ -1,8 +1,9 @@
-// Instantiations of the kernels for payloads that stream: wrap-around int32 elements.  See stream.hpp.
-#include "stream.hpp"
+// Instantiation of the kernel for stages that wait for one another: int32 elements,
+// 32 columns per lane.  See kernel.hpp.
+#include "kernel.hpp"
 
 namespace blink {
 
-KernelFn kernel_i32_stream(int flavour, bool direct) { return pick_stream_kernel_of<unsigned>(flavour, direct); }
+KernelFn kernel_i32_stream() { return blink_consume<unsigned, kColumnsStream>; }
 
 }  // namespace blink

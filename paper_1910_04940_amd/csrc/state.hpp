@@ -4,7 +4,7 @@
 #include <cstddef>
 #include <cstdint>
 
-#include "schedule.hpp"
+#include "fold_plan.hpp"
 
 namespace blink {
 
@@ -14,25 +14,35 @@ namespace blink {
 // count tiles, so the tile size may not change while they hold progress).
 struct LaunchPlan {
     bool made = false;
+    unsigned tile_elems = 0;       // elements per tile (ticket)
+    // schedules whose stages wait for one another (kernel.hpp)
     bool wide = false;             // small payload: use every wave that fits
-    int flavour = 0;               // cache policy of the kernel (see kernel.hpp)
-    unsigned tile_elems = 0;       // elements per tile
-    unsigned tile_shift = 0;       // log2 of it
+    unsigned tile_shift = 0;       // log2 of tile_elems
     uint32_t tiles_per_chunk = 1;  // most tiles any stage instance has
-    uint32_t grid_shift = 0;       // elements the tile grid is moved down by (see execute)
     uint64_t n_items = 0;          // tickets per call
-    uint64_t n_items_turns = 0;    // the same when the trees take turns chunk by chunk (group 1)
-    bool read_heavy = false;
-    bool direct = false;           // the schedule CAN run on the streaming kernel (stream.hpp)
+    // schedules without dependencies (fold.hpp)
+    bool fold = false;
+    bool small = false;            // a workgroup for every tile
+    bool half = false;             // tiles of half the size
+    bool all = false;              // every stage writes all the ranks it reads
+    bool tables_inline = false;    // flows and levels travel in the kernel's arguments
+    uint32_t n_load = 0;           // ranks a stage reads
+    uint32_t grid_shift = 0;       // the tile grid `levels` was made for (tables_inline only)
+    std::vector<FoldFlow> flows;
+    std::vector<FoldLevel> levels;
 };
 
 // Layout of the device block of a schedule, in bytes from its start:
 //   status record (kStatusWords 64-bit words), ticket counters, one counter of
 //   finished tiles per stage instance (counters kCounterStride words apart),
-//   stage templates, stage instances.
+//   stage templates, stage instances.  A schedule without dependencies counts no
+//   finished tiles and its kernel knows neither templates nor instances: its flow
+//   and level tables, where they do not travel in the kernel's arguments, lie where
+//   the counters of finished tiles would (they need a third of that space).
 struct BlockLayout {
     size_t ticket = 0, done = 0, tmpl = 0, inst = 0, bytes = 0;
     size_t counters_end = 0;  // status record and counters are [0, counters_end)
+    size_t words = 0, levels = 0;
 };
 
 }  // namespace blink
@@ -40,23 +50,21 @@ struct BlockLayout {
 struct blink_schedule {
     blink::Schedule s;
     blink::LaunchPlan plan;
-    int device = -1;              // HIP device holding the block; -1 = not uploaded yet
-    void* d_block = nullptr;      // see BlockLayout
-    uint64_t id = 0;              // unique per handle (names the owner of a device's static block)
+    int device = -1;              // HIP device the schedule has run on; -1 = none yet
+    void* d_block = nullptr;      // its block there (see BlockLayout); null = not needed so far
+    bool tables_stale = true;     // the block's tables are not those of the plan
+    uint64_t id = 0;              // names the owner of a device's static block: unique per handle and set of tables
     uint64_t epoch = 0;           // calls made so far on d_block; its counters hold epoch * tiles
     uint64_t ticket_base[16] = {};  // value of each ticket counter when the next call starts
     uint64_t wait_limit_us = 0;   // longest wait for another stage; 0 = default
     int n_cu = 0;
     int wg_per_cu = 0;            // launch override (0 = automatic)
     unsigned tile_override = 0;   // elements per tile requested by the caller (0 = automatic)
-    int occupancy[2][2] = {};     // waves per CU of the kernel in use, per dtype and per (streaming kernel or not)
+    int occupancy[2] = {};        // waves per CU of the kernel in use, per dtype (schedules with dependencies)
     unsigned last_grid = 0;
-    int last_kernel = 0;          // how the latest call ran: 1 = blink_consume, 2 = blink_stream, 3 = blink_consume, trees in turns
+    int last_kernel = 0;          // the way the latest call ran (see choose_way), 0 = none yet
     int last_static_device = -1;  // device whose static block the latest call used; -1 = it used d_block
-    // What serves a schedule that has the choice (see execute): blink_consume (1),
-    // blink_stream (2), or blink_consume with the trees taking turns chunk by
-    // chunk instead of tile by tile (3).
-    int kernel_choice = 0;        // the caller's wish: 0 = pick the fastest, else one of the three
+    int kernel_choice = 0;        // the caller's wish: 0 = pick the fastest way, else one of the three
     bool sweep_alternates = true; // calls on a schedule without dependencies walk the tiles in alternating directions
     int picked = 0;               // the pick once made (1, 2 or 3); 0 = not yet
     int trial_calls = 0;          // timed calls launched so far (the candidates take turns)
