@@ -85,18 +85,20 @@ typedef enum {
 typedef enum { BLINK_SUM = 0, BLINK_PROD = 1, BLINK_MIN = 2, BLINK_MAX = 3 } blink_redop_t;
 typedef enum { BLINK_STEP_REDUCE = 0, BLINK_STEP_COPY = 1 } blink_step_kind_t;
 
-/* How many tree-edge transfers one wavefront carries a tile through before the
- * data returns to HBM.  The result is bit-identical for all three.
- *   EDGE  one transfer per step, as the paper issues them: a REDUCE reads both
- *         rank buffers and writes the parent's, a COPY reads the parent's and
- *         writes the child's; steps of one chunk hand over through device-side
- *         completion counters.
+/* Which of a tree's transfers are written to the rank buffers.  The result is
+ * bit-identical for all three.
+ *   EDGE  every one, as the paper issues them: a REDUCE adds the child's value to the
+ *         parent's and writes the parent's buffer, a COPY writes the child's.
  *   NODE  the fan-in of one tree node (own data + all children) is one pass and
- *         its fan-out (to all children) another; counters between nodes.  This
- *         is what one GPU would do locally if every rank were its own GPU.
- *   TREE  a tile is carried through all transfers of its tree at once: every
- *         rank buffer is read once and written once; partial sums stay in LDS.
- */
+ *         its fan-out (to all children) another.  This is what one GPU would do
+ *         locally if every rank were its own GPU.
+ *   TREE  every rank buffer is read once and written once; partial sums stay in
+ *         registers and LDS.
+ * The stages of an EDGE or NODE program (blink_schedule_get_stages) depend on one
+ * another.  A wavefront either carries a tile through all of them in turn (NODE; EDGE
+ * payloads that fit the GPU's 256 MiB memory-side cache), or the stages of one chunk
+ * hand over to one another through device-side completion counters (larger EDGE
+ * payloads). */
 typedef enum { BLINK_FUSE_EDGE = 0, BLINK_FUSE_NODE = 1, BLINK_FUSE_TREE = 2 } blink_fusion_t;
 
 typedef struct blink_trees blink_trees_t;
@@ -388,8 +390,8 @@ int blink_schedule_last_kernel(const blink_schedule_t* s);
  * dependencies and blink_allreduce_noalloc always go forwards. */
 blink_status_t blink_schedule_set_sweep(blink_schedule_t* s, int alternate);
 
-/* What became of the calls made on a schedule so far.  In the per-edge and
- * per-node programs a stage waits, chunk by chunk, for the stages it depends on
+/* What became of the calls made on a schedule so far.  Where chunks are handed
+ * over (see blink_fusion_t) a stage waits, chunk by chunk, for the stages it depends on
  * (section 4.1: an event per chunk).  Such a wait is bounded: after the wait
  * limit (default 5 s) the waiting wavefront records what it waited for and
  * leaves the kernel, every other wait of that call then ends as well, the
@@ -417,7 +419,8 @@ blink_status_t blink_schedule_reset(blink_schedule_t* s);
 blink_status_t blink_schedule_set_wait_limit(blink_schedule_t* s, uint64_t microseconds);
 /* For tests of the give-up path only: counts one call as made without
  * launching it.  The stages of the next call then wait for progress that never
- * comes, the waits run into the limit, and the call ends as described above. */
+ * comes, the waits run into the limit, and the call ends as described above.  Until the
+ * next blink_schedule_reset chunks are handed over whatever the fusion level and size. */
 blink_status_t blink_schedule_test_skip_call(blink_schedule_t* s);
 
 /* ---- chunk-size selection across iterations (host only) ---------------------- */

@@ -14,7 +14,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libblink.so")
 SOURCES = ["kernel_f32_stream.hip", "kernel_i32_stream.hip", "kernel_f32_many.hip", "kernel_i32_many.hip",
-           "fold_f32_sum.hip", "fold_i32_sum.hip", "fold_f32_other.hip", "fold_i32_other.hip", "fold_copy.hip", "exec.hip",
+           "fold_f32_sum.hip", "fold_i32_sum.hip", "fold_f32_other.hip", "fold_i32_other.hip",
+           "fold_f32_mid.hip", "fold_i32_mid.hip", "fold_copy.hip", "exec.hip",
            "api.cpp", "pack.cpp", "schedule.cpp", "miad.cpp"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-c",

@@ -305,7 +305,17 @@ blink_status_t blink_schedule_set_wait_limit(blink_schedule_t* s, uint64_t micro
 
 blink_status_t blink_schedule_test_skip_call(blink_schedule_t* s) {
     if (!s) return BLINK_EINVAL;
+    if (s->device < 0) return BLINK_OK;   // the first call starts the count
     s->epoch += 1;
+    if (s->s.has_deps && !s->call_skipped) {   // from now on the stages wait, whatever served the calls so far
+        s->call_skipped = true;
+        if (s->plan.fold) {
+            s->plan = blink::LaunchPlan();
+            s->tables_stale = true;
+            s->id = blink::next_schedule_id();
+            for (uint64_t& b : s->ticket_base) b = 0;
+        }
+    }
     return BLINK_OK;
 }
 

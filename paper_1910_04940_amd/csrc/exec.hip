@@ -104,30 +104,29 @@ blink_status_t bind_device(blink_schedule* h) {
     return BLINK_OK;
 }
 
-// The schedule's own block: one allocation, made at the first call that needs it,
-// zeroed and filled synchronously.  Nothing is left behind when a step fails.
+// The schedule's own block: one allocation, made at the first call that needs it.
+// Synchronously zeroed and filled, then and when a new plan needs other tables.
+// Nothing is left behind when a step fails.
 blink_status_t upload(blink_schedule* h, const BlockLayout& l) {
     if (h->d_block && !h->tables_stale) return BLINK_OK;
     void* block = h->d_block;
-    if (!block) {
+    if (block)
+        BLINK_HIP(hipDeviceSynchronize());   // calls under the old plan
+    else
         BLINK_HIP(hipMalloc(&block, l.bytes));
-        hipError_t zeroed = hipMemset(block, 0, cleared_bytes(h->plan, l));
-        if (zeroed == hipSuccess) zeroed = hipDeviceSynchronize();
-        if (zeroed != hipSuccess) {
-            (void)hipFree(block);
-            BLINK_HIP(zeroed);
-        }
+    blink_status_t st = BLINK_OK;
+    const hipError_t zeroed = hipMemset(block, 0, cleared_bytes(h->plan, l));
+    if (zeroed != hipSuccess) {
+        std::fprintf(stderr, "blink: hipMemset failed: %s\n", hipGetErrorString(zeroed));
+        st = BLINK_EHIP;
     }
-    const blink_status_t st = copy_tables(*h, l, static_cast<char*>(block));
+    if (st == BLINK_OK) st = copy_tables(*h, l, static_cast<char*>(block));
     if (st != BLINK_OK) {
         if (!h->d_block) (void)hipFree(block);
         return st;
     }
-    if (!h->d_block) {
-        h->d_block = block;
-        h->epoch = 0;
-        for (uint64_t& b : h->ticket_base) b = 0;
-    }
+    BLINK_HIP(hipDeviceSynchronize());
+    h->d_block = block;
     h->tables_stale = false;
     return BLINK_OK;
 }
@@ -173,7 +172,7 @@ blink_status_t claim_static_block(blink_schedule* h, const BlockLayout& l, hipSt
     return BLINK_OK;
 }
 
-// The plan of a schedule whose stages wait for one another.  Tickets move about
+// The plan where stages wait for one another.  Tickets move about
 // kTicketBytesHandOver bytes.  A payload too small to give the machine 16 such
 // tickets per CU is latency-bound instead ("wide"): then all the waves that fit
 // are used and the tile shrinks until a time slot, the part of the work that can
@@ -200,7 +199,7 @@ void plan_hand_over(blink_schedule* h) {
     pl.n_items = ticket_count(s, 1, pl.tile_shift, 0, &pl.tiles_per_chunk);
 }
 
-// The plan of a schedule without dependencies.  A ticket is one sub-tile of the
+// The plan where the fold kernel runs the schedule.  A ticket is one sub-tile of the
 // kernel, or as many as make it move 96 KiB: the one ticket counter then has to
 // serve about 65 draws per microsecond at most.
 // A payload of at most five tiles per CU gets a workgroup for every tile: they are
@@ -214,9 +213,10 @@ constexpr unsigned kFoldHalfTilesPerCu = 2;   // up to here half tiles are faste
 void plan_fold(blink_schedule* h) {
     LaunchPlan& pl = h->plan;
     const Schedule& s = h->s;
-    pl.n_load = s.tmpl[s.inst[0].tmpl].n_load;
-    uint32_t n_store = s.tmpl[s.inst[0].tmpl].n_store;
+    pl.n_load = s.fused[0].stage.n_load;
+    const uint32_t n_store = s.fused[0].stage.n_store;
     pl.all = pl.n_load > 1 && n_store == pl.n_load;
+    for (const FusedFlow& f : s.fused) pl.mid = pl.mid || f.mid_store != 0;
     const int n = static_cast<int>(pl.n_load);
     const unsigned sub = fold_sub_elems(n, pl.all, false);
     unsigned tile = sub;
@@ -235,6 +235,23 @@ void plan_fold(blink_schedule* h) {
     pl.n_items = fold_levels(pl.flows, tile, 0, !pl.tables_inline, &pl.levels);
 }
 
+// Whether a schedule runs on the fold kernel.  Without dependencies: always.  With them
+// the fold kernel carries a tile through all its transfers in one wave and writes each of
+// them to its rank buffer; the alternative is to hand chunks over from wave to wave, through
+// counters and memory.  Measured on 8 ranks, us, handed over / in one wave:
+//   per-node: 5 MiB 97 / 16, 20 MiB 156 / 62, 64 MiB 310 / 180, 256 MiB 1059 / 723: always.
+//   per-edge: 0.1 MiB 49 / 6, 8 MiB 124 / 30, 30 MiB 226 / 96.  In one wave where the
+//     payload fits the memory-side cache.  A larger one keeps the paper's pipeline of
+//     chunks that are handed on transfer by transfer: its speed is what callers who tune
+//     the chunk size (section 4.2.1, blink_miad_*) measure.
+// blink_schedule_test_skip_call asks for waiting stages.
+bool may_fold(const blink_schedule& h) {
+    const Schedule& s = h.s;
+    if (!s.has_deps) return true;
+    if (h.call_skipped) return false;
+    return s.fusion == BLINK_FUSE_NODE || static_cast<uint64_t>(s.k) * s.n * 4 <= kMemorySideCacheBytes;
+}
+
 blink_status_t make_plan(blink_schedule* h) {
     LaunchPlan& pl = h->plan;
     if (pl.made) return BLINK_OK;
@@ -245,7 +262,7 @@ blink_status_t make_plan(blink_schedule* h) {
         if (n_cu < 1) return BLINK_EHIP;
         h->n_cu = n_cu;
     }
-    pl.fold = fold_flows(h->s, &pl.flows);
+    pl.fold = may_fold(*h) && fold_flows(h->s, &pl.flows);
     if (pl.fold)
         plan_fold(h);
     else
@@ -263,8 +280,8 @@ blink_status_t make_plan(blink_schedule* h) {
 blink_status_t reset_progress(blink_schedule* h) {
     h->epoch = 0;
     for (uint64_t& b : h->ticket_base) b = 0;
-    const size_t cleared = cleared_bytes(h->plan, layout_of(h->s));
     h->plan = LaunchPlan();
+    h->call_skipped = false;
     h->tables_stale = true;       // the next plan may have others
     h->id = next_schedule_id();   // in a static block, too
     h->occupancy[0] = h->occupancy[1] = 0;
@@ -274,7 +291,8 @@ blink_status_t reset_progress(blink_schedule* h) {
     if (h->device < 0) return BLINK_OK;
     BLINK_HIP(hipDeviceSynchronize());
     if (!h->d_block) return BLINK_OK;
-    BLINK_HIP(hipMemset(h->d_block, 0, cleared));
+    // the next call's tables go in with it (see upload); the status record is read before
+    BLINK_HIP(hipMemset(h->d_block, 0, layout_of(h->s).counters_end));
     BLINK_HIP(hipDeviceSynchronize());
     return BLINK_OK;
 }
@@ -307,7 +325,7 @@ blink_status_t read_status(blink_schedule* h, blink_progress_t* out) {
     return BLINK_ESTUCK;
 }
 
-// Picking the way a schedule without dependencies is served at streaming size: the
+// Picking the way a whole-tree schedule is served at streaming size: the
 // order in which the fold kernel goes through the payload, and with it whether
 // results stream past the memory-side cache.
 //   1  tile by tile across the trees (section 4.2.2; chunk by chunk where a stage
@@ -461,12 +479,12 @@ FoldFn pick_fold(blink_dtype_t dtype, bool sum, const LaunchPlan& pl, int policy
     const int n = static_cast<int>(pl.n_load);
     const bool stream = policy == kFoldStream;
     if (n == 1) return fold_copy(policy);
+    if (pl.mid) return dtype == BLINK_FP32 ? fold_f32_mid(n, pl.all, sum, pl.half) : fold_i32_mid(n, pl.all, sum, pl.half);
     if (dtype == BLINK_FP32) return sum ? fold_f32_sum(n, pl.all, stream, pl.half) : fold_f32_other(n, pl.all, pl.half);
     return sum ? fold_i32_sum(n, pl.all, stream, pl.half) : fold_i32_other(n, pl.all, pl.half);
 }
 
-// A schedule without dependencies.  block: the static block, or null for the
-// schedule's own, which is only made where tickets are drawn or the tables
+// A call on the fold kernel.  block: the static block, or null for the schedule's own, which is only made where tickets are drawn or the tables
 // do not travel with the launch.
 blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtype, blink_redop_t redop, hipStream_t stream,
                         const BlockLayout& l, char* block) {
@@ -488,9 +506,10 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     }
 
     const bool sum = redop == BLINK_SUM;
-    const bool by_tile = s.max_slots <= 8 && pl.flows.size() <= 64;
+    const bool by_tile = pl.n_load <= 8 && pl.flows.size() <= 64;
     int timed = -1;
-    const int way = choose_way(h, static_block, sum, !pl.small && s.max_stack <= 4, !pl.small && by_tile && pl.flows.size() > 1, &timed);
+    const bool choice = !pl.small && !s.has_deps;   // programs with dependencies have way 1 only
+    const int way = choose_way(h, static_block, sum, choice && s.max_stack <= 4, choice && by_tile && pl.flows.size() > 1, &timed);
     const uint64_t chunk_tiles = std::max<uint64_t>(1, s.chunk / pl.tile_elems);
     const uint32_t chunk_turn = static_cast<uint32_t>(std::min<uint64_t>(chunk_tiles, kTurnPayload));
 
@@ -503,9 +522,9 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     // works on other buffers; the trial decides.
     const bool fits_cache = static_cast<uint64_t>(s.k) * s.n * 4 <= kMemorySideCacheBytes;
     int policy = kFoldKeep;
-    if (pl.n_load == 1 && s.traffic_bytes >= 3 * s.read_bytes)
+    if (pl.n_load == 1 && s.fused[0].stage.n_store > 1)
         policy = kFoldSpread;
-    else if (!fits_cache && (way == 2 || !h->sweep_alternates))
+    else if (!fits_cache && (way == 2 || s.has_deps || !h->sweep_alternates))
         policy = kFoldStream;
     const FoldFn fn = pick_fold(dtype, sum, pl, policy);
     if (!fn) return BLINK_EINVAL;
@@ -542,13 +561,13 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     p.n_items = static_cast<unsigned>(pl.n_items);
     p.n_flows = static_cast<unsigned>(pl.flows.size());
     p.n_levels = static_cast<unsigned>(pl.levels.size());
-    p.turn = way == 2 ? kTurnPayload : (way == 3 || !by_tile) ? chunk_turn : 1u;
+    p.turn = way == 2 || s.has_deps ? kTurnPayload : (way == 3 || !by_tile) ? chunk_turn : 1u;
     p.tile_elems = pl.tile_elems;
     p.grid_shift = grid_shift;
     p.redop = static_cast<unsigned>(redop);
     // Calls sweep the payload in alternating directions (the second, fourth, ... call
     // backwards), unless switched off.
-    p.reverse = !static_block && h->sweep_alternates && (h->epoch & 1) != 0;
+    p.reverse = !s.has_deps && !static_block && h->sweep_alternates && (h->epoch & 1) != 0;
     p.dealt = dealt;
     if (blink_status_t st = launch(h, reinterpret_cast<const void*>(fn), grid, kFoldThreads, &p, stream, timed)) return st;
     h->last_kernel = way;
@@ -558,7 +577,7 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     return BLINK_OK;
 }
 
-// A schedule whose stages wait for one another.
+// A call whose stages wait for one another.
 blink_status_t run_hand_over(blink_schedule* h, void* const* bufs, blink_dtype_t dtype, blink_redop_t redop, hipStream_t stream,
                              const BlockLayout& l, char* block) {
     const Schedule& s = h->s;

@@ -1,7 +1,10 @@
-// The fold kernel: schedules in which no stage waits for another (whole-tree
-// fusion; paper sections 3.3, 4.1, 4.2.2).  Every rank buffer is read once and
-// written once, so the kernel is bound by HBM at large payloads and by the
-// latency of one pass (arguments -> rank data -> stores) at small ones.
+// The fold kernel: a tile is carried along its whole tree in one pass (paper sections
+// 3.3, 4.1, 4.2.2): every rank buffer is read once and written once, so the kernel is
+// bound by HBM at large payloads and by the latency of one pass (arguments -> rank data
+// -> stores) at small ones.  It runs the whole-tree programs, and the per-node and
+// small per-edge ones, in which a wave also writes every partial sum to the buffer of
+// the rank that would hold it (MID; see exec.hip for where that beats the hand-over of
+// chunks between waves).
 //
 // How a workgroup works, and why:
 //
@@ -110,7 +113,8 @@ struct FoldPiece {
     long long org;              // a multiple of 4
     unsigned from, to;
     unsigned seq[(N + 3) / 4];  // FoldFlow::seq, four to a word
-    unsigned stores;
+    unsigned stores;            // FoldFlow::stores
+    unsigned long long mid_rank;
     __device__ __forceinline__ unsigned rank(int i) const { return (seq[i / 4] >> ((i & 3) * 8)) & 15u; }
     __device__ __forceinline__ bool push(int i) const { return (seq[i / 4] >> ((i & 3) * 8)) & 16u; }
     __device__ __forceinline__ unsigned folds(int i) const { return (seq[i / 4] >> ((i & 3) * 8 + 5)) & 7u; }
@@ -135,7 +139,7 @@ __device__ __forceinline__ void fold_in(unsigned redop, U4 (&acc)[U], const U4 (
 
 // Up to three elements at either end of a flow that do not fill a 16-byte column,
 // one per lane.
-template <typename T, int N, bool SUM, int LD, int ST>
+template <typename T, int N, bool SUM, bool MID, int LD, int ST>
 __device__ __forceinline__ void fold_edges(RankTable ranks, const FoldPiece<N>& pc, unsigned redop, unsigned* park, int lane) {
     const unsigned head_end = min((pc.from + 3) & ~3u, pc.to);
     const unsigned tail = max(pc.to & ~3u, head_end);
@@ -149,6 +153,18 @@ __device__ __forceinline__ void fold_edges(RankTable ranks, const FoldPiece<N>& 
     unsigned seq[kWords];
 #pragma unroll
     for (int q = 0; q < kWords; ++q) seq[q] = pc.seq[q];
+    unsigned mids = pc.stores >> 16;
+    unsigned long long mid_rank = pc.mid_rank;
+    auto add = [&](unsigned x) {
+        acc = combine1<T>(SUM ? static_cast<unsigned>(BLINK_SUM) : redop, acc, x);
+        if constexpr (MID) {
+            if (mids & 1u)
+                __builtin_amdgcn_raw_buffer_store_b32(
+                    acc, rank_window(ranks, static_cast<unsigned>(mid_rank) & 15u, byte_off, bytes), at, 0, kPolicyThrough);
+            mids >>= 1;
+            mid_rank >>= 4;
+        }
+    };
     // not unrolled: rarely run, and every load's answer is read in the iteration that asks for it
 #pragma unroll 1
     for (int i = 0; i < N; ++i) {
@@ -161,14 +177,13 @@ __device__ __forceinline__ void fold_edges(RankTable ranks, const FoldPiece<N>& 
             if (i) park[depth++ * kLanes + lane] = acc;
             acc = x;
         } else {
-            acc = combine1<T>(SUM ? static_cast<unsigned>(BLINK_SUM) : redop, acc, x);
+            add(x);
         }
 #pragma unroll 1
-        for (unsigned f = code >> 5; f; --f)
-            acc = combine1<T>(SUM ? static_cast<unsigned>(BLINK_SUM) : redop, acc, park[--depth * kLanes + lane]);
+        for (unsigned f = code >> 5; f; --f) add(park[--depth * kLanes + lane]);
     }
 #pragma unroll 1
-    for (unsigned left = pc.stores; left; left &= left - 1) {
+    for (unsigned left = pc.stores & 0xffffu; left; left &= left - 1) {
         const __amdgpu_buffer_rsrc_t win = rank_window(ranks, __builtin_ctz(left), byte_off, bytes);
         __builtin_amdgcn_raw_buffer_store_b32(acc, win, at, 0, ST);
     }
@@ -176,8 +191,12 @@ __device__ __forceinline__ void fold_edges(RankTable ranks, const FoldPiece<N>& 
 
 // T: element type (float, or unsigned for wrap-around int32).  N: ranks a stage
 // reads.  ALL: it writes the same ranks, else one; stages that read one write those in
-// the flow's `stores`.  SUM: the operator is the sum, else params' redop (PROD, MIN or MAX).  HALF: tiles of half the size.
-template <typename T, int N, bool ALL, bool SUM, int POLICY, bool HALF>
+// the flow's `stores`.  SUM: the operator is the sum, else params' redop (PROD, MIN or MAX).
+// HALF: tiles of half the size.  MID: partial sums are written on the way (see
+// FusedFlow::mid_store), through the L2 like the result that overwrites them: left in the
+// L2 as modified lines they cost far more (per node, 8 x 64 MiB, us: stores by default
+// policy 260, nt 216, nt sc1 211, sc1 180; 8 x 5 MiB 30.6 / 22.0 / 16.3 / 16.3).
+template <typename T, int N, bool ALL, bool SUM, int POLICY, bool HALF, bool MID>
 __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) {
     constexpr int U = fold_columns(N, ALL, HALF);
     constexpr int LD = FoldPolicyBits<POLICY>::kLoad, ST = FoldPolicyBits<POLICY>::kStore;
@@ -215,6 +234,7 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
     unsigned lo = 0, hi = 0;   // the ticket's elements, from org
     unsigned sub = 0;          // where its next sub-tile starts, from org
     unsigned seq[(N + 3) / 4], stores = 0;
+    unsigned long long mid_rank = 0;
     auto resolve = [&](unsigned t) {
         if (reverse) t = n_items - 1 - t;
         unsigned l = 0, f, tile;
@@ -245,6 +265,7 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
 #pragma unroll
         for (int q = 0; q < (N + 3) / 4; ++q) seq[q] = word[kFlowSeq + q];
         stores = word[kFlowStores];
+        mid_rank = wide(kFlowMid);
     };
     auto piece = [&]() {
         FoldPiece<N> pc;
@@ -255,6 +276,7 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
 #pragma unroll
         for (int q = 0; q < (N + 3) / 4; ++q) pc.seq[q] = seq[q];
         pc.stores = stores;
+        pc.mid_rank = mid_rank;
         return pc;
     };
     U4 r[N][U];
@@ -277,12 +299,14 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
         }
     };
 
-    auto store = [&](const U4 (&v)[U], unsigned rank, unsigned long long byte_off, unsigned bytes) {
+    auto store = [&](const U4 (&v)[U], unsigned rank, unsigned long long byte_off, unsigned bytes, auto policy) {
         const __amdgpu_buffer_rsrc_t win = rank_window(ranks, rank, byte_off, bytes);
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            __builtin_amdgcn_raw_buffer_store_b128(v[u], win, column + u * kLanes * 16, 0, ST);
+            __builtin_amdgcn_raw_buffer_store_b128(v[u], win, column + u * kLanes * 16, 0, policy.value);
     };
+    constexpr std::integral_constant<int, ST> final_policy;
+    constexpr std::integral_constant<int, kPolicyThrough> mid_policy;
     // A ticket is drawn ahead: when the loads of the last sub-tile of the one in front
     // have been issued, and before any stores, so that the counter's answer waits for
     // neither.  Every ticket is followed by one draw: a call advances the counter by
@@ -308,14 +332,26 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
     if constexpr (N > 1) {
         const U4 nothing[U] = {};
 #pragma unroll
-        for (int j = 0; j < kStores; ++j) store(nothing, 0, 0, 0);
+        for (int j = 0; j < kStores; ++j) store(nothing, 0, 0, 0, final_policy);
     }
     for (;;) {
+        unsigned long long byte_off;
+        const unsigned bytes = vector_bytes(cur, &byte_off);
         U4 acc[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) acc[u] = r[0][u];
         if constexpr (N > 1) {
             unsigned depth = 0;   // accumulators parked in LDS, the oldest at the bottom
+            unsigned mids = cur.stores >> 16;
+            unsigned long long mid_rank = cur.mid_rank;
+            auto add = [&](const U4 (&x)[U]) {
+                fold_in<T, SUM, U>(redop, acc, x);
+                if constexpr (MID) {
+                    if (mids & 1u) store(acc, static_cast<unsigned>(mid_rank) & 15u, byte_off, bytes, mid_policy);
+                    mids >>= 1;
+                    mid_rank >>= 4;
+                }
+            };
 #pragma unroll
             for (int i = 1; i < N; ++i) {
                 if (N >= 4 && cur.push(i)) {
@@ -325,7 +361,7 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
 #pragma unroll
                     for (int u = 0; u < U; ++u) acc[u] = r[i][u];
                 } else {
-                    fold_in<T, SUM, U>(redop, acc, r[i]);
+                    add(r[i]);
                 }
                 if (N >= 4)
 #pragma unroll 1
@@ -334,7 +370,7 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
                         U4 below[U];
 #pragma unroll
                         for (int u = 0; u < U; ++u) below[u] = parked[(depth * U + u) * kFoldThreads + threadIdx.x];
-                        fold_in<T, SUM, U>(redop, acc, below);
+                        add(below);
                     }
             }
         }
@@ -362,16 +398,15 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
             raw = draw();
         }
 
-        unsigned long long byte_off;
-        const unsigned bytes = vector_bytes(cur, &byte_off);
         if constexpr (N > 1) {
 #pragma unroll
-            for (int j = 0; j < kStores; ++j) store(acc, ALL ? j : __builtin_ctz(cur.stores), byte_off, bytes);
+            for (int j = 0; j < kStores; ++j) store(acc, ALL ? j : __builtin_ctz(cur.stores), byte_off, bytes, final_policy);
         } else {
-            for (unsigned left = cur.stores; left; left &= left - 1) store(acc, __builtin_ctz(left), byte_off, bytes);
+            for (unsigned left = cur.stores & 0xffffu; left; left &= left - 1)
+                store(acc, __builtin_ctz(left), byte_off, bytes, final_policy);
         }
         if (((cur.from | cur.to) & 3u) && cur.from < cur.to && wave == 0)
-            fold_edges<T, N, SUM, LD, ST>(ranks, cur, redop, edge_parked, lane);
+            fold_edges<T, N, SUM, MID, LD, ST>(ranks, cur, redop, edge_parked, lane);
         if (!more) break;
         cur = next;
     }
@@ -385,28 +420,28 @@ using FoldFn = void (*)(const FoldParams);
 
 // The kernel for stages that read n ranks and write them all (pick_fold_all) or one
 // (pick_fold_one); null where there is none.
-template <typename T, bool SUM, int POLICY>
+template <typename T, bool SUM, int POLICY, bool MID = false>
 FoldFn pick_fold_all(int n) {
     switch (n) {
-#define BLINK_CASE(N) case N: return blink_fold<T, N, true, SUM, POLICY, false>;
+#define BLINK_CASE(N) case N: return blink_fold<T, N, true, SUM, POLICY, false, MID>;
         BLINK_FOLD_CASES
 #undef BLINK_CASE
         default: return nullptr;
     }
 }
-template <typename T, bool SUM>
+template <typename T, bool SUM, bool MID = false>
 FoldFn pick_fold_half(int n) {
     switch (n) {
-#define BLINK_CASE(N) case N: return blink_fold<T, N, true, SUM, kFoldKeep, fold_has_half(N, true)>;
+#define BLINK_CASE(N) case N: return blink_fold<T, N, true, SUM, kFoldKeep, fold_has_half(N, true), MID>;
         BLINK_FOLD_CASES
 #undef BLINK_CASE
         default: return nullptr;
     }
 }
-template <typename T, bool SUM>
+template <typename T, bool SUM, bool MID = false>
 FoldFn pick_fold_one(int n) {
     switch (n) {
-#define BLINK_CASE(N) case N: return blink_fold<T, N, false, SUM, kFoldKeep, false>;
+#define BLINK_CASE(N) case N: return blink_fold<T, N, false, SUM, kFoldKeep, false, MID>;
         BLINK_FOLD_CASES
 #undef BLINK_CASE
         default: return nullptr;
@@ -416,11 +451,13 @@ FoldFn pick_fold_one(int n) {
 // Per element type and operator class, each in a translation unit of its own so
 // that they compile side by side.  all: a stage writes the ranks it reads, else one;
 // stream, half: the kernels for sums that stream their results, and with tiles of half the
-// size (sums and others).
+// size (sums and others); mid: those that write partial sums on the way.
 FoldFn fold_f32_sum(int n, bool all, bool stream, bool half);
 FoldFn fold_f32_other(int n, bool all, bool half);
+FoldFn fold_f32_mid(int n, bool all, bool sum, bool half);
 FoldFn fold_i32_sum(int n, bool all, bool stream, bool half);
 FoldFn fold_i32_other(int n, bool all, bool half);
+FoldFn fold_i32_mid(int n, bool all, bool sum, bool half);
 FoldFn fold_copy(int policy);   // one rank read: nothing is combined
 
 }  // namespace blink

@@ -4,9 +4,9 @@
 namespace blink {
 
 FoldFn fold_copy(int policy) {
-    return policy == kFoldSpread   ? blink_fold<unsigned, 1, false, true, kFoldSpread, false>
-           : policy == kFoldStream ? blink_fold<unsigned, 1, false, true, kFoldStream, false>
-                                   : blink_fold<unsigned, 1, false, true, kFoldKeep, false>;
+    return policy == kFoldSpread   ? blink_fold<unsigned, 1, false, true, kFoldSpread, false, false>
+           : policy == kFoldStream ? blink_fold<unsigned, 1, false, true, kFoldStream, false, false>
+                                   : blink_fold<unsigned, 1, false, true, kFoldKeep, false, false>;
 }
 
 }  // namespace blink

@@ -1,5 +1,4 @@
-// The work of a schedule in which no stage waits for another (whole-tree fusion)
-// as the fold kernel (fold.hpp) sees it: flows (one tree carrying one contiguous
+// A schedule's work as the fold kernel (fold.hpp) sees it: flows (one tree carrying one contiguous
 // range, chunk boundaries mean nothing there) cut into tiles, and the order in
 // which tiles are handed out.  Plain data and the one mapping that host and device
 // share; no HIP in here.
@@ -17,11 +16,12 @@ struct FoldFlow {
     uint64_t off, len;                // elements
     uint8_t seq[BLINK_MAX_RANKS];     // the stack program of StageTmpl: the ranks in the order in which they
                                       // are consumed, rank | push << 4 | folds << 5
-    uint32_t stores;                  // bit r: the result goes to rank r
+    uint32_t stores;                  // bit r: the result goes to rank r; bit 16 + i: FusedFlow::mid_store
+    uint64_t mid_rank;                // FusedFlow::mid_rank
 };
 // What the kernel reads of a flow, 32-bit words: word w of flow f lies at
 // words[w * stride + f], so that one load per word fetches it for all flows.
-enum : uint32_t { kFlowOff = 0, kFlowLen = 2, kFlowSeq = 4, kFlowStores = 8, kFlowWords = 9 };
+enum : uint32_t { kFlowOff = 0, kFlowLen = 2, kFlowSeq = 4, kFlowStores = 8, kFlowMid = 9, kFlowWords = 11 };
 inline void fold_words(const std::vector<FoldFlow>& flows, uint32_t stride, uint32_t* words) {
     for (size_t f = 0; f < flows.size(); ++f) {
         const FoldFlow& fl = flows[f];
@@ -32,6 +32,7 @@ inline void fold_words(const std::vector<FoldFlow>& flows, uint32_t stride, uint
             put(kFlowSeq + q, fl.seq[4 * q] | fl.seq[4 * q + 1] << 8 | fl.seq[4 * q + 2] << 16 |
                                   static_cast<uint32_t>(fl.seq[4 * q + 3]) << 24);
         put(kFlowStores, fl.stores);
+        put(kFlowMid, fl.mid_rank), put(kFlowMid + 1, fl.mid_rank >> 32);
     }
 }
 
@@ -91,32 +92,29 @@ inline uint32_t fold_tiles(uint64_t off, uint64_t len, uint32_t tile_elems, uint
     return static_cast<uint32_t>((((off + grid_shift) & 255u) + len + tile_elems - 1) / tile_elems);
 }
 
-// The flows of a schedule without dependencies: one stage each (the chunks of a
-// flow share their stage).  False where the fold kernel cannot run the schedule (no
-// whole-tree program is like that): stages that read different numbers of ranks, that
-// read several and write neither one nor as many, or whose stack program is missing or
+// The flows of a schedule, longest first.  False where the fold kernel cannot run them
+// (no program is like that): flows that read different numbers of ranks, that read
+// several and write neither one nor as many, or whose stack program is missing or
 // deeper than the kernel's parking space (N / 2 accumulators always suffice).
 inline bool fold_flows(const Schedule& s, std::vector<FoldFlow>* out) {
     out->clear();
-    if (s.has_deps || s.inst.empty()) return false;
-    const uint32_t n_load = s.tmpl[s.inst[0].tmpl].n_load, n_store0 = s.tmpl[s.inst[0].tmpl].n_store;
-    if (n_load > 1 && n_store0 != n_load && n_store0 != 1) return false;
-    std::vector<int> at(s.n_flows, -1);
-    for (size_t i = 0; i < s.inst.size(); ++i) {
-        const StageInst& in = s.inst[i];
-        const StageTmpl& st = s.tmpl[in.tmpl];
-        if (st.n_load != n_load || (n_load > 1 && st.n_store != n_store0) || st.seq_depth < 1 || st.seq_depth > (n_load < 4 ? 1u : n_load / 2)) return false;
-        int& f = at[static_cast<size_t>(s.inst_where[i].flow)];
-        if (f < 0) {
-            f = static_cast<int>(out->size());
-            FoldFlow fl{};
-            fl.off = in.off;
-            for (uint32_t i = 0; i < n_load; ++i)   // at most n_load / 2 - 1 folds: three bits
-                fl.seq[i] = static_cast<uint8_t>(st.seq_rank[i] | (st.seq_code[i] & 1) << 4 | (st.seq_code[i] >> 1) << 5);
-            for (int j = 0; j < st.n_store; ++j) fl.stores |= 1u << st.store_rank[j];
-            out->push_back(fl);
-        }
-        (*out)[static_cast<size_t>(f)].len += in.len;
+    if (s.fused.empty()) return false;
+    const uint32_t n_load = s.fused[0].stage.n_load, n_store = s.fused[0].stage.n_store;
+    if (n_load > 1 && n_store != n_load && n_store != 1) return false;
+    for (const FusedFlow& one : s.fused) {
+        const StageTmpl& st = one.stage;
+        if (st.n_load != n_load || (n_load > 1 && st.n_store != n_store) || st.seq_depth < 1 ||
+            st.seq_depth > (n_load < 4 ? 1u : n_load / 2))
+            return false;
+        FoldFlow fl{};
+        fl.off = one.lo;
+        fl.len = one.hi - one.lo;
+        for (uint32_t i = 0; i < n_load; ++i)   // at most n_load / 2 - 1 folds: three bits
+            fl.seq[i] = static_cast<uint8_t>(st.seq_rank[i] | (st.seq_code[i] & 1) << 4 | (st.seq_code[i] >> 1) << 5);
+        for (int j = 0; j < st.n_store; ++j) fl.stores |= 1u << st.store_rank[j];
+        fl.stores |= static_cast<uint32_t>(one.mid_store) << 16;
+        fl.mid_rank = one.mid_rank;
+        out->push_back(fl);
     }
     std::stable_sort(out->begin(), out->end(), [](const FoldFlow& a, const FoldFlow& b) { return a.len > b.len; });
     return true;

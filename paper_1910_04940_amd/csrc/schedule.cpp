@@ -189,33 +189,41 @@ std::vector<StageTmpl> node_stages(int k, int root, const ParentVec& parent, uin
 // addition and multiplication commute bit for bit, and min/max are taken under
 // a total order, so the bits equal x_v (+) S(c_1)); before a later child
 // that has children of its own the running sum is parked in v's slot, which is
-// free once x_v has been consumed.
-void eval_tree(int v, const std::vector<std::vector<int>>& ch, StageTmpl& t) {
+// free once x_v has been consumed.  Every OP_ADD is one transfer of the reduce phase:
+// `sums` receives, per addition, the vertex whose running sum it forms and whether
+// that is the vertex's last.
+struct Sum {
+    int vertex;
+    bool last;
+};
+void eval_tree(int v, const std::vector<std::vector<int>>& ch, StageTmpl& t, std::vector<Sum>& sums) {
     if (ch[v].empty()) {
         t.op[t.n_op++] = make_op(OP_LD, static_cast<uint8_t>(v));
         return;
     }
-    eval_tree(ch[v][0], ch, t);
+    eval_tree(ch[v][0], ch, t, sums);
     t.op[t.n_op++] = make_op(OP_ADD, static_cast<uint8_t>(v));
+    sums.push_back({v, ch[v].size() == 1});
     for (size_t i = 1; i < ch[v].size(); ++i) {
         const int c = ch[v][i];
         if (ch[c].empty()) {
             t.op[t.n_op++] = make_op(OP_ADD, static_cast<uint8_t>(c));
         } else {
             t.op[t.n_op++] = make_op(OP_ST, static_cast<uint8_t>(v));
-            eval_tree(c, ch, t);
+            eval_tree(c, ch, t, sums);
             t.op[t.n_op++] = make_op(OP_ADD, static_cast<uint8_t>(v));
         }
+        sums.push_back({v, i + 1 == ch[v].size()});
     }
 }
 
 // The whole tree in one stage: every rank read once and written once.
 std::vector<StageTmpl> tree_stage(int k, int root, const ParentVec& parent, uint16_t late,
-                                  blink_op_t op) {
+                                  blink_op_t op, std::vector<Sum>& sums) {
     StageTmpl t = blank();
     if (op != BLINK_OP_BROADCAST) {
         for (int v = 0; v < k; ++v) t.load_rank[t.n_load++] = static_cast<uint8_t>(v);
-        eval_tree(root, ordered_children(k, parent, late), t);
+        eval_tree(root, ordered_children(k, parent, late), t, sums);
         if (op == BLINK_OP_REDUCE)
             t.store_rank[t.n_store++] = static_cast<uint8_t>(root);
         else
@@ -447,10 +455,27 @@ void finish(const std::vector<Flow>& flows, std::vector<Flow> fused_flows, blink
     if (fusion != BLINK_FUSE_EDGE) {
         fused.resize(ff.size());
         for (size_t f = 0; f < ff.size(); ++f) {
+            std::vector<Sum> sums;
             fused[f] = fusion == BLINK_FUSE_NODE ? node_stages(k, ff[f].root, ff[f].parent, ff[f].late, build_as)
-                                                 : tree_stage(k, ff[f].root, ff[f].parent, ff[f].late, build_as);
+                                                 : tree_stage(k, ff[f].root, ff[f].parent, ff[f].late, build_as, sums);
             finish_levels(fused[f]);
         }
+    }
+    // the same flows in one pass each, with what the program writes on the way
+    for (const Flow& fl : ff) {
+        if (fl.lo == fl.hi) continue;
+        FusedFlow one;
+        std::vector<Sum> sums;
+        one.lo = fl.lo;
+        one.hi = fl.hi;
+        one.stage = tree_stage(k, fl.root, fl.parent, fl.late, build_as, sums)[0];
+        stack_program(one.stage);
+        for (size_t i = 0; i < sums.size(); ++i) {
+            one.mid_rank |= static_cast<uint64_t>(sums[i].vertex) << (4 * i);
+            const bool written = fusion == BLINK_FUSE_EDGE || (fusion == BLINK_FUSE_NODE && sums[i].last);
+            if (written && i + 1 < sums.size()) one.mid_store = static_cast<uint16_t>(one.mid_store | 1u << i);
+        }
+        out.fused.push_back(one);
     }
     Built e = instantiate(edge, flows, chunk);
     out.steps.resize(e.inst.size());

@@ -68,6 +68,18 @@ struct InstWhere {
     int tree, chunk, flow;
 };
 
+// A flow carried through in one pass: every rank it takes from is read once, the
+// sums travel along its tree in registers, and every transfer of the program is
+// written to its rank buffer, those that a later one overwrites included.  What the
+// fold kernel runs (fold.hpp).
+struct FusedFlow {
+    uint64_t lo, hi;            // element range
+    StageTmpl stage;            // the whole tree as one stage; its stores are the final ones
+    uint64_t mid_rank = 0;      // rank whose running sum the i-th addition forms, four bits each
+    uint16_t mid_store = 0;     // bit i: the program writes that sum to the rank's buffer on the way
+                                // (per-edge: all but the last, per-node: a node's last; whole-tree: none)
+};
+
 struct Schedule {
     int k = 0;
     int n_trees = 0;
@@ -82,6 +94,7 @@ struct Schedule {
     std::vector<StageTmpl> tmpl;
     std::vector<StageInst> inst;         // execution (ticket) order; dependencies point backwards
     std::vector<InstWhere> inst_where;   // per instance: what it belongs to
+    std::vector<FusedFlow> fused;        // the same work as one pass per flow
     uint32_t max_slots = 1;              // largest n_load
     uint32_t max_stack = 0;              // most accumulators any stage's stack program needs (255: some stage has none)
     bool has_deps = false;               // some stage waits for another

@@ -15,16 +15,17 @@ namespace blink {
 struct LaunchPlan {
     bool made = false;
     unsigned tile_elems = 0;       // elements per tile (ticket)
-    // schedules whose stages wait for one another (kernel.hpp)
+    // stages that wait for one another (kernel.hpp)
     bool wide = false;             // small payload: use every wave that fits
     unsigned tile_shift = 0;       // log2 of tile_elems
     uint32_t tiles_per_chunk = 1;  // most tiles any stage instance has
     uint64_t n_items = 0;          // tickets per call
-    // schedules without dependencies (fold.hpp)
+    // what the fold kernel runs (fold.hpp)
     bool fold = false;
     bool small = false;            // a workgroup for every tile
     bool half = false;             // tiles of half the size
     bool all = false;              // every stage writes all the ranks it reads
+    bool mid = false;              // partial sums are written on the way
     bool tables_inline = false;    // flows and levels travel in the kernel's arguments
     uint32_t n_load = 0;           // ranks a stage reads
     uint32_t grid_shift = 0;       // the tile grid `levels` was made for (tables_inline only)
@@ -35,8 +36,8 @@ struct LaunchPlan {
 // Layout of the device block of a schedule, in bytes from its start:
 //   status record (kStatusWords 64-bit words), ticket counters, one counter of
 //   finished tiles per stage instance (counters kCounterStride words apart),
-//   stage templates, stage instances.  A schedule without dependencies counts no
-//   finished tiles and its kernel knows neither templates nor instances: its flow
+//   stage templates, stage instances.  The fold kernel counts no finished tiles and
+//   knows neither templates nor instances: its flow
 //   and level tables, where they do not travel in the kernel's arguments, lie where
 //   the counters of finished tiles would (they need a third of that space).
 struct BlockLayout {
@@ -56,6 +57,7 @@ struct blink_schedule {
     uint64_t id = 0;              // names the owner of a device's static block: unique per handle and set of tables
     uint64_t epoch = 0;           // calls made so far on d_block; its counters hold epoch * tiles
     uint64_t ticket_base[16] = {};  // value of each ticket counter when the next call starts
+    bool call_skipped = false;    // blink_schedule_test_skip_call was used: stages wait for one another
     uint64_t wait_limit_us = 0;   // longest wait for another stage; 0 = default
     int n_cu = 0;
     int wg_per_cu = 0;            // launch override (0 = automatic)

@@ -1,0 +1,226 @@
+"""The kernel that carries a tile along its whole tree in one pass, at the sizes where
+its tables, tiles and variants change: the edges of a tile and of a flow, one tile and
+several per compute unit, tickets dealt out and drawn, every number of ranks, tables in
+the kernel's arguments, in a wave's lanes and in memory, and the per-edge and
+per-node programs, whose intermediate writes must be those of the step list.  Bit for
+bit against the oracle."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+from oracle import execute as ox
+from oracle import schedule as osch
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_1910_04940_amd as bl  # noqa: E402
+
+FUSIONS = {"edge": bl.BLINK_FUSE_EDGE, "node": bl.BLINK_FUSE_NODE, "tree": bl.BLINK_FUSE_TREE}
+REDOPS = {"sum": (bl.BLINK_SUM, ox.SUM), "prod": (bl.BLINK_PROD, ox.PROD), "min": (bl.BLINK_MIN, ox.MIN),
+          "max": (bl.BLINK_MAX, ox.MAX)}
+
+
+def _stream():
+    assert torch.cuda.is_available()
+    torch.cuda.set_device(0)
+    return torch.cuda.current_stream().cuda_stream
+
+
+def _tree(k, seed):
+    """A random tree on k ranks: its root and parents."""
+    rng = np.random.default_rng([7, k, seed])
+    order = [int(v) for v in rng.permutation(k)]
+    parent = [-1] * k
+    for i in range(1, k):
+        parent[order[i]] = order[int(rng.integers(max(0, i - 3), i))]
+    return order[0], parent
+
+
+def _slab(x, guard=64):
+    """Rank buffers inside one allocation, guard elements between them, and a check
+    that nothing but the buffers was written."""
+    n = len(x[0])
+    step = (n + guard + 255) // 256 * 256
+    slab = torch.zeros(len(x) * step, dtype=torch.int32, device="cuda")
+    bufs = [slab[r * step:r * step + n] for r in range(len(x))]
+    for b, a in zip(bufs, x):
+        b.copy_(torch.from_numpy(a.view(np.int32)))
+
+    def untouched():
+        return all(int(torch.count_nonzero(slab[r * step + n:(r + 1) * step])) == 0 for r in range(len(x)))
+    return bufs, untouched
+
+
+@pytest.mark.parametrize("fusion", FUSIONS)
+@pytest.mark.parametrize("k", range(2, 17))
+def test_every_number_of_ranks_at_the_edges_of_a_tile(k, fusion):
+    """One random tree; payloads of a few elements, one element around a tile of
+    4 * U KiB for U = 1, 2, 3, 4, 6 and 8, and three tiles and a ragged end."""
+    stream = _stream()
+    root, parent = _tree(k, 0)
+    trees = bl.blink_trees_from_arrays(k, [root], [parent], [1.0])
+    for n in (1, 3, 4, 5, 255, 1023, 1024, 1025, 2047, 2049, 3073, 4097, 6145, 8191, 8193, 25_003):
+        x = [si.hash_payload(11, r, 0, n, "fp32") for r in range(k)]
+        want = ox.tree_order_allreduce(x, [root], [parent], [1.0])
+        bufs, untouched = _slab(x)
+        sched = bl.blink_make_schedule(trees, bl.BLINK_OP_ALLREDUCE, n, 1000, FUSIONS[fusion])
+        bl.blink_allreduce(bufs, n, bl.BLINK_FP32, sched, stream)
+        torch.cuda.synchronize()
+        for r, b in enumerate(bufs):
+            assert b.cpu().numpy().tobytes() == want.tobytes(), (k, fusion, n, r)
+        assert untouched()
+
+
+# elements per rank: half tiles, whole tiles, a workgroup per tile, drawn tickets, larger than the memory-side cache
+@pytest.mark.parametrize("n", [70_001, 1_100_003, 2_000_006, 3_000_001, 9_000_002])
+@pytest.mark.parametrize("fusion", FUSIONS)
+@pytest.mark.parametrize("op,dtype", [("sum", "int32"), ("max", "int32"), ("min", "fp32"), ("prod", "int32")])
+def test_sizes_where_the_launch_changes(n, fusion, op, dtype):
+    """8 ranks, 4 packed trees; two calls in place (a whole-tree call's second goes backwards)."""
+    stream = _stream()
+    top = si.hybrid_cube_mesh()
+    trees = bl.blink_pack_trees(top.k, top.src, top.dst, top.cap, 0)
+    roots, parents, w = trees.as_lists()
+    code, oracle_op = REDOPS[op]
+    x = [si.hash_payload(13, r, 0, n, dtype) for r in range(top.k)]
+    bufs, untouched = _slab(x)
+    sched = bl.blink_make_schedule(trees, bl.BLINK_OP_ALLREDUCE, n, 1 << 16, FUSIONS[fusion])
+    for call in range(2):
+        want = ox.tree_order_allreduce(x, roots, parents, w, oracle_op)
+        x = [want] * top.k
+        bl.blink_allreduce_op(bufs, n, bl.BLINK_INT32 if dtype == "int32" else bl.BLINK_FP32, code, sched, stream)
+        torch.cuda.synchronize()
+        for r in (0, 3, 7):
+            assert bufs[r].cpu().numpy().tobytes() == want.tobytes(), (call, r)
+    assert untouched()
+    assert sched.status()[0] == bl.BLINK_OK
+
+
+@pytest.mark.parametrize("fusion", ["edge", "node"])
+@pytest.mark.parametrize("k", [3, 5, 8, 13, 16])
+@pytest.mark.parametrize("n", [4_099, 300_002])
+def test_a_reduce_leaves_what_the_program_writes_on_the_way(k, n, fusion):
+    """The reduce phase alone: every rank's buffer, not only the root's, holds what
+    the step list leaves there.  The per-edge program writes a vertex's running sum
+    after every child and the per-node program once, so both leave the vertex's sum."""
+    stream = _stream()
+    forest = [_tree(k, s) for s in range(3)]
+    roots, parents, w = [r for r, _ in forest], [p for _, p in forest], [1.0, 2.0, 1.5]
+    trees = bl.blink_trees_from_arrays(k, roots, parents, w)
+    x = [si.payload(17, r, n, "uniform", "fp32") for r in range(k)]
+    want = [a.copy() for a in x]
+    ox.run_steps(want, osch.make_steps(roots, parents, w, osch.REDUCE_TO_ROOT, n, 5_000))
+    bufs, untouched = _slab(x)
+    sched = bl.blink_make_schedule(trees, bl.BLINK_OP_REDUCE, n, 5_000, FUSIONS[fusion])
+    bl.blink_reduce(bufs, n, bl.BLINK_FP32, bl.BLINK_SUM, sched, stream)
+    torch.cuda.synchronize()
+    for r, b in enumerate(bufs):
+        assert b.cpu().numpy().tobytes() == want[r].tobytes(), r
+    assert untouched()
+
+
+@pytest.mark.parametrize("fusion", FUSIONS)
+@pytest.mark.parametrize("op", ["broadcast", "reduce", "allreduce"])
+@pytest.mark.parametrize("n", [5_003, 400_001])
+def test_a_star_has_several_stages_that_wait_for_nothing(op, fusion, n):
+    """Two stars round one centre: the per-edge broadcast is five copies per chunk and tree
+    without a dependency among them."""
+    stream = _stream()
+    k, root = 6, 2
+    parent = [root] * k
+    parent[root] = -1
+    trees = bl.blink_trees_from_arrays(k, [root, root], [parent, parent], [1.0, 1.0])
+    x = [si.hash_payload(19, r, 0, n, "int32") for r in range(k)]
+    bufs, untouched = _slab(x)
+    which = {"broadcast": bl.BLINK_OP_BROADCAST, "reduce": bl.BLINK_OP_REDUCE, "allreduce": bl.BLINK_OP_ALLREDUCE}[op]
+    sched = bl.blink_make_schedule(trees, which, n, 1_000, FUSIONS[fusion])
+    if op == "broadcast":
+        bl.blink_broadcast(bufs, n, bl.BLINK_INT32, sched, stream)
+        want = [x[root]] * k
+    elif op == "reduce":
+        bl.blink_reduce(bufs, n, bl.BLINK_INT32, bl.BLINK_SUM, sched, stream)
+        want = list(x)
+        want[root] = ox.allreduce_int32_definition(x)
+    else:
+        bl.blink_allreduce(bufs, n, bl.BLINK_INT32, sched, stream)
+        want = [ox.allreduce_int32_definition(x)] * k
+    torch.cuda.synchronize()
+    for r, b in enumerate(bufs):
+        assert np.array_equal(b.cpu().numpy(), want[r]), r
+    assert untouched()
+
+
+@pytest.mark.parametrize("fusion", FUSIONS)
+@pytest.mark.parametrize("k,n_trees", [(4, 1), (5, 3), (8, 8), (16, 16)])
+@pytest.mark.parametrize("m", [5, 1_237, 70_001])
+def test_allgather_with_few_and_many_flows(k, n_trees, m, fusion):
+    """4, 15, 64 and 256 flows: tables in the arguments, in a wave's lanes and in memory."""
+    stream = _stream()
+    n = k * m
+    forest = [_tree(k, s) for s in range(n_trees)]
+    trees = bl.blink_trees_from_arrays(k, [r for r, _ in forest], [p for _, p in forest], [1.0] * n_trees)
+    x = [si.hash_payload(23, r, 0, n, "int32") for r in range(k)]
+    want = ox.allgather_definition(x)
+    bufs, untouched = _slab(x)
+    sched = bl.blink_make_schedule(trees, bl.BLINK_OP_ALLGATHER, n, 4_096, FUSIONS[fusion])
+    for _ in range(2):
+        bl.blink_allgather(bufs, n, bl.BLINK_INT32, sched, stream)
+    torch.cuda.synchronize()
+    for r, b in enumerate(bufs):
+        assert np.array_equal(b.cpu().numpy(), want), r
+    assert untouched()
+
+
+@pytest.mark.parametrize("fusion", ["node", "tree"])
+@pytest.mark.parametrize("wg,tile", [(1, 256), (2, 1024), (0, 16_384), (4, 65_536)])
+def test_launch_overrides(fusion, wg, tile):
+    """Tiles smaller and larger than the kernel's own, few and many workgroups, then automatic again."""
+    stream = _stream()
+    top = si.hybrid_cube_mesh()
+    trees = bl.blink_pack_trees(top.k, top.src, top.dst, top.cap, 0)
+    n = 1_000_003
+    x = [si.hash_payload(29, r, 0, n, "int32") for r in range(top.k)]
+    want = ox.allreduce_int32_definition(x).view(np.uint32).astype(np.uint64)
+    bufs, untouched = _slab(x)
+    sched = bl.blink_make_schedule(trees, bl.BLINK_OP_ALLREDUCE, n, 1 << 16, FUSIONS[fusion])
+    for call, launch in enumerate([(0, 0), (wg, tile), (wg, tile), (0, 0)]):
+        sched.set_launch(*launch)
+        bl.blink_allreduce(bufs, n, bl.BLINK_INT32, sched, stream)
+        torch.cuda.synchronize()
+        expect = ((want * np.uint64(pow(8, call, 1 << 32))) & np.uint64(0xFFFFFFFF)).astype(np.uint32)
+        for r in (0, 5):
+            assert np.array_equal(bufs[r].cpu().numpy().view(np.uint32), expect), (call, r)
+    assert untouched()
+
+
+def test_waiting_stages_after_calls_that_did_not_wait():
+    """A per-node schedule that has run on this kernel hands chunks over once a call has been
+    skipped, and is itself again after a reset."""
+    stream = _stream()
+    top = si.hybrid_cube_mesh()
+    trees = bl.blink_pack_trees(top.k, top.src, top.dst, top.cap, 0)
+    n = 3_000_001       # drawn tickets: the block's counters have moved
+    x = [si.hash_payload(31, r, 0, n, "int32") for r in range(top.k)]
+    want = ox.allreduce_int32_definition(x)
+    sched = bl.blink_make_schedule(trees, bl.BLINK_OP_ALLREDUCE, n, 1 << 16, bl.BLINK_FUSE_NODE)
+
+    def call():
+        bufs, untouched = _slab(x)
+        bl.blink_allreduce(bufs, n, bl.BLINK_INT32, sched, stream)
+        torch.cuda.synchronize()
+        return bufs, untouched
+    for _ in range(2):
+        bufs, untouched = call()
+        assert all(np.array_equal(b.cpu().numpy(), want) for b in bufs) and untouched()
+    sched.set_wait_limit(2000)
+    sched.test_skip_call()
+    call()
+    st, rec = sched.status()
+    assert st == bl.BLINK_ESTUCK and rec["call"] == 4 and rec["seen"] < rec["wanted"]
+    sched.reset()
+    sched.set_wait_limit(0)
+    for _ in range(2):
+        bufs, untouched = call()
+        assert all(np.array_equal(b.cpu().numpy(), want) for b in bufs) and untouched()
+    assert sched.status()[0] == bl.BLINK_OK
