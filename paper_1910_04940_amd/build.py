@@ -13,7 +13,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libblink.so")
-SOURCES = ["kernel_f32_stream.hip", "kernel_i32_stream.hip", "kernel_f32_many.hip", "kernel_i32_many.hip",
+SOURCES = ["kernel_f32.hip", "kernel_i32.hip",
            "fold_f32_sum.hip", "fold_i32_sum.hip", "fold_f32_other.hip", "fold_i32_other.hip",
            "fold_f32_mid.hip", "fold_i32_mid.hip", "fold_copy.hip", "exec.hip",
            "api.cpp", "pack.cpp", "schedule.cpp", "miad.cpp"]

@@ -54,10 +54,7 @@ void drop_trial_events(blink_schedule* h);  // below, with the choice among the 
         }                                                                                 \
     } while (0)
 
-KernelFn pick_kernel(blink_dtype_t dtype, bool many_waves) {
-    if (dtype == BLINK_FP32) return many_waves ? kernel_f32_many() : kernel_f32_stream();
-    return many_waves ? kernel_i32_many() : kernel_i32_stream();
-}
+KernelFn pick_kernel(blink_dtype_t dtype) { return dtype == BLINK_FP32 ? kernel_f32() : kernel_i32(); }
 
 size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -173,11 +170,7 @@ blink_status_t claim_static_block(blink_schedule* h, const BlockLayout& l, hipSt
 }
 
 // The plan where stages wait for one another.  Tickets move about
-// kTicketBytesHandOver bytes.  A payload too small to give the machine 16 such
-// tickets per CU is latency-bound instead ("wide"): then all the waves that fit
-// are used and the tile shrinks until a time slot, the part of the work that can
-// run at a time, has about 64 tiles; waves beyond what a slot can use do nothing
-// but poll.
+// kTicketBytesHandOver bytes.
 void plan_hand_over(blink_schedule* h) {
     LaunchPlan& pl = h->plan;
     const Schedule& s = h->s;
@@ -189,9 +182,6 @@ void plan_hand_over(blink_schedule* h) {
     unsigned tile = kMinTile;
     while (tile < kMaxTile && 2ull * tile * tile * bytes_per_elem * bytes_per_elem < ticket_bytes * ticket_bytes)
         tile *= 2;
-    pl.wide = work / tile < 16ull * h->n_cu;
-    if (pl.wide)
-        while (tile > kMinTile && work / s.n_slots / tile < 64) tile /= 2;
     if (h->tile_override) tile = h->tile_override;
     pl.tile_elems = tile;
     pl.tile_shift = 0;
@@ -587,7 +577,7 @@ blink_status_t run_hand_over(blink_schedule* h, void* const* bufs, blink_dtype_t
         if (blink_status_t st = upload(h, l)) return st;
         block = static_cast<char*>(h->d_block);
     }
-    KernelFn fn = pick_kernel(dtype, pl.wide);
+    KernelFn fn = pick_kernel(dtype);
     int& occ = h->occupancy[dtype == BLINK_FP32];
     if (occ == 0) {
         BLINK_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, kLanes, 0));
@@ -596,11 +586,11 @@ blink_status_t run_hand_over(blink_schedule* h, void* const* bufs, blink_dtype_t
             return BLINK_EHIP;
         }
     }
-    // Waves per CU: 4, some waves always wait (8 x 256 MiB per node 1.088 -> 1.023 ms
-    // against 3, per edge 1.242 -> 1.230); all that fit for small payloads.
-    int per_cu = std::min(occ, 4);
-    if (h->wg_per_cu > 0) per_cu = std::min(occ, h->wg_per_cu);
-    if (pl.wide && h->wg_per_cu == 0) per_cu = occ;
+    // Waves per CU: 3 (some always wait), with more than 8 ranks, whose programs have more
+    // stages that can run at a time, 4.  Per-edge AllReduce, us with 2 / 3 / 4: 8 ranks x
+    // 64 MiB in 1 MiB chunks 337 / 345 / 368, in 64 KiB chunks 342 / 325 / 331, in 16 KiB
+    // chunks 420 / 342 / 328; 16 ranks, one-hop trees, 64 MiB - / 694 / 670.
+    const int per_cu = std::min(occ, h->wg_per_cu > 0 ? h->wg_per_cu : (s.k > 8 ? 4 : 3));
     unsigned long long max_grid = static_cast<unsigned long long>(per_cu) * h->n_cu;
     const unsigned long long n_items = pl.n_items;
     // no more waves than three time slots' worth of tickets can be busy
@@ -627,10 +617,7 @@ blink_status_t run_hand_over(blink_schedule* h, void* const* bufs, blink_dtype_t
     p.tile_shift = pl.tile_shift;
     p.redop = static_cast<unsigned>(redop);
     p.n_inst = static_cast<unsigned>(s.inst.size());
-    // Waiting waves look at their dependency every ~0.2 us in small schedules,
-    // where a hand-over is most of the time (16 one-hop trees, 256 elements,
-    // per-edge: 47 -> 36 us), and back off to ~0.8 us in large ones.
-    p.max_naps = pl.wide ? 1 : 4;
+    p.max_naps = 4;   // looks at a dependency back off to ~0.8 us apart
 
     if (static_block)
         if (blink_status_t st = launch_clear(block, l.counters_end, stream)) return st;

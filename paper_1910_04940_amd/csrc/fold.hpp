@@ -120,23 +120,6 @@ struct FoldPiece {
     __device__ __forceinline__ unsigned folds(int i) const { return (seq[i / 4] >> ((i & 3) * 8 + 5)) & 7u; }
 };
 
-template <typename T, bool SUM, int U>
-__device__ __forceinline__ void fold_in(unsigned redop, U4 (&acc)[U], const U4 (&in)[U]) {
-    if constexpr (SUM) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) acc[u] = combine4<T>(BLINK_SUM, acc[u], in[u]);
-    } else if (redop == BLINK_MAX) {   // wave-uniform: one branch per operand, not per element
-#pragma unroll
-        for (int u = 0; u < U; ++u) acc[u] = combine4<T>(BLINK_MAX, acc[u], in[u]);
-    } else if (redop == BLINK_MIN) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) acc[u] = combine4<T>(BLINK_MIN, acc[u], in[u]);
-    } else {
-#pragma unroll
-        for (int u = 0; u < U; ++u) acc[u] = combine4<T>(BLINK_PROD, acc[u], in[u]);
-    }
-}
-
 // Up to three elements at either end of a flow that do not fill a 16-byte column,
 // one per lane.
 template <typename T, int N, bool SUM, bool MID, int LD, int ST>
@@ -345,7 +328,7 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
             unsigned mids = cur.stores >> 16;
             unsigned long long mid_rank = cur.mid_rank;
             auto add = [&](const U4 (&x)[U]) {
-                fold_in<T, SUM, U>(redop, acc, x);
+                combine_columns<T, SUM, U>(redop, acc, x);
                 if constexpr (MID) {
                     if (mids & 1u) store(acc, static_cast<unsigned>(mid_rank) & 15u, byte_off, bytes, mid_policy);
                     mids >>= 1;

@@ -1,9 +1,8 @@
 // The device side of schedules whose stages wait for one another (per-edge and
 // per-node programs; fold.hpp has the others): one persistent gfx950 kernel that
 // consumes the stage list of all trees concurrently (paper sections 3.3, 4.1, 4.2.1,
-// 4.2.2).  The kernel is a template; kernel_{f32,i32}_{many,stream}.hip instantiate it
-// for the two element types and the two column budgets (four translation units, so
-// that they compile side by side), exec.hip holds the launcher.
+// 4.2.2).  kernel_{f32,i32}.hip instantiate it for the two element types, exec.hip holds
+// the launcher.
 //
 // A workgroup is ONE 64-lane wavefront: nothing in the kernel needs a
 // workgroup barrier, and a wave that waits for a dependency holds up nobody
@@ -12,19 +11,11 @@
 // to wait for has already been drawn by a running wave, or is about to be (see
 // the kernel's loop): waiting can never deadlock, whatever the grid size.
 //
-// A tile (256..65536 elements, chosen per schedule) is cut into sub-tiles; a
-// sub-tile of a stage is processed in three phases by the 64 lanes, each owning
-// U 128-bit columns, where U is as large as the stage allows under a budget of
-// 32 columns in registers and LDS (a stage that reads 8 ranks gets U = 4, a
-// plain copy the maximum, 16), so that every wave keeps up to 32 KiB of loads
-// in flight whatever the stage looks like (16 columns for small payloads):
-//   1. load the sub-tile from every rank the stage reads; all loads are issued
-//      before the first is consumed, then parked in per-lane LDS slots;
-//   2. run the stage's micro-program (acc = slot / acc += slot / slot = acc)
-//      over the slots: this is where the tree's summation order is applied,
-//      with partial sums staged in LDS instead of going back to HBM;
-//   3. store acc to every rank the stage writes.
-// LDS slots are private to a lane (lane l only touches column l).
+// A tile (256..65536 elements, chosen per schedule) is cut into sub-tiles of up to U
+// 128-bit columns per lane and rank; a stage reads its ranks in order, combines them one
+// after the other and writes the result to its ranks.  A sub-tile's loads are issued
+// before the stores of the one in front of it, whose registers are free by then: vector
+// memory operations complete in order, so loads behind stores would wait for them.
 //
 // Chunk-granular hand-over (the paper's per-chunk event): a stage instance has
 // a 64-bit counter of finished tiles.  Counters are never reset; call number e
@@ -46,14 +37,6 @@
 namespace blink {
 
 constexpr int kLanes = 64;        // one wavefront per workgroup
-// 128-bit columns a lane holds in registers (and LDS slots) at once = ranks
-// read x U: 32 (32 KiB of LDS per wave) for payloads large enough to stream,
-// which run fastest with few waves that each keep many bytes in flight
-// (measured on 8 x 256 MiB, against 16 columns and one more wave per CU: per-node
-// stages 1.35 -> 1.19 ms, per-edge stages 1.52 -> 1.41 ms); 16 where every wave that
-// fits is wanted (small payloads).
-constexpr int kColumnsMany = 16;
-constexpr int kColumnsStream = 32;
 constexpr unsigned kMinTile = kLanes * 4;   // elements: one column per lane
 constexpr unsigned kMaxTile = 65536;        // elements
 // Progress counters sit 256 bytes apart: the few counters that are hot at any
@@ -159,6 +142,25 @@ __device__ __forceinline__ U4 combine4(unsigned op, U4 a, U4 b) {
     return r;
 }
 
+// acc (+)= in, U columns at a time; `redop` is wave-uniform: one branch per operand, not
+// per element (dispatched per column, minima and maxima took twice as long as sums).
+template <typename T, bool SUM, int U>
+__device__ __forceinline__ void combine_columns(unsigned redop, U4 (&acc)[U], const U4 (&in)[U]) {
+    if constexpr (SUM) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[u] = combine4<T>(BLINK_SUM, acc[u], in[u]);
+    } else if (redop == BLINK_MAX) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[u] = combine4<T>(BLINK_MAX, acc[u], in[u]);
+    } else if (redop == BLINK_MIN) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[u] = combine4<T>(BLINK_MIN, acc[u], in[u]);
+    } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[u] = combine4<T>(BLINK_PROD, acc[u], in[u]);
+    }
+}
+
 // Byte `field_offset + i` of a stage template, fetched as part of a 32-bit word
 // so that the scalar unit can do it.
 __device__ __forceinline__ unsigned tmpl_byte(ConstTmpl st, unsigned byte_index) {
@@ -206,139 +208,77 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rank_window(RankTable t, unsig
     return __builtin_amdgcn_make_buffer_rsrc(base, 0, static_cast<int>(bytes), kRawDword3);
 }
 
-// The micro-program of a stage over the LDS slots of one sub-tile, U columns per
-// lane.  All LDS reads of an operation are issued before the first is used, and
-// the sum, by far the most common operator, has a loop of its own: with the
-// operator dispatched per column inside one loop the compiler emitted a chain
-// of branches and a full wait after every single column read.
-// The operations come off a shift register that holds the whole program
-// (fetched with two wide scalar loads per tile), not from memory one by one.
-template <typename T, int U, bool SUM>
-__device__ __forceinline__ void run_program(U4* __restrict__ slots, const unsigned long long (&prog)[5], int n_op,
-                                            unsigned redop, int lane, U4 (&acc)[U]) {
-    unsigned long long q0 = prog[0], q1 = prog[1], q2 = prog[2], q3 = prog[3], q4 = prog[4];
-    for (int o = 0; o < n_op; ++o) {
-        const unsigned code = static_cast<unsigned>(q0) & 0xffu;
-        q0 = (q0 >> 8) | (q1 << 56);
-        q1 = (q1 >> 8) | (q2 << 56);
-        q2 = (q2 >> 8) | (q3 << 56);
-        q3 = (q3 >> 8) | (q4 << 56);
-        q4 >>= 8;
-        U4* sl = slots + (code & 63u) * (U * kLanes) + lane;
-        const unsigned kind = code >> 6;
-        if (kind == OP_ST) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) sl[u * kLanes] = acc[u];
-            continue;
-        }
-        U4 in[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) in[u] = sl[u * kLanes];
-        if (kind == OP_LD) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) acc[u] = in[u];
-        } else {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if constexpr (!SUM)
-                    acc[u] = combine4<T>(redop, acc[u], in[u]);
-                else if constexpr (std::is_same<T, float>::value)
-                    acc[u] = __builtin_bit_cast(U4, __builtin_bit_cast(F4, acc[u]) + __builtin_bit_cast(F4, in[u]));
-                else
-                    acc[u] = acc[u] + in[u];
-            }
-        }
-    }
-}
-
-// Phases 1-3 over `bytes` bytes (a multiple of 16) at byte_off for a stage that
-// reads N ranks, U columns per lane and sub-tile.
-//
-// The U columns of a sub-tile are not neighbours: with n sub-tiles to the tile,
-// sub-tile s takes columns s, s + n, s + 2n, ... (a column is one 16-byte access
-// per lane, 1 KiB).  All ranks are read at the same offsets at the same time,
-// and rank buffers an unlucky distance apart put equal offsets of all of them
-// on the same memory channel: neighbouring columns then make one burst of
-// N * U KiB into a single channel, spread columns several smaller ones into
-// different channels (measured with a standalone probe, 6 ranks x 128 MiB,
-// buffers 4 KiB or 68 KiB more than their size apart: 0.68 -> 0.80 of the HBM
-// peak; 5 ranks: 0.72 -> 0.78; buffers exactly their size apart: 0.80 -> 0.79).
-// Columns past the end of a ragged tile fall outside the window: such loads
-// return zeros and such stores are dropped.
+// A stage that reads N ranks over `bytes` bytes (a multiple of 16) at byte_off, U
+// columns per lane and sub-tile.  Columns past the end of a ragged tile fall outside
+// the window: such loads return zeros and such stores are dropped.
 template <typename T, int N, int U>
-__device__ __forceinline__ void run_vec(U4* __restrict__ slots, ConstParams p, RankTable ranks, ConstTmpl st,
-                                        unsigned long long byte_off, unsigned bytes, int lane) {
+__device__ __forceinline__ void run_stage(ConstParams p, RankTable ranks, ConstTmpl st, unsigned long long byte_off,
+                                          unsigned bytes, int lane) {
     constexpr unsigned kSubBytes = kLanes * U * 16;
     const unsigned redop = p->redop;
-    const int n_op = BLINK_TMPL(st, n_op, 0);
     const int n_store = BLINK_TMPL(st, n_store, 0);
-    const BLINK_CONST uint32_t* w = reinterpret_cast<const BLINK_CONST uint32_t*>(st);
-    constexpr unsigned kOpWord = offsetof(StageTmpl, op) / 4;
-    static_assert(offsetof(StageTmpl, op) % 8 == 0 && kMaxOps == 40, "the micro-program is fetched as five 64-bit words");
-    unsigned long long prog[5];
-#pragma unroll
-    for (int q = 0; q < 5; ++q)
-        prog[q] = static_cast<unsigned long long>(w[kOpWord + 2 * q]) |
-                  (static_cast<unsigned long long>(w[kOpWord + 2 * q + 1]) << 32);
-    const unsigned n_sub = (bytes + kSubBytes - 1) / kSubBytes;
-    for (unsigned sub = 0; sub < n_sub; ++sub) {
-        // phase 1: issue every load, then park the values in LDS
-        U4 r[N][U];
+    U4 r[N][U];
+    auto load = [&](unsigned at) {
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const __amdgpu_buffer_rsrc_t win = rank_window(ranks, BLINK_TMPL(st, load_rank, i), byte_off, bytes);
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                r[i][u] = __builtin_amdgcn_raw_buffer_load_b128(win, ((u * n_sub + sub) * kLanes + lane) * 16, 0, kPolicyLoadHandOver);
+                r[i][u] = __builtin_amdgcn_raw_buffer_load_b128(win, at + (u * kLanes + lane) * 16, 0, kPolicyLoadHandOver);
         }
-#pragma unroll
-        for (int i = 0; i < N; ++i)
-#pragma unroll
-            for (int u = 0; u < U; ++u) slots[(i * U + u) * kLanes + lane] = r[i][u];
-        // phase 2: the stage's micro-program
+    };
+    load(0);
+    for (unsigned at = 0; at < bytes; at += kSubBytes) {
         U4 acc[U];
-        if (redop == BLINK_SUM)
-            run_program<T, U, true>(slots, prog, n_op, redop, lane, acc);
-        else
-            run_program<T, U, false>(slots, prog, n_op, redop, lane, acc);
-        // phase 3: stores
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[u] = r[0][u];
+#pragma unroll
+        for (int i = 1; i < N; ++i) {
+            if (redop == BLINK_SUM)
+                combine_columns<T, true, U>(redop, acc, r[i]);
+            else
+                combine_columns<T, false, U>(redop, acc, r[i]);
+        }
+        if (at + kSubBytes < bytes) load(at + kSubBytes);
         for (int j = 0; j < n_store; ++j) {
             const __amdgpu_buffer_rsrc_t win = rank_window(ranks, BLINK_TMPL(st, store_rank, j), byte_off, bytes);
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                __builtin_amdgcn_raw_buffer_store_b128(acc[u], win, ((u * n_sub + sub) * kLanes + lane) * 16, 0, kPolicyStoreHandOver);
+                __builtin_amdgcn_raw_buffer_store_b128(acc[u], win, at + (u * kLanes + lane) * 16, 0, kPolicyStoreHandOver);
         }
     }
 }
 
-// Pick U for a stage that reads N ranks: the largest power of two (at most 16)
-// with N * U <= COLS that does not exceed the tile (cols = tile columns per lane).
-template <typename T, int N, int COLS>
-__device__ __forceinline__ void run_vec_n(U4* __restrict__ slots, ConstParams p, RankTable ranks, ConstTmpl st,
-                                          unsigned long long byte_off, unsigned bytes, unsigned cols, int lane) {
-    constexpr int kFit = COLS / N;
-    constexpr int kBudget = kFit >= 16 ? 16 : (kFit >= 8 ? 8 : (kFit >= 4 ? 4 : (kFit >= 2 ? 2 : 1)));
-    if constexpr (kBudget >= 16)
-        if (cols >= 16) return run_vec<T, N, 16>(slots, p, ranks, st, byte_off, bytes, lane);
-    if constexpr (kBudget >= 8)
-        if (cols >= 8) return run_vec<T, N, 8>(slots, p, ranks, st, byte_off, bytes, lane);
-    if constexpr (kBudget >= 4)
-        if (cols >= 4) return run_vec<T, N, 4>(slots, p, ranks, st, byte_off, bytes, lane);
-    if constexpr (kBudget >= 2)
-        if (cols >= 2) return run_vec<T, N, 2>(slots, p, ranks, st, byte_off, bytes, lane);
-    run_vec<T, N, 1>(slots, p, ranks, st, byte_off, bytes, lane);
-}
-
-template <typename T, int COLS>
-__device__ __forceinline__ void run_vec_any(U4* __restrict__ slots, ConstParams p, RankTable ranks, ConstTmpl st,
-                                            unsigned long long byte_off, unsigned bytes, unsigned cols, int lane) {
-    switch (BLINK_TMPL(st, n_load, 0)) {
-#define BLINK_CASE(N) case N: run_vec_n<T, N, COLS>(slots, p, ranks, st, byte_off, bytes, cols, lane); break;
-        BLINK_CASE(1) BLINK_CASE(2) BLINK_CASE(3) BLINK_CASE(4) BLINK_CASE(5) BLINK_CASE(6)
-        BLINK_CASE(7) BLINK_CASE(8) BLINK_CASE(9) BLINK_CASE(10) BLINK_CASE(11) BLINK_CASE(12)
-        BLINK_CASE(13) BLINK_CASE(14) BLINK_CASE(15) BLINK_CASE(16)
-#undef BLINK_CASE
-        default: break;
+// The same for any number of ranks, one after the other: the fan-ins of per-node programs,
+// which only come here after a skipped call (see blink_schedule_test_skip_call).
+template <typename T>
+__device__ __forceinline__ void run_stage_any(ConstParams p, RankTable ranks, ConstTmpl st, unsigned long long byte_off,
+                                              unsigned bytes, int lane) {
+    constexpr int U = 4;
+    const unsigned redop = p->redop;
+    const int n_load = BLINK_TMPL(st, n_load, 0), n_store = BLINK_TMPL(st, n_store, 0);
+    for (unsigned at = 0; at < bytes; at += kLanes * U * 16) {
+        U4 acc[U], in[U];
+        for (int i = 0; i < n_load; ++i) {
+            const __amdgpu_buffer_rsrc_t win = rank_window(ranks, BLINK_TMPL(st, load_rank, i), byte_off, bytes);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                in[u] = __builtin_amdgcn_raw_buffer_load_b128(win, at + (u * kLanes + lane) * 16, 0, kPolicyLoadHandOver);
+            if (i == 0) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) acc[u] = in[u];
+            } else if (redop == BLINK_SUM) {
+                combine_columns<T, true, U>(redop, acc, in);
+            } else {
+                combine_columns<T, false, U>(redop, acc, in);
+            }
+        }
+        for (int j = 0; j < n_store; ++j) {
+            const __amdgpu_buffer_rsrc_t win = rank_window(ranks, BLINK_TMPL(st, store_rank, j), byte_off, bytes);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                __builtin_amdgcn_raw_buffer_store_b128(acc[u], win, at + (u * kLanes + lane) * 16, 0, kPolicyStoreHandOver);
+        }
     }
 }
 
@@ -346,49 +286,36 @@ __device__ __forceinline__ void run_vec_any(U4* __restrict__ slots, ConstParams 
 // whose length is not a multiple of 4 elements, and chunks that do not start on
 // a 16-byte boundary.  Slow path; one element per lane.
 template <typename T>
-__device__ __forceinline__ void run_scalar(unsigned* __restrict__ slots, ConstParams p, RankTable ranks, ConstTmpl st,
-                                           unsigned long long byte_off, unsigned bytes, int lane) {
-    const int n_load = BLINK_TMPL(st, n_load, 0);
+__device__ __forceinline__ void run_scalar(ConstParams p, RankTable ranks, ConstTmpl st, unsigned long long byte_off,
+                                           unsigned bytes, int lane) {
+    const int n_load = BLINK_TMPL(st, n_load, 0), n_store = BLINK_TMPL(st, n_store, 0);
+    unsigned acc = 0;
     for (int i = 0; i < n_load; ++i) {
         const __amdgpu_buffer_rsrc_t win = rank_window(ranks, BLINK_TMPL(st, load_rank, i), byte_off, bytes);
-        slots[i * kLanes + lane] = __builtin_amdgcn_raw_buffer_load_b32(win, lane * 4, 0, kPolicyLoadHandOver);
+        const unsigned x = __builtin_amdgcn_raw_buffer_load_b32(win, lane * 4, 0, kPolicyLoadHandOver);
+        acc = i == 0 ? x : combine1<T>(p->redop, acc, x);
     }
-    unsigned acc = 0;
-    const unsigned redop = p->redop;
-    const int n_op = BLINK_TMPL(st, n_op, 0);
-    for (int o = 0; o < n_op; ++o) {
-        const unsigned code = BLINK_TMPL(st, op, o);
-        unsigned* sl = slots + (code & 63u) * kLanes + lane;
-        const unsigned kind = code >> 6;
-        if (kind == OP_LD)
-            acc = *sl;
-        else if (kind == OP_ADD)
-            acc = combine1<T>(redop, acc, *sl);
-        else
-            *sl = acc;
-    }
-    const int n_store = BLINK_TMPL(st, n_store, 0);
     for (int j = 0; j < n_store; ++j) {
         const __amdgpu_buffer_rsrc_t win = rank_window(ranks, BLINK_TMPL(st, store_rank, j), byte_off, bytes);
         __builtin_amdgcn_raw_buffer_store_b32(acc, win, lane * 4, 0, kPolicyStoreHandOver);
     }
 }
 
-// T: element type (float, or unsigned for wrap-around int32).  COLS: the column
-// budget (LDS slots per lane).  Stages hand chunks over to each other, possibly across
-// XCDs whose L2 caches are not coherent with one another: all rank-buffer accesses
-// use system-scope cache policy (loads bypass, stores write through; the loads also
-// carry the streaming hint, which changes no scope), so the hand-over needs no L2
-// write-back or invalidate, only "my stores have completed" before the counter is
-// bumped.
-// The kernel takes all 256 vector registers and 96 accumulation registers, so
-// one wave per SIMD fits (4 per CU); two, with spills, lose (per node, 8 x 256 MiB,
-// 1.054 -> 1.207 ms).
+// T: element type (float, or unsigned for wrap-around int32).  Stages hand chunks over
+// to each other, possibly across XCDs whose L2 caches are not coherent with one another:
+// all rank-buffer accesses use system-scope cache policy (loads bypass, stores write
+// through; the loads also carry the streaming hint, which changes no scope), so the
+// hand-over needs no L2 write-back or invalidate, only "my stores have completed" before
+// the counter is bumped.
+// Programs whose stages wait for one another combine their ranks in the order of
+// load_rank (edge_stages, node_stages in schedule.cpp): the micro-program is not looked at.
+// Bound by the memory side, which serves 140 bytes per element for 8 ranks: 8 x 64 MiB
+// per edge in 1 MiB chunks 345 us, 6.8 TB/s of requests (through LDS slots and the
+// micro-program, sub-tiles not overlapped: fp32 376, int32 410 us).
 // The by-value argument is only there to size the kernel-argument segment; it is
 // read through the constant address space (see ConstParams).
-template <typename T, int COLS>
+template <typename T>
 __global__ __launch_bounds__(kLanes, 1) void blink_consume(const KParams) {
-    __shared__ U4 slots[COLS * kLanes];  // 16 or 32 KiB: COLS columns per lane
     const int lane = threadIdx.x;
     ConstParams p = (ConstParams)__builtin_amdgcn_kernarg_segment_ptr();
     const RankTable ranks = load_rank_table(p, lane);
@@ -401,7 +328,6 @@ __global__ __launch_bounds__(kLanes, 1) void blink_consume(const KParams) {
     const unsigned tiles_per_chunk = p->tiles_per_chunk;
     const unsigned tile_shift = p->tile_shift;
     const unsigned tile_elems = 1u << tile_shift;
-    const unsigned cols = min(tile_elems / kMinTile, static_cast<unsigned>(COLS));
     const unsigned n_inst = p->n_inst;
 
     // Lane-dependent regions.  readfirstlane needs lane 0 present, so the
@@ -516,16 +442,21 @@ __global__ __launch_bounds__(kLanes, 1) void blink_consume(const KParams) {
             const unsigned long long e0 = lo_e;  // first element of the tile
             if ((e0 & 3ull) == 0) {
                 const unsigned vec_bytes = (tlen >> 2) * 16u;
-                if (vec_bytes) run_vec_any<T, COLS>(slots, p, ranks, st, e0 * 4ull, vec_bytes, cols, lane);
+                if (vec_bytes) {
+                    const unsigned n_load = BLINK_TMPL(st, n_load, 0);
+                    if (n_load == 1)
+                        run_stage<T, 1, 16>(p, ranks, st, e0 * 4ull, vec_bytes, lane);
+                    else if (n_load == 2)
+                        run_stage<T, 2, 16>(p, ranks, st, e0 * 4ull, vec_bytes, lane);
+                    else
+                        run_stage_any<T>(p, ranks, st, e0 * 4ull, vec_bytes, lane);
+                }
                 const unsigned rem = tlen & 3u;  // only where the payload itself ends off a 16-byte boundary
-                if (rem)
-                    run_scalar<T>(reinterpret_cast<unsigned*>(slots), p, ranks, st, e0 * 4ull + vec_bytes,
-                                          rem * 4u, lane);
+                if (rem) run_scalar<T>(p, ranks, st, e0 * 4ull + vec_bytes, rem * 4u, lane);
             } else {
                 // chunk size not a multiple of 4 elements: element-wise, slow but correct
                 for (unsigned b = 0; b < tlen * 4u; b += kLanes * 4u)
-                    run_scalar<T>(reinterpret_cast<unsigned*>(slots), p, ranks, st, e0 * 4ull + b,
-                                          min(static_cast<unsigned>(kLanes) * 4u, tlen * 4u - b), lane);
+                    run_scalar<T>(p, ranks, st, e0 * 4ull + b, min(static_cast<unsigned>(kLanes) * 4u, tlen * 4u - b), lane);
             }
 
             if (BLINK_TMPL(st, signals, 0)) {
@@ -541,11 +472,9 @@ __global__ __launch_bounds__(kLanes, 1) void blink_consume(const KParams) {
 // ---- what the launcher sees ---------------------------------------------------------
 using KernelFn = void (*)(const KParams);
 
-// Per element type and column budget (many: kColumnsMany, stream: kColumnsStream),
-// each in a translation unit of its own, so that the four compile side by side.
-KernelFn kernel_f32_many();
-KernelFn kernel_f32_stream();
-KernelFn kernel_i32_many();
-KernelFn kernel_i32_stream();
+// Per element type, each in a translation unit of its own, so that they compile side by
+// side.
+KernelFn kernel_f32();
+KernelFn kernel_i32();
 
 }  // namespace blink

@@ -16,7 +16,6 @@ struct LaunchPlan {
     bool made = false;
     unsigned tile_elems = 0;       // elements per tile (ticket)
     // stages that wait for one another (kernel.hpp)
-    bool wide = false;             // small payload: use every wave that fits
     unsigned tile_shift = 0;       // log2 of tile_elems
     uint32_t tiles_per_chunk = 1;  // most tiles any stage instance has
     uint64_t n_items = 0;          // tickets per call
