@@ -192,12 +192,12 @@ void plan_hand_over(blink_schedule* h) {
 // The plan where the fold kernel runs the schedule.  A ticket is one sub-tile of the
 // kernel, or as many as make it move 96 KiB: the one ticket counter then has to
 // serve about 65 draws per microsecond at most.
-// A payload of at most five tiles per CU gets a workgroup for every tile: they are
-// all resident at once or nearly so, and no ticket has to be drawn (probe, 8 ranks,
+// A payload of at most five tiles (of 128 KiB read and written) per CU gets a workgroup for
+// every tile: they are all resident at once or nearly so, and no ticket has to be drawn (probe, 8 ranks,
 // workgroup per tile against 224 that draw: 2 MiB per rank 5.1 / 7.2 us, 4 MiB 9.6 /
 // 10.8, 7 MiB (3.5 tiles per CU) 14.4 / 16.2, 10.4 MiB (5.2) 25 / 25, 16 MiB 51 / 47).
 constexpr unsigned kFoldTicketBytes = 96 * 1024;
-constexpr unsigned kFoldSmallTilesPerCu = 5;
+constexpr uint64_t kFoldSmallBytesPerCu = 5 * 128 * 1024;
 constexpr unsigned kFoldHalfTilesPerCu = 2;   // up to here half tiles are faster (see fold_columns)
 
 void plan_fold(blink_schedule* h) {
@@ -214,7 +214,7 @@ void plan_fold(blink_schedule* h) {
     uint64_t tiles = 0;
     for (const FoldFlow& f : pl.flows) tiles += (f.len + sub - 1) / sub;
     const uint64_t cus = static_cast<uint64_t>(h->n_cu);
-    pl.small = tiles <= kFoldSmallTilesPerCu * cus;
+    pl.small = tiles * sub * 4 * (pl.n_load + n_store) <= kFoldSmallBytesPerCu * cus;
     // a tile per flow more than that: shares need not be whole tiles
     pl.half = tiles <= kFoldHalfTilesPerCu * cus + pl.flows.size() && fold_has_half(n, pl.all);
     if (pl.small) tile = fold_sub_elems(n, pl.all, pl.half);
@@ -519,11 +519,15 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     const FoldFn fn = pick_fold(dtype, sum, pl, policy);
     if (!fn) return BLINK_EINVAL;
 
-    // Workgroups: all tiles of a small payload; otherwise 7 on 8 CUs (see fold.hpp), where
-    // one rank is read and others written 6 on 8 (Broadcast to 7 ranks, probe, 64 MiB:
-    // 128 / 192 / 256 workgroups 76.8 / 69.0 / 74.0 us).
+    // Workgroups: all tiles of a small payload; otherwise 7 on 8 CUs (see fold.hpp).  Copies
+    // have 16 KiB of loads per workgroup and n_store times that of stores in flight: 6 on 8 CUs
+    // where seven ranks or more are written, one on each where one is (us with 192 / 224 / 256
+    // workgroups: Broadcast to 7, 64 MiB, 73.2 / 75.5 / 78.4; to 4, 60 MiB, 44.1 / 44.2 / 44.3; to 2,
+    // 200 MiB, 114 / 106 / 102; Gather of 3 ranks, 200 MiB, 57.9 / 53.2 / 51.3).
     const uint64_t cus = static_cast<uint64_t>(h->n_cu);
-    uint64_t most = pl.small ? pl.n_items : cus * (pl.n_load == 1 ? 6 : 7) / 8;
+    const uint32_t n_store = s.fused[0].stage.n_store;
+    const uint64_t eighths = pl.n_load > 1 ? 7 : n_store >= 7 ? 6 : n_store > 2 ? 7 : 8;
+    uint64_t most = pl.small ? pl.n_items : cus * eighths / 8;
     if (h->wg_per_cu > 0) most = h->wg_per_cu * cus;
     const unsigned grid = static_cast<unsigned>(std::max<uint64_t>(1, std::min(most, pl.n_items)));
     const bool dealt = pl.small || grid == pl.n_items;
