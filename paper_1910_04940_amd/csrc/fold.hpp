@@ -37,8 +37,9 @@ constexpr int kFoldWaves = 4;
 constexpr int kFoldThreads = kFoldWaves * kLanes;
 // Tables of at most this many flows (and no more levels) travel in the kernel's
 // arguments: a schedule that fits needs no block on the device for small payloads.
-// (Copying arguments costs the host: room for 16 flows made a call 0.2 us longer.)
-constexpr int kInlineFlows = 8;
+// (Copying arguments costs the host: room for 16 flows instead of 4 made a call 0.3 us
+// longer.)
+constexpr int kInlineFlows = 4;
 // Up to this many flows a wave keeps the tables in vector registers, lane f holding
 // flow f's words and lane l level l's: they are fetched beside the arguments, not
 // after them, and a ticket is resolved without touching memory.  (With scalar loads
