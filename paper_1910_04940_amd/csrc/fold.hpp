@@ -133,10 +133,13 @@ __device__ __forceinline__ void fold_edges(RankTable ranks, const FoldPiece<N>& 
     const unsigned bytes = (pc.to - pc.from) * 4u;
     const unsigned at = mine ? (e - pc.from) * 4u : 0x7ffffff0u;  // outside the window: nothing happens
     unsigned acc = 0, depth = 0;
-    constexpr int kWords = (N + 3) / 4;
-    unsigned seq[kWords];
+    // All loads first: they travel together (one after the other they cost a payload of
+    // 16 Ki elements on 8 ranks 1 us).  After the wait nothing of this path is outstanding.
+    unsigned x[N];
 #pragma unroll
-    for (int q = 0; q < kWords; ++q) seq[q] = pc.seq[q];
+    for (int i = 0; i < N; ++i)
+        x[i] = __builtin_amdgcn_raw_buffer_load_b32(rank_window(ranks, pc.rank(i), byte_off, bytes), at, 0, LD);
+    __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));   // vmcnt(0)
     unsigned mids = pc.stores >> 16;
     unsigned long long mid_rank = pc.mid_rank;
     auto add = [&](unsigned x) {
@@ -149,22 +152,18 @@ __device__ __forceinline__ void fold_edges(RankTable ranks, const FoldPiece<N>& 
             mid_rank >>= 4;
         }
     };
-    // not unrolled: rarely run, and every load's answer is read in the iteration that asks for it
-#pragma unroll 1
-    for (int i = 0; i < N; ++i) {
-        const unsigned code = seq[0] & 0xffu;
+    acc = x[0];
 #pragma unroll
-        for (int q = 0; q < kWords; ++q) seq[q] = (seq[q] >> 8) | (q + 1 < kWords ? seq[(q + 1) % kWords] << 24 : 0u);
-        const __amdgpu_buffer_rsrc_t win = rank_window(ranks, code & 15u, byte_off, bytes);
-        const unsigned x = __builtin_amdgcn_raw_buffer_load_b32(win, at, 0, LD);
-        if (code & 16u) {
-            if (i) park[depth++ * kLanes + lane] = acc;
-            acc = x;
+    for (int i = 1; i < N; ++i) {
+        if (N >= 4 && pc.push(i)) {
+            park[depth++ * kLanes + lane] = acc;
+            acc = x[i];
         } else {
-            add(x);
+            add(x[i]);
         }
+        if (N >= 4)
 #pragma unroll 1
-        for (unsigned f = code >> 5; f; --f) add(park[--depth * kLanes + lane]);
+            for (unsigned f = pc.folds(i); f; --f) add(park[--depth * kLanes + lane]);
     }
 #pragma unroll 1
     for (unsigned left = pc.stores & 0xffffu; left; left &= left - 1) {
@@ -319,6 +318,9 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
         for (int j = 0; j < kStores; ++j) store(nothing, 0, 0, 0, final_policy);
     }
     for (;;) {
+        // the tile's loads are on their way; one wave's join them
+        if (((cur.from | cur.to) & 3u) && cur.from < cur.to && wave == kFoldWaves - 1)
+            fold_edges<T, N, SUM, MID, LD, ST>(ranks, cur, redop, edge_parked, lane);
         unsigned long long byte_off;
         const unsigned bytes = vector_bytes(cur, &byte_off);
         U4 acc[U];
@@ -389,8 +391,6 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
             for (unsigned left = cur.stores & 0xffffu; left; left &= left - 1)
                 store(acc, __builtin_ctz(left), byte_off, bytes, final_policy);
         }
-        if (((cur.from | cur.to) & 3u) && cur.from < cur.to && wave == 0)
-            fold_edges<T, N, SUM, MID, LD, ST>(ranks, cur, redop, edge_parked, lane);
         if (!more) break;
         cur = next;
     }
