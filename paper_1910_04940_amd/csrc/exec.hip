@@ -393,11 +393,14 @@ int choose_way(blink_schedule* h, bool static_block, bool sum, bool can_front, b
         if (c >= n_ways) best[c % n_ways] = std::min(best[c % n_ways], ms);
     }
     if (!ok) (void)hipGetLastError();
-    // The first way keeps the schedule unless another beats it by more than the
-    // 2 % by which such minima scatter from one trial to the next.
-    int fastest = 0;
-    float bar = best[0] * 0.98f;
-    for (int w = 1; ok && w < n_ways; ++w)
+    // Way 2, or way 1 where there is none, gets the schedule unless another beats it by more
+    // than the 2 % by which such minima scatter from one trial to the next: it is the fastest
+    // or within 1 % of it on most shapes (three sets of buffers in turn, us for ways 1 / 2 / 3:
+    // two servers of 8 x 64 MiB 344 / 336 / -, 6 ranks x 97.6 MiB 209 / 196 / 204, 8 x 230 MiB
+    // 664 / 614 / 634; the other way round 8 x 256 MiB 717 / 735 / 786).
+    int fastest = can_front ? 1 : 0;
+    float bar = best[fastest] * 0.98f;
+    for (int w = 0; ok && w < n_ways; ++w)
         if (best[w] < bar) {
             fastest = w;
             bar = best[w];
