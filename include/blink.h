@@ -303,7 +303,7 @@ void blink_schedule_free(blink_schedule_t* s);
  * k, n_elems and the collective must be those the schedule was made for
  * (BLINK_EMISMATCH otherwise).  With n_elems == 0 the call does nothing and
  * does not look at the entries of bufs (they may be null).  The first call
- * on a schedule also allocates and fills its small device-side tables
+ * on a schedule that needs them also allocates and fills its small device-side tables
  * (synchronously). */
 blink_status_t blink_allreduce(void* const* bufs, int k, size_t n_elems, blink_dtype_t dtype,
                                blink_schedule_t* s, void* stream);
@@ -364,7 +364,7 @@ blink_status_t blink_schedule_set_launch(blink_schedule_t* s, int wg_per_cu, int
  * be served in up to three ways at streaming sizes; they give the same bits.
  * 1 = tile by tile across the trees (chunk by chunk where a stage reads more than 8
  * ranks); 2 = one front through the payload, results written past the GPU's
- * memory-side cache where they do not fit it (sums only, stages whose partial sums
+ * memory-side cache from twice its size (sums only, stages whose partial sums
  * need at most four accumulators); 3 = the trees taking turns chunk by
  * chunk (section 4.2.2 at the paper's own granularity) instead of tile by tile
  * (several trees only).  kernel: 0 = automatic: the first calls of at least
@@ -382,8 +382,8 @@ int blink_schedule_last_kernel(const blink_schedule_t* s);
  * waits for another (whole-tree fusion).  alternate = 1 (the default): the
  * second, fourth, ... call on such a schedule goes through the tiles backwards
  * and results are written with a policy that lets them stay in the GPU's
- * 256 MiB memory-side cache (way 2 of blink_schedule_set_kernel: only where they fit
- * it), so a call on the buffers of the call before it
+ * 256 MiB memory-side cache (way 2 of blink_schedule_set_kernel: below twice
+ * that), so a call on the buffers of the call before it
  * (training iterations without much else in between, benchmark loops) starts
  * on data that is still there.  alternate = 0: every call goes forwards and
  * streams its stores past the cache.  Same bits either way; schedules with

@@ -97,6 +97,7 @@ blink_status_t blink_make_schedule(const blink_trees_t* trees, blink_op_t op, si
     h->id = blink::next_schedule_id();
     const blink_status_t st = blink::make_schedule(trees->t, op, n_elems, chunk_elems, fusion, h->s);
     if (st != BLINK_OK) return st;
+    blink::fold_tables(h->s, &h->fold);
     *out = h.release();
     return BLINK_OK;
     BLINK_GUARD_END
@@ -123,6 +124,7 @@ blink_status_t blink_make_schedule_servers(int n_servers, const blink_trees_t* c
     h->id = blink::next_schedule_id();
     const blink_status_t st = blink::make_schedule_servers(servers, n_elems, chunk_elems, fusion, h->s);
     if (st != BLINK_OK) return st;
+    blink::fold_tables(h->s, &h->fold);
     *out = h.release();
     return BLINK_OK;
     BLINK_GUARD_END

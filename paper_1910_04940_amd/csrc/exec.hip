@@ -76,6 +76,11 @@ BlockLayout layout_of(const Schedule& s) {
 // Bytes at the head of a block that are zero when a schedule is new.
 size_t cleared_bytes(const LaunchPlan& pl, const BlockLayout& l) { return pl.fold ? l.done : l.counters_end; }
 
+// What of a fold plan travels in the kernel's arguments.  Levels that do not are those of
+// the plan's tile size for every distance past a 1 KiB boundary.
+bool words_inline(const blink_schedule& h) { return h.fold.flows.size() <= kInlineFlows; }
+bool levels_inline(const blink_schedule& h) { return h.fold.levels.size() <= kInlineFlows; }
+
 // Copy a schedule's tables into a block on the current device.  Synchronous.
 blink_status_t copy_tables(const blink_schedule& h, const BlockLayout& l, char* block) {
     const LaunchPlan& pl = h.plan;
@@ -83,11 +88,11 @@ blink_status_t copy_tables(const blink_schedule& h, const BlockLayout& l, char* 
     if (!pl.fold) {
         BLINK_HIP(hipMemcpy(block + l.tmpl, s.tmpl.data(), s.tmpl.size() * sizeof(StageTmpl), hipMemcpyHostToDevice));
         BLINK_HIP(hipMemcpy(block + l.inst, s.inst.data(), s.inst.size() * sizeof(StageInst), hipMemcpyHostToDevice));
-    } else if (!pl.tables_inline) {
-        std::vector<uint32_t> words(kFlowWords * pl.flows.size());
-        fold_words(pl.flows, static_cast<uint32_t>(pl.flows.size()), words.data());
-        BLINK_HIP(hipMemcpy(block + l.words, words.data(), words.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-        BLINK_HIP(hipMemcpy(block + l.levels, pl.levels.data(), pl.levels.size() * sizeof(FoldLevel), hipMemcpyHostToDevice));
+    } else if (!words_inline(h)) {
+        const FoldTables& t = h.fold;
+        BLINK_HIP(hipMemcpy(block + l.words, t.words.data(), t.words.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
+        if (!levels_inline(h))
+            BLINK_HIP(hipMemcpy(block + l.levels, t.levels.data(), t.levels.size() * sizeof(FoldLevel), hipMemcpyHostToDevice));
     }
     return BLINK_OK;
 }
@@ -212,17 +217,16 @@ void plan_fold(blink_schedule* h) {
     unsigned tile = sub;
     while (tile * 4 * (pl.n_load + n_store) < kFoldTicketBytes) tile += sub;
     uint64_t tiles = 0;
-    for (const FoldFlow& f : pl.flows) tiles += (f.len + sub - 1) / sub;
+    for (const FoldFlow& f : h->fold.flows) tiles += (f.len + sub - 1) / sub;
     const uint64_t cus = static_cast<uint64_t>(h->n_cu);
     pl.small = tiles * sub * 4 * (pl.n_load + n_store) <= kFoldSmallBytesPerCu * cus;
     // a tile per flow more than that: shares need not be whole tiles
-    pl.half = tiles <= kFoldHalfTilesPerCu * cus + pl.flows.size() && fold_has_half(n, pl.all);
+    pl.half = tiles <= kFoldHalfTilesPerCu * cus + h->fold.flows.size() && fold_has_half(n, pl.all);
     if (pl.small) tile = fold_sub_elems(n, pl.all, pl.half);
     if (h->tile_override) tile = h->tile_override;
     pl.tile_elems = tile;
-    pl.tables_inline = pl.flows.size() <= kInlineFlows;
     pl.grid_shift = 0;
-    pl.n_items = fold_levels(pl.flows, tile, 0, !pl.tables_inline, &pl.levels);
+    pl.n_items = fold_levels(h->fold.flows, tile, 0, !words_inline(*h), &h->fold.levels);
 }
 
 // Whether a schedule runs on the fold kernel.  Without dependencies: always.  With them
@@ -252,7 +256,7 @@ blink_status_t make_plan(blink_schedule* h) {
         if (n_cu < 1) return BLINK_EHIP;
         h->n_cu = n_cu;
     }
-    pl.fold = may_fold(*h) && fold_flows(h->s, &pl.flows);
+    pl.fold = may_fold(*h) && h->fold.fits;
     if (pl.fold)
         plan_fold(h);
     else
@@ -270,10 +274,12 @@ blink_status_t make_plan(blink_schedule* h) {
 blink_status_t reset_progress(blink_schedule* h) {
     h->epoch = 0;
     for (uint64_t& b : h->ticket_base) b = 0;
+    // The next plan may need other tables, in a static block too: levels that lie there, or the
+    // flows' words after calls whose stages waited.
+    if (h->call_skipped || (h->plan.fold && !levels_inline(*h))) h->id = next_schedule_id();
+    h->tables_stale = true;
     h->plan = LaunchPlan();
     h->call_skipped = false;
-    h->tables_stale = true;       // the next plan may have others
-    h->id = next_schedule_id();   // in a static block, too
     h->occupancy[0] = h->occupancy[1] = 0;
     drop_trial_events(h);
     h->picked = 0;
@@ -493,31 +499,34 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     bool common = true;
     for (int i = 1; i < s.k; ++i) common = common && (reinterpret_cast<uintptr_t>(bufs[i]) & 1023u) == past;
     if (common) grid_shift = static_cast<uint32_t>(past / 4);
-    if (pl.tables_inline && grid_shift != pl.grid_shift) {
-        pl.n_items = fold_levels(pl.flows, pl.tile_elems, grid_shift, false, &pl.levels);
+    const FoldTables& t = h->fold;
+    if (words_inline(*h) && grid_shift != pl.grid_shift) {
+        pl.n_items = fold_levels(t.flows, pl.tile_elems, grid_shift, false, &h->fold.levels);
         pl.grid_shift = grid_shift;
     }
 
     const bool sum = redop == BLINK_SUM;
-    const bool by_tile = pl.n_load <= 8 && pl.flows.size() <= 64;
+    const bool by_tile = pl.n_load <= 8 && t.flows.size() <= 64;
     int timed = -1;
     const bool choice = !pl.small && !s.has_deps;   // programs with dependencies have way 1 only
-    const int way = choose_way(h, static_block, sum, choice && s.max_stack <= 4, choice && by_tile && pl.flows.size() > 1, &timed);
+    const int way = choose_way(h, static_block, sum, choice && s.max_stack <= 4, choice && by_tile && t.flows.size() > 1, &timed);
     const uint64_t chunk_tiles = std::max<uint64_t>(1, s.chunk / pl.tile_elems);
     const uint32_t chunk_turn = static_cast<uint32_t>(std::min<uint64_t>(chunk_tiles, kTurnPayload));
 
     // Rank buffers that together fit the memory-side cache (256 MiB) are written
     // so that results may stay there: whoever reads them next (here: the next call)
     // finds them.  Larger ones too where calls alternate their direction: a call
-    // then starts on the last 256 MiB that the call before it wrote (3 ranks x
-    // 128 MiB, repeated in place: 0.75 -> 0.83 of the HBM peak, 8 x 256 MiB 0.774 ->
-    // 0.787).  Way 2 streams such results, which is 1 to 2 % faster where the next call
-    // works on other buffers; the trial decides.
-    const bool fits_cache = static_cast<uint64_t>(s.k) * s.n * 4 <= kMemorySideCacheBytes;
+    // then starts on the last 256 MiB that the call before it wrote (repeated in place,
+    // 3 ranks x 98 MiB 98 -> 86 us, 8 x 256 MiB 701 -> 687).  From twice the cache way 2
+    // streams them, which is 1 to 3 % faster where the next call works on other buffers (6 ranks x
+    // 98 MiB 196 -> 191).
+    const uint64_t payload_bytes = static_cast<uint64_t>(s.k) * s.n * 4;
+    const bool fits_cache = payload_bytes <= kMemorySideCacheBytes;
+    const bool streams = s.has_deps || !h->sweep_alternates || (way == 2 && payload_bytes >= 2 * kMemorySideCacheBytes);
     int policy = kFoldKeep;
     if (pl.n_load == 1 && s.fused[0].stage.n_store > 1)
         policy = kFoldSpread;
-    else if (!fits_cache && (way == 2 || s.has_deps || !h->sweep_alternates))
+    else if (!fits_cache && streams)
         policy = kFoldStream;
     const FoldFn fn = pick_fold(dtype, sum, pl, policy);
     if (!fn) return BLINK_EINVAL;
@@ -538,26 +547,21 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     if (static_block) {
         if (!dealt)
             if (blink_status_t st = launch_clear(block, l.done, stream)) return st;
-    } else if (!dealt || !pl.tables_inline) {
+    } else if (!dealt || !words_inline(*h)) {
         if (blink_status_t st = upload(h, l)) return st;
         block = static_cast<char*>(h->d_block);
     }
     FoldParams p;   // every field that is read is set
     for (int i = 0; i < BLINK_MAX_RANKS; ++i) p.buf[i] = i < s.k ? bufs[i] : nullptr;
-    p.words = nullptr;
-    p.levels = nullptr;
-    if (pl.tables_inline) {
-        fold_words(pl.flows, kInlineFlows, p.inline_words);
-        std::copy(pl.levels.begin(), pl.levels.end(), p.inline_levels);
-    } else {
-        p.words = reinterpret_cast<const unsigned*>(block + l.words);
-        p.levels = reinterpret_cast<const FoldLevel*>(block + l.levels);
-    }
+    p.words = words_inline(*h) ? nullptr : reinterpret_cast<const unsigned*>(block + l.words);
+    p.levels = levels_inline(*h) ? nullptr : reinterpret_cast<const FoldLevel*>(block + l.levels);
+    if (!p.words) fold_words(t.flows, kInlineFlows, p.inline_words);
+    if (!p.levels) std::copy(t.levels.begin(), t.levels.end(), p.inline_levels);
     p.ticket = block ? reinterpret_cast<unsigned long long*>(block + l.ticket) : nullptr;
     p.ticket_base = static_block ? 0 : h->ticket_base[0];
     p.n_items = static_cast<unsigned>(pl.n_items);
-    p.n_flows = static_cast<unsigned>(pl.flows.size());
-    p.n_levels = static_cast<unsigned>(pl.levels.size());
+    p.n_flows = static_cast<unsigned>(t.flows.size());
+    p.n_levels = static_cast<unsigned>(t.levels.size());
     p.turn = way == 2 || s.has_deps ? kTurnPayload : (way == 3 || !by_tile) ? chunk_turn : 1u;
     p.tile_elems = pl.tile_elems;
     p.grid_shift = grid_shift;

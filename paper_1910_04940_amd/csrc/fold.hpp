@@ -35,8 +35,8 @@ namespace blink {
 
 constexpr int kFoldWaves = 4;
 constexpr int kFoldThreads = kFoldWaves * kLanes;
-// Tables of at most this many flows (and no more levels) travel in the kernel's
-// arguments: a schedule that fits needs no block on the device for small payloads.
+// At most this many flows, and levels, travel in the kernel's arguments: a schedule
+// whose flows fit needs no block on the device for small payloads.
 // (Copying arguments costs the host: room for 16 flows instead of 4 made a call 0.3 us
 // longer.)
 constexpr int kInlineFlows = 4;

@@ -120,28 +120,41 @@ inline bool fold_flows(const Schedule& s, std::vector<FoldFlow>* out) {
     return true;
 }
 
-// The levels of flows that are sorted longest first; returns the ticket count.
+// The levels of flows that are sorted longest first; returns the ticket count.  A flow
+// has a level of its own at most: with room for that many nothing is allocated.
 // every_shift: tile counts that suffice for any grid_shift (a flow may then get a
 // ticket that stands for no element).
 inline uint64_t fold_levels(const std::vector<FoldFlow>& flows, uint32_t tile_elems, uint32_t grid_shift, bool every_shift,
                             std::vector<FoldLevel>* out) {
     out->clear();
-    std::vector<uint32_t> count(flows.size());
-    for (size_t f = 0; f < flows.size(); ++f)
-        count[f] = every_shift ? static_cast<uint32_t>((flows[f].len + 255 + tile_elems - 1) / tile_elems)
-                               : fold_tiles(flows[f].off, flows[f].len, tile_elems, grid_shift);
-    // a flow that is no longer than the one before it may still touch one tile more
-    for (size_t f = flows.size(); f-- > 1;) count[f - 1] = std::max(count[f - 1], count[f]);
     uint64_t tickets = 0;
     uint32_t base = 0;
     for (size_t m = flows.size(); m > 0; --m) {
-        if (count[m - 1] == base) continue;
-        const uint32_t tiles = count[m - 1] - base;
-        out->push_back({static_cast<uint32_t>(tickets), base, tiles, static_cast<uint32_t>(m)});
-        tickets += static_cast<uint64_t>(tiles) * m;
-        base = count[m - 1];
+        // a flow that is no longer than the one before it may still touch one tile more:
+        // that one then gets a ticket without elements
+        const uint32_t count = every_shift ? static_cast<uint32_t>((flows[m - 1].len + 255 + tile_elems - 1) / tile_elems)
+                                           : fold_tiles(flows[m - 1].off, flows[m - 1].len, tile_elems, grid_shift);
+        if (count <= base) continue;
+        out->push_back({static_cast<uint32_t>(tickets), base, count - base, static_cast<uint32_t>(m)});
+        tickets += static_cast<uint64_t>(count - base) * m;
+        base = count;
     }
     return tickets;
+}
+
+// What the fold kernel needs of a schedule, worked out with it: calls allocate nothing.
+struct FoldTables {
+    bool fits = false;               // the kernel can run the schedule
+    std::vector<FoldFlow> flows;
+    std::vector<uint32_t> words;     // fold_words, stride = number of flows
+    std::vector<FoldLevel> levels;   // room for one per flow; filled by the launch plan
+};
+inline void fold_tables(const Schedule& s, FoldTables* out) {
+    out->fits = fold_flows(s, &out->flows);
+    if (!out->fits) out->flows.clear();
+    out->words.assign(kFlowWords * out->flows.size(), 0);
+    fold_words(out->flows, static_cast<uint32_t>(out->flows.size()), out->words.data());
+    out->levels.reserve(out->flows.size());
 }
 
 }  // namespace blink

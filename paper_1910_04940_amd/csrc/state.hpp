@@ -25,11 +25,8 @@ struct LaunchPlan {
     bool half = false;             // tiles of half the size
     bool all = false;              // every stage writes all the ranks it reads
     bool mid = false;              // partial sums are written on the way
-    bool tables_inline = false;    // flows and levels travel in the kernel's arguments
     uint32_t n_load = 0;           // ranks a stage reads
-    uint32_t grid_shift = 0;       // the tile grid `levels` was made for (tables_inline only)
-    std::vector<FoldFlow> flows;
-    std::vector<FoldLevel> levels;
+    uint32_t grid_shift = 0;       // the tile grid the levels were made for
 };
 
 // Layout of the device block of a schedule, in bytes from its start:
@@ -37,8 +34,8 @@ struct LaunchPlan {
 //   finished tiles per stage instance (counters kCounterStride words apart),
 //   stage templates, stage instances.  The fold kernel counts no finished tiles and
 //   knows neither templates nor instances: its flow
-//   and level tables, where they do not travel in the kernel's arguments, lie where
-//   the counters of finished tiles would (they need a third of that space).
+//   words, where they do not travel in the kernel's arguments, lie where the counters
+//   of finished tiles would (they need a fifth of that space), behind them the levels.
 struct BlockLayout {
     size_t ticket = 0, done = 0, tmpl = 0, inst = 0, bytes = 0;
     size_t counters_end = 0;  // status record and counters are [0, counters_end)
@@ -49,6 +46,7 @@ struct BlockLayout {
 
 struct blink_schedule {
     blink::Schedule s;
+    blink::FoldTables fold;       // of s; the levels belong to the plan
     blink::LaunchPlan plan;
     int device = -1;              // HIP device the schedule has run on; -1 = none yet
     void* d_block = nullptr;      // its block there (see BlockLayout); null = not needed so far
