@@ -8,6 +8,10 @@
 
 namespace blink {
 
+// At most this many levels of a fold plan travel in the kernel's arguments (kInlineFlows
+// of the kernel); more lie in the device block and are those of the plan's tile size.
+constexpr size_t kInlineLevels = 4;
+
 // What a launch needs besides the schedule itself.  It depends only on the
 // schedule, the device and the caller's overrides, so it is worked out once, at
 // the first call, and kept until an override changes (the progress counters

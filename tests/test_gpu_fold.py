@@ -194,6 +194,26 @@ def test_launch_overrides(fusion, wg, tile):
     assert untouched()
 
 
+@pytest.mark.parametrize("before,after", [(65_536, 256), (256, 65_536), (256, 1024), (0, 256)])
+def test_tile_sizes_of_calls_that_allocate_nothing(before, after):
+    """Six shares of different lengths: one stretch of tile positions with large tiles, which
+    travels with the launch, six with small ones, which lie in the block that such calls share."""
+    stream = _stream()
+    k, n = 4, 100_003
+    forest = [_tree(k, seed) for seed in range(6)]
+    trees = bl.blink_trees_from_arrays(k, [r for r, _ in forest], [p for _, p in forest], [1.0, 2.0, 3.0, 4.0, 5.0, 6.0])
+    x = [si.hash_payload(37, r, 0, n, "int32") for r in range(k)]
+    want = ox.allreduce_int32_definition(x)
+    sched = bl.blink_make_schedule(trees, bl.BLINK_OP_ALLREDUCE, n, 1 << 20, bl.BLINK_FUSE_TREE)
+    for tile in (before, after, before):
+        sched.set_launch(0, tile)
+        bufs, untouched = _slab(x)
+        bl.blink_allreduce_noalloc(bufs, n, bl.BLINK_INT32, sched, stream)
+        torch.cuda.synchronize()
+        assert all(np.array_equal(b.cpu().numpy(), want) for b in bufs), tile
+        assert untouched()
+
+
 def test_waiting_stages_after_calls_that_did_not_wait():
     """A per-node schedule that has run on this kernel hands chunks over once a call has been
     skipped, and is itself again after a reset."""
