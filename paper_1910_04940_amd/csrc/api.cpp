@@ -325,7 +325,6 @@ blink_status_t blink_schedule_test_skip_call(blink_schedule_t* s) {
         if (s->plan.fold) {
             s->plan = blink::LaunchPlan();
             s->tables_stale = true;
-            s->id = blink::next_schedule_id();
             for (uint64_t& b : s->ticket_base) b = 0;
         }
     }

@@ -26,6 +26,7 @@ constexpr int kMaxDevices = 64;
 struct StaticBlock {
     char* ptr = nullptr;   // device address of `scratch` on this GPU
     uint64_t owner = 0;    // id of the schedule whose tables the block holds (0 = none)
+    bool fold = false;     // they are the fold kernel's, not those of stages that wait
 };
 StaticBlock g_static[kMaxDevices];
 std::mutex g_static_mutex;
@@ -154,7 +155,7 @@ blink_status_t claim_static_block(blink_schedule* h, const BlockLayout& l, hipSt
         if (!ptr) return BLINK_EHIP;
         sb.ptr = ptr;
     }
-    if (sb.owner != h->id) {
+    if (sb.owner != h->id || sb.fold != h->plan.fold) {
         // waiting and copying are not things a capturing stream can record
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
@@ -168,6 +169,7 @@ blink_status_t claim_static_block(blink_schedule* h, const BlockLayout& l, hipSt
         BLINK_HIP(hipStreamSynchronize(stream));
         if (const blink_status_t st = copy_tables(*h, l, sb.ptr)) return st;
         sb.owner = h->id;
+        sb.fold = h->plan.fold;
     }
     h->last_static_device = dev;
     *out = sb.ptr;
@@ -274,9 +276,8 @@ blink_status_t make_plan(blink_schedule* h) {
 blink_status_t reset_progress(blink_schedule* h) {
     h->epoch = 0;
     for (uint64_t& b : h->ticket_base) b = 0;
-    // The next plan may need other tables, in a static block too: levels that lie there, or the
-    // flows' words after calls whose stages waited.
-    if (h->call_skipped || (h->plan.fold && !levels_inline(*h))) h->id = next_schedule_id();
+    // The next plan may need other levels, in a static block too.
+    if (h->plan.fold && !levels_inline(*h)) h->id = next_schedule_id();
     h->tables_stale = true;
     h->plan = LaunchPlan();
     h->call_skipped = false;
@@ -302,8 +303,11 @@ blink_status_t read_status(blink_schedule* h, blink_progress_t* out) {
         int dev = -1;
         BLINK_HIP(hipGetDevice(&dev));
         std::lock_guard<std::mutex> lock(g_static_mutex);
-        if (dev != h->last_static_device || g_static[dev].owner != h->id) return BLINK_OK;  // record gone
-        block = g_static[dev].ptr;
+        const StaticBlock& sb = g_static[dev];
+        // record gone: the block has passed to another schedule, or there is no plan for the
+        // tables it holds (a reset or a skipped call since; a fold call need not clear the record)
+        if (dev != h->last_static_device || sb.owner != h->id || sb.fold != h->plan.fold) return BLINK_OK;
+        block = sb.ptr;
     } else if (h->device < 0) {
         return BLINK_OK;  // never ran: nothing can have gone wrong
     }

@@ -55,7 +55,7 @@ struct blink_schedule {
     int device = -1;              // HIP device the schedule has run on; -1 = none yet
     void* d_block = nullptr;      // its block there (see BlockLayout); null = not needed so far
     bool tables_stale = true;     // the block's tables are not those of the plan
-    uint64_t id = 0;              // names the owner of a device's static block: unique per handle and set of tables
+    uint64_t id = 0;              // names, with the kernel the tables are for, the owner of a device's static block
     uint64_t epoch = 0;           // calls made so far on d_block; its counters hold epoch * tiles
     uint64_t ticket_base[16] = {};  // value of each ticket counter when the next call starts
     bool call_skipped = false;    // blink_schedule_test_skip_call was used: stages wait for one another
