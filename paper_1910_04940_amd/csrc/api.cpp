@@ -273,24 +273,14 @@ blink_status_t blink_gather(void* const* bufs, int k, size_t n_elems, blink_dtyp
     BLINK_GUARD_END
 }
 
-// Whether a tile size can give the schedule more levels than travel with a launch: flows
-// of one length are always in the same level.
-static bool levels_may_overflow(const blink_schedule_t& s) {
-    const auto& flows = s.fold.flows;   // longest first
-    size_t lengths = 0;
-    for (size_t f = 0; f < flows.size(); ++f) lengths += f == 0 || flows[f].len != flows[f - 1].len;
-    return lengths > blink::kInlineLevels;
-}
-
 blink_status_t blink_schedule_set_launch(blink_schedule_t* s, int wg_per_cu, int tile_elems) {
-    const bool tile_ok = tile_elems == 0 || (tile_elems >= 256 && tile_elems <= 65536 &&
+    const bool tile_ok = tile_elems == 0 || (tile_elems >= static_cast<int>(blink::kLeastTileOverride) &&
+                                             tile_elems <= static_cast<int>(blink::kMostTileOverride) &&
                                              (tile_elems & (tile_elems - 1)) == 0);
     if (!s || wg_per_cu < 0 || !tile_ok) return BLINK_EINVAL;
     s->wg_per_cu = wg_per_cu;
     if (static_cast<unsigned>(tile_elems) != s->tile_override) {
         s->tile_override = static_cast<unsigned>(tile_elems);
-        // a static block that holds this schedule's tables may lack the levels of the new tile
-        if (levels_may_overflow(*s)) s->id = blink::next_schedule_id();
         return blink::reset_progress(s);  // counters were counted in tiles of the old size
     }
     return BLINK_OK;

@@ -70,15 +70,16 @@ BlockLayout layout_of(const Schedule& s) {
     l.bytes = round_up(l.inst + s.inst.size() * sizeof(StageInst), 256);
     l.words = l.done;   // a flow has an instance at least, hence kLine bytes
     l.levels = l.words + s.inst.size() * kFlowWords * sizeof(uint32_t);
-    static_assert(kLine >= kFlowWords * sizeof(uint32_t) + sizeof(FoldLevel), "the tables fit the space of the counters");
+    static_assert(kLine >= kFlowWords * sizeof(uint32_t) + kLevelSets * sizeof(FoldLevel),
+                  "the tables fit the space of the counters");
     return l;
 }
 
 // Bytes at the head of a block that are zero when a schedule is new.
 size_t cleared_bytes(const LaunchPlan& pl, const BlockLayout& l) { return pl.fold ? l.done : l.counters_end; }
 
-// What of a fold plan travels in the kernel's arguments.  Levels that do not are those of
-// the plan's tile size for every distance past a 1 KiB boundary.
+// What of a fold plan travels in the kernel's arguments.  Tables that do not are the same for
+// every tile size (see kLevelSets) and every distance past a 1 KiB boundary.
 bool words_inline(const blink_schedule& h) { return h.fold.flows.size() <= kInlineFlows; }
 bool levels_inline(const blink_schedule& h) { return h.fold.levels.size() <= kInlineFlows; }
 
@@ -92,8 +93,7 @@ blink_status_t copy_tables(const blink_schedule& h, const BlockLayout& l, char* 
     } else if (!words_inline(h)) {
         const FoldTables& t = h.fold;
         BLINK_HIP(hipMemcpy(block + l.words, t.words.data(), t.words.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-        if (!levels_inline(h))
-            BLINK_HIP(hipMemcpy(block + l.levels, t.levels.data(), t.levels.size() * sizeof(FoldLevel), hipMemcpyHostToDevice));
+        BLINK_HIP(hipMemcpy(block + l.levels, t.sets.data(), t.sets.size() * sizeof(FoldLevel), hipMemcpyHostToDevice));
     }
     return BLINK_OK;
 }
@@ -225,6 +225,7 @@ void plan_fold(blink_schedule* h) {
     // a tile per flow more than that: shares need not be whole tiles
     pl.half = tiles <= kFoldHalfTilesPerCu * cus + h->fold.flows.size() && fold_has_half(n, pl.all);
     if (pl.small) tile = fold_sub_elems(n, pl.all, pl.half);
+    if (!words_inline(*h)) h->fold.fill_set(level_set(0), tile);
     if (h->tile_override) tile = h->tile_override;
     pl.tile_elems = tile;
     pl.grid_shift = 0;
@@ -276,8 +277,6 @@ blink_status_t make_plan(blink_schedule* h) {
 blink_status_t reset_progress(blink_schedule* h) {
     h->epoch = 0;
     for (uint64_t& b : h->ticket_base) b = 0;
-    // The next plan may need other levels, in a static block too.
-    if (h->plan.fold && !levels_inline(*h)) h->id = next_schedule_id();
     h->tables_stale = true;
     h->plan = LaunchPlan();
     h->call_skipped = false;
@@ -558,7 +557,8 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     FoldParams p;   // every field that is read is set
     for (int i = 0; i < BLINK_MAX_RANKS; ++i) p.buf[i] = i < s.k ? bufs[i] : nullptr;
     p.words = words_inline(*h) ? nullptr : reinterpret_cast<const unsigned*>(block + l.words);
-    p.levels = levels_inline(*h) ? nullptr : reinterpret_cast<const FoldLevel*>(block + l.levels);
+    p.levels = levels_inline(*h) ? nullptr
+                                 : reinterpret_cast<const FoldLevel*>(block + l.levels) + level_set(h->tile_override) * t.flows.size();
     if (!p.words) fold_words(t.flows, kInlineFlows, p.inline_words);
     if (!p.levels) std::copy(t.levels.begin(), t.levels.end(), p.inline_levels);
     p.ticket = block ? reinterpret_cast<unsigned long long*>(block + l.ticket) : nullptr;

@@ -142,12 +142,32 @@ inline uint64_t fold_levels(const std::vector<FoldFlow>& flows, uint32_t tile_el
     return tickets;
 }
 
+// Tile sizes a caller may ask for: powers of two.
+constexpr uint32_t kLeastTileOverride = 256, kMostTileOverride = 65536;
+// Sets of levels that lie on the device where a schedule's tables do: one per such tile
+// size (from the smallest up) and, last, that of the tile the launcher chooses.  With all of
+// them there a new tile size needs no new tables, so a call can be recorded after it.
+constexpr uint32_t kLevelSets = 10;
+inline uint32_t level_set(uint32_t tile_override) {
+    uint32_t set = 0;
+    if (tile_override == 0) return kLevelSets - 1;
+    while ((kLeastTileOverride << set) < tile_override) ++set;
+    return set;
+}
+static_assert((kLeastTileOverride << (kLevelSets - 2)) == kMostTileOverride, "a set of levels per tile size");
+
 // What the fold kernel needs of a schedule, worked out with it: calls allocate nothing.
 struct FoldTables {
     bool fits = false;               // the kernel can run the schedule
     std::vector<FoldFlow> flows;
     std::vector<uint32_t> words;     // fold_words, stride = number of flows
     std::vector<FoldLevel> levels;   // room for one per flow; filled by the launch plan
+    std::vector<FoldLevel> sets;     // kLevelSets times as many, for tables on the device
+    // Tile counts of the sets suffice for any distance of the buffers from a 1 KiB boundary.
+    void fill_set(uint32_t set, uint32_t tile_elems) {
+        fold_levels(flows, tile_elems, 0, true, &levels);
+        std::copy(levels.begin(), levels.end(), sets.begin() + set * flows.size());
+    }
 };
 inline void fold_tables(const Schedule& s, FoldTables* out) {
     out->fits = fold_flows(s, &out->flows);
@@ -155,6 +175,8 @@ inline void fold_tables(const Schedule& s, FoldTables* out) {
     out->words.assign(kFlowWords * out->flows.size(), 0);
     fold_words(out->flows, static_cast<uint32_t>(out->flows.size()), out->words.data());
     out->levels.reserve(out->flows.size());
+    out->sets.assign(kLevelSets * out->flows.size(), FoldLevel{});
+    for (uint32_t set = 0; set + 1 < kLevelSets; ++set) out->fill_set(set, kLeastTileOverride << set);
 }
 
 }  // namespace blink

@@ -8,10 +8,6 @@
 
 namespace blink {
 
-// At most this many levels of a fold plan travel in the kernel's arguments (kInlineFlows
-// of the kernel); more lie in the device block and are those of the plan's tile size.
-constexpr size_t kInlineLevels = 4;
-
 // What a launch needs besides the schedule itself.  It depends only on the
 // schedule, the device and the caller's overrides, so it is worked out once, at
 // the first call, and kept until an override changes (the progress counters
@@ -39,7 +35,7 @@ struct LaunchPlan {
 //   stage templates, stage instances.  The fold kernel counts no finished tiles and
 //   knows neither templates nor instances: its flow
 //   words, where they do not travel in the kernel's arguments, lie where the counters
-//   of finished tiles would (they need a fifth of that space), behind them the levels.
+//   of finished tiles would, behind them the sets of levels (together 204 of every 256 bytes there).
 struct BlockLayout {
     size_t ticket = 0, done = 0, tmpl = 0, inst = 0, bytes = 0;
     size_t counters_end = 0;  // status record and counters are [0, counters_end)
@@ -50,7 +46,7 @@ struct BlockLayout {
 
 struct blink_schedule {
     blink::Schedule s;
-    blink::FoldTables fold;       // of s; the levels belong to the plan
+    blink::FoldTables fold;       // of s; the levels, and the last of the sets, belong to the plan
     blink::LaunchPlan plan;
     int device = -1;              // HIP device the schedule has run on; -1 = none yet
     void* d_block = nullptr;      // its block there (see BlockLayout); null = not needed so far

@@ -92,3 +92,32 @@ def test_a_record_on_the_block_is_not_taken_for_another_schedules():
     quick.reset()
     assert quick.status()[0] == bl.BLINK_OK
     assert all(np.array_equal(b.cpu().numpy(), ox.allreduce_int32_definition(x)) for b in bufs)
+
+
+@pytest.mark.parametrize("before,after", [(0, 256), (65_536, 1_024), (256, 0), (256, 256)])
+def test_a_call_can_be_recorded_after_a_new_tile_size_or_a_reset(before, after):
+    """Six shares of different lengths, whose tables lie in the block for every tile size.  The
+    recorded call is replayed with the program's own work in between."""
+    stream = _stream()
+    k, n = 5, 100_003
+    x = [si.hash_payload(53, r, 0, n, "int32") for r in range(k)]
+    want = ox.allreduce_int32_definition(x)
+    sched = bl.blink_make_schedule(_forest(k, 6), bl.BLINK_OP_ALLREDUCE, n, 1 << 20, bl.BLINK_FUSE_TREE)
+    sched.set_launch(0, before)
+    src = _bufs(x)
+    bufs = [b.clone() for b in src]
+    bl.blink_allreduce_noalloc(bufs, n, bl.BLINK_INT32, sched, stream)
+    torch.cuda.synchronize()
+    if before == after:
+        sched.reset()
+    sched.set_launch(0, after)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        bl.blink_allreduce_noalloc(bufs, n, bl.BLINK_INT32, sched, torch.cuda.current_stream().cuda_stream)
+    for replay in range(3):
+        for b, s0 in zip(bufs, src):
+            b.copy_(s0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(np.array_equal(b.cpu().numpy(), want) for b in bufs), replay
