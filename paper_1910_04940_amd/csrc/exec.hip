@@ -8,8 +8,6 @@
 
 namespace blink {
 
-constexpr uint64_t kMemorySideCacheBytes = 256ull << 20;
-
 // ---- a device block that needs no allocation ------------------------------------------
 // For callers that may not allocate (a stream under HIP graph capture, a tight
 // serving loop, a harness that forbids it): a block of fixed size in the
@@ -232,23 +230,6 @@ void plan_fold(blink_schedule* h) {
     pl.n_items = fold_levels(h->fold.flows, tile, 0, !words_inline(*h), &h->fold.levels);
 }
 
-// Whether a schedule runs on the fold kernel.  Without dependencies: always.  With them
-// the fold kernel carries a tile through all its transfers in one wave and writes each of
-// them to its rank buffer; the alternative is to hand chunks over from wave to wave, through
-// counters and memory.  Measured on 8 ranks, us, handed over / in one wave:
-//   per-node: 5 MiB 97 / 16, 20 MiB 156 / 62, 64 MiB 310 / 180, 256 MiB 1059 / 723: always.
-//   per-edge: 0.1 MiB 49 / 6, 8 MiB 124 / 30, 30 MiB 226 / 96.  In one wave where the
-//     payload fits the memory-side cache.  A larger one keeps the paper's pipeline of
-//     chunks that are handed on transfer by transfer: its speed is what callers who tune
-//     the chunk size (section 4.2.1, blink_miad_*) measure.
-// blink_schedule_test_skip_call asks for waiting stages.
-bool may_fold(const blink_schedule& h) {
-    const Schedule& s = h.s;
-    if (!s.has_deps) return true;
-    if (h.call_skipped) return false;
-    return s.fusion == BLINK_FUSE_NODE || static_cast<uint64_t>(s.k) * s.n * 4 <= kMemorySideCacheBytes;
-}
-
 blink_status_t make_plan(blink_schedule* h) {
     LaunchPlan& pl = h->plan;
     if (pl.made) return BLINK_OK;
@@ -259,7 +240,9 @@ blink_status_t make_plan(blink_schedule* h) {
         if (n_cu < 1) return BLINK_EHIP;
         h->n_cu = n_cu;
     }
-    pl.fold = may_fold(*h) && h->fold.fits;
+    const Served served = served_by(h->s, h->fold.fits, h->call_skipped);   // a skipped call asks for waiting stages
+    if (served == Served::kNot) return BLINK_EINVAL;
+    pl.fold = served == Served::kFold;
     if (pl.fold)
         plan_fold(h);
     else

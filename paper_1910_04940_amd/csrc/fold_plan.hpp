@@ -142,6 +142,28 @@ inline uint64_t fold_levels(const std::vector<FoldFlow>& flows, uint32_t tile_el
     return tickets;
 }
 
+constexpr uint64_t kMemorySideCacheBytes = 256ull << 20;
+
+// Which kernel serves a schedule.  Without dependencies the fold kernel: the other one
+// combines a stage's ranks in the order of load_rank, which is not that of a whole tree's
+// stack program, so a schedule the fold kernel cannot run is not run at all.  With
+// dependencies the fold kernel carries a tile through all its transfers in one wave and writes
+// each of them to its rank buffer; the alternative is to hand chunks over from wave to wave,
+// through counters and memory.  Measured on 8 ranks, us, handed over / in one wave:
+//   per-node: 5 MiB 97 / 16, 20 MiB 156 / 62, 64 MiB 310 / 180, 256 MiB 1059 / 723: always.
+//   per-edge: 0.1 MiB 49 / 6, 8 MiB 124 / 30, 30 MiB 226 / 96.  In one wave where the
+//     payload fits the memory-side cache.  A larger one keeps the paper's pipeline of
+//     chunks that are handed on transfer by transfer: its speed is what callers who tune
+//     the chunk size (section 4.2.1, blink_miad_*) measure.
+// hand_over: waiting stages are asked for.
+enum class Served { kFold, kHandOver, kNot };
+inline Served served_by(const Schedule& s, bool fold_fits, bool hand_over) {
+    if (!s.has_deps) return fold_fits ? Served::kFold : Served::kNot;
+    if (hand_over || !fold_fits) return Served::kHandOver;
+    const bool in_cache = static_cast<uint64_t>(s.k) * s.n * 4 <= kMemorySideCacheBytes;
+    return s.fusion == BLINK_FUSE_NODE || in_cache ? Served::kFold : Served::kHandOver;
+}
+
 // Tile sizes a caller may ask for: powers of two.
 constexpr uint32_t kLeastTileOverride = 256, kMostTileOverride = 65536;
 // Sets of levels that lie on the device where a schedule's tables do: one per such tile
