@@ -381,9 +381,9 @@ def main():
 
     per_elem = ({"edge": 8 * (k - 1), "node": None, "tree": 4 * k} if broadcast else
                 {"edge": 20 * (k - 1), "node": None, "tree": 8 * k})[args.fusion]
-    alg_bytes = sum(s.traffic_bytes for s in scheds)      # == per_elem * n for edge and tree
     if per_elem is not None:
-        assert alg_bytes == per_elem * total
+        assert sum(s.traffic_bytes for s in scheds) == per_elem * total
+    alg_bytes = sum(s.kernel_bytes for s in scheds)       # what the kernel requests, whichever serves
     achieved = alg_bytes / (avg_kernel_ms * 1e-3) / 1e9
     prof_name = (f"blink_consume_{collective}_cube8_{n * 4 >> 20}MiB_{args.fusion}.txt" if args.config == "headline"
                  else f"config{args.config}_{collective}_{args.fusion}.txt")
@@ -401,8 +401,10 @@ def main():
                 "launches_per_step": len(calls),
                 "bytes_per_element": alg_bytes / total,
                 "accounting": {"edge": "per-edge: every tree edge is a transfer between two rank buffers, "
-                                       "20(k-1) B/elt (broadcast: 8(k-1))",
-                               "node": "per-node: one pass per fan-in and per fan-out",
+                                       "20(k-1) B/elt (broadcast: 8(k-1)); payloads within 256 MiB in all: every "
+                                       "rank buffer read and written once, and every partial sum written",
+                               "node": "per-node: every rank buffer read and written once, and every inner "
+                                       "node's partial sum written",
                                "tree": "staged minimum: every rank buffer read once and written once, 8k B/elt "
                                        "(broadcast: the root read once, the others written once, 4k)"}[args.fusion],
                 "kernel": "blink_fold / blink_consume", "avg_kernel_ms": avg_kernel_ms,

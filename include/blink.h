@@ -277,9 +277,14 @@ blink_status_t blink_schedule_get_tickets(const blink_schedule_t* s, uint32_t ti
                                           int32_t* stage, int32_t* tile);
 /* out[T+1] (host): share boundaries b_0 = 0 .. b_T = n_elems. */
 blink_status_t blink_schedule_get_bounds(const blink_schedule_t* s, uint64_t* out);
-/* Bytes the kernel reads plus writes in rank buffers for one call with 4-byte
- * elements, by construction of the stages (no cache effects). */
+/* Bytes read plus written in rank buffers for one call with 4-byte elements (no cache
+ * effects).  traffic: by the stages (blink_schedule_get_stages), each of which reads its
+ * ranks and writes its result.  kernel: by the kernel that serves the schedule's next call.
+ * The two are the same unless a wavefront carries a tile through all the stages of an
+ * EDGE or NODE program (see blink_fusion_t): it reads every rank once, and writes every
+ * rank of the result and, on the way, every partial sum of the program once. */
 uint64_t blink_schedule_traffic_bytes(const blink_schedule_t* s);
+uint64_t blink_schedule_kernel_bytes(const blink_schedule_t* s);
 void blink_schedule_free(blink_schedule_t* s);
 
 /* ---- execution (needs the GPU) -------------------------------------------------- */

@@ -54,6 +54,7 @@ EXPORTS = [
     "blink_schedule_get_stages", "blink_schedule_status", "blink_schedule_reset",
     "blink_schedule_set_wait_limit", "blink_schedule_test_skip_call", "blink_allreduce_noalloc",
     "blink_schedule_set_kernel", "blink_schedule_last_kernel", "blink_schedule_set_sweep", "blink_schedule_get_tickets", "blink_schedule_batch",
+    "blink_schedule_kernel_bytes",
 ]
 
 
@@ -128,6 +129,8 @@ def lib() -> C.CDLL:
     L.blink_schedule_get_bounds.argtypes = [vp, C.POINTER(C.c_uint64)]
     L.blink_schedule_traffic_bytes.argtypes = [vp]
     L.blink_schedule_traffic_bytes.restype = C.c_uint64
+    L.blink_schedule_kernel_bytes.argtypes = [vp]
+    L.blink_schedule_kernel_bytes.restype = C.c_uint64
     L.blink_schedule_free.argtypes = [vp]
     L.blink_schedule_free.restype = None
     for name in ("blink_allreduce", "blink_broadcast", "blink_allgather", "blink_gather", "blink_allreduce_noalloc"):
@@ -268,7 +271,13 @@ class Schedule:
 
     @property
     def traffic_bytes(self) -> int:
+        """Bytes per call by the stages, each run by itself."""
         return lib().blink_schedule_traffic_bytes(self._h)
+
+    @property
+    def kernel_bytes(self) -> int:
+        """Bytes per call that the kernel serving the schedule requests."""
+        return lib().blink_schedule_kernel_bytes(self._h)
 
     def steps(self) -> np.ndarray:
         out = np.zeros(self.num_steps, STEP_DTYPE)

@@ -218,6 +218,12 @@ blink_status_t blink_schedule_get_tickets(const blink_schedule_t* s, uint32_t ti
 
 uint64_t blink_schedule_traffic_bytes(const blink_schedule_t* s) { return s ? s->s.traffic_bytes : 0; }
 
+uint64_t blink_schedule_kernel_bytes(const blink_schedule_t* s) {
+    if (!s) return 0;
+    const bool fold = blink::served_by(s->s, s->fold.fits, s->call_skipped) == blink::Served::kFold;
+    return fold ? blink::fold_bytes(s->s) : s->s.traffic_bytes;
+}
+
 void blink_schedule_free(blink_schedule_t* s) {
     if (!s) return;
     blink::release_device_state(s);

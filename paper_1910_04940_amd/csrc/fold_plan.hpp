@@ -164,6 +164,15 @@ inline Served served_by(const Schedule& s, bool fold_fits, bool hand_over) {
     return s.fusion == BLINK_FUSE_NODE || in_cache ? Served::kFold : Served::kHandOver;
 }
 
+// Bytes the fold kernel reads plus writes in rank buffers per call: every rank it takes from
+// once, every rank of the result once, and the sums written on the way.
+inline uint64_t fold_bytes(const Schedule& s) {
+    uint64_t bytes = 0;
+    for (const FusedFlow& f : s.fused)
+        bytes += (f.hi - f.lo) * 4u * (f.stage.n_load + f.stage.n_store + static_cast<unsigned>(__builtin_popcount(f.mid_store)));
+    return bytes;
+}
+
 // Tile sizes a caller may ask for: powers of two.
 constexpr uint32_t kLeastTileOverride = 256, kMostTileOverride = 65536;
 // Sets of levels that lie on the device where a schedule's tables do: one per such tile
