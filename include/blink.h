@@ -374,10 +374,13 @@ blink_status_t blink_schedule_set_launch(blink_schedule_t* s, int wg_per_cu, int
  * chunk (section 4.2.2 at the paper's own granularity) instead of tile by tile
  * (several trees only).  kernel: 0 = automatic: the first calls of at least
  * 64 MiB of traffic go round the ways the schedule has, four times each (eight
- * or twelve calls), timed with events on the caller's stream; the call after
- * them waits for them, and the fastest way serves from then on, whatever the operator
- * (blink_allreduce_noalloc takes no part in the timing and uses way 1; so do payloads
- * of a few tiles per compute unit);
+ * or twelve calls, all forwards through the payload), timed with events on the caller's
+ * stream; the call after them waits for them, and the fastest way serves from then on,
+ * whatever the operator.  Sums, and the other operators on either element type, go
+ * round by themselves; whichever is done first decides.  blink_allreduce_noalloc takes no
+ * part in the timing: it uses way 1 until there is a pick, then that.  Payloads of a few
+ * tiles per compute unit use way 1.  blink_schedule_reset, blink_schedule_set_sweep to
+ * another mode and blink_schedule_set_launch to another tile size start the timing afresh;
  * 1, 2, 3 = that way, or way 1 where the schedule does not have it.
  * blink_schedule_last_kernel: the way the latest call ran (0 before the first
  * call). */
@@ -391,7 +394,8 @@ int blink_schedule_last_kernel(const blink_schedule_t* s);
  * that), so a call on the buffers of the call before it
  * (training iterations without much else in between, benchmark loops) starts
  * on data that is still there.  alternate = 0: every call goes forwards and
- * streams its stores past the cache.  Same bits either way; schedules with
+ * streams its stores past the cache (sums whose buffers do not fit it).  Same bits either
+ * way; schedules with
  * dependencies and blink_allreduce_noalloc always go forwards. */
 blink_status_t blink_schedule_set_sweep(blink_schedule_t* s, int alternate);
 

@@ -337,7 +337,9 @@ int blink_schedule_last_kernel(const blink_schedule_t* s) { return s ? s->last_k
 
 blink_status_t blink_schedule_set_sweep(blink_schedule_t* s, int alternate) {
     if (!s || (alternate != 0 && alternate != 1)) return BLINK_EINVAL;
+    if (s->sweep_alternates == (alternate == 1)) return BLINK_OK;
     s->sweep_alternates = alternate == 1;   // order and cache policy follow it, call by call
+    blink::forget_trial(s);                 // times under the other policy
     return BLINK_OK;
 }
 

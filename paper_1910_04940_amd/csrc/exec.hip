@@ -42,8 +42,6 @@ uint64_t next_schedule_id() { return g_next_id.fetch_add(1); }
 // ---- host side ------------------------------------------------------------------------
 namespace {
 
-void drop_trial_events(blink_schedule* h);  // below, with the choice among the ways to serve a schedule
-
 #define BLINK_HIP(call)                                                                   \
     do {                                                                                  \
         hipError_t err__ = (call);                                                        \
@@ -264,9 +262,7 @@ blink_status_t reset_progress(blink_schedule* h) {
     h->plan = LaunchPlan();
     h->call_skipped = false;
     h->occupancy[0] = h->occupancy[1] = 0;
-    drop_trial_events(h);
-    h->picked = 0;
-    h->trial_calls = 0;
+    forget_trial(h);
     if (h->device < 0) return BLINK_OK;
     BLINK_HIP(hipDeviceSynchronize());
     if (!h->d_block) return BLINK_OK;
@@ -307,101 +303,77 @@ blink_status_t read_status(blink_schedule* h, blink_progress_t* out) {
     return BLINK_ESTUCK;
 }
 
-// Picking the way a whole-tree schedule is served at streaming size: the
-// order in which the fold kernel goes through the payload, and with it whether
-// results stream past the memory-side cache.
-//   1  tile by tile across the trees (section 4.2.2; chunk by chunk where a stage
-//      reads more than 8 ranks: 16 x 16 streams at a time are too many)
-//   2  one front through the payload, one tree's share after the other
-//   3  chunk by chunk across the trees (several trees, at most 8 ranks)
-// Which is fastest depends on where the buffers lie in HBM and how far apart the
-// trees' shares are, in ways addresses do not reveal.  With the standalone probe
-// (8 ranks, 4 trees, buffers in allocations of their own, three sets in turn; us for
-// ways 1 / 2): 64 MiB per rank 182 / 163, 114 MiB 324 / 294, 400 MiB 1119 / 1042, but
-// 256 MiB, where the shares are a power of two apart, 658 / 691.  So the first calls on
-// such a schedule go round the candidates, kTrialSamples times each, each call timed
-// with a pair of events on the caller's stream; the next call waits for the last of
-// them (the one time a call waits for the device, besides a schedule's first) and
-// the candidate with the smallest minimum serves the rest.  All give the same
-// bits.
-constexpr int kTrialSamples = 4;
-constexpr uint64_t kTrialMinBytes = 64ull << 20;  // smaller calls are too short to time against one another
+// Calls with less traffic are too short to time against one another.  (On all 256 CUs a payload
+// that does not get a workgroup for every tile moves more; on a part of them it need not.)
+constexpr uint64_t kTrialMinBytes = 64ull << 20;
 
 namespace {
+// The pair of events around a timed call; index < 0: the call is not timed.
+struct Timed {
+    int cls = 0, index = -1;
+};
+
 void drop_trial_events(blink_schedule* h) {
-    for (void*& e : h->trial_event) {
-        if (e) (void)hipEventDestroy(static_cast<hipEvent_t>(e));
-        e = nullptr;
-    }
-    h->trial_events_made = false;
+    for (auto& per_class : h->trial_event)
+        for (void*& e : per_class) {
+            if (e) (void)hipEventDestroy(static_cast<hipEvent_t>(e));
+            e = nullptr;
+        }
+}
+hipEvent_t trial_event(const blink_schedule* h, Timed t, int which) {
+    return static_cast<hipEvent_t>(h->trial_event[t.cls][2 * t.index + which]);
 }
 
-// How this call is served (1, 2 or 3, see above); *timed: index of the event
-// pair to put around it, or -1.  can_front, can_turns: the schedule has ways 2, 3.
+// No more timed calls: `way` serves from now on.
+int pick(blink_schedule* h, int way) {
+    drop_trial_events(h);
+    h->trial.picked = way;
+    return way;
+}
+
+// How this call is served (1, 2 or 3, see way_trial.hpp); *timed: the events to put around
+// it.  can_front, can_turns: the schedule has ways 2, 3.
 // A caller who asks for way 2 gets it for sums only, as the interface says; picked by
 // the trial it serves every operator.
-int choose_way(blink_schedule* h, bool static_block, bool sum, bool can_front, bool can_turns, int* timed) {
-    *timed = -1;
+int choose_way(blink_schedule* h, bool static_block, blink_dtype_t dtype, bool sum, bool can_front, bool can_turns, Timed* timed) {
     if (h->kernel_choice == 2) return can_front && sum ? 2 : 1;
     if (h->kernel_choice == 3) return can_turns ? 3 : 1;
     if (h->kernel_choice) return 1;
-    if (h->picked) return h->picked;
-    int ways[3], n_ways = 0;
-    ways[n_ways++] = 1;
-    if (can_front) ways[n_ways++] = 2;
-    if (can_turns) ways[n_ways++] = 3;
+    if (h->trial.picked) return h->trial.picked;
+    const Ways ways = ways_of(can_front, can_turns);
     // no trial: one way only / nothing may be created here / too short
-    if (n_ways == 1 || static_block || h->s.traffic_bytes < kTrialMinBytes) return 1;
-    const int trial_calls = n_ways * kTrialSamples;
-    if (h->trial_calls < trial_calls) {
-        if (!h->trial_events_made) {
-            for (int e = 0; e < 2 * trial_calls; ++e) {
-                hipEvent_t ev = nullptr;
-                if (hipEventCreate(&ev) != hipSuccess) {
-                    (void)hipGetLastError();
-                    drop_trial_events(h);
-                    h->picked = 1;
-                    return 1;
-                }
-                h->trial_event[e] = ev;
+    if (ways.count == 1 || static_block || h->s.traffic_bytes < kTrialMinBytes) return 1;
+    const int cls = trial_class(sum, dtype == BLINK_FP32);
+    const int n = ways.count * kTrialSamples;
+    if (const int way = timed_way(h->trial, ways, cls)) {
+        for (int e = 0; e < 2 * n; ++e) {
+            if (h->trial_event[cls][e]) continue;
+            hipEvent_t ev = nullptr;
+            if (hipEventCreate(&ev) != hipSuccess) {
+                (void)hipGetLastError();
+                return pick(h, 1);
             }
-            h->trial_events_made = true;
+            h->trial_event[cls][e] = ev;
         }
-        *timed = h->trial_calls;
-        return ways[h->trial_calls % n_ways];
+        *timed = {cls, h->trial.calls[cls]};
+        return way;
     }
-    // All trial calls are launched: wait for the last of them (once per
-    // schedule) and compare the fastest of each candidate's calls but its first
-    // (which carries what happens once: the code's first launch, tables not yet
-    // in any cache).  Kernels of a tenth of a millisecond differ by a few
-    // percent, which is also what the event pair around a single launch
-    // scatters by: hence three samples each, not one.
-    float best[3] = {1e30f, 1e30f, 1e30f};
-    bool ok = hipEventSynchronize(static_cast<hipEvent_t>(h->trial_event[2 * trial_calls - 1])) == hipSuccess;
-    for (int c = 0; ok && c < trial_calls; ++c) {
-        float ms = 0.f;
-        ok = hipEventElapsedTime(&ms, static_cast<hipEvent_t>(h->trial_event[2 * c]),
-                                 static_cast<hipEvent_t>(h->trial_event[2 * c + 1])) == hipSuccess;
-        if (c >= n_ways) best[c % n_ways] = std::min(best[c % n_ways], ms);
-    }
+    // All of this class's timed calls are launched: wait for the last of them (once per
+    // schedule) and compare.
+    float ms[kMostWays * kTrialSamples] = {};
+    bool ok = hipEventSynchronize(trial_event(h, {cls, n - 1}, 1)) == hipSuccess;
+    for (int c = 0; ok && c < n; ++c)
+        ok = hipEventElapsedTime(&ms[c], trial_event(h, {cls, c}, 0), trial_event(h, {cls, c}, 1)) == hipSuccess;
     if (!ok) (void)hipGetLastError();
-    // Way 2, or way 1 where there is none, gets the schedule unless another beats it by more
-    // than the 2 % by which such minima scatter from one trial to the next: it is the fastest
-    // or within 1 % of it on most shapes (three sets of buffers in turn, us for ways 1 / 2 / 3:
-    // two servers of 8 x 64 MiB 344 / 336 / -, 6 ranks x 97.6 MiB 209 / 196 / 204, 8 x 230 MiB
-    // 664 / 614 / 634; the other way round 8 x 256 MiB 717 / 735 / 786).
-    int fastest = can_front ? 1 : 0;
-    float bar = best[fastest] * 0.98f;
-    for (int w = 0; ok && w < n_ways; ++w)
-        if (best[w] < bar) {
-            fastest = w;
-            bar = best[w];
-        }
-    h->picked = ways[fastest];
-    drop_trial_events(h);
-    return h->picked;
+    return pick(h, ok ? fastest_way(ways, ms) : can_front ? 2 : 1);
 }
 }  // namespace
+
+// Forget the picked way and the times so far: later calls are timed afresh.
+void forget_trial(blink_schedule* h) {
+    drop_trial_events(h);
+    h->trial = WayTrial();
+}
 
 void release_device_state(blink_schedule* h) {
     drop_trial_events(h);
@@ -415,15 +387,14 @@ namespace {
 // One launch on `stream`.  Its own status decides whether the call counts: an error
 // some earlier HIP call of this thread left behind is not this launch's, and a
 // launch that failed must not consume a call number or move the ticket bases
-// (the next call would wait for tiles that nobody ever counted).  timed: index of
-// the event pair to record around it, or -1.
+// (the next call would wait for tiles that nobody ever counted).  timed: the events to
+// record around it.
 blink_status_t launch(blink_schedule* h, const void* fn, unsigned grid, unsigned threads, void* params, hipStream_t stream,
-                      int timed) {
-    if (timed >= 0 && hipEventRecord(static_cast<hipEvent_t>(h->trial_event[2 * timed]), stream) != hipSuccess) {
+                      Timed timed) {
+    if (timed.index >= 0 && hipEventRecord(trial_event(h, timed, 0), stream) != hipSuccess) {
         (void)hipGetLastError();  // e.g. a capturing stream: give the trial up
-        drop_trial_events(h);
-        h->picked = 1;
-        timed = -1;
+        pick(h, 1);
+        timed = Timed();
     }
     void* args[] = {params};
     const hipError_t launched = hipLaunchKernel(fn, dim3(grid), dim3(threads), args, 0, stream);
@@ -432,13 +403,12 @@ blink_status_t launch(blink_schedule* h, const void* fn, unsigned grid, unsigned
         (void)hipGetLastError();  // the failed launch's error is reported here, not left for later calls
         return BLINK_EHIP;
     }
-    if (timed >= 0) {
-        if (hipEventRecord(static_cast<hipEvent_t>(h->trial_event[2 * timed + 1]), stream) == hipSuccess) {
-            h->trial_calls += 1;
+    if (timed.index >= 0) {
+        if (hipEventRecord(trial_event(h, timed, 1), stream) == hipSuccess) {
+            h->trial.calls[timed.cls] += 1;
         } else {
             (void)hipGetLastError();
-            drop_trial_events(h);
-            h->picked = 1;
+            pick(h, 1);
         }
     }
     h->last_grid = grid;
@@ -493,9 +463,9 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
 
     const bool sum = redop == BLINK_SUM;
     const bool by_tile = pl.n_load <= 8 && t.flows.size() <= 64;
-    int timed = -1;
+    Timed timed;
     const bool choice = !pl.small && !s.has_deps;   // programs with dependencies have way 1 only
-    const int way = choose_way(h, static_block, sum, choice && s.max_stack <= 4, choice && by_tile && t.flows.size() > 1, &timed);
+    const int way = choose_way(h, static_block, dtype, sum, choice && s.max_stack <= 4, choice && by_tile && t.flows.size() > 1, &timed);
     const uint64_t chunk_tiles = std::max<uint64_t>(1, s.chunk / pl.tile_elems);
     const uint32_t chunk_turn = static_cast<uint32_t>(std::min<uint64_t>(chunk_tiles, kTurnPayload));
 
@@ -554,8 +524,8 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     p.grid_shift = grid_shift;
     p.redop = static_cast<unsigned>(redop);
     // Calls sweep the payload in alternating directions (the second, fourth, ... call
-    // backwards), unless switched off.
-    p.reverse = !s.has_deps && !static_block && h->sweep_alternates && (h->epoch & 1) != 0;
+    // backwards), unless switched off or timed.
+    p.reverse = goes_backwards(!s.has_deps && !static_block && h->sweep_alternates, timed.index >= 0, h->epoch);
     p.dealt = dealt;
     if (blink_status_t st = launch(h, reinterpret_cast<const void*>(fn), grid, kFoldThreads, &p, stream, timed)) return st;
     h->last_kernel = way;
@@ -619,7 +589,7 @@ blink_status_t run_hand_over(blink_schedule* h, void* const* bufs, blink_dtype_t
 
     if (static_block)
         if (blink_status_t st = launch_clear(block, l.counters_end, stream)) return st;
-    if (blink_status_t st = launch(h, reinterpret_cast<const void*>(fn), static_cast<unsigned>(grid), kLanes, &p, stream, -1)) return st;
+    if (blink_status_t st = launch(h, reinterpret_cast<const void*>(fn), static_cast<unsigned>(grid), kLanes, &p, stream, Timed())) return st;
     h->last_kernel = 1;
     if (static_block) return BLINK_OK;
     h->epoch += 1;

@@ -5,6 +5,7 @@
 #include <cstdint>
 
 #include "fold_plan.hpp"
+#include "way_trial.hpp"
 
 namespace blink {
 
@@ -65,10 +66,8 @@ struct blink_schedule {
     int last_static_device = -1;  // device whose static block the latest call used; -1 = it used d_block
     int kernel_choice = 0;        // the caller's wish: 0 = pick the fastest way, else one of the three
     bool sweep_alternates = true; // calls on a schedule without dependencies walk the tiles in alternating directions
-    int picked = 0;               // the pick once made (1, 2 or 3); 0 = not yet
-    int trial_calls = 0;          // timed calls launched so far (the candidates take turns)
-    void* trial_event[24] = {};   // hipEvent_t pairs around the timed calls
-    bool trial_events_made = false;
+    blink::WayTrial trial;        // the timed calls so far and the pick
+    void* trial_event[blink::kTrialClasses][2 * blink::kMostWays * blink::kTrialSamples] = {};   // hipEvent_t pairs around them
 };
 
 namespace blink {
@@ -77,6 +76,7 @@ blink_status_t execute(blink_schedule* h, void* const* bufs, int k, size_t n, bl
                        blink_op_t op, blink_redop_t redop, void* stream, bool static_block = false);
 uint64_t next_schedule_id();
 blink_status_t reset_progress(blink_schedule* h);
+void forget_trial(blink_schedule* h);
 blink_status_t read_status(blink_schedule* h, blink_progress_t* out);
 void release_device_state(blink_schedule* h);
 }  // namespace blink

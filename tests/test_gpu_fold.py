@@ -244,3 +244,38 @@ def test_waiting_stages_after_calls_that_did_not_wait():
         bufs, untouched = call()
         assert all(np.array_equal(b.cpu().numpy(), want) for b in bufs) and untouched()
     assert sched.status()[0] == bl.BLINK_OK
+
+
+def test_the_timed_choice_compares_like_with_like():
+    """A job that alternates sums and maxima on one schedule: either kind of call goes round the
+    ways by itself.  Another sweep mode has a choice of its own, and calls that allocate nothing
+    use the pick."""
+    stream = _stream()
+    k, n = 7, 4_000_001
+    root, parent = _tree(k, 1)
+    trees = bl.blink_trees_from_arrays(k, [root], [parent], [1.0])
+    sched = bl.blink_make_schedule(trees, bl.BLINK_OP_ALLREDUCE, n, 1 << 18, bl.BLINK_FUSE_TREE)
+    bufs = [torch.ones(n, dtype=torch.int32, device="cuda") for _ in range(k)]
+    seen = {bl.BLINK_SUM: [], bl.BLINK_MAX: []}
+    value = 1
+
+    def call(op):
+        nonlocal value
+        bl.blink_allreduce_op(bufs, n, bl.BLINK_INT32, op, sched, stream)
+        value = (value * k) % (1 << 32) if op == bl.BLINK_SUM else value
+        return sched.last_kernel
+
+    for i in range(22):
+        op = (bl.BLINK_SUM, bl.BLINK_MAX)[i % 2]
+        seen[op].append(call(op))
+    picked = seen[bl.BLINK_SUM][-1]
+    for ways in seen.values():
+        assert ways[:8] == [1, 2] * 4 and set(ways[8:]) == {picked}
+    bl.blink_allreduce_noalloc(bufs, n, bl.BLINK_INT32, sched, stream)
+    value = (value * k) % (1 << 32)
+    assert sched.last_kernel == picked
+    sched.set_sweep(False)
+    assert [call(bl.BLINK_MAX) for _ in range(8)] == [1, 2] * 4
+    torch.cuda.synchronize()
+    for b in bufs:
+        assert int(b.min()) == int(b.max()) and int(b.min()) % (1 << 32) == value
