@@ -65,9 +65,7 @@ BlockLayout layout_of(const Schedule& s) {
     l.inst = round_up(l.tmpl + s.tmpl.size() * sizeof(StageTmpl), 256);
     l.bytes = round_up(l.inst + s.inst.size() * sizeof(StageInst), 256);
     l.words = l.done;   // a flow has an instance at least, hence kLine bytes
-    l.levels = l.words + s.inst.size() * kFlowWords * sizeof(uint32_t);
-    static_assert(kLine >= kFlowWords * sizeof(uint32_t) + kLevelSets * sizeof(FoldLevel),
-                  "the tables fit the space of the counters");
+    static_assert(kLine >= FoldTables::words_per_flow() * sizeof(uint32_t), "the tables fit the space of the counters");
     return l;
 }
 
@@ -87,9 +85,8 @@ blink_status_t copy_tables(const blink_schedule& h, const BlockLayout& l, char* 
         BLINK_HIP(hipMemcpy(block + l.tmpl, s.tmpl.data(), s.tmpl.size() * sizeof(StageTmpl), hipMemcpyHostToDevice));
         BLINK_HIP(hipMemcpy(block + l.inst, s.inst.data(), s.inst.size() * sizeof(StageInst), hipMemcpyHostToDevice));
     } else if (!words_inline(h)) {
-        const FoldTables& t = h.fold;
-        BLINK_HIP(hipMemcpy(block + l.words, t.words.data(), t.words.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-        BLINK_HIP(hipMemcpy(block + l.levels, t.sets.data(), t.sets.size() * sizeof(FoldLevel), hipMemcpyHostToDevice));
+        const std::vector<uint32_t>& t = h.fold.tables;
+        BLINK_HIP(hipMemcpy(block + l.words, t.data(), t.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
     }
     return BLINK_OK;
 }
@@ -509,9 +506,9 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     }
     FoldParams p;   // every field that is read is set
     for (int i = 0; i < BLINK_MAX_RANKS; ++i) p.buf[i] = i < s.k ? bufs[i] : nullptr;
-    p.words = words_inline(*h) ? nullptr : reinterpret_cast<const unsigned*>(block + l.words);
-    p.levels = levels_inline(*h) ? nullptr
-                                 : reinterpret_cast<const FoldLevel*>(block + l.levels) + level_set(h->tile_override) * t.flows.size();
+    const unsigned* const tables = reinterpret_cast<const unsigned*>(block + l.words);
+    p.words = words_inline(*h) ? nullptr : tables;
+    p.levels = levels_inline(*h) ? nullptr : reinterpret_cast<const FoldLevel*>(tables + t.level_word(level_set(h->tile_override)));
     if (!p.words) fold_words(t.flows, kInlineFlows, p.inline_words);
     if (!p.levels) std::copy(t.levels.begin(), t.levels.end(), p.inline_levels);
     p.ticket = block ? reinterpret_cast<unsigned long long*>(block + l.ticket) : nullptr;

@@ -191,22 +191,27 @@ static_assert((kLeastTileOverride << (kLevelSets - 2)) == kMostTileOverride, "a 
 struct FoldTables {
     bool fits = false;               // the kernel can run the schedule
     std::vector<FoldFlow> flows;
-    std::vector<uint32_t> words;     // fold_words, stride = number of flows
     std::vector<FoldLevel> levels;   // room for one per flow; filled by the launch plan
-    std::vector<FoldLevel> sets;     // kLevelSets times as many, for tables on the device
+    // Tables on the device, copied as they are: fold_words with the number of flows as stride,
+    // then the sets of levels, room for one level per flow in each.
+    std::vector<uint32_t> tables;
+    static constexpr size_t words_per_flow() { return kFlowWords + kLevelSets * sizeof(FoldLevel) / sizeof(uint32_t); }
+    size_t level_word(uint32_t set) const {   // where a set starts
+        return (kFlowWords + set * sizeof(FoldLevel) / sizeof(uint32_t)) * flows.size();
+    }
     // Tile counts of the sets suffice for any distance of the buffers from a 1 KiB boundary.
     void fill_set(uint32_t set, uint32_t tile_elems) {
         fold_levels(flows, tile_elems, 0, true, &levels);
-        std::copy(levels.begin(), levels.end(), sets.begin() + set * flows.size());
+        uint32_t* to = tables.data() + level_word(set);
+        for (const FoldLevel& l : levels) *to++ = l.first, *to++ = l.base, *to++ = l.tiles, *to++ = l.members;
     }
 };
 inline void fold_tables(const Schedule& s, FoldTables* out) {
     out->fits = fold_flows(s, &out->flows);
     if (!out->fits) out->flows.clear();
-    out->words.assign(kFlowWords * out->flows.size(), 0);
-    fold_words(out->flows, static_cast<uint32_t>(out->flows.size()), out->words.data());
     out->levels.reserve(out->flows.size());
-    out->sets.assign(kLevelSets * out->flows.size(), FoldLevel{});
+    out->tables.assign(FoldTables::words_per_flow() * out->flows.size(), 0);
+    fold_words(out->flows, static_cast<uint32_t>(out->flows.size()), out->tables.data());
     for (uint32_t set = 0; set + 1 < kLevelSets; ++set) out->fill_set(set, kLeastTileOverride << set);
 }
 

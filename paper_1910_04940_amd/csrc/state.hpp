@@ -34,13 +34,13 @@ struct LaunchPlan {
 //   status record (kStatusWords 64-bit words), ticket counters, one counter of
 //   finished tiles per stage instance (counters kCounterStride words apart),
 //   stage templates, stage instances.  The fold kernel counts no finished tiles and
-//   knows neither templates nor instances: its flow
-//   words, where they do not travel in the kernel's arguments, lie where the counters
-//   of finished tiles would, behind them the sets of levels (together 204 of every 256 bytes there).
+//   knows neither templates nor instances: its
+//   tables, where they do not travel in the kernel's arguments, lie where the counters
+//   of finished tiles would (they need 204 of every 256 bytes there).
 struct BlockLayout {
     size_t ticket = 0, done = 0, tmpl = 0, inst = 0, bytes = 0;
     size_t counters_end = 0;  // status record and counters are [0, counters_end)
-    size_t words = 0, levels = 0;
+    size_t words = 0;         // FoldTables::tables
 };
 
 }  // namespace blink
