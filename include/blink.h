@@ -57,7 +57,7 @@ typedef enum {
     BLINK_ENOMEM = 3,        /* host or device allocation failed */
     BLINK_EMISMATCH = 4,     /* schedule does not fit the call (k, n, collective) */
     BLINK_EHIP = 5,          /* a HIP runtime call failed (no device, launch error) */
-    BLINK_ESTUCK = 6,        /* a stage gave up waiting for another one (see blink_schedule_status) */
+    BLINK_ESTUCK = 6,        /* a stage gave up waiting for another one, or calls overlapped (see blink_schedule_status) */
     BLINK_ELIMIT = 7         /* the schedule does not fit the fixed device block of blink_allreduce_noalloc */
 } blink_status_t;
 
@@ -407,14 +407,19 @@ blink_status_t blink_schedule_set_sweep(blink_schedule_t* s, int alternate);
  * kernel finishes normally, and later calls on the schedule do nothing until
  * blink_schedule_reset.  The rank buffers of an abandoned call hold partial
  * results.  Nothing but a bug (or two calls overlapping on one schedule) makes
- * a wait that long. */
+ * a wait that long.
+ * Payloads of more than a few tiles per compute unit that are served in one pass have their
+ * tiles dealt out by a counter.  There a call that overlaps with another call on the schedule is
+ * noticed by the counter's answers: the record is set, with no stage in it, both calls' results
+ * are partial, and later calls do nothing until blink_schedule_reset. */
 typedef struct {
-    int32_t state;          /* 0: every call so far ran to completion; 1: a wait was abandoned */
+    int32_t state;          /* 0: every call so far ran to completion; 1: a wait was abandoned, or calls overlapped */
     int32_t stage;          /* index (blink_schedule_get_stages order) of the stage that gave up; -1 if none */
     int32_t awaited_stage;  /* the stage it waited for; -1 if none */
     int32_t reserved;
-    uint64_t seen;          /* finished tiles the awaited stage had counted, over all calls */
-    uint64_t wanted;        /* the count it had to reach */
+    uint64_t seen;          /* finished tiles the awaited stage had counted, over all calls; without a stage: the
+                               tickets the counter had dealt out */
+    uint64_t wanted;        /* the count it had to reach; without a stage: dealt out when the call starts */
     uint64_t call;          /* number of the call on this schedule (1 = first) */
 } blink_progress_t;
 /* Waits for the device (hipDeviceSynchronize), then fills *out (host).

@@ -58,7 +58,7 @@ size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 BlockLayout layout_of(const Schedule& s) {
     constexpr size_t kLine = static_cast<size_t>(kCounterStride) * sizeof(unsigned long long);
     BlockLayout l;
-    l.ticket = static_cast<size_t>(kStatusWords) * sizeof(unsigned long long);
+    l.ticket = static_cast<size_t>(kStatusWords) * sizeof(unsigned long long);   // the fold kernel relies on it
     l.done = l.ticket + kMaxQueues * kLine;
     l.counters_end = l.done + s.inst.size() * kLine;
     l.tmpl = round_up(l.counters_end, 256);
@@ -280,15 +280,16 @@ blink_status_t read_status(blink_schedule* h, blink_progress_t* out) {
         std::lock_guard<std::mutex> lock(g_static_mutex);
         const StaticBlock& sb = g_static[dev];
         // record gone: the block has passed to another schedule, or there is no plan for the
-        // tables it holds (a reset or a skipped call since; a fold call need not clear the record)
+        // tables it holds (a reset or a skipped call since)
         if (dev != h->last_static_device || sb.owner != h->id || sb.fold != h->plan.fold) return BLINK_OK;
+        if (!h->static_record) return BLINK_OK;
         block = sb.ptr;
     } else if (h->device < 0) {
         return BLINK_OK;  // never ran: nothing can have gone wrong
     }
     unsigned long long rec[kStatusWords] = {};
     BLINK_HIP(hipDeviceSynchronize());
-    if (!block || h->plan.fold) return BLINK_OK;  // no stage waits for another: nothing can have gone wrong
+    if (!block) return BLINK_OK;  // no stage waits for another, no ticket is drawn: nothing can have gone wrong
     BLINK_HIP(hipMemcpy(rec, block, sizeof rec, hipMemcpyDeviceToHost));
     out->state = static_cast<int32_t>(rec[kStatusState]);
     if (rec[kStatusState] == 0) return BLINK_OK;
@@ -498,6 +499,7 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     const bool dealt = pl.small || grid == pl.n_items;
 
     if (static_block) {
+        h->static_record = !dealt;
         if (!dealt)
             if (blink_status_t st = launch_clear(block, l.done, stream)) return st;
     } else if (!dealt || !words_inline(*h)) {
@@ -524,6 +526,7 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     // backwards), unless switched off or timed.
     p.reverse = goes_backwards(!s.has_deps && !static_block && h->sweep_alternates, timed.index >= 0, h->epoch);
     p.dealt = dealt;
+    p.call = static_block ? 1 : static_cast<unsigned>(h->epoch + 1);
     if (blink_status_t st = launch(h, reinterpret_cast<const void*>(fn), grid, kFoldThreads, &p, stream, timed)) return st;
     h->last_kernel = way;
     if (static_block) return BLINK_OK;
@@ -584,8 +587,10 @@ blink_status_t run_hand_over(blink_schedule* h, void* const* bufs, blink_dtype_t
     p.n_inst = static_cast<unsigned>(s.inst.size());
     p.max_naps = 4;   // looks at a dependency back off to ~0.8 us apart
 
-    if (static_block)
+    if (static_block) {
+        h->static_record = true;
         if (blink_status_t st = launch_clear(block, l.counters_end, stream)) return st;
+    }
     if (blink_status_t st = launch(h, reinterpret_cast<const void*>(fn), static_cast<unsigned>(grid), kLanes, &p, stream, Timed())) return st;
     h->last_kernel = 1;
     if (static_block) return BLINK_OK;

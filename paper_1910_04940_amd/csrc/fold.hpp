@@ -61,6 +61,7 @@ struct FoldParams {
     unsigned redop;                  // blink_redop_t
     unsigned reverse;                // tickets walk from the last to the first
     unsigned dealt;                  // workgroup w takes tickets w, w + grid, ...; the counter is not used
+    unsigned call;                   // number of the call on its schedule
     FoldLevel inline_levels[kInlineFlows];
     unsigned inline_words[kFlowWords * kInlineFlows];
 };
@@ -304,9 +305,18 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
     };
     unsigned t = blockIdx.x;   // the grid has at most n_items workgroups
     unsigned slot = 0;
+    // Where tickets are drawn the status record lies in front of the counter.  If it is set
+    // (see the end) the buffers are left alone: asked for, by the scalar unit, beside the tables,
+    // and looked at when the first tile's loads are on their way, by one thread for all.
+    const unsigned state = dealt ? 0 : *as_const<unsigned>(p->ticket - kStatusWords + kStatusState);
     resolve(t);
     FoldPiece<N> cur = piece();
     load(cur);
+    if (!dealt) {
+        if (threadIdx.x == 0) drawn[1] = state;
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(drawn[1])) return;
+    }
     unsigned raw = draw();
     // In the loop a tile's loads are followed by the stores of the tile in front of it.
     // Stores into an empty window (dropped) give the first tile the same, and the
@@ -393,6 +403,19 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
         }
         if (!more) break;
         cur = next;
+    }
+    // A call's draws end less than a grid's width past its last ticket.  If this one did
+    // not, the counter was not where the host counted it to be when the call started, or has been
+    // moved since: another call on the schedule overlaps with this one.  Both have gone wrong
+    // (tickets are lost, or drawn twice).
+    if (!dealt && t - n_items >= gridDim.x && threadIdx.x == 0) {
+        unsigned long long* const status = p->ticket - kStatusWords;
+        if (__hip_atomic_exchange(status + kStatusState, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
+            status[kStatusStage] = status[kStatusAwaited] = ~0ull;
+            status[kStatusSeen] = p->ticket_base + static_cast<long long>(static_cast<int>(t - gridDim.x));
+            status[kStatusWanted] = p->ticket_base;
+            status[kStatusCall] = p->call;
+        }
     }
 }
 

@@ -93,3 +93,60 @@ def test_status_of_a_dependency_free_schedule_stays_ok():
     sched.test_skip_call()        # no stage waits for another: a skipped call number changes nothing
     bl.blink_allreduce(bufs, n, bl.BLINK_INT32, sched, torch.cuda.current_stream().cuda_stream)
     assert sched.status()[0] == bl.BLINK_OK
+
+
+@pytest.mark.parametrize("fusion", [bl.BLINK_FUSE_EDGE, bl.BLINK_FUSE_NODE, bl.BLINK_FUSE_TREE])
+def test_overlapping_calls_on_one_schedule_are_reported(fusion):
+    """Calls on one schedule must not overlap in time.  Where tickets are drawn from a counter a
+    call that does is noticed: here the later of two calls, on a stream of its own, runs while the
+    earlier one is still held up behind other work.  Each has buffers of its own, and every wave
+    leaves as soon as the counter's answers make no sense."""
+    dev = torch.device("cuda:0")
+    torch.cuda.set_device(dev)
+    stream = torch.cuda.current_stream().cuda_stream
+    k, n = 7, 4_000_003
+    parent = [-1] + [(v - 1) // 2 for v in range(1, k)]
+    trees = bl.blink_trees_from_arrays(k, [0], [parent], [1.0])
+    sched = bl.blink_make_schedule(trees, bl.BLINK_OP_ALLREDUCE, n, 1 << 18, fusion)
+    sched.set_kernel(1)           # no timed calls, which wait for events
+    x = [si.hash_payload(59, r, 0, n, "int32") for r in range(k)]
+    want = ox.allreduce_int32_definition(x)
+    src = [torch.from_numpy(a).to(dev) for a in x]
+
+    def call(bufs, on=stream):
+        bl.blink_allreduce(bufs, n, bl.BLINK_INT32, sched, on)
+
+    for _ in range(2):
+        bufs = [b.clone() for b in src]
+        call(bufs)
+        assert sched.status()[0] == bl.BLINK_OK
+        assert all(np.array_equal(b.cpu().numpy(), want) for b in bufs)
+
+    first, second = [b.clone() for b in src], [b.clone() for b in src]
+    held, done = torch.cuda.Stream(), torch.cuda.Event()
+    work = torch.zeros(1 << 28, device=dev)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(held):
+        for _ in range(200):          # 0.4 ms each
+            work.add_(1.0)
+    call(first, held.cuda_stream)
+    call(second)
+    done.record()
+    done.synchronize()
+    assert not held.query(), "the earlier call was to be held up"
+    st, rec = sched.status()
+    assert st == bl.BLINK_ESTUCK and rec["state"] == 1
+    assert rec["stage"] == -1 and rec["awaited_stage"] == -1
+    assert rec["call"] == 4 and rec["seen"] < rec["wanted"]
+
+    # until the reset calls leave the buffers alone
+    bufs = [b.clone() for b in src]
+    call(bufs)
+    assert sched.status() == (st, rec)
+    assert all(torch.equal(b, s) for b, s in zip(bufs, src))
+    sched.reset()
+    for _ in range(3):
+        bufs = [b.clone() for b in src]
+        call(bufs)
+        assert sched.status()[0] == bl.BLINK_OK
+        assert all(np.array_equal(b.cpu().numpy(), want) for b in bufs)
