@@ -98,7 +98,7 @@ typedef enum { BLINK_STEP_REDUCE = 0, BLINK_STEP_COPY = 1 } blink_step_kind_t;
  * another.  A wavefront either carries a tile through all of them in turn (NODE; EDGE
  * payloads that fit the GPU's 256 MiB memory-side cache), or the stages of one chunk
  * hand over to one another through device-side completion counters (larger EDGE
- * payloads). */
+ * payloads; any where blink_schedule_set_hand_over asks for it). */
 typedef enum { BLINK_FUSE_EDGE = 0, BLINK_FUSE_NODE = 1, BLINK_FUSE_TREE = 2 } blink_fusion_t;
 
 typedef struct blink_trees blink_trees_t;
@@ -399,6 +399,15 @@ int blink_schedule_last_kernel(const blink_schedule_t* s);
  * dependencies and blink_allreduce_noalloc always go forwards. */
 blink_status_t blink_schedule_set_sweep(blink_schedule_t* s, int alternate);
 
+/* always = 1: the stages of an EDGE or NODE program hand their chunks over to one another
+ * whatever the payload (the paper's own pipeline, which the chunk size paces); 0 (the default):
+ * the library decides, see blink_fusion_t.  Same bits either way.  A change waits for the device
+ * and restarts the schedule's progress counters; before a call is recorded into a graph it needs
+ * one call of blink_allreduce_noalloc.  blink_schedule_handed_over: 1 if the latest call handed
+ * chunks over, 0 if a wavefront carried its tiles through all stages, -1 before the first call. */
+blink_status_t blink_schedule_set_hand_over(blink_schedule_t* s, int always);
+int blink_schedule_handed_over(const blink_schedule_t* s);
+
 /* What became of the calls made on a schedule so far.  Where chunks are handed
  * over (see blink_fusion_t) a stage waits, chunk by chunk, for the stages it depends on
  * (section 4.1: an event per chunk).  Such a wait is bounded: after the wait
@@ -447,7 +456,9 @@ blink_status_t blink_schedule_test_skip_call(blink_schedule_t* s);
  * at the best chunk measured.  Chunks are kept inside [lo, hi] (elements, lo >=
  * 1).  Usage per iteration: make a schedule with blink_miad_chunk(), run and
  * time the collective, blink_miad_report(throughput, any unit); stop tuning
- * once blink_miad_steady() is non-zero (further reports change nothing). */
+ * once blink_miad_steady() is non-zero (further reports change nothing).  The chunk size
+ * changes the speed of programs that hand chunks over; others move the same tiles
+ * whatever it is, but for way 3 of blink_schedule_set_kernel. */
 typedef struct blink_miad blink_miad_t;
 blink_status_t blink_miad_create(size_t initial_chunk, double factor, size_t step, size_t lo,
                                  size_t hi, double rel_tol, blink_miad_t** out);

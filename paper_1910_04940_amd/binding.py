@@ -54,7 +54,7 @@ EXPORTS = [
     "blink_schedule_get_stages", "blink_schedule_status", "blink_schedule_reset",
     "blink_schedule_set_wait_limit", "blink_schedule_test_skip_call", "blink_allreduce_noalloc",
     "blink_schedule_set_kernel", "blink_schedule_last_kernel", "blink_schedule_set_sweep", "blink_schedule_get_tickets", "blink_schedule_batch",
-    "blink_schedule_kernel_bytes",
+    "blink_schedule_kernel_bytes", "blink_schedule_set_hand_over", "blink_schedule_handed_over",
 ]
 
 
@@ -129,6 +129,8 @@ def lib() -> C.CDLL:
     L.blink_schedule_get_bounds.argtypes = [vp, C.POINTER(C.c_uint64)]
     L.blink_schedule_traffic_bytes.argtypes = [vp]
     L.blink_schedule_traffic_bytes.restype = C.c_uint64
+    L.blink_schedule_set_hand_over.argtypes = [vp, C.c_int]
+    L.blink_schedule_handed_over.argtypes = [vp]
     L.blink_schedule_kernel_bytes.argtypes = [vp]
     L.blink_schedule_kernel_bytes.restype = C.c_uint64
     L.blink_schedule_free.argtypes = [vp]
@@ -315,6 +317,16 @@ class Schedule:
 
     def set_sweep(self, alternate: bool) -> None:
         _check(lib().blink_schedule_set_sweep(self._h, 1 if alternate else 0), "blink_schedule_set_sweep")
+
+    def set_hand_over(self, always: bool) -> None:
+        """True: the stages of a per-edge or per-node program hand chunks over to one another
+        whatever the payload; False: the library decides."""
+        _check(lib().blink_schedule_set_hand_over(self._h, 1 if always else 0), "blink_schedule_set_hand_over")
+
+    @property
+    def handed_over(self) -> int:
+        """1 if the latest call handed chunks over, 0 if not, -1 before the first call."""
+        return lib().blink_schedule_handed_over(self._h)
 
     @property
     def last_kernel(self) -> int:

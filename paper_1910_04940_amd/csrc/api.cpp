@@ -220,7 +220,7 @@ uint64_t blink_schedule_traffic_bytes(const blink_schedule_t* s) { return s ? s-
 
 uint64_t blink_schedule_kernel_bytes(const blink_schedule_t* s) {
     if (!s) return 0;
-    const bool fold = blink::served_by(s->s, s->fold.fits, s->call_skipped) == blink::Served::kFold;
+    const bool fold = blink::served_by(s->s, s->fold.fits, s->must_wait()) == blink::Served::kFold;
     return fold ? blink::fold_bytes(s->s) : s->s.traffic_bytes;
 }
 
@@ -326,6 +326,18 @@ blink_status_t blink_schedule_test_skip_call(blink_schedule_t* s) {
     }
     return BLINK_OK;
 }
+
+blink_status_t blink_schedule_set_hand_over(blink_schedule_t* s, int always) {
+    if (!s || (always != 0 && always != 1)) return BLINK_EINVAL;
+    if (s->hand_over == (always == 1)) return BLINK_OK;
+    s->hand_over = always == 1;
+    if (!s->s.has_deps) return BLINK_OK;   // no stage waits for another
+    BLINK_GUARD_BEGIN
+    return blink::reset_progress(s);
+    BLINK_GUARD_END
+}
+
+int blink_schedule_handed_over(const blink_schedule_t* s) { return s ? s->handed_over : -1; }
 
 blink_status_t blink_schedule_set_kernel(blink_schedule_t* s, int kernel) {
     if (!s || kernel < 0 || kernel > 3) return BLINK_EINVAL;

@@ -235,7 +235,7 @@ blink_status_t make_plan(blink_schedule* h) {
         if (n_cu < 1) return BLINK_EHIP;
         h->n_cu = n_cu;
     }
-    const Served served = served_by(h->s, h->fold.fits, h->call_skipped);   // a skipped call asks for waiting stages
+    const Served served = served_by(h->s, h->fold.fits, h->must_wait());
     if (served == Served::kNot) return BLINK_EINVAL;
     pl.fold = served == Served::kFold;
     if (pl.fold)
@@ -529,6 +529,7 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     p.call = static_block ? 1 : static_cast<unsigned>(h->epoch + 1);
     if (blink_status_t st = launch(h, reinterpret_cast<const void*>(fn), grid, kFoldThreads, &p, stream, timed)) return st;
     h->last_kernel = way;
+    h->handed_over = 0;
     if (static_block) return BLINK_OK;
     h->epoch += 1;
     if (!dealt) h->ticket_base[0] += pl.n_items;   // every ticket is followed by one draw
@@ -593,6 +594,7 @@ blink_status_t run_hand_over(blink_schedule* h, void* const* bufs, blink_dtype_t
     }
     if (blink_status_t st = launch(h, reinterpret_cast<const void*>(fn), static_cast<unsigned>(grid), kLanes, &p, stream, Timed())) return st;
     h->last_kernel = 1;
+    h->handed_over = 1;
     if (static_block) return BLINK_OK;
     h->epoch += 1;
     // queue q holds the tickets q, q + n_queues, ...; every wave draws exactly one

@@ -250,7 +250,7 @@ __device__ __forceinline__ void run_stage(ConstParams p, RankTable ranks, ConstT
 }
 
 // The same for any number of ranks, one after the other: the fan-ins of per-node programs,
-// which only come here after a skipped call (see blink_schedule_test_skip_call).
+// which only come here where the caller asks for it (see blink_schedule_set_hand_over).
 template <typename T>
 __device__ __forceinline__ void run_stage_any(ConstParams p, RankTable ranks, ConstTmpl st, unsigned long long byte_off,
                                               unsigned bytes, int lane) {

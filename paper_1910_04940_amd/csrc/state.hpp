@@ -56,6 +56,9 @@ struct blink_schedule {
     uint64_t epoch = 0;           // calls made so far on d_block; its counters hold epoch * tiles
     uint64_t ticket_base[16] = {};  // value of each ticket counter when the next call starts
     bool call_skipped = false;    // blink_schedule_test_skip_call was used: stages wait for one another
+    bool hand_over = false;       // so does the caller want it (blink_schedule_set_hand_over)
+    int handed_over = -1;         // whether the latest call's stages waited; -1 = none yet
+    bool must_wait() const { return call_skipped || hand_over; }
     uint64_t wait_limit_us = 0;   // longest wait for another stage; 0 = default
     int n_cu = 0;
     int wg_per_cu = 0;            // launch override (0 = automatic)

@@ -221,9 +221,11 @@ def test_int32_hand_over_kernels_at_streaming_size(dev, fusion):
     x = [si.payload(32, r, n, "int", "int32") for r in range(8)]
     bufs = [torch.from_numpy(a).to(dev) for a in x]
     sched = bl.blink_make_schedule(trees, bl.BLINK_OP_ALLREDUCE, n, chunk, FUSION[fusion])
+    sched.set_hand_over(True)     # per-node programs are served in one pass otherwise
     bl.blink_allreduce(bufs, n, bl.BLINK_INT32, sched, stream())
     want = ox.allreduce_int32_definition(x)
     torch.cuda.synchronize()
+    assert sched.handed_over == 1 and sched.status()[0] == bl.BLINK_OK
     for b in bufs:
         assert np.array_equal(b.cpu().numpy(), want)
 

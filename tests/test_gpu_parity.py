@@ -431,6 +431,7 @@ def test_many_hand_overs_between_waves_stay_exact(dev, fusion):
     n, chunk, k = 1 << 21, 1 << 10, 8
     trees = pack(top, 0)
     sched = bl.blink_make_schedule(trees, bl.BLINK_OP_ALLREDUCE, n, chunk, fusion)
+    sched.set_hand_over(True)     # a payload of this size is served in one pass otherwise
     assert sched.num_stages >= 2048 * 8
     x = [si.hash_payload(17, r, 0, n, "int32") for r in range(k)]
     bufs = to_dev(x, dev)
@@ -445,3 +446,4 @@ def test_many_hand_overs_between_waves_stay_exact(dev, fusion):
         for r in (0, 3, 7):
             got = bufs[r].cpu().numpy().view(np.uint32).astype(np.uint64)
             assert np.array_equal(got, want), f"after {calls} calls, rank {r}"
+        assert sched.handed_over == 1 and sched.status()[0] == bl.BLINK_OK

@@ -21,7 +21,8 @@ import paper_1910_04940_amd as bl  # noqa: E402
 
 @pytest.mark.parametrize("fusion", [bl.BLINK_FUSE_EDGE, bl.BLINK_FUSE_NODE])
 @pytest.mark.parametrize("n,chunk", [(1 << 16, 1 << 12), (1 << 22, 1 << 16)])
-def test_abandoned_wait_is_reported_and_reset_recovers(fusion, n, chunk):
+@pytest.mark.parametrize("hand_over", [False, True])     # the calls before the skipped one and after the reset
+def test_abandoned_wait_is_reported_and_reset_recovers(hand_over, fusion, n, chunk):
     assert torch.cuda.is_available()
     dev = torch.device("cuda:0")
     torch.cuda.set_device(dev)
@@ -35,6 +36,7 @@ def test_abandoned_wait_is_reported_and_reset_recovers(fusion, n, chunk):
     ox.run_steps(want, steps)
 
     sched = bl.blink_make_schedule(trees, bl.BLINK_OP_ALLREDUCE, n, chunk, fusion)
+    sched.set_hand_over(hand_over)
     st, rec = sched.status()
     assert st == bl.BLINK_OK and rec["state"] == 0 and rec["stage"] == -1     # never ran
 
@@ -42,7 +44,7 @@ def test_abandoned_wait_is_reported_and_reset_recovers(fusion, n, chunk):
     bufs = [torch.from_numpy(a).to(dev) for a in x]
     bl.blink_allreduce(bufs, n, bl.BLINK_INT32, sched, stream)
     st, rec = sched.status()
-    assert st == bl.BLINK_OK and rec["state"] == 0
+    assert st == bl.BLINK_OK and rec["state"] == 0 and sched.handed_over == int(hand_over)
     for b, wv in zip(bufs, want):
         assert np.array_equal(b.cpu().numpy(), wv)
 
@@ -52,7 +54,7 @@ def test_abandoned_wait_is_reported_and_reset_recovers(fusion, n, chunk):
     bufs = [torch.from_numpy(a).to(dev) for a in x]
     bl.blink_allreduce(bufs, n, bl.BLINK_INT32, sched, stream)
     st, rec = sched.status()                       # waits for the kernel, which ends by itself
-    assert st == bl.BLINK_ESTUCK and rec["state"] == 1
+    assert st == bl.BLINK_ESTUCK and rec["state"] == 1 and sched.handed_over == 1
     stages = sched.stages()
     assert 0 <= rec["stage"] < len(stages) and 0 <= rec["awaited_stage"] < rec["stage"]
     assert rec["awaited_stage"] in [int(d) for d in stages[rec["stage"]]["deps"][:stages[rec["stage"]]["n_dep"]]]
@@ -79,7 +81,7 @@ def test_abandoned_wait_is_reported_and_reset_recovers(fusion, n, chunk):
         torch.cuda.synchronize()
         for b, wv in zip(bufs, want):
             assert np.array_equal(b.cpu().numpy(), wv)
-    assert sched.status()[0] == bl.BLINK_OK
+    assert sched.status()[0] == bl.BLINK_OK and sched.handed_over == int(hand_over)
 
 
 def test_status_of_a_dependency_free_schedule_stays_ok():
