@@ -243,7 +243,7 @@ blink_status_t blink_hybrid_split(double d_total, double bw_slow, double bw_fast
                                   double* d_slow, double* d_fast);
 
 size_t blink_schedule_num_steps(const blink_schedule_t* s);   /* tree-edge transfers */
-size_t blink_schedule_num_stages(const blink_schedule_t* s);  /* passes the kernel makes (== steps for EDGE) */
+size_t blink_schedule_num_stages(const blink_schedule_t* s);  /* the program's passes (== steps for EDGE) */
 int blink_schedule_num_trees(const blink_schedule_t* s);
 /* Chunks of a tree that share a time slot of the step list.  The list is ordered
  * by time slots of a fully pipelined execution in which the chunks advance from
@@ -253,24 +253,28 @@ int blink_schedule_num_trees(const blink_schedule_t* s);
 uint64_t blink_schedule_batch(const blink_schedule_t* s);
 /* out[num_steps] (host, caller-allocated): the step list in execution order. */
 blink_status_t blink_schedule_get_steps(const blink_schedule_t* s, blink_step_t* out);
-/* out[num_stages] (host, caller-allocated): the kernel's passes in the order
- * in which their tickets are handed out (a topological order of the deps). */
+/* out[num_stages] (host, caller-allocated): the program's passes in a topological order
+ * of the deps; where chunks are handed over (see blink_fusion_t) that in which the kernel's
+ * tickets are handed out. */
 blink_status_t blink_schedule_get_stages(const blink_schedule_t* s, blink_stage_t* out);
-/* The order in which the kernel hands out its work when a tile has tile_elems
+/* The program's work as a list of tickets when a tile has tile_elems
  * elements (a power of two in [256, 65536]; the library's own choice depends on
  * the device): ticket t is tile tile[t] of stage stage[t] (an index into
  * blink_schedule_get_stages; tile i of a stage covers the stage's elements in
  * block (off / tile_elems + i) of the payload's tile_elems-element blocks), or
  * tile[t] == -1 for a ticket that stands for nothing (stages shorter than the
- * longest one).  Wavefronts take tickets in ascending order.  Where the order
- * is free (no stage waits for another) the tickets walk tile by tile across the
+ * longest one).  Where chunks are handed over (see blink_fusion_t) wavefronts take
+ * these very tickets in ascending order.  Where the order is free (no stage waits for
+ * another) the tickets walk tile by tile across the
  * trees (section 4.2.2: trees sharing the machine take turns) unless a stage
  * reads more than 8 ranks.  There the list states the turns, not the very tiles: the
  * library may also serve such a schedule in another order where it measured that to
  * be faster (blink_schedule_set_kernel), in alternating directions
  * (blink_schedule_set_sweep), it pays no heed to chunk boundaries inside a tree's
  * share, and tiles start on 1 KiB boundaries of the rank buffers where all of these
- * start the same distance past one.
+ * start the same distance past one.  EDGE and NODE programs whose tiles are carried through
+ * all stages at once do not follow the list: there the trees take no turns, one tree's share
+ * comes after the other.
  * *n_tickets receives the count; stage and tile (host, caller-allocated, that
  * many entries) may both be null to ask for the count. */
 blink_status_t blink_schedule_get_tickets(const blink_schedule_t* s, uint32_t tile_elems, uint64_t* n_tickets,
@@ -443,7 +447,9 @@ blink_status_t blink_schedule_set_wait_limit(blink_schedule_t* s, uint64_t micro
 /* For tests of the give-up path only: counts one call as made without
  * launching it.  The stages of the next call then wait for progress that never
  * comes, the waits run into the limit, and the call ends as described above.  Until the
- * next blink_schedule_reset chunks are handed over whatever the fusion level and size. */
+ * next blink_schedule_reset the stages of EDGE and NODE programs hand chunks over whatever the
+ * size.  Before the schedule's first call, and for calls of blink_allreduce_noalloc, which start
+ * from cleared counters, it counts nothing; TREE programs have no waits to miss it. */
 blink_status_t blink_schedule_test_skip_call(blink_schedule_t* s);
 
 /* ---- chunk-size selection across iterations (host only) ---------------------- */

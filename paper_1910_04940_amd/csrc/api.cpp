@@ -200,7 +200,7 @@ blink_status_t blink_schedule_get_tickets(const blink_schedule_t* s, uint32_t ti
     while ((1u << shift) < tile_elems) ++shift;
     uint32_t tiles_per_chunk = 1;
     const unsigned group = blink::ticket_group(sc);
-    const uint64_t n = blink::ticket_count(sc, group, shift, 0, &tiles_per_chunk);
+    const uint64_t n = blink::ticket_count(sc, group, shift, &tiles_per_chunk);
     *n_tickets = n;
     if (!stage && !tile) return BLINK_OK;
     if (!stage || !tile) return BLINK_EINVAL;

@@ -186,7 +186,7 @@ void plan_hand_over(blink_schedule* h) {
     pl.tile_elems = tile;
     pl.tile_shift = 0;
     while ((1u << pl.tile_shift) < tile) ++pl.tile_shift;
-    pl.n_items = ticket_count(s, 1, pl.tile_shift, 0, &pl.tiles_per_chunk);
+    pl.n_items = ticket_count(s, 1, pl.tile_shift, &pl.tiles_per_chunk);
 }
 
 // The plan where the fold kernel runs the schedule.  A ticket is one sub-tile of the
@@ -462,7 +462,9 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     const bool sum = redop == BLINK_SUM;
     const bool by_tile = pl.n_load <= 8 && t.flows.size() <= 64;
     Timed timed;
-    const bool choice = !pl.small && !s.has_deps;   // programs with dependencies have way 1 only
+    // Programs with dependencies have way 1 only.  Way 2 is offered up to four accumulators, as the
+    // interface says; the kernel has no such limit, and what it gives deeper stages was not measured.
+    const bool choice = !pl.small && !s.has_deps;
     const int way = choose_way(h, static_block, dtype, sum, choice && s.max_stack <= 4, choice && by_tile && t.flows.size() > 1, &timed);
     const uint64_t chunk_tiles = std::max<uint64_t>(1, s.chunk / pl.tile_elems);
     const uint32_t chunk_turn = static_cast<uint32_t>(std::min<uint64_t>(chunk_tiles, kTurnPayload));

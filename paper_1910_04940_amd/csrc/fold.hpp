@@ -9,9 +9,9 @@
 // How a workgroup works, and why:
 //
 //   * Four waves share one tile; a wave owns U columns of 1 KiB per rank, so a
-//     tile is 4 * U KiB of every rank, and about 64 KiB of loads per workgroup are in
-//     flight whatever the number of ranks (fold_columns).  One such workgroup on
-//     seven of eight CUs is what HBM likes best.  Measured with a standalone probe
+//     tile is 4 * U KiB of every rank.  U falls with the number of ranks (fold_columns): where
+//     all ranks are written 44 to 80 KiB of loads per workgroup are in flight.  One such
+//     workgroup on seven of eight CUs is what HBM likes best.  Measured with a standalone probe
 //     (8 ranks, three sets of buffers in turn, 64 MiB per rank): 128 / 160 / 192 /
 //     224 / 256 workgroups 211 / 180 / 168 / 165 / 169 us; twice the bytes per
 //     workgroup on 112 of them 213 us; two single waves of 32 KiB per CU, 4 KiB of
@@ -67,17 +67,17 @@ struct FoldParams {
 };
 static_assert(sizeof(FoldParams) <= 4096, "kernel arguments");
 
-// Columns per wave and rank for stages that read n ranks: n * U of about 16 where all
-// ranks are written, twice that where one is (a tile is then hardly more than its loads;
-// 8 ranks, Reduce, 64 MiB: 118 -> 86 us), and never so many that one counter would
-// have to serve more than about 60 tickets per microsecond (it sustains 80).
+// Columns per wave and rank for stages that read n ranks: n * U of 14 to 20 (from 11 ranks
+// on one column).  7 and 8 ranks of which one is written get twice as many (a tile is then
+// hardly more than its loads; 8 ranks, Reduce, 64 MiB: 118 -> 86 us); with other numbers of
+// ranks that was not measured.  One rank that is copied: 4, 16 KiB of loads per workgroup.
 constexpr int fold_columns(int n, bool all) {
     return n == 1 ? 4 : n == 2 ? 8 : n == 3 ? 6 : n == 4 ? 4 : n <= 6 ? 3 : n <= 8 ? (all ? 2 : 4) : n <= 10 ? 2 : 1;
 }
-// A payload of about two tiles per CU or less is latency-bound; there tiles of half the
-// size are faster (us, 4 MiB per rank, full / half: 8 ranks 13.3 / 11.4, 5 ranks 8.2 / 7.6, 4
-// ranks 7.7 / 7.2; with three tiles per CU, 8 ranks x 6 MiB, 16.1 / 17.8).  Only where all
-// ranks are written (Reduce, 8 x 4 MiB: 7.6 / 8.6; Broadcast 6.5 / 9.4).
+// A payload of about two tiles per CU or less is latency-bound; where all ranks are written,
+// tiles of half the size are faster there (us, 4 MiB per rank, full / half: 8 ranks 13.3 / 11.4,
+// 5 ranks 8.2 / 7.6, 4 ranks 7.7 / 7.2; with three tiles per CU, 8 ranks x 6 MiB, 16.1 / 17.8), but
+// not where one is (Reduce, 8 x 4 MiB: 7.6 / 8.6; Broadcast 6.5 / 9.4).
 constexpr bool fold_has_half(int n, bool all) { return all && fold_columns(n, all) > 1; }
 constexpr int fold_columns(int n, bool all, bool half) {
     return half && fold_has_half(n, all) ? (fold_columns(n, all) + 1) / 2 : fold_columns(n, all);

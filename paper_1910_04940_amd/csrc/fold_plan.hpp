@@ -149,12 +149,15 @@ constexpr uint64_t kMemorySideCacheBytes = 256ull << 20;
 // stack program, so a schedule the fold kernel cannot run is not run at all.  With
 // dependencies the fold kernel carries a tile through all its transfers in one wave and writes
 // each of them to its rank buffer; the alternative is to hand chunks over from wave to wave,
-// through counters and memory.  Measured on 8 ranks, us, handed over / in one wave:
-//   per-node: 5 MiB 97 / 16, 20 MiB 156 / 62, 64 MiB 310 / 180, 256 MiB 1059 / 723: always.
-//   per-edge: 0.1 MiB 49 / 6, 8 MiB 124 / 30, 30 MiB 226 / 96.  In one wave where the
-//     payload fits the memory-side cache.  A larger one keeps the paper's pipeline of
-//     chunks that are handed on transfer by transfer: its speed is what callers who tune
-//     the chunk size (section 4.2.1, blink_miad_*) measure.
+// through counters and memory.  Measured on 8 ranks, fp32 sums, three sets of buffers in turn,
+// us, handed over (the best of 16 KiB to 4 MiB chunks) / in one wave:
+//   MiB per rank      8           16          32           64          128         256
+//   per-node      58 / 24     88 / 53    162 / 93    309 / 176   588 / 350   1132 / 719
+//   per-edge      61 / 26     96 / 54    173 / 95    325 / 179   603 / 354   1169 / 725
+// One wave is about twice as fast at every size.  Per-edge payloads larger than the memory-side
+// cache are handed over all the same, not for speed: they are the paper's pipeline of chunks,
+// and its pace is what callers who tune the chunk size (section 4.2.1, blink_miad_*) measure
+// there; blink_schedule_set_hand_over gives them the same on smaller ones.
 // hand_over: waiting stages are asked for.
 enum class Served { kFold, kHandOver, kNot };
 inline Served served_by(const Schedule& s, bool fold_fits, bool hand_over) {

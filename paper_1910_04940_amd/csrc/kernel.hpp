@@ -1,5 +1,5 @@
-// The device side of schedules whose stages wait for one another (per-edge and
-// per-node programs; fold.hpp has the others): one persistent gfx950 kernel that
+// The device side of schedules whose stages wait for one another (large per-edge programs,
+// and any with dependencies where the caller asks for it; fold.hpp has the others): one persistent gfx950 kernel that
 // consumes the stage list of all trees concurrently (paper sections 3.3, 4.1, 4.2.1,
 // 4.2.2).  kernel_{f32,i32}.hip instantiate it for the two element types, exec.hip holds
 // the launcher.

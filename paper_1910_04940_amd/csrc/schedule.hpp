@@ -12,8 +12,8 @@ namespace blink {
 constexpr int kMaxOps = 40;    // micro-operations of one stage (<= 2k - 2 for k <= 16, see eval_tree)
 constexpr int kMaxDeps = 8;    // stages one stage may wait for
 
-// Micro-operations on the per-thread accumulator `acc` and the per-thread LDS
-// slots (slot i initially holds what was loaded from rank load_rank[i]).
+// Micro-operations on an accumulator `acc` and slots (slot i initially holds what was
+// loaded from rank load_rank[i]).
 enum : uint8_t { OP_LD = 0, OP_ADD = 1, OP_ST = 2 };  // acc = slot; acc += slot; slot = acc
 inline uint8_t make_op(uint8_t kind, uint8_t slot) { return static_cast<uint8_t>((kind << 6) | slot); }
 
@@ -98,17 +98,18 @@ struct Schedule {
     uint32_t max_slots = 1;              // largest n_load
     uint32_t max_stack = 0;              // most accumulators any stage's stack program needs (255: some stage has none)
     bool has_deps = false;               // some stage waits for another
-    uint64_t traffic_bytes = 0;          // bytes read plus written in rank buffers per call
-    uint64_t read_bytes = 0;             // the part of it that is read
+    uint64_t traffic_bytes = 0;          // bytes the stages read plus write in rank buffers per call
 };
 
-// ---- the order in which the kernels hand out their work (section 4.2.2) ---------------
+// ---- the order of a schedule's work (section 4.2.2) -----------------------------------
 // A ticket is (stage instance, tile).  Instances come in the schedule's
 // execution order (time slot = chunk + level, the trees taking turns inside a
 // slot); `group` consecutive instances (the trees' turns at one chunk position)
 // have their tiles handed out in turn, tile by tile across the instances, so
 // that all trees advance together; group == 1 keeps an instance's tiles
-// together.  Host and device use this one function.
+// together.  The kernel for waiting stages and the published list
+// (blink_schedule_get_tickets) use this one function, the kernel with group == 1; the
+// one-pass kernel has fold_ticket instead.
 #if defined(__HIP__) || defined(__HIPCC__)
 #define BLINK_HOST_DEVICE __host__ __device__
 #else
@@ -124,7 +125,7 @@ BLINK_HOST_DEVICE inline void ticket_to_tile(unsigned long long t, unsigned grou
     *tile = within / members;
 }
 
-// `group` for a schedule.  Without dependencies the order of tiles is free: the
+// `group` of the published list.  Without dependencies the order of tiles is free: the
 // trees are interleaved tile by tile, all of them while a stage reads at most 8
 // ranks.  With more ranks per stage that makes too many request streams at a
 // time (16 ranks x 16 one-hop trees = 256): there the trees take turns chunk by
@@ -135,9 +136,8 @@ inline unsigned ticket_group(const Schedule& s) {
     return s.n_flows < 1u ? 1u : (s.n_flows > 64u ? 64u : s.n_flows);
 }
 
-// Number of tickets of a schedule for tiles of 2^tile_shift elements on a grid
-// moved down by grid_shift elements, handed out in groups of `group` instances
-// (see ticket_to_tile); *tiles_per_chunk receives the tile count
+// Number of tickets of a schedule for tiles of 2^tile_shift elements, handed out in groups
+// of `group` instances (see ticket_to_tile); *tiles_per_chunk receives the tile count
 // of the instance that has most (every group of instances but the last gets
 // that many tickets per member).  The last group gets only as many per member
 // as its own largest instance has: with trees of equal weight every tree's
@@ -145,11 +145,10 @@ inline unsigned ticket_group(const Schedule& s) {
 // their holder a trip to the counter (25.6 MB shares in 4 MiB chunks: an
 // eighth of the tickets were such, and 8 % of the time).  Schedules with
 // dependencies keep the full count: their groups are single instances.
-inline uint64_t ticket_count(const Schedule& s, unsigned group, unsigned tile_shift, uint32_t grid_shift,
-                             uint32_t* tiles_per_chunk) {
+inline uint64_t ticket_count(const Schedule& s, unsigned group, unsigned tile_shift, uint32_t* tiles_per_chunk) {
     const uint64_t tile = 1ull << tile_shift;
     auto tiles_of = [&](const StageInst& in) {
-        return ((in.off + grid_shift + in.len + tile - 1) >> tile_shift) - ((in.off + grid_shift) >> tile_shift);
+        return ((in.off + in.len + tile - 1) >> tile_shift) - (in.off >> tile_shift);
     };
     uint64_t most = 1;
     for (const StageInst& in : s.inst) most = most > tiles_of(in) ? most : tiles_of(in);

@@ -6,9 +6,10 @@ the second, and so on, instead of one tree running ahead and the others being
 The oracle states the scheme (oracle.schedule.fair_order) and a model to judge
 orders by (link_timeline: unit-time steps, one step per directed link at a
 time, served in list order).  Its numbers on the section's own example are
-pinned to values derived by hand below.  The library's two orderings are then
-held to the same properties: the public step list (per-edge program) and the
-order in which the kernel hands out tiles (whole-tree program).  No GPU."""
+pinned to values derived by hand below.  The library's two published orderings are then
+held to the same properties: the step list (per-edge program) and the list of tickets
+(whole-tree program).  The kernel that serves whole-tree programs has a mapping of its own
+with the same turns, which tests/test_fold_plan.py holds to them.  No GPU."""
 import numpy as np
 import pytest
 
@@ -138,9 +139,8 @@ def test_library_step_list_shares_every_link_chunk_by_chunk(coll):
 
 
 def test_tile_order_of_the_whole_tree_program_walks_across_the_trees():
-    """The kernel hands out tickets in ascending order; where no stage waits for
-    another, ticket -> (stage, tile) goes tile by tile across the trees: the
-    finest form of taking turns.  This is the function the kernels call."""
+    """Where no stage waits for another, ticket -> (stage, tile) of the published list goes
+    tile by tile across the trees: the finest form of taking turns."""
     top = si.hybrid_cube_mesh()
     trees = bl.blink_pack_trees(top.k, top.src, top.dst, top.cap, 0)
     T = trees.count
@@ -175,8 +175,8 @@ def test_tile_order_of_the_whole_tree_program_walks_across_the_trees():
 
 
 def test_tile_order_keeps_stages_together_where_that_is_the_rule():
-    """Stages that wait for one another follow the execution order itself; so do
-    whole-tree stages that read more than 8 ranks (too many request streams at a
+    """Stages that wait for one another (handed over, their kernel's order) follow the execution
+    order itself; so do whole-tree stages that read more than 8 ranks (too many request streams at a
     time otherwise)."""
     top = si.complete_graph(16)
     trees = bl.blink_pack_trees(16, top.src, top.dst, top.cap, bl.BLINK_ROOT_ANY)

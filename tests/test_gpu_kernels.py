@@ -1,9 +1,8 @@
-"""The two kernels that can run a whole-tree sum at streaming size (the
-ticket-drawing kernel with loads staged through registers, and the streaming
-kernel with loads straight into LDS and the stage computed as a stack program),
-each forced in turn, and the automatic choice between them: all against the
-oracle, bit for bit.  Sizes are large enough that the schedules stream (below
-that size both choices run the small-payload kernel)."""
+"""The ways in which a whole-tree program can be served at streaming size (tile by tile
+across the trees, one front through the payload, chunk by chunk across the trees), each
+forced in turn, and the automatic choice among them: all against the oracle, bit for bit.
+Sizes are large enough that the schedules stream (smaller payloads get a workgroup for
+every tile, and way 1)."""
 import numpy as np
 import pytest
 
@@ -39,8 +38,8 @@ CASES = [
     ("k16", bl.BLINK_ROOT_ANY, (1 << 23) + 12, 1 << 20),
     ("k2", 1, (1 << 26) + 1, 1 << 20),
     ("chain5", 2, 30_000_002, 1 << 19),
-    ("deep8", 0, (1 << 24) + 7, 1 << 18),          # 4 accumulators: the most the streaming kernel takes
-    ("deep12", 0, 9_000_001, 1 << 18),             # 6 accumulators: only the ticket-drawing kernel can run it
+    ("deep8", 0, (1 << 24) + 7, 1 << 18),          # 4 accumulators: the most way 2 is offered for
+    ("deep12", 0, 9_000_001, 1 << 18),             # 6 accumulators: way 1 only, as the interface says
 ]
 
 
@@ -97,7 +96,7 @@ def test_streaming_kernel_on_reduce_and_broadcast(coll):
         assert np.array_equal(bufs[0].cpu().numpy(), ox.allreduce_int32_definition(x))
         for r in range(1, k):
             assert np.array_equal(bufs[r].cpu().numpy(), x[r])
-        # another operator than the sum runs on the ticket-drawing kernel, whatever was asked for
+        # another operator than the sum is served the first way, whatever was asked for
         bufs = [torch.from_numpy(a).to(dev) for a in x]
         bl.blink_reduce(bufs, n, bl.BLINK_INT32, bl.BLINK_MAX, sched, stream)
         torch.cuda.synchronize()
@@ -130,8 +129,7 @@ def test_automatic_choice_times_every_way_and_settles():
         torch.cuda.synchronize()
         for b in bufs:
             assert np.array_equal(b.cpu().numpy(), want), call
-    # the timed calls go round the three ways (either kernel, and the first with
-    # the trees taking turns chunk by chunk), then one of them serves
+    # the timed calls go round the three ways, then one of them serves
     assert seen[:12] == [1, 2, 3] * 4
     assert len(set(seen[12:])) == 1 and seen[12] in (1, 2, 3)
     # one tree: nothing to take turns, two ways
@@ -228,10 +226,9 @@ def test_rank_buffers_that_do_not_start_on_1k_boundaries(kernel, past):
 
 @pytest.mark.parametrize("n", [1_500_003, 2_713_001, 4_200_005, 6_000_002])
 def test_payloads_whose_tickets_are_dealt_out_in_several_rounds(n):
-    """Between the smallest payloads (one ticket per wave) and the streaming
-    sizes the tickets are dealt out over every wave that fits, two to five each,
-    on the 16-column kernel with two waves per SIMD.  Two calls in place, both
-    element types, against the oracle."""
+    """Round the size up to which every tile gets a workgroup of its own (2.6 M elements
+    on 8 ranks): more workgroups than fit at a time below, drawn tickets above.  Two calls in
+    place, both element types, against the oracle."""
     dev, stream = _dev()
     top = si.hybrid_cube_mesh()
     k, chunk = 8, 1 << 18
