@@ -378,9 +378,8 @@ blink_status_t blink_schedule_set_launch(blink_schedule_t* s, int wg_per_cu, int
  * chunk (section 4.2.2 at the paper's own granularity) instead of tile by tile
  * (several trees only).  kernel: 0 = automatic: the first calls of at least
  * 64 MiB of traffic go round the ways the schedule has, four times each (eight
- * or twelve calls, all forwards through the payload), timed with events on the caller's
- * stream; the call after them waits for them, and the fastest way serves from then on,
- * whatever the operator.  Sums, and the other operators on either element type, go
+ * or twelve calls), timed with events on the caller's stream; the call after
+ * them waits for them, and the fastest way serves from then on, whatever the operator.  Sums, and the other operators on either element type, go
  * round by themselves; whichever is done first decides.  blink_allreduce_noalloc takes no
  * part in the timing: it uses way 1 until there is a pick, then that.  Payloads of a few
  * tiles per compute unit use way 1.  blink_schedule_reset, blink_schedule_set_sweep to

@@ -525,8 +525,8 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     p.grid_shift = grid_shift;
     p.redop = static_cast<unsigned>(redop);
     // Calls sweep the payload in alternating directions (the second, fourth, ... call
-    // backwards), unless switched off or timed.
-    p.reverse = goes_backwards(!s.has_deps && !static_block && h->sweep_alternates, timed.index >= 0, h->epoch);
+    // backwards), unless switched off.
+    p.reverse = !s.has_deps && !static_block && h->sweep_alternates && (h->epoch & 1) != 0;
     p.dealt = dealt;
     p.call = static_block ? 1 : static_cast<unsigned>(h->epoch + 1);
     if (blink_status_t st = launch(h, reinterpret_cast<const void*>(fn), grid, kFoldThreads, &p, stream, timed)) return st;

@@ -1,6 +1,6 @@
 // Plays the timed choice among the ways to serve a schedule through a list of calls:
 //   way_trial_check CAN_FRONT CAN_TURNS  CLASS CLASS ...
-// one line per call: class, way, timed, backwards.  Every call of way 3 takes 1 ms, of way 2
+// one line per call: class, way, timed.  Every call of way 3 takes 1 ms, of way 2
 // 2 ms, of way 1 3 ms.
 #include <cstdio>
 #include <cstdlib>
@@ -23,7 +23,7 @@ int main(int argc, char** argv) {
             else
                 way = trial.picked = blink::fastest_way(ways, ms[cls]);
         }
-        std::printf("%d %d %d %d\n", cls, way, timed, blink::goes_backwards(true, timed, static_cast<uint64_t>(call)));
+        std::printf("%d %d %d\n", cls, way, timed);
     }
     return 0;
 }
