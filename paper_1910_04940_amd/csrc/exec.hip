@@ -258,6 +258,7 @@ blink_status_t reset_progress(blink_schedule* h) {
     h->tables_stale = true;
     h->plan = LaunchPlan();
     h->call_skipped = false;
+    h->static_record = false;
     h->occupancy[0] = h->occupancy[1] = 0;
     forget_trial(h);
     if (h->device < 0) return BLINK_OK;
@@ -278,11 +279,11 @@ blink_status_t read_status(blink_schedule* h, blink_progress_t* out) {
         int dev = -1;
         BLINK_HIP(hipGetDevice(&dev));
         std::lock_guard<std::mutex> lock(g_static_mutex);
+        // no record of this schedule's: its latest call kept none or a reset has dropped it, or the
+        // block has passed to another schedule or to tables for the other kernel
+        if (!h->static_record || dev != h->last_static_device) return BLINK_OK;
         const StaticBlock& sb = g_static[dev];
-        // record gone: the block has passed to another schedule, or there is no plan for the
-        // tables it holds (a reset or a skipped call since)
-        if (dev != h->last_static_device || sb.owner != h->id || sb.fold != h->plan.fold) return BLINK_OK;
-        if (!h->static_record) return BLINK_OK;
+        if (sb.owner != h->id || sb.fold != h->plan.fold) return BLINK_OK;
         block = sb.ptr;
     } else if (h->device < 0) {
         return BLINK_OK;  // never ran: nothing can have gone wrong

@@ -3,8 +3,8 @@
 // bound by HBM at large payloads and by the latency of one pass (arguments -> rank data
 // -> stores) at small ones.  It runs the whole-tree programs, and the per-node and
 // small per-edge ones, in which a wave also writes every partial sum to the buffer of
-// the rank that would hold it (MID; see exec.hip for where that beats the hand-over of
-// chunks between waves).
+// the rank that would hold it (MID; see served_by for where that is used rather than the
+// hand-over of chunks between waves).
 //
 // How a workgroup works, and why:
 //

@@ -67,7 +67,7 @@ struct blink_schedule {
     unsigned last_grid = 0;
     int last_kernel = 0;          // the way the latest call ran (see choose_way), 0 = none yet
     int last_static_device = -1;  // device whose static block the latest call used; -1 = it used d_block
-    bool static_record = false;   // that call cleared the block's status record and may have set it
+    bool static_record = false;   // that call cleared the block's status record and may have set it; no reset since
     int kernel_choice = 0;        // the caller's wish: 0 = pick the fastest way, else one of the three
     bool sweep_alternates = true; // calls on a schedule without dependencies walk the tiles in alternating directions
     blink::WayTrial trial;        // the timed calls so far and the pick

@@ -93,6 +93,14 @@ def test_a_record_on_the_block_is_not_taken_for_another_schedules():
     assert quick.status()[0] == bl.BLINK_OK
     assert all(np.array_equal(b.cpu().numpy(), ox.allreduce_int32_definition(x)) for b in bufs)
 
+    slow.reset()                  # its own record goes with a reset, on the block too
+    bl.blink_allreduce(big, n, bl.BLINK_INT32, slow, stream)
+    slow.test_skip_call()
+    bl.blink_allreduce_noalloc(big, n, bl.BLINK_INT32, slow, stream)
+    assert slow.status()[0] == bl.BLINK_ESTUCK
+    slow.reset()
+    assert slow.status()[0] == bl.BLINK_OK
+
 
 @pytest.mark.parametrize("before,after", [(0, 256), (65_536, 1_024), (256, 0), (256, 256)])
 def test_a_call_can_be_recorded_after_a_new_tile_size_or_a_reset(before, after):
