@@ -385,7 +385,7 @@ def main():
         assert sum(s.traffic_bytes for s in scheds) == per_elem * total
     alg_bytes = sum(s.kernel_bytes for s in scheds)       # what the kernel requests, whichever serves
     achieved = alg_bytes / (avg_kernel_ms * 1e-3) / 1e9
-    prof_name = (f"blink_consume_{collective}_cube8_{n * 4 >> 20}MiB_{args.fusion}.txt" if args.config == "headline"
+    prof_name = (f"headline_{collective}_{k}x{n * 4 >> 20}MiB_{args.fusion}.txt" if args.config == "headline"
                  else f"config{args.config}_{collective}_{args.fusion}.txt")
     say("timed steps done")
     traffic, traffic_digest = traffic_from_profiles(prof_name)
