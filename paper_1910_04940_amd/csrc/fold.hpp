@@ -198,6 +198,7 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
     const unsigned n_items = p->n_items, n_levels = p->n_levels, turn = p->turn, tile_elems = p->tile_elems;
     const unsigned grid_shift = p->grid_shift, redop = p->redop;
     const bool reverse = p->reverse != 0, dealt = p->dealt != 0;
+    unsigned long long* const ticket = p->ticket;
     const BLINK_CONST unsigned* const words = p->words ? as_const<unsigned>(p->words) : p->inline_words;
     const BLINK_CONST FoldLevel* const levels = p->levels ? as_const<FoldLevel>(p->levels) : p->inline_levels;
     const unsigned n_flows = p->n_flows;
@@ -300,24 +301,28 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
     auto draw = [&]() {
         unsigned raw = 0;
         if (!dealt && sub >= hi && threadIdx.x == 0)
-            raw = static_cast<unsigned>(__hip_atomic_fetch_add(p->ticket, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            raw = static_cast<unsigned>(__hip_atomic_fetch_add(ticket, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         return raw;
     };
     unsigned t = blockIdx.x;   // the grid has at most n_items workgroups
     unsigned slot = 0;
-    // Where tickets are drawn the status record lies in front of the counter.  If it is set
-    // (see the end) the buffers are left alone: asked for, by the scalar unit, beside the tables,
-    // and looked at when the first tile's loads are on their way, by one thread for all.
-    const unsigned state = dealt ? 0 : *as_const<unsigned>(p->ticket - kStatusWords + kStatusState);
     resolve(t);
     FoldPiece<N> cur = piece();
+    // Where tickets are drawn the status record lies in front of the counter.  If it is set
+    // (see the end) the buffers are left alone.  Asked for in front of the first tile's loads, a
+    // load like them (its window is empty where tickets are dealt), so that its answer is there
+    // before theirs: a wave that finds it set has nothing to do of its first ticket, and the wave
+    // that hands tickets on hands on that there is none.  (Waves that find different things
+    // end all the same: each reaches one barrier per ticket.)
+    const unsigned state = __builtin_amdgcn_raw_buffer_load_b32(
+        __builtin_amdgcn_make_buffer_rsrc(ticket - kStatusWords + kStatusState, 0, dealt ? 0 : 4, kRawDword3), 0, 0, 0);
     load(cur);
-    if (!dealt) {
-        if (threadIdx.x == 0) drawn[1] = state;
-        __syncthreads();
-        if (__builtin_amdgcn_readfirstlane(drawn[1])) return;
-    }
     unsigned raw = draw();
+    const bool leave = __builtin_amdgcn_readfirstlane(state) != 0;
+    if (leave) {
+        cur.to = cur.from;
+        sub = hi;
+    }
     // In the loop a tile's loads are followed by the stores of the tile in front of it.
     // Stores into an empty window (dropped) give the first tile the same, and the
     // compiler the same number of operations to leave outstanding on both ways in:
@@ -378,7 +383,7 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
             if (dealt) {
                 t += gridDim.x;
             } else {
-                if (wave == 0) drawn[slot] = answer - static_cast<unsigned>(p->ticket_base) + gridDim.x;
+                if (wave == 0) drawn[slot] = leave ? ~0u : answer - static_cast<unsigned>(p->ticket_base) + gridDim.x;
                 __syncthreads();
                 t = __builtin_amdgcn_readfirstlane(drawn[slot]);
                 slot ^= 1;   // the other word: a wave may still be reading this one
@@ -409,7 +414,7 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
     // moved since: another call on the schedule overlaps with this one.  Both have gone wrong
     // (tickets are lost, or drawn twice).
     if (!dealt && t - n_items >= gridDim.x && threadIdx.x == 0) {
-        unsigned long long* const status = p->ticket - kStatusWords;
+        unsigned long long* const status = ticket - kStatusWords;
         if (__hip_atomic_exchange(status + kStatusState, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
             status[kStatusStage] = status[kStatusAwaited] = ~0ull;
             status[kStatusSeen] = p->ticket_base + static_cast<long long>(static_cast<int>(t - gridDim.x));
