@@ -208,7 +208,9 @@ void plan_fold(blink_schedule* h) {
     pl.all = pl.n_load > 1 && n_store == pl.n_load;
     for (const FusedFlow& f : s.fused) pl.mid = pl.mid || f.mid_store != 0;
     const int n = static_cast<int>(pl.n_load);
-    const unsigned sub = fold_sub_elems(n, pl.all, false);
+    const bool in_cache = s.traffic_bytes <= (n_store == 1 ? kMemorySideCacheBytes / 8 * 5 : kMemorySideCacheBytes);
+    pl.copy_columns = n == 1 ? fold_copy_columns(n_store, in_cache) : 0;
+    const unsigned sub = fold_sub_elems(n == 1 ? pl.copy_columns : fold_columns(n, pl.all));
     unsigned tile = sub;
     while (tile * 4 * (pl.n_load + n_store) < kFoldTicketBytes) tile += sub;
     uint64_t tiles = 0;
@@ -217,7 +219,11 @@ void plan_fold(blink_schedule* h) {
     pl.small = tiles * sub * 4 * (pl.n_load + n_store) <= kFoldSmallBytesPerCu * cus;
     // a tile per flow more than that: shares need not be whole tiles
     pl.half = tiles <= kFoldHalfTilesPerCu * cus + h->fold.flows.size() && fold_has_half(n, pl.all);
-    if (pl.small) tile = fold_sub_elems(n, pl.all, pl.half);
+    if (pl.small) tile = pl.half ? fold_sub_elems(fold_columns(n, pl.all, true)) : sub;
+    if (pl.small && n == 1 && n_store > 1 && tiles > cus) {   // (one tile per CU at most: no difference)
+        pl.copy_columns = kCopyColumnsSmall;
+        tile = fold_sub_elems(kCopyColumnsSmall);
+    }
     if (!words_inline(*h)) h->fold.fill_set(level_set(0), tile);
     if (h->tile_override) tile = h->tile_override;
     pl.tile_elems = tile;
@@ -432,7 +438,7 @@ blink_status_t launch_clear(char* block, size_t bytes, hipStream_t stream) {
 FoldFn pick_fold(blink_dtype_t dtype, bool sum, const LaunchPlan& pl, int policy) {
     const int n = static_cast<int>(pl.n_load);
     const bool stream = policy == kFoldStream;
-    if (n == 1) return fold_copy(policy);
+    if (n == 1) return fold_copy(policy, pl.copy_columns);
     if (pl.mid) return dtype == BLINK_FP32 ? fold_f32_mid(n, pl.all, sum, pl.half) : fold_i32_mid(n, pl.all, sum, pl.half);
     if (dtype == BLINK_FP32) return sum ? fold_f32_sum(n, pl.all, stream, pl.half) : fold_f32_other(n, pl.all, pl.half);
     return sum ? fold_i32_sum(n, pl.all, stream, pl.half) : fold_i32_other(n, pl.all, pl.half);
@@ -489,13 +495,18 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     if (!fn) return BLINK_EINVAL;
 
     // Workgroups: all tiles of a small payload; otherwise 7 on 8 CUs (see fold.hpp).  Copies
-    // have 16 KiB of loads per workgroup and n_store times that of stores in flight: 6 on 8 CUs
-    // where seven ranks or more are written, one on each where one is (us with 192 / 224 / 256
-    // workgroups: Broadcast to 7, 64 MiB, 73.2 / 75.5 / 78.4; to 4, 60 MiB, 44.1 / 44.2 / 44.3; to 2,
-    // 200 MiB, 114 / 106 / 102; Gather of 3 ranks, 200 MiB, 57.9 / 53.2 / 51.3).
+    // have few loads per workgroup and n_store times that of stores in flight: one workgroup on each CU
+    // where one, two, five or six ranks are written, 7 on 8 CUs where three, four, seven or eight are, 6 on 8
+    // with more; and one on eight CUs more than that from seven ranks and four times the memory-side cache on (us with
+    // 192 / 224 / 256 workgroups: Gather of 3 ranks, 400 MiB, - / 89 / 90; Broadcast to 2, 400 MiB, 197 /
+    // 192 / 190; to 3, 300 MiB, 195 / 193 / 194; to 5, 85 MiB, 72 / 70 / 70, 200 MiB, 207 / 192 / 190; to 7,
+    // 64 MiB 70 / 68 / 71, 500 MiB 712 / 646 / 642; to 15, 64 MiB 148 / 155 / -, 150 MiB 424 / 408 / -).
     const uint64_t cus = static_cast<uint64_t>(h->n_cu);
     const uint32_t n_store = s.fused[0].stage.n_store;
-    const uint64_t eighths = pl.n_load > 1 ? 7 : n_store >= 7 ? 6 : n_store > 2 ? 7 : 8;
+    const bool copy_many = pl.n_load == 1 && n_store > 6;
+    const uint64_t eighths = pl.n_load > 1 ? 7
+                             : copy_many   ? (n_store > 8 ? 6 : 7) + (payload_bytes > 4 * kMemorySideCacheBytes ? 1 : 0)
+                             : n_store == 3 || n_store == 4 ? 7 : 8;
     uint64_t most = pl.small ? pl.n_items : cus * eighths / 8;
     if (h->wg_per_cu > 0) most = h->wg_per_cu * cus;
     const unsigned grid = static_cast<unsigned>(std::max<uint64_t>(1, std::min(most, pl.n_items)));

@@ -21,12 +21,20 @@
 //     launcher picks the kernel.  Loads land in registers in the order in which the
 //     stack program consumes the ranks (StageTmpl), the top accumulator is in
 //     registers and the others are parked in LDS.  Nothing else is staged.
-//   * A tile's loads are issued before the stores of the tile in front of it
-//     (its registers are free by then): vector memory operations complete in
-//     order, so loads issued after stores would wait for them (probe as above,
-//     35.5 MiB per rank 102.8 -> 96.5 us, 114 MiB 322 -> 292 us).
-//   * Tiles are dealt out by one counter, a ticket ahead; a small payload has a
-//     workgroup for every tile and no counter (see the launcher).
+//   * What decides the rate beyond that is how tight the front is along which all workgroups
+//     move: HBM serves a stretch of memory best while all its requests come at one time.  So a
+//     tile's results are stored as soon as they are there, in front of the next tile's loads,
+//     and the next ticket is drawn late, when the first rank's data of the present tile has
+//     arrived; its answer travels while the ranks are combined and the results stored.  Measured
+//     against a ticket drawn a tile ahead and loads in front of the stores (us, three sets of
+//     buffers in turn): 8 ranks x 64 MiB 166.5 -> 164.4, x 256 MiB 709 -> 681, x 20 MB 56.9 -> 55.8,
+//     16 ranks x 1 GiB 5585 -> 5178, 3 ranks x 98 MiB 98.8 -> 97.4, Broadcast to 7 ranks, 64 MiB,
+//     72.6 -> 69.7, largest value (fp32) 8 x 64 MiB 181 -> 171.  For the same reason a workgroup
+//     that takes two neighbouring tiles one after the other is 10 % slower (168 -> 185) though it
+//     draws half the tickets, and loads issued one by one as registers become free, which keeps
+//     more in flight, are slower as well (probe, 8 x 64 MiB: 170 against 161).
+//   * Tiles are dealt out by one counter; a small payload has a workgroup for every tile and
+//     no counter (see the launcher).
 #pragma once
 #include "fold_plan.hpp"
 #include "kernel.hpp"
@@ -70,9 +78,9 @@ static_assert(sizeof(FoldParams) <= 4096, "kernel arguments");
 // Columns per wave and rank for stages that read n ranks: n * U of 14 to 20 (from 11 ranks
 // on one column).  7 and 8 ranks of which one is written get twice as many (a tile is then
 // hardly more than its loads; 8 ranks, Reduce, 64 MiB: 118 -> 86 us); with other numbers of
-// ranks that was not measured.  One rank that is copied: 4, 16 KiB of loads per workgroup.
+// ranks that was not measured.  For one rank that is copied see fold_copy_columns.
 constexpr int fold_columns(int n, bool all) {
-    return n == 1 ? 4 : n == 2 ? 8 : n == 3 ? 6 : n == 4 ? 4 : n <= 6 ? 3 : n <= 8 ? (all ? 2 : 4) : n <= 10 ? 2 : 1;
+    return n == 2 ? 8 : n == 3 ? 6 : n == 4 ? 4 : n <= 6 ? 3 : n <= 8 ? (all ? 2 : 4) : n <= 10 ? 2 : 1;
 }
 // A payload of about two tiles per CU or less is latency-bound; where all ranks are written,
 // tiles of half the size are faster there (us, 4 MiB per rank, full / half: 8 ranks 13.3 / 11.4,
@@ -82,8 +90,24 @@ constexpr bool fold_has_half(int n, bool all) { return all && fold_columns(n, al
 constexpr int fold_columns(int n, bool all, bool half) {
     return half && fold_has_half(n, all) ? (fold_columns(n, all) + 1) / 2 : fold_columns(n, all);
 }
-constexpr unsigned fold_sub_elems(int n, bool all, bool half) {
-    return static_cast<unsigned>(fold_columns(n, all, half)) * kFoldWaves * 256u;
+constexpr unsigned fold_sub_elems(int columns) { return static_cast<unsigned>(columns) * kFoldWaves * 256u; }
+// One rank read and copied to n_store of them: fewer columns the more stores follow each load, and
+// fewer while a payload has a workgroup for every tile.  us with 2 / 3 / 4 / 8 / 16 columns:
+//   Broadcast to 15, 64 MiB        148 / 158 / 164 / - / -
+//   to 7, 64 MiB                    73 /  68 /  69 / 76 / -      10 MiB  17.2 / 17.6 / 17.9 / - / -
+//   to 5, 85 MiB                     - /  73 /  69 / - / -       13 MiB  14.2 / 15.1 / 15.6 / - / -
+//   to 3, 300 MiB                    - /   - / 207 / 193 / 207   32 MiB  18.6 / 19.2 / 20.7 / 21.9 / 25.1
+//   to 2, 107 MiB                    - /   - /  57 / 50 / 54     43 MiB  17.3 / 17.4 / 17.5 / 18.8 / 19.5
+//   Gather of 4 ranks, 300 MiB       - /   - /  87 / 78 / 77     80 MiB     - /    - / 18.8 / 20.0 / 19.3
+// (to 2 to 4 ranks the line lies where the traffic no longer fits the memory-side cache, to one rank
+// where it takes 5/8 of it: Gather of 4 ranks, 100 MiB each, with 4 / 16 columns 22.9 / 23.9, of 5, 102 MiB, 34.2 / 25.7).
+constexpr int kCopyColumnsSmall = 2, kCopyColumnsMost = 2, kCopyColumnsMany = 3, kCopyColumns = 4, kCopyColumnsFew = 8,
+              kCopyColumnsOne = 16;
+constexpr int fold_copy_columns(unsigned n_store, bool in_cache) {
+    return n_store > 8 ? kCopyColumnsMost
+           : n_store > 6 ? kCopyColumnsMany
+           : n_store > 4 || in_cache ? kCopyColumns
+           : n_store > 1 ? kCopyColumnsFew : kCopyColumnsOne;
 }
 
 // Cache policies of the rank buffers' loads and stores.  Measured with the probe
@@ -176,15 +200,14 @@ __device__ __forceinline__ void fold_edges(RankTable ranks, const FoldPiece<N>& 
 // T: element type (float, or unsigned for wrap-around int32).  N: ranks a stage
 // reads.  ALL: it writes the same ranks, else one; stages that read one write those in
 // the flow's `stores`.  SUM: the operator is the sum, else params' redop (PROD, MIN or MAX).
-// HALF: tiles of half the size.  MID: partial sums are written on the way (see
+// U: columns per wave and rank.  MID: partial sums are written on the way (see
 // FusedFlow::mid_store), through the L2 like the result that overwrites them: left in the
 // L2 as modified lines they cost far more (per node, 8 x 64 MiB, us: stores by default
 // policy 260, nt 216, nt sc1 211, sc1 180; 8 x 5 MiB 30.6 / 22.0 / 16.3 / 16.3).
-template <typename T, int N, bool ALL, bool SUM, int POLICY, bool HALF, bool MID>
+template <typename T, int N, bool ALL, bool SUM, int POLICY, int U, bool MID>
 __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) {
-    constexpr int U = fold_columns(N, ALL, HALF);
     constexpr int LD = FoldPolicyBits<POLICY>::kLoad, ST = FoldPolicyBits<POLICY>::kStore;
-    constexpr unsigned kSub = fold_sub_elems(N, ALL, HALF);
+    constexpr unsigned kSub = fold_sub_elems(U);
     constexpr int kStores = ALL ? N : 1;   // N == 1: those in the flow's `stores` instead
     constexpr int kParked = N < 4 ? 1 : N / 2 - 1;   // a stack program over N ranks needs at most N / 2 accumulators
     __shared__ U4 parked[N < 4 ? 1 : kParked * U * kFoldThreads];
@@ -290,19 +313,26 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
         for (int u = 0; u < U; ++u)
             __builtin_amdgcn_raw_buffer_store_b128(v[u], win, column + u * kLanes * 16, 0, policy.value);
     };
+    // A new accumulator, in registers of its own: where it shares those of a load the compiler
+    // waits for all memory operations, the counter's answer among them, at every loop that it enters.
+    auto take = [&](U4 (&acc)[U], const U4 (&x)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            acc[u] = x[u];
+            asm volatile("" : "+v"(acc[u]));
+        }
+    };
     constexpr std::integral_constant<int, ST> final_policy;
     constexpr std::integral_constant<int, kPolicyThrough> mid_policy;
-    // A ticket is drawn ahead: when the loads of the last sub-tile of the one in front
-    // have been issued, and before any stores, so that the counter's answer waits for
-    // neither.  Every ticket is followed by one draw: a call advances the counter by
-    // n_items.  The answer is read by whole waves on every path (readfirstlane below):
-    // a register that may still be awaited on some path costs a wait for all memory
-    // operations wherever the compiler uses it again.
+    // Every ticket is followed by one draw: a call advances the counter by n_items (32 bits of it:
+    // only differences matter).  A buffer operation whose window is empty unless there is a draw to
+    // make, and holds lane 0's word alone then: issued by every wave on every path, it lets the
+    // compiler count what is outstanding; behind a branch it waited for the answer wherever it
+    // waited for the last loads.
     auto draw = [&]() {
-        unsigned raw = 0;
-        if (!dealt && sub >= hi && threadIdx.x == 0)
-            raw = static_cast<unsigned>(__hip_atomic_fetch_add(ticket, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        return raw;
+        const bool due = !dealt && sub >= hi && wave == 0;
+        return static_cast<unsigned>(__builtin_amdgcn_raw_ptr_buffer_atomic_add_i32(
+            1, __builtin_amdgcn_make_buffer_rsrc(ticket, 0, due ? 4 : 0, kRawDword3), lane * 4, 0, 0));
     };
     unsigned t = blockIdx.x;   // the grid has at most n_items workgroups
     unsigned slot = 0;
@@ -317,20 +347,10 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
     const unsigned state = __builtin_amdgcn_raw_buffer_load_b32(
         __builtin_amdgcn_make_buffer_rsrc(ticket - kStatusWords + kStatusState, 0, dealt ? 0 : 4, kRawDword3), 0, 0, 0);
     load(cur);
-    unsigned raw = draw();
-    const bool leave = __builtin_amdgcn_readfirstlane(state) != 0;
-    if (leave) {
+    if (__builtin_amdgcn_readfirstlane(state) != 0) {
         cur.to = cur.from;
         sub = hi;
-    }
-    // In the loop a tile's loads are followed by the stores of the tile in front of it.
-    // Stores into an empty window (dropped) give the first tile the same, and the
-    // compiler the same number of operations to leave outstanding on both ways in:
-    // otherwise it waits for the stores wherever it waits for a load.
-    if constexpr (N > 1) {
-        const U4 nothing[U] = {};
-#pragma unroll
-        for (int j = 0; j < kStores; ++j) store(nothing, 0, 0, 0, final_policy);
+        t = ~0u;   // the next ticket, whatever the counter says
     }
     for (;;) {
         // the tile's loads are on their way; one wave's join them
@@ -339,8 +359,9 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
         unsigned long long byte_off;
         const unsigned bytes = vector_bytes(cur, &byte_off);
         U4 acc[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) acc[u] = r[0][u];
+        take(acc, r[0]);
+        // the first rank's data is here: time to ask for the next ticket
+        const unsigned raw = draw();
         if constexpr (N > 1) {
             unsigned depth = 0;   // accumulators parked in LDS, the oldest at the bottom
             unsigned mids = cur.stores >> 16;
@@ -359,8 +380,7 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
 #pragma unroll
                     for (int u = 0; u < U; ++u) parked[(depth * U + u) * kFoldThreads + threadIdx.x] = acc[u];
                     ++depth;
-#pragma unroll
-                    for (int u = 0; u < U; ++u) acc[u] = r[i][u];
+                    take(acc, r[i]);
                 } else {
                     add(r[i]);
                 }
@@ -375,30 +395,6 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
                     }
             }
         }
-
-        // the next sub-tile: of this ticket, or of the next one
-        const unsigned answer = __builtin_amdgcn_readfirstlane(raw);
-        bool more = true;
-        if (sub >= hi) {
-            if (dealt) {
-                t += gridDim.x;
-            } else {
-                if (wave == 0) drawn[slot] = leave ? ~0u : answer - static_cast<unsigned>(p->ticket_base) + gridDim.x;
-                __syncthreads();
-                t = __builtin_amdgcn_readfirstlane(drawn[slot]);
-                slot ^= 1;   // the other word: a wave may still be reading this one
-            }
-            more = t < n_items;
-            if (more) resolve(t);
-        }
-        FoldPiece<N> next = cur;
-        raw = 0;
-        if (more) {
-            next = piece();
-            load(next);
-            raw = draw();
-        }
-
         if constexpr (N > 1) {
 #pragma unroll
             for (int j = 0; j < kStores; ++j) store(acc, ALL ? j : __builtin_ctz(cur.stores), byte_off, bytes, final_policy);
@@ -406,8 +402,23 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
             for (unsigned left = cur.stores & 0xffffu; left; left &= left - 1)
                 store(acc, __builtin_ctz(left), byte_off, bytes, final_policy);
         }
-        if (!more) break;
-        cur = next;
+        __builtin_amdgcn_sched_barrier(0);
+        // the next sub-tile: of this ticket, or of the next one
+        const unsigned answer = __builtin_amdgcn_readfirstlane(raw);
+        if (sub >= hi) {
+            if (dealt) {
+                t += gridDim.x;
+            } else {
+                if (wave == 0) drawn[slot] = t == ~0u ? t : answer - static_cast<unsigned>(p->ticket_base) + gridDim.x;
+                __syncthreads();
+                t = __builtin_amdgcn_readfirstlane(drawn[slot]);
+                slot ^= 1;   // the other word: a wave may still be reading this one
+            }
+            if (t >= n_items) break;
+            resolve(t);
+        }
+        cur = piece();
+        load(cur);
     }
     // A call's draws end less than a grid's width past its last ticket.  If this one did
     // not, the counter was not where the host counted it to be when the call started, or has been
@@ -435,7 +446,7 @@ using FoldFn = void (*)(const FoldParams);
 template <typename T, bool SUM, int POLICY, bool MID = false>
 FoldFn pick_fold_all(int n) {
     switch (n) {
-#define BLINK_CASE(N) case N: return blink_fold<T, N, true, SUM, POLICY, false, MID>;
+#define BLINK_CASE(N) case N: return blink_fold<T, N, true, SUM, POLICY, fold_columns(N, true), MID>;
         BLINK_FOLD_CASES
 #undef BLINK_CASE
         default: return nullptr;
@@ -444,7 +455,7 @@ FoldFn pick_fold_all(int n) {
 template <typename T, bool SUM, bool MID = false>
 FoldFn pick_fold_half(int n) {
     switch (n) {
-#define BLINK_CASE(N) case N: return blink_fold<T, N, true, SUM, kFoldKeep, fold_has_half(N, true), MID>;
+#define BLINK_CASE(N) case N: return blink_fold<T, N, true, SUM, kFoldKeep, fold_columns(N, true, true), MID>;
         BLINK_FOLD_CASES
 #undef BLINK_CASE
         default: return nullptr;
@@ -453,7 +464,7 @@ FoldFn pick_fold_half(int n) {
 template <typename T, bool SUM, bool MID = false>
 FoldFn pick_fold_one(int n) {
     switch (n) {
-#define BLINK_CASE(N) case N: return blink_fold<T, N, false, SUM, kFoldKeep, false, MID>;
+#define BLINK_CASE(N) case N: return blink_fold<T, N, false, SUM, kFoldKeep, fold_columns(N, false), MID>;
         BLINK_FOLD_CASES
 #undef BLINK_CASE
         default: return nullptr;
@@ -470,6 +481,6 @@ FoldFn fold_f32_mid(int n, bool all, bool sum, bool half);
 FoldFn fold_i32_sum(int n, bool all, bool stream, bool half);
 FoldFn fold_i32_other(int n, bool all, bool half);
 FoldFn fold_i32_mid(int n, bool all, bool sum, bool half);
-FoldFn fold_copy(int policy);   // one rank read: nothing is combined
+FoldFn fold_copy(int policy, int columns);   // one rank read: nothing is combined
 
 }  // namespace blink

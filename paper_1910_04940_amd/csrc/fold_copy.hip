@@ -3,10 +3,26 @@
 
 namespace blink {
 
-FoldFn fold_copy(int policy) {
-    return policy == kFoldSpread   ? blink_fold<unsigned, 1, false, true, kFoldSpread, false, false>
-           : policy == kFoldStream ? blink_fold<unsigned, 1, false, true, kFoldStream, false, false>
-                                   : blink_fold<unsigned, 1, false, true, kFoldKeep, false, false>;
+namespace {
+template <int POLICY, int U>
+constexpr FoldFn kCopy = blink_fold<unsigned, 1, false, true, POLICY, U, false>;
+}
+
+FoldFn fold_copy(int policy, int columns) {
+    if (policy == kFoldSpread) {
+        switch (columns) {
+            case 2: return kCopy<kFoldSpread, 2>;
+            case 3: return kCopy<kFoldSpread, 3>;
+            case 4: return kCopy<kFoldSpread, 4>;
+            case 8: return kCopy<kFoldSpread, 8>;
+            default: return nullptr;
+        }
+    }
+    switch (columns) {   // to one rank
+        case 4: return policy == kFoldStream ? kCopy<kFoldStream, 4> : kCopy<kFoldKeep, 4>;
+        case 16: return policy == kFoldStream ? kCopy<kFoldStream, 16> : kCopy<kFoldKeep, 16>;
+        default: return nullptr;
+    }
 }
 
 }  // namespace blink

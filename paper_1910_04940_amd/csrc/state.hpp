@@ -27,6 +27,7 @@ struct LaunchPlan {
     bool all = false;              // every stage writes all the ranks it reads
     bool mid = false;              // partial sums are written on the way
     uint32_t n_load = 0;           // ranks a stage reads
+    int copy_columns = 0;          // where it reads one: columns per wave
     uint32_t grid_shift = 0;       // the tile grid the levels were made for
 };
 

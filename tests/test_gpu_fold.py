@@ -97,6 +97,38 @@ def test_sizes_where_the_launch_changes(n, fusion, op, dtype):
     assert sched.status()[0] == bl.BLINK_OK
 
 
+# a copy's columns per wave follow the ranks written and the traffic: two (a workgroup per tile, or more
+# than eight ranks written), three (more than six), four, eight and sixteen (beyond the memory-side cache)
+@pytest.mark.parametrize("k,sizes", [(2, (41_000_002, 43_000_002)), (3, (2_000_003, 12_000_001, 20_000_003, 23_000_003)),
+                                     (8, (1_500_003, 6_000_001)), (10, (600_003, 4_500_003))])
+def test_copies_of_every_width(k, sizes):
+    """Broadcast from, and Gather to, the middle of a star; two calls, the second goes backwards."""
+    stream = _stream()
+    trees = bl.blink_trees_from_arrays(k, [1], [[-1 if r == 1 else 1 for r in range(k)]], [1.0])
+    rng = torch.Generator(device="cuda")
+    rng.manual_seed(k)
+    for n in sizes:
+        m = n - n % k
+        slab = torch.zeros(k, n + 64 - n % 64 + 64, dtype=torch.int32, device="cuda")
+        bufs = [slab[r, :n] for r in range(k)]
+        bcast = bl.blink_make_schedule(trees, bl.BLINK_OP_BROADCAST, n, 1 << 18)
+        gather = bl.blink_make_schedule(trees, bl.BLINK_OP_GATHER, m, 1 << 18)
+        for _ in range(2):
+            for b in bufs:
+                b.random_(generator=rng)
+            want = bufs[1].clone()
+            bl.blink_broadcast(bufs, n, bl.BLINK_INT32, bcast, stream)
+            assert all(torch.equal(b, want) for b in bufs), n
+            for b in bufs:
+                b.random_(generator=rng)
+            others = [b.clone() for b in bufs]
+            want = torch.cat([others[r][r * (m // k):(r + 1) * (m // k)] for r in range(k)] + [others[1][m:]])
+            bl.blink_gather(bufs, m, bl.BLINK_INT32, gather, stream)
+            assert torch.equal(bufs[1], want), n
+            assert all(torch.equal(bufs[r], others[r]) for r in range(k) if r != 1), n
+        assert int(torch.count_nonzero(slab[:, n:])) == 0
+
+
 @pytest.mark.parametrize("fusion", ["edge", "node"])
 @pytest.mark.parametrize("k", [3, 5, 8, 13, 16])
 @pytest.mark.parametrize("n", [4_099, 300_002])
