@@ -189,16 +189,21 @@ void plan_hand_over(blink_schedule* h) {
     pl.n_items = ticket_count(s, 1, pl.tile_shift, &pl.tiles_per_chunk);
 }
 
-// The plan where the fold kernel runs the schedule.  A ticket is one sub-tile of the
-// kernel, or as many as make it move 96 KiB: the one ticket counter then has to
-// serve about 65 draws per microsecond at most.
+// The plan where the fold kernel runs the schedule.  A drawn ticket is one sub-tile of the
+// kernel, or as many as make it move 56 KiB: at 6.5 TB/s that is 113 draws per microsecond, and a
+// counter serves 80.  Tickets of less than 128 KiB draw from two counters; from 128 KiB one
+// keeps up, and the front along which one hands them out is the tighter (two servers of 8, 64 MiB of
+// zeros, with one / two 324 / 328 us).
 // A payload of at most five tiles (of 128 KiB read and written) per CU gets a workgroup for
 // every tile: they are all resident at once or nearly so, and no ticket has to be drawn (probe, 8 ranks,
 // workgroup per tile against 224 that draw: 2 MiB per rank 5.1 / 7.2 us, 4 MiB 9.6 /
 // 10.8, 7 MiB (3.5 tiles per CU) 14.4 / 16.2, 10.4 MiB (5.2) 25 / 25, 16 MiB 51 / 47).
-constexpr unsigned kFoldTicketBytes = 96 * 1024;
+constexpr unsigned kFoldTicketBytes = 56 * 1024;
+constexpr unsigned kFoldOneCounterBytes = 128 * 1024;
 constexpr uint64_t kFoldSmallBytesPerCu = 5 * 128 * 1024;
 constexpr unsigned kFoldHalfTilesPerCu = 2;   // up to here half tiles are faster (see fold_columns)
+
+FoldTile fold_tile(const LaunchPlan& pl) { return pl.half ? FoldTile::kHalf : pl.small ? FoldTile::kWhole : FoldTile::kDrawn; }
 
 void plan_fold(blink_schedule* h) {
     LaunchPlan& pl = h->plan;
@@ -210,20 +215,17 @@ void plan_fold(blink_schedule* h) {
     const int n = static_cast<int>(pl.n_load);
     const bool in_cache = s.traffic_bytes <= (n_store == 1 ? kMemorySideCacheBytes / 8 * 5 : kMemorySideCacheBytes);
     pl.copy_columns = n == 1 ? fold_copy_columns(n_store, in_cache) : 0;
-    const unsigned sub = fold_sub_elems(n == 1 ? pl.copy_columns : fold_columns(n, pl.all));
-    unsigned tile = sub;
-    while (tile * 4 * (pl.n_load + n_store) < kFoldTicketBytes) tile += sub;
+    const unsigned sub = fold_sub_elems(n == 1 ? pl.copy_columns : fold_columns(n, pl.all, FoldTile::kWhole));
     uint64_t tiles = 0;
     for (const FoldFlow& f : h->fold.flows) tiles += (f.len + sub - 1) / sub;
     const uint64_t cus = static_cast<uint64_t>(h->n_cu);
     pl.small = tiles * sub * 4 * (pl.n_load + n_store) <= kFoldSmallBytesPerCu * cus;
     // a tile per flow more than that: shares need not be whole tiles
-    pl.half = tiles <= kFoldHalfTilesPerCu * cus + h->fold.flows.size() && fold_has_half(n, pl.all);
-    if (pl.small) tile = pl.half ? fold_sub_elems(fold_columns(n, pl.all, true)) : sub;
-    if (pl.small && n == 1 && n_store > 1 && tiles > cus) {   // (one tile per CU at most: no difference)
-        pl.copy_columns = kCopyColumnsSmall;
-        tile = fold_sub_elems(kCopyColumnsSmall);
-    }
+    pl.half = pl.small && pl.all && tiles <= kFoldHalfTilesPerCu * cus + h->fold.flows.size();
+    if (pl.small && n == 1 && n_store > 1 && tiles > cus) pl.copy_columns = kCopyColumnsSmall;   // (one tile per CU at most: no difference)
+    const unsigned least = fold_sub_elems(n == 1 ? pl.copy_columns : fold_columns(n, pl.all, fold_tile(pl)));
+    unsigned tile = least;
+    while (!pl.small && tile * 4 * (pl.n_load + n_store) < kFoldTicketBytes) tile += least;
     if (!words_inline(*h)) h->fold.fill_set(level_set(0), tile);
     if (h->tile_override) tile = h->tile_override;
     pl.tile_elems = tile;
@@ -438,10 +440,11 @@ blink_status_t launch_clear(char* block, size_t bytes, hipStream_t stream) {
 FoldFn pick_fold(blink_dtype_t dtype, bool sum, const LaunchPlan& pl, int policy) {
     const int n = static_cast<int>(pl.n_load);
     const bool stream = policy == kFoldStream;
+    const FoldTile tile = fold_tile(pl);
     if (n == 1) return fold_copy(policy, pl.copy_columns);
-    if (pl.mid) return dtype == BLINK_FP32 ? fold_f32_mid(n, pl.all, sum, pl.half) : fold_i32_mid(n, pl.all, sum, pl.half);
-    if (dtype == BLINK_FP32) return sum ? fold_f32_sum(n, pl.all, stream, pl.half) : fold_f32_other(n, pl.all, pl.half);
-    return sum ? fold_i32_sum(n, pl.all, stream, pl.half) : fold_i32_other(n, pl.all, pl.half);
+    if (pl.mid) return dtype == BLINK_FP32 ? fold_f32_mid(n, pl.all, tile, sum) : fold_i32_mid(n, pl.all, tile, sum);
+    if (dtype == BLINK_FP32) return sum ? fold_f32_sum(n, pl.all, tile, stream) : fold_f32_other(n, pl.all, tile);
+    return sum ? fold_i32_sum(n, pl.all, tile, stream) : fold_i32_other(n, pl.all, tile);
 }
 
 // A call on the fold kernel.  block: the static block, or null for the schedule's own, which is only made where tickets are drawn or the tables
@@ -494,7 +497,8 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     const FoldFn fn = pick_fold(dtype, sum, pl, policy);
     if (!fn) return BLINK_EINVAL;
 
-    // Workgroups: all tiles of a small payload; otherwise 7 on 8 CUs (see fold.hpp).  Copies
+    // Workgroups: all tiles of a small payload; otherwise 7 on 8 CUs (see fold.hpp), one on each where one
+    // rank is written (Reduce of 8 ranks, 64 MiB, with 224 / 256 workgroups 84.5 / 83 us, of 4 48 / 46).  Copies
     // have few loads per workgroup and n_store times that of stores in flight: one workgroup on each CU
     // where one, two, five or six ranks are written, 7 on 8 CUs where three, four, seven or eight are, 6 on 8
     // with more; and one on eight CUs more than that from seven ranks and four times the memory-side cache on (us with
@@ -504,13 +508,15 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     const uint64_t cus = static_cast<uint64_t>(h->n_cu);
     const uint32_t n_store = s.fused[0].stage.n_store;
     const bool copy_many = pl.n_load == 1 && n_store > 6;
-    const uint64_t eighths = pl.n_load > 1 ? 7
+    const uint64_t eighths = pl.n_load > 1 ? (pl.all ? 7 : 8)
                              : copy_many   ? (n_store > 8 ? 6 : 7) + (payload_bytes > 4 * kMemorySideCacheBytes ? 1 : 0)
                              : n_store == 3 || n_store == 4 ? 7 : 8;
     uint64_t most = pl.small ? pl.n_items : cus * eighths / 8;
     if (h->wg_per_cu > 0) most = h->wg_per_cu * cus;
-    const unsigned grid = static_cast<unsigned>(std::max<uint64_t>(1, std::min(most, pl.n_items)));
+    unsigned grid = static_cast<unsigned>(std::max<uint64_t>(1, std::min(most, pl.n_items)));
     const bool dealt = pl.small || grid == pl.n_items;
+    const bool two = !dealt && grid >= kTwoCountersGrid && pl.tile_elems * 4 * (pl.n_load + n_store) < kFoldOneCounterBytes;
+    if (two) grid -= grid % kTwoCountersGrid;
 
     if (static_block) {
         h->static_record = !dealt;
@@ -528,7 +534,7 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     if (!p.words) fold_words(t.flows, kInlineFlows, p.inline_words);
     if (!p.levels) std::copy(t.levels.begin(), t.levels.end(), p.inline_levels);
     p.ticket = block ? reinterpret_cast<unsigned long long*>(block + l.ticket) : nullptr;
-    p.ticket_base = static_block ? 0 : h->ticket_base[0];
+    for (int c = 0; c < 2; ++c) p.ticket_base[c] = static_block ? 0 : h->ticket_base[c];
     p.n_items = static_cast<unsigned>(pl.n_items);
     p.n_flows = static_cast<unsigned>(t.flows.size());
     p.n_levels = static_cast<unsigned>(t.levels.size());
@@ -544,13 +550,16 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     // backwards), unless switched off.
     p.reverse = !s.has_deps && !static_block && h->sweep_alternates && (h->epoch & 1) != 0;
     p.dealt = dealt;
+    p.two = two;
+    p.width = two ? grid / 2 : grid;
     p.call = static_block ? 1 : static_cast<unsigned>(h->epoch + 1);
     if (blink_status_t st = launch(h, reinterpret_cast<const void*>(fn), grid, kFoldThreads, &p, stream, timed)) return st;
     h->last_kernel = way;
     h->handed_over = 0;
     if (static_block) return BLINK_OK;
     h->epoch += 1;
-    if (!dealt) h->ticket_base[0] += pl.n_items;   // every ticket is followed by one draw
+    if (!dealt)   // every ticket is followed by one draw
+        for (uint32_t c = 0; c < (two ? 2u : 1u); ++c) h->ticket_base[c] += fold_share(p.n_items, c, two);
     return BLINK_OK;
 }
 

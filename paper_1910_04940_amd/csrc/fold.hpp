@@ -10,12 +10,9 @@
 //
 //   * Four waves share one tile; a wave owns U columns of 1 KiB per rank, so a
 //     tile is 4 * U KiB of every rank.  U falls with the number of ranks (fold_columns): where
-//     all ranks are written 44 to 80 KiB of loads per workgroup are in flight.  One such
-//     workgroup on seven of eight CUs is what HBM likes best.  Measured with a standalone probe
-//     (8 ranks, three sets of buffers in turn, 64 MiB per rank): 128 / 160 / 192 /
-//     224 / 256 workgroups 211 / 180 / 168 / 165 / 169 us; twice the bytes per
-//     workgroup on 112 of them 213 us; two single waves of 32 KiB per CU, 4 KiB of
-//     every rank at a time, 208 us.
+//     all ranks are written 40 to 72 KiB of loads per workgroup are in flight.  More in flight than HBM
+//     needs to be busy only spreads the requests out (probe, 8 ranks x 64 MiB, 208 / 224 / 256 / 320 / 448
+//     workgroups 160 / 160 / 168 / 178 / 188 us): one workgroup on seven of eight CUs.
 //   * The number of ranks a stage reads, and whether it writes them all, are
 //     template parameters: all stages of such a schedule agree on them, so the
 //     launcher picks the kernel.  Loads land in registers in the order in which the
@@ -33,8 +30,8 @@
 //     that takes two neighbouring tiles one after the other is 10 % slower (168 -> 185) though it
 //     draws half the tickets, and loads issued one by one as registers become free, which keeps
 //     more in flight, are slower as well (probe, 8 x 64 MiB: 170 against 161).
-//   * Tiles are dealt out by one counter; a small payload has a workgroup for every tile and
-//     no counter (see the launcher).
+//   * Tiles are dealt out by two counters (see fold_class; large ones by one); a small payload has
+//     a workgroup for every tile and no counter (see the launcher).
 #pragma once
 #include "fold_plan.hpp"
 #include "kernel.hpp"
@@ -60,7 +57,7 @@ struct FoldParams {
     const unsigned* words;           // flow words (see fold_words); null: the inline ones
     const FoldLevel* levels;         // null: the inline ones
     unsigned long long* ticket;
-    unsigned long long ticket_base;  // the counter's value when this call starts
+    unsigned long long ticket_base[2];   // the counters' values when this call starts
     unsigned n_items;                // tickets
     unsigned n_flows, n_levels;
     unsigned turn;                   // see fold_ticket
@@ -68,27 +65,37 @@ struct FoldParams {
     unsigned grid_shift;             // see fold_range
     unsigned redop;                  // blink_redop_t
     unsigned reverse;                // tickets walk from the last to the first
-    unsigned dealt;                  // workgroup w takes tickets w, w + grid, ...; the counter is not used
+    unsigned dealt;                  // workgroup w takes tickets w, w + width, ...; no counter is used
+    unsigned two;                    // tickets come from two counters (see fold_class), else from one
+    unsigned width;                  // workgroups that share a counter (of all of them where tickets are dealt)
     unsigned call;                   // number of the call on its schedule
     FoldLevel inline_levels[kInlineFlows];
     unsigned inline_words[kFlowWords * kInlineFlows];
 };
 static_assert(sizeof(FoldParams) <= 4096, "kernel arguments");
 
-// Columns per wave and rank for stages that read n ranks: n * U of 14 to 20 (from 11 ranks
-// on one column).  7 and 8 ranks of which one is written get twice as many (a tile is then
-// hardly more than its loads; 8 ranks, Reduce, 64 MiB: 118 -> 86 us); with other numbers of
-// ranks that was not measured.  For one rank that is copied see fold_copy_columns.
-constexpr int fold_columns(int n, bool all) {
-    return n == 2 ? 8 : n == 3 ? 6 : n == 4 ? 4 : n <= 6 ? 3 : n <= 8 ? (all ? 2 : 4) : n <= 10 ? 2 : 1;
-}
-// A payload of about two tiles per CU or less is latency-bound; where all ranks are written,
-// tiles of half the size are faster there (us, 4 MiB per rank, full / half: 8 ranks 13.3 / 11.4,
-// 5 ranks 8.2 / 7.6, 4 ranks 7.7 / 7.2; with three tiles per CU, 8 ranks x 6 MiB, 16.1 / 17.8), but
-// not where one is (Reduce, 8 x 4 MiB: 7.6 / 8.6; Broadcast 6.5 / 9.4).
-constexpr bool fold_has_half(int n, bool all) { return all && fold_columns(n, all) > 1; }
-constexpr int fold_columns(int n, bool all, bool half) {
-    return half && fold_has_half(n, all) ? (fold_columns(n, all) + 1) / 2 : fold_columns(n, all);
+// Columns per wave and rank for stages that read n ranks.
+//
+// Where all ranks are written: the less a ticket holds, the tighter the front, as long as the counters keep
+// up and a tile costs little beside its loads and stores.  us with more / the columns of drawn tickets, random
+// elements, three sets of buffers in turn: 3 ranks x 98 MiB, 6 / 4, 96.4 / 95.0, 4 ranks, 4 / 3, 129 / 126.5, 6 ranks, 3 / 2,
+// 180 / 178.5; 8 ranks x 114 MiB with 2 / 1 columns on 224 / 256 workgroups 284 / 291.  (On buffers of zeros one
+// column is 1 to 3 % faster: figures for these tables are taken with random elements.)
+// A payload of about two tiles per CU or less gets a workgroup for every half tile (4 MiB per rank, whole
+// / half: 8 ranks 13.3 / 11.4, 5 ranks 8.2 / 7.6, 4 ranks 7.7 / 7.2; with three tiles per CU, 8 ranks x 6 MiB,
+// 16.1 / 17.8), up to five for every whole one (6 ranks x 12 MiB, with 3 columns 19.8, with 2 22.3).
+//
+// Where one is written a tile is hardly more than its loads, and drawn ones are larger.  Reduce with
+// fewer columns and two sub-tiles per ticket / with these: 3 ranks x 64 MiB 44 / 36, 5 ranks 60 / 55,
+// 6 ranks 71 / 65, 12 ranks 149 / 123; 8 ranks 88 / 83; a workgroup for every tile, 5 ranks x 5 MiB, with 3 / 4
+// columns 7.0 / 7.7.
+enum class FoldTile { kHalf, kWhole, kDrawn };   // a workgroup for every tile: up to two per CU, more; drawn tickets
+constexpr int fold_columns(int n, bool all, FoldTile tile) {
+    if (!all && tile != FoldTile::kDrawn) return n == 2 ? 8 : n == 3 ? 6 : n == 4 ? 4 : n <= 6 ? 3 : n <= 8 ? 4 : n <= 10 ? 2 : 1;
+    if (!all) return n == 2 ? 8 : n == 3 ? 6 : n == 4 ? 5 : n <= 8 ? 4 : n <= 10 ? 3 : 2;
+    if (tile == FoldTile::kHalf) return n == 2 ? 4 : n == 3 ? 3 : n <= 6 ? 2 : 1;
+    if (tile == FoldTile::kWhole) return n == 2 ? 8 : n == 3 ? 6 : n == 4 ? 4 : n <= 6 ? 3 : n <= 10 ? 2 : 1;
+    return n == 2 ? 6 : n == 3 ? 4 : n <= 5 ? 3 : n <= 10 ? 2 : 1;
 }
 constexpr unsigned fold_sub_elems(int columns) { return static_cast<unsigned>(columns) * kFoldWaves * 256u; }
 // One rank read and copied to n_store of them: fewer columns the more stores follow each load, and
@@ -218,24 +225,42 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
     const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
     const unsigned long long mine = reinterpret_cast<unsigned long long>(p->buf[lane & (BLINK_MAX_RANKS - 1)]);
     const RankTable ranks = {static_cast<unsigned>(mine), static_cast<unsigned>(mine >> 32)};
-    const unsigned n_items = p->n_items, n_levels = p->n_levels, turn = p->turn, tile_elems = p->tile_elems;
-    const unsigned grid_shift = p->grid_shift, redop = p->redop;
-    const bool reverse = p->reverse != 0, dealt = p->dealt != 0;
+    const unsigned n_items = p->n_items, n_flows = p->n_flows, n_levels = p->n_levels, turn = p->turn;
+    const unsigned tile_elems = p->tile_elems, grid_shift = p->grid_shift, redop = p->redop, width = p->width;
+    const bool reverse = p->reverse != 0, dealt = p->dealt != 0, two = p->two != 0;
     unsigned long long* const ticket = p->ticket;
-    const BLINK_CONST unsigned* const words = p->words ? as_const<unsigned>(p->words) : p->inline_words;
-    const BLINK_CONST FoldLevel* const levels = p->levels ? as_const<FoldLevel>(p->levels) : p->inline_levels;
-    const unsigned n_flows = p->n_flows;
-    const unsigned stride = p->words ? n_flows : static_cast<unsigned>(kInlineFlows);
-    const bool in_lanes = n_flows <= kLaneFlows;   // and with them the levels
+    // The tables in the arguments are fetched beside the other arguments; only where they are
+    // elsewhere does a wave fetch them again (measured from a kernel's start, us: arguments there 0.4,
+    // tables that are fetched after them 0.7).
     unsigned flow_word[kFlowWords], level_word[4];
-    {
-        const unsigned f = min(static_cast<unsigned>(lane), min(n_flows, kLaneFlows) - 1);
-        const unsigned l = min(static_cast<unsigned>(lane), min(n_levels, kLaneFlows) - 1);
+    auto fetch_words = [&](const BLINK_CONST unsigned* words, unsigned stride, unsigned f) {
 #pragma unroll
         for (unsigned w = 0; w < kFlowWords; ++w) flow_word[w] = words[w * stride + f];
+    };
+    auto fetch_levels = [&](const BLINK_CONST FoldLevel* levels, unsigned l) {
         level_word[0] = levels[l].first, level_word[1] = levels[l].base;
         level_word[2] = levels[l].tiles, level_word[3] = levels[l].members;
+    };
+    {   // (buffer loads: others would be merged with the ones below, and wait for the arguments)
+        const __amdgpu_buffer_rsrc_t args = __builtin_amdgcn_make_buffer_rsrc(
+            reinterpret_cast<void*>(reinterpret_cast<unsigned long long>(p)), 0, static_cast<int>(sizeof(FoldParams)), kRawDword3);
+        const int mine = lane & static_cast<int>(kInlineFlows - 1);
+#pragma unroll
+        for (unsigned w = 0; w < kFlowWords; ++w)
+            flow_word[w] = __builtin_amdgcn_raw_buffer_load_b32(
+                args, mine * 4, static_cast<int>(offsetof(FoldParams, inline_words) + w * kInlineFlows * 4), 0);
+        const U4 level = __builtin_amdgcn_raw_buffer_load_b128(
+            args, mine * static_cast<int>(sizeof(FoldLevel)), static_cast<int>(offsetof(FoldParams, inline_levels)), 0);
+        level_word[0] = level.x, level_word[1] = level.y, level_word[2] = level.z, level_word[3] = level.w;
     }
+    // all of them with one wait
+    asm volatile("" ::"s"(n_items), "s"(turn), "s"(tile_elems), "s"(grid_shift), "s"(redop), "s"(width), "s"(p->reverse),
+                 "s"(p->dealt), "s"(p->two), "s"(ticket), "s"(p->words), "s"(p->levels));
+    const BLINK_CONST unsigned* const words = as_const<unsigned>(p->words);
+    const BLINK_CONST FoldLevel* const levels = p->levels ? as_const<FoldLevel>(p->levels) : p->inline_levels;
+    const bool in_lanes = n_flows <= kLaneFlows;   // and with them the levels
+    if (p->words) fetch_words(words, n_flows, min(static_cast<unsigned>(lane), min(n_flows, kLaneFlows) - 1));
+    if (p->levels) fetch_levels(levels, min(static_cast<unsigned>(lane), min(n_levels, kLaneFlows) - 1));
 
     // Ticket -> its flow and elements; then its sub-tiles one after the other.
     long long org = 0;
@@ -263,7 +288,7 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
             }
             fold_ticket(t - levels[l].first, levels[l].base, levels[l].tiles, levels[l].members, turn, &f, &tile);
 #pragma unroll
-            for (unsigned w = 0; w < kFlowWords; ++w) word[w] = words[w * stride + f];
+            for (unsigned w = 0; w < kFlowWords; ++w) word[w] = words[w * n_flows + f];
         }
         auto wide = [&](unsigned w) { return (static_cast<unsigned long long>(word[w + 1]) << 32) | word[w]; };
         int64_t start;
@@ -324,17 +349,20 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
     };
     constexpr std::integral_constant<int, ST> final_policy;
     constexpr std::integral_constant<int, kPolicyThrough> mid_policy;
-    // Every ticket is followed by one draw: a call advances the counter by n_items (32 bits of it:
+    // Every ticket is followed by one draw: a call advances its counters by n_items (32 bits of them:
     // only differences matter).  A buffer operation whose window is empty unless there is a draw to
     // make, and holds lane 0's word alone then: issued by every wave on every path, it lets the
     // compiler count what is outstanding; behind a branch it waited for the answer wherever it
     // waited for the last loads.
+    const unsigned cls = fold_class(blockIdx.x, two);
+    unsigned long long* const counter = ticket + cls * kCounterStride;
     auto draw = [&]() {
         const bool due = !dealt && sub >= hi && wave == 0;
         return static_cast<unsigned>(__builtin_amdgcn_raw_ptr_buffer_atomic_add_i32(
-            1, __builtin_amdgcn_make_buffer_rsrc(ticket, 0, due ? 4 : 0, kRawDword3), lane * 4, 0, 0));
+            1, __builtin_amdgcn_make_buffer_rsrc(counter, 0, due ? 4 : 0, kRawDword3), lane * 4, 0, 0));
     };
-    unsigned t = blockIdx.x;   // the grid has at most n_items workgroups
+    unsigned nth = fold_place(blockIdx.x, two);   // of the counter's tickets; the grid has at most n_items workgroups
+    unsigned t = fold_nth(nth, cls, two);
     unsigned slot = 0;
     resolve(t);
     FoldPiece<N> cur = piece();
@@ -350,7 +378,7 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
     if (__builtin_amdgcn_readfirstlane(state) != 0) {
         cur.to = cur.from;
         sub = hi;
-        t = ~0u;   // the next ticket, whatever the counter says
+        nth = ~0u;   // the next ticket, whatever the counter says
     }
     for (;;) {
         // the tile's loads are on their way; one wave's join them
@@ -407,11 +435,12 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
         const unsigned answer = __builtin_amdgcn_readfirstlane(raw);
         if (sub >= hi) {
             if (dealt) {
-                t += gridDim.x;
+                t += width;
             } else {
-                if (wave == 0) drawn[slot] = t == ~0u ? t : answer - static_cast<unsigned>(p->ticket_base) + gridDim.x;
+                if (wave == 0) drawn[slot] = nth == ~0u ? nth : answer - static_cast<unsigned>(p->ticket_base[cls]) + width;
                 __syncthreads();
-                t = __builtin_amdgcn_readfirstlane(drawn[slot]);
+                nth = __builtin_amdgcn_readfirstlane(drawn[slot]);
+                t = fold_nth(nth, cls, two);
                 slot ^= 1;   // the other word: a wave may still be reading this one
             }
             if (t >= n_items) break;
@@ -420,16 +449,17 @@ __global__ __launch_bounds__(kFoldThreads, 2) void blink_fold(const FoldParams) 
         cur = piece();
         load(cur);
     }
-    // A call's draws end less than a grid's width past its last ticket.  If this one did
-    // not, the counter was not where the host counted it to be when the call started, or has been
+    // A counter's draws end less than the width of its share of the grid past its last ticket.  If these
+    // did not, the counter was not where the host counted it to be when the call started, or has been
     // moved since: another call on the schedule overlaps with this one.  Both have gone wrong
     // (tickets are lost, or drawn twice).
-    if (!dealt && t - n_items >= gridDim.x && threadIdx.x == 0) {
+    if (!dealt && nth - fold_share(n_items, cls, two) >= width && threadIdx.x == 0) {
         unsigned long long* const status = ticket - kStatusWords;
         if (__hip_atomic_exchange(status + kStatusState, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
+            const unsigned long long base = p->ticket_base[cls];
             status[kStatusStage] = status[kStatusAwaited] = ~0ull;
-            status[kStatusSeen] = p->ticket_base + static_cast<long long>(static_cast<int>(t - gridDim.x));
-            status[kStatusWanted] = p->ticket_base;
+            status[kStatusSeen] = base + static_cast<long long>(static_cast<int>(nth - width));
+            status[kStatusWanted] = base;
             status[kStatusCall] = p->call;
         }
     }
@@ -441,46 +471,54 @@ using FoldFn = void (*)(const FoldParams);
     BLINK_CASE(2) BLINK_CASE(3) BLINK_CASE(4) BLINK_CASE(5) BLINK_CASE(6) BLINK_CASE(7) BLINK_CASE(8) BLINK_CASE(9) \
     BLINK_CASE(10) BLINK_CASE(11) BLINK_CASE(12) BLINK_CASE(13) BLINK_CASE(14) BLINK_CASE(15) BLINK_CASE(16)
 
-// The kernel for stages that read n ranks and write them all (pick_fold_all) or one
-// (pick_fold_one); null where there is none.
+// The kernel for stages that read n ranks and write them all (drawn tickets: pick_fold_drawn, others:
+// pick_fold_dealt) or one (pick_fold_one); null where there is none.
 template <typename T, bool SUM, int POLICY, bool MID = false>
-FoldFn pick_fold_all(int n) {
+FoldFn pick_fold_drawn(int n) {
     switch (n) {
-#define BLINK_CASE(N) case N: return blink_fold<T, N, true, SUM, POLICY, fold_columns(N, true), MID>;
+#define BLINK_CASE(N) case N: return blink_fold<T, N, true, SUM, POLICY, fold_columns(N, true, FoldTile::kDrawn), MID>;
         BLINK_FOLD_CASES
 #undef BLINK_CASE
         default: return nullptr;
     }
 }
-template <typename T, bool SUM, bool MID = false>
-FoldFn pick_fold_half(int n) {
+template <typename T, bool SUM, FoldTile TILE, bool MID = false>
+FoldFn pick_fold_dealt(int n) {
     switch (n) {
-#define BLINK_CASE(N) case N: return blink_fold<T, N, true, SUM, kFoldKeep, fold_columns(N, true, true), MID>;
+#define BLINK_CASE(N) case N: return blink_fold<T, N, true, SUM, kFoldKeep, fold_columns(N, true, TILE), MID>;
         BLINK_FOLD_CASES
 #undef BLINK_CASE
         default: return nullptr;
     }
 }
-template <typename T, bool SUM, bool MID = false>
+template <typename T, bool SUM, FoldTile TILE, bool MID = false>
 FoldFn pick_fold_one(int n) {
     switch (n) {
-#define BLINK_CASE(N) case N: return blink_fold<T, N, false, SUM, kFoldKeep, fold_columns(N, false), MID>;
+#define BLINK_CASE(N) case N: return blink_fold<T, N, false, SUM, kFoldKeep, fold_columns(N, false, TILE), MID>;
         BLINK_FOLD_CASES
 #undef BLINK_CASE
         default: return nullptr;
     }
+}
+template <typename T, bool SUM, bool MID = false>
+FoldFn pick_fold(int n, bool all, FoldTile tile) {
+    if (!all)
+        return tile == FoldTile::kDrawn ? pick_fold_one<T, SUM, FoldTile::kDrawn, MID>(n) : pick_fold_one<T, SUM, FoldTile::kWhole, MID>(n);
+    return tile == FoldTile::kHalf    ? pick_fold_dealt<T, SUM, FoldTile::kHalf, MID>(n)
+           : tile == FoldTile::kWhole ? pick_fold_dealt<T, SUM, FoldTile::kWhole, MID>(n)
+                                      : pick_fold_drawn<T, SUM, kFoldKeep, MID>(n);
 }
 
 // Per element type and operator class, each in a translation unit of its own so
 // that they compile side by side.  all: a stage writes the ranks it reads, else one;
-// stream, half: the kernels for sums that stream their results, and with tiles of half the
-// size (sums and others); mid: those that write partial sums on the way.
-FoldFn fold_f32_sum(int n, bool all, bool stream, bool half);
-FoldFn fold_f32_other(int n, bool all, bool half);
-FoldFn fold_f32_mid(int n, bool all, bool sum, bool half);
-FoldFn fold_i32_sum(int n, bool all, bool stream, bool half);
-FoldFn fold_i32_other(int n, bool all, bool half);
-FoldFn fold_i32_mid(int n, bool all, bool sum, bool half);
+// stream: the kernels for sums that stream their results, where tickets are drawn; mid: those that
+// write partial sums on the way.
+FoldFn fold_f32_sum(int n, bool all, FoldTile tile, bool stream);
+FoldFn fold_f32_other(int n, bool all, FoldTile tile);
+FoldFn fold_f32_mid(int n, bool all, FoldTile tile, bool sum);
+FoldFn fold_i32_sum(int n, bool all, FoldTile tile, bool stream);
+FoldFn fold_i32_other(int n, bool all, FoldTile tile);
+FoldFn fold_i32_mid(int n, bool all, FoldTile tile, bool sum);
 FoldFn fold_copy(int policy, int columns);   // one rank read: nothing is combined
 
 }  // namespace blink

@@ -4,10 +4,8 @@
 
 namespace blink {
 
-FoldFn fold_f32_mid(int n, bool all, bool sum, bool half) {
-    if (!all) return sum ? pick_fold_one<float, true, true>(n) : pick_fold_one<float, false, true>(n);
-    if (half) return sum ? pick_fold_half<float, true, true>(n) : pick_fold_half<float, false, true>(n);
-    return sum ? pick_fold_all<float, true, kFoldKeep, true>(n) : pick_fold_all<float, false, kFoldKeep, true>(n);
+FoldFn fold_f32_mid(int n, bool all, FoldTile tile, bool sum) {
+    return sum ? pick_fold<float, true, true>(n, all, tile) : pick_fold<float, false, true>(n, all, tile);
 }
 
 }  // namespace blink

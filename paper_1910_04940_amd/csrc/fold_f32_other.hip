@@ -4,9 +4,6 @@
 
 namespace blink {
 
-FoldFn fold_f32_other(int n, bool all, bool half) {
-    if (!all) return pick_fold_one<float, false>(n);
-    return half ? pick_fold_half<float, false>(n) : pick_fold_all<float, false, kFoldKeep>(n);
-}
+FoldFn fold_f32_other(int n, bool all, FoldTile tile) { return pick_fold<float, false>(n, all, tile); }
 
 }  // namespace blink

@@ -3,10 +3,8 @@
 
 namespace blink {
 
-FoldFn fold_f32_sum(int n, bool all, bool stream, bool half) {
-    if (!all) return pick_fold_one<float, true>(n);
-    if (half) return pick_fold_half<float, true>(n);
-    return stream ? pick_fold_all<float, true, kFoldStream>(n) : pick_fold_all<float, true, kFoldKeep>(n);
+FoldFn fold_f32_sum(int n, bool all, FoldTile tile, bool stream) {
+    return stream && all && tile == FoldTile::kDrawn ? pick_fold_drawn<float, true, kFoldStream>(n) : pick_fold<float, true>(n, all, tile);
 }
 
 }  // namespace blink

@@ -4,10 +4,8 @@
 
 namespace blink {
 
-FoldFn fold_i32_mid(int n, bool all, bool sum, bool half) {
-    if (!all) return sum ? pick_fold_one<unsigned, true, true>(n) : pick_fold_one<unsigned, false, true>(n);
-    if (half) return sum ? pick_fold_half<unsigned, true, true>(n) : pick_fold_half<unsigned, false, true>(n);
-    return sum ? pick_fold_all<unsigned, true, kFoldKeep, true>(n) : pick_fold_all<unsigned, false, kFoldKeep, true>(n);
+FoldFn fold_i32_mid(int n, bool all, FoldTile tile, bool sum) {
+    return sum ? pick_fold<unsigned, true, true>(n, all, tile) : pick_fold<unsigned, false, true>(n, all, tile);
 }
 
 }  // namespace blink

@@ -4,9 +4,6 @@
 
 namespace blink {
 
-FoldFn fold_i32_other(int n, bool all, bool half) {
-    if (!all) return pick_fold_one<unsigned, false>(n);
-    return half ? pick_fold_half<unsigned, false>(n) : pick_fold_all<unsigned, false, kFoldKeep>(n);
-}
+FoldFn fold_i32_other(int n, bool all, FoldTile tile) { return pick_fold<unsigned, false>(n, all, tile); }
 
 }  // namespace blink

@@ -3,10 +3,8 @@
 
 namespace blink {
 
-FoldFn fold_i32_sum(int n, bool all, bool stream, bool half) {
-    if (!all) return pick_fold_one<unsigned, true>(n);
-    if (half) return pick_fold_half<unsigned, true>(n);
-    return stream ? pick_fold_all<unsigned, true, kFoldStream>(n) : pick_fold_all<unsigned, true, kFoldKeep>(n);
+FoldFn fold_i32_sum(int n, bool all, FoldTile tile, bool stream) {
+    return stream && all && tile == FoldTile::kDrawn ? pick_fold_drawn<unsigned, true, kFoldStream>(n) : pick_fold<unsigned, true>(n, all, tile);
 }
 
 }  // namespace blink

@@ -88,6 +88,24 @@ BLINK_HOST_DEVICE inline void fold_range(uint64_t off, uint64_t len, uint32_t ti
     *b = high < 0 ? 0 : (high > 0 || low > tile_elems) ? tile_elems : low;
 }
 
+// Drawn tickets come from two counters where the grid allows (`two`; one alone sustains about 80
+// draws per microsecond): the even tickets from one, the odd ones from the other.  Workgroups
+// take turns in groups of eight, so that each XCD's use both.  A workgroup starts on the ticket of its
+// own place and goes on with what its counter answers, counted on from the grid's share of it.
+constexpr uint32_t kTwoCountersGrid = 16;   // grids are a multiple of this then
+BLINK_HOST_DEVICE inline uint32_t fold_class(uint32_t workgroup, bool two) { return two ? (workgroup >> 3) & 1u : 0u; }
+BLINK_HOST_DEVICE inline uint32_t fold_place(uint32_t workgroup, bool two) {
+    return two ? (workgroup >> 4) * 8u + (workgroup & 7u) : workgroup;
+}
+// The nth ticket of a counter; beyond all tickets where nth makes no sense.
+BLINK_HOST_DEVICE inline uint32_t fold_nth(uint32_t nth, uint32_t cls, bool two) {
+    return two ? (nth < 0x7fffffffu ? nth : 0x7fffffffu) * 2u + cls : nth;
+}
+// Of n_items tickets those of a counter; each is followed by one draw.
+BLINK_HOST_DEVICE inline uint32_t fold_share(uint32_t n_items, uint32_t cls, bool two) {
+    return two ? (n_items + 1u - cls) / 2u : n_items;
+}
+
 inline uint32_t fold_tiles(uint64_t off, uint64_t len, uint32_t tile_elems, uint32_t grid_shift) {
     return static_cast<uint32_t>((((off + grid_shift) & 255u) + len + tile_elems - 1) / tile_elems);
 }

@@ -23,7 +23,7 @@ struct LaunchPlan {
     // what the fold kernel runs (fold.hpp)
     bool fold = false;
     bool small = false;            // a workgroup for every tile
-    bool half = false;             // tiles of half the size
+    bool half = false;             // tiles of half the size (where small)
     bool all = false;              // every stage writes all the ranks it reads
     bool mid = false;              // partial sums are written on the way
     uint32_t n_load = 0;           // ranks a stage reads

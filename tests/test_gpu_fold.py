@@ -311,3 +311,28 @@ def test_the_timed_choice_compares_like_with_like():
     torch.cuda.synchronize()
     for b in bufs:
         assert int(b.min()) == int(b.max()) and int(b.min()) % (1 << 32) == value
+
+
+@pytest.mark.parametrize("n_trees", [1, 6])
+@pytest.mark.parametrize("k,n", [(4, 9_000_005), (6, 5_000_003), (8, 6_000_002)])
+def test_sums_and_other_operators_by_turns(k, n, n_trees):
+    """Drawn tickets, from two counters where a ticket is small (four and six ranks) and from one: calls of all operators on
+    one schedule, with its tables in the arguments (one tree) and on the device (six)."""
+    stream = _stream()
+    forest = [_tree(k, s) for s in range(n_trees)]
+    roots, parents, w = [r for r, _ in forest], [p for _, p in forest], [1.0 + s for s in range(n_trees)]
+    trees = bl.blink_trees_from_arrays(k, roots, parents, w)
+    sched = bl.blink_make_schedule(trees, bl.BLINK_OP_ALLREDUCE, n, 1 << 16, bl.BLINK_FUSE_TREE)
+    x = [si.hash_payload(17, r, 0, n, "int32") for r in range(k)]
+    bufs, untouched = _slab(x)
+    for op in ("sum", "max", "sum", "prod", "min", "sum"):
+        code, oracle_op = REDOPS[op]
+        want = ox.tree_order_allreduce(x, roots, parents, w, oracle_op)
+        bl.blink_allreduce_op(bufs, n, bl.BLINK_INT32, code, sched, stream)
+        torch.cuda.synchronize()
+        assert all(b.cpu().numpy().tobytes() == want.tobytes() for b in bufs), op
+        x = [si.hash_payload(19, r, len(op), n, "int32") for r in range(k)]
+        for b, a in zip(bufs, x):
+            b.copy_(torch.from_numpy(a))
+    assert untouched()
+    assert sched.status()[0] == bl.BLINK_OK
