@@ -371,11 +371,11 @@ blink_status_t blink_allreduce_noalloc(void* const* bufs, int k, size_t n_elems,
 blink_status_t blink_schedule_set_launch(blink_schedule_t* s, int wg_per_cu, int tile_elems);
 /* A schedule whose stages do not wait for one another (whole-tree fusion) can
  * be served in up to three ways at streaming sizes; they give the same bits.
- * 1 = tile by tile across the trees (chunk by chunk where a stage reads more than 8
- * ranks); 2 = one front through the payload, results written past the GPU's
+ * 1 = in turns of 128 KiB of every rank across the trees (chunk by chunk where a stage reads
+ * more than 8 ranks); 2 = one front through the payload, results written past the GPU's
  * memory-side cache from twice its size (sums only, stages whose partial sums
  * need at most four accumulators); 3 = the trees taking turns chunk by
- * chunk (section 4.2.2 at the paper's own granularity) instead of tile by tile
+ * chunk (section 4.2.2 at the paper's own granularity) instead
  * (several trees only).  kernel: 0 = automatic: the first calls of at least
  * 64 MiB of traffic go round the ways the schedule has, four times each (eight
  * or twelve calls), timed with events on the caller's stream; the call after

@@ -311,7 +311,7 @@ class Schedule:
 
     def set_kernel(self, kernel: int) -> None:
         """0 = the library times the ways it can serve this schedule and keeps the
-        fastest; 1 = tile by tile across the trees, 2 = one front through the payload,
+        fastest; 1 = in short turns across the trees, 2 = one front through the payload,
         3 = the trees taking turns chunk by chunk (see blink.h)."""
         _check(lib().blink_schedule_set_kernel(self._h, kernel), "blink_schedule_set_kernel")
 

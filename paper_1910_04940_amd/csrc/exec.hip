@@ -199,6 +199,7 @@ void plan_hand_over(blink_schedule* h) {
 // workgroup per tile against 224 that draw: 2 MiB per rank 5.1 / 7.2 us, 4 MiB 9.6 /
 // 10.8, 7 MiB (3.5 tiles per CU) 14.4 / 16.2, 10.4 MiB (5.2) 25 / 25, 16 MiB 51 / 47).
 constexpr unsigned kFoldTicketBytes = 56 * 1024;
+constexpr unsigned kFoldRunElems = 32 * 1024;
 constexpr unsigned kFoldOneCounterBytes = 128 * 1024;
 constexpr uint64_t kFoldSmallBytesPerCu = 5 * 128 * 1024;
 constexpr unsigned kFoldHalfTilesPerCu = 2;   // up to here half tiles are faster (see fold_columns)
@@ -542,7 +543,11 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     // written on the way the trees' turns cost up to a tenth (per node, us on the same buffers,
     // one front / turns: 8 ranks x 8 MiB 26.1 / 24.0, 20 MiB 60.8 / 62.3, 64 MiB 175 / 192, 128 MiB
     // 351 / 388, 256 MiB 738 / 735; 6 ranks x 98 MiB 200 / 216).
-    p.turn = way == 2 || s.has_deps ? kTurnPayload : (way == 3 || !by_tile) ? chunk_turn : 1u;
+    // Way 1 gives a tree 128 KiB of every rank at a turn: HBM serves a stretch like that best in one go
+    // (8 ranks, us in turns of a tile / 64 / 128 / 256 KiB, on one set of buffers: 230 MiB 663 / 658 / 642 / 646,
+    // 256 MiB 675 / 671 / 658 / 668, on another 729 / 724 / 707 / 734, 400 MiB 1127 / 1116 / 1094 / 1098).
+    const uint32_t run_turn = pl.small ? 1u : std::max(1u, kFoldRunElems / pl.tile_elems);
+    p.turn = way == 2 || s.has_deps ? kTurnPayload : (way == 3 || !by_tile) ? chunk_turn : run_turn;
     p.tile_elems = pl.tile_elems;
     p.grid_shift = grid_shift;
     p.redop = static_cast<unsigned>(redop);

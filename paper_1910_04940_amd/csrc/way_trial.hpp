@@ -1,7 +1,7 @@
 // Picking the way a whole-tree schedule is served at streaming size: the
 // order in which the fold kernel goes through the payload, and with it whether
 // results stream past the memory-side cache.
-//   1  tile by tile across the trees (section 4.2.2; chunk by chunk where a stage
+//   1  the trees taking turns of 128 KiB of every rank (section 4.2.2; chunk by chunk where a stage
 //      reads more than 8 ranks: 16 x 16 streams at a time are too many)
 //   2  one front through the payload, one tree's share after the other
 //   3  chunk by chunk across the trees (several trees, at most 8 ranks)
