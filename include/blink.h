@@ -394,7 +394,7 @@ int blink_schedule_last_kernel(const blink_schedule_t* s);
  * second, fourth, ... call on such a schedule goes through the tiles backwards
  * and results are written with a policy that lets them stay in the GPU's
  * 256 MiB memory-side cache (way 2 of blink_schedule_set_kernel: below twice
- * that), so a call on the buffers of the call before it
+ * that, the others: below twelve times that), so a call on the buffers of the call before it
  * (training iterations without much else in between, benchmark loops) starts
  * on data that is still there.  alternate = 0: every call goes forwards and
  * streams its stores past the cache (sums whose buffers do not fit it).  Same bits either

@@ -486,10 +486,12 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     // then starts on the last 256 MiB that the call before it wrote (repeated in place,
     // 3 ranks x 98 MiB 98 -> 86 us, 8 x 256 MiB 701 -> 687).  From twice the cache way 2
     // streams them, which is 1 to 3 % faster where the next call works on other buffers (6 ranks x
-    // 98 MiB 196 -> 191).
+    // 98 MiB 196 -> 191); the other ways from twelve times, where a call gains nothing any more from what the
+    // one before it left (kept / streamed, way 1: 8 ranks x 256 MiB on changing buffers 658 / 645, in place 636 / 649;
+    // x 400 MiB 1094 / 1060, 1080 / 1072; 16 ranks x 1 GiB 5316 / 5189, 5412 / 5246).
     const uint64_t payload_bytes = static_cast<uint64_t>(s.k) * s.n * 4;
     const bool fits_cache = payload_bytes <= kMemorySideCacheBytes;
-    const bool streams = s.has_deps || !h->sweep_alternates || (way == 2 && payload_bytes >= 2 * kMemorySideCacheBytes);
+    const bool streams = s.has_deps || !h->sweep_alternates || payload_bytes >= (way == 2 ? 2 : 12) * kMemorySideCacheBytes;
     int policy = kFoldKeep;
     if (pl.n_load == 1 && s.fused[0].stage.n_store > 1)
         policy = kFoldSpread;
