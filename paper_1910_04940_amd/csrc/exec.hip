@@ -190,17 +190,13 @@ void plan_hand_over(blink_schedule* h) {
 }
 
 // The plan where the fold kernel runs the schedule.  A drawn ticket is one sub-tile of the
-// kernel, or as many as make it move 56 KiB: at 6.5 TB/s that is 113 draws per microsecond, and a
-// counter serves 80.  Tickets of less than 128 KiB draw from two counters; from 128 KiB one
-// keeps up, and the front along which one hands them out is the tighter (two servers of 8, 64 MiB of
-// zeros, with one / two 324 / 328 us).
+// kernel, or as many as make it move 56 KiB, which two counters keep up with (see fold_grid).
 // A payload of at most five tiles (of 128 KiB read and written) per CU gets a workgroup for
 // every tile: they are all resident at once or nearly so, and no ticket has to be drawn (probe, 8 ranks,
 // workgroup per tile against 224 that draw: 2 MiB per rank 5.1 / 7.2 us, 4 MiB 9.6 /
 // 10.8, 7 MiB (3.5 tiles per CU) 14.4 / 16.2, 10.4 MiB (5.2) 25 / 25, 16 MiB 51 / 47).
 constexpr unsigned kFoldTicketBytes = 56 * 1024;
 constexpr unsigned kFoldRunElems = 32 * 1024;
-constexpr unsigned kFoldOneCounterBytes = 128 * 1024;
 constexpr uint64_t kFoldSmallBytesPerCu = 5 * 128 * 1024;
 constexpr unsigned kFoldHalfTilesPerCu = 2;   // up to here half tiles are faster (see fold_columns)
 
@@ -516,10 +512,7 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
                              : n_store == 3 || n_store == 4 ? 7 : 8;
     uint64_t most = pl.small ? pl.n_items : cus * eighths / 8;
     if (h->wg_per_cu > 0) most = h->wg_per_cu * cus;
-    unsigned grid = static_cast<unsigned>(std::max<uint64_t>(1, std::min(most, pl.n_items)));
-    const bool dealt = pl.small || grid == pl.n_items;
-    const bool two = !dealt && grid >= kTwoCountersGrid && pl.tile_elems * 4 * (pl.n_load + n_store) < kFoldOneCounterBytes;
-    if (two) grid -= grid % kTwoCountersGrid;
+    const auto [grid, dealt, two] = fold_grid(most, pl.n_items, pl.small, 4ull * pl.tile_elems * (pl.n_load + n_store));
 
     if (static_block) {
         h->static_record = !dealt;

@@ -92,7 +92,7 @@ BLINK_HOST_DEVICE inline void fold_range(uint64_t off, uint64_t len, uint32_t ti
 // draws per microsecond): the even tickets from one, the odd ones from the other.  Workgroups
 // take turns in groups of eight, so that each XCD's use both.  A workgroup starts on the ticket of its
 // own place and goes on with what its counter answers, counted on from the grid's share of it.
-constexpr uint32_t kTwoCountersGrid = 16;   // grids are a multiple of this then
+constexpr uint32_t kTwoCountersGroup = 16;   // the grid is a multiple of it
 BLINK_HOST_DEVICE inline uint32_t fold_class(uint32_t workgroup, bool two) { return two ? (workgroup >> 3) & 1u : 0u; }
 BLINK_HOST_DEVICE inline uint32_t fold_place(uint32_t workgroup, bool two) {
     return two ? (workgroup >> 4) * 8u + (workgroup & 7u) : workgroup;
@@ -104,6 +104,27 @@ BLINK_HOST_DEVICE inline uint32_t fold_nth(uint32_t nth, uint32_t cls, bool two)
 // Of n_items tickets those of a counter; each is followed by one draw.
 BLINK_HOST_DEVICE inline uint32_t fold_share(uint32_t n_items, uint32_t cls, bool two) {
     return two ? (n_items + 1u - cls) / 2u : n_items;
+}
+
+// The workgroups of a call and how they get their tickets.  most: as many workgroups as the launcher wants;
+// for_every_tile: a payload that is to have one for every ticket; ticket_bytes: read and written per ticket.
+struct FoldGrid {
+    uint32_t grid;
+    bool dealt;   // workgroup w takes tickets w, w + grid, ...
+    bool two;     // two counters
+};
+// Two counters where one does not keep up: 224 workgroups that move tickets of 56 KiB at 6.5 TB/s draw 113 times
+// per microsecond, half a draw each, and a counter serves 80, so up to 158 workgroups (a part of the card) one is
+// enough.  From 128 KiB per ticket one is enough for all 256, and the front along which one hands tickets out is the
+// tighter (two servers of 8, 64 MiB of zeros, with one / two 324 / 328 us).  Where the mapping of workgroups to two counters
+// (fold_place) does not come out even, one serves: no workgroup is given up for it.
+constexpr uint64_t kFoldOneCounterBytes = 128 * 1024;
+constexpr uint32_t kTwoCountersGrid = 160;
+inline FoldGrid fold_grid(uint64_t most, uint64_t n_items, bool for_every_tile, uint64_t ticket_bytes) {
+    FoldGrid g{static_cast<uint32_t>(std::max<uint64_t>(1, std::min(most, n_items))), false, false};
+    g.dealt = for_every_tile || g.grid == n_items;
+    g.two = !g.dealt && g.grid >= kTwoCountersGrid && g.grid % kTwoCountersGroup == 0 && ticket_bytes < kFoldOneCounterBytes;
+    return g;
 }
 
 inline uint32_t fold_tiles(uint64_t off, uint64_t len, uint32_t tile_elems, uint32_t grid_shift) {
