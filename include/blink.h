@@ -372,8 +372,8 @@ blink_status_t blink_schedule_set_launch(blink_schedule_t* s, int wg_per_cu, int
 /* A schedule whose stages do not wait for one another (whole-tree fusion) can
  * be served in up to three ways at streaming sizes; they give the same bits.
  * 1 = in turns of 128 KiB of every rank across the trees (chunk by chunk where a stage reads
- * more than 8 ranks); 2 = one front through the payload, results written past the GPU's
- * memory-side cache from twice its size (sums only, stages whose partial sums
+ * more than 8 ranks); 2 = one front through the payload, results of larger payloads written past
+ * the GPU's memory-side cache (see blink_schedule_set_sweep; sums only, stages whose partial sums
  * need at most four accumulators); 3 = the trees taking turns chunk by
  * chunk (section 4.2.2 at the paper's own granularity) instead
  * (several trees only).  kernel: 0 = automatic: the first calls of at least
@@ -393,11 +393,14 @@ int blink_schedule_last_kernel(const blink_schedule_t* s);
  * waits for another (whole-tree fusion).  alternate = 1 (the default): the
  * second, fourth, ... call on such a schedule goes through the tiles backwards
  * and results are written with a policy that lets them stay in the GPU's
- * 256 MiB memory-side cache (way 2 of blink_schedule_set_kernel: below twice
- * that, the others: below twelve times that), so a call on the buffers of the call before it
+ * 256 MiB memory-side cache, so a call on the buffers of the call before it
  * (training iterations without much else in between, benchmark loops) starts
- * on data that is still there.  alternate = 0: every call goes forwards and
- * streams its stores past the cache (sums whose buffers do not fit it).  Same bits either
+ * on data that is still there.  Exceptions, which stream past it: sums that all ranks get
+ * from twelve times its size (way 2 of blink_schedule_set_kernel: from twice), and in way 2
+ * copies to one rank that move more than it holds, from the same line; and data that one rank
+ * sends to several always streams.  alternate = 0: every call goes forwards and
+ * streams its stores past the cache (sums whose buffers, and copies to one rank whose
+ * traffic, do not fit it).  Same bits either
  * way; schedules with
  * dependencies and blink_allreduce_noalloc always go forwards. */
 blink_status_t blink_schedule_set_sweep(blink_schedule_t* s, int alternate);

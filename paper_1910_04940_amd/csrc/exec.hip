@@ -209,6 +209,7 @@ void plan_fold(blink_schedule* h) {
     const uint32_t n_store = s.fused[0].stage.n_store;
     pl.all = pl.n_load > 1 && n_store == pl.n_load;
     for (const FusedFlow& f : s.fused) pl.mid = pl.mid || f.mid_store != 0;
+    pl.kernel_bytes = fold_bytes(s);
     const int n = static_cast<int>(pl.n_load);
     const bool in_cache = s.traffic_bytes <= (n_store == 1 ? kMemorySideCacheBytes / 8 * 5 : kMemorySideCacheBytes);
     pl.copy_columns = n == 1 ? fold_copy_columns(n_store, in_cache) : 0;
@@ -476,23 +477,9 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     const uint64_t chunk_tiles = std::max<uint64_t>(1, s.chunk / pl.tile_elems);
     const uint32_t chunk_turn = static_cast<uint32_t>(std::min<uint64_t>(chunk_tiles, kTurnPayload));
 
-    // Rank buffers that together fit the memory-side cache (256 MiB) are written
-    // so that results may stay there: whoever reads them next (here: the next call)
-    // finds them.  Larger ones too where calls alternate their direction: a call
-    // then starts on the last 256 MiB that the call before it wrote (repeated in place,
-    // 3 ranks x 98 MiB 98 -> 86 us, 8 x 256 MiB 701 -> 687).  From twice the cache way 2
-    // streams them, which is 1 to 3 % faster where the next call works on other buffers (6 ranks x
-    // 98 MiB 196 -> 191); the other ways from twelve times, where a call gains nothing any more from what the
-    // one before it left (kept / streamed, way 1: 8 ranks x 256 MiB on changing buffers 658 / 645, in place 636 / 649;
-    // x 400 MiB 1094 / 1060, 1080 / 1072; 16 ranks x 1 GiB 5316 / 5189, 5412 / 5246).
     const uint64_t payload_bytes = static_cast<uint64_t>(s.k) * s.n * 4;
-    const bool fits_cache = payload_bytes <= kMemorySideCacheBytes;
-    const bool streams = s.has_deps || !h->sweep_alternates || payload_bytes >= (way == 2 ? 2 : 12) * kMemorySideCacheBytes;
-    int policy = kFoldKeep;
-    if (pl.n_load == 1 && s.fused[0].stage.n_store > 1)
-        policy = kFoldSpread;
-    else if (!fits_cache && streams)
-        policy = kFoldStream;
+    const uint32_t n_store = s.fused[0].stage.n_store;
+    const FoldPolicy policy = fold_policy(pl.n_load, n_store, payload_bytes, pl.kernel_bytes, s.has_deps, way, h->sweep_alternates);
     const FoldFn fn = pick_fold(dtype, sum, pl, policy);
     if (!fn) return BLINK_EINVAL;
 
@@ -505,7 +492,6 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     // 192 / 190; to 3, 300 MiB, 195 / 193 / 194; to 5, 85 MiB, 72 / 70 / 70, 200 MiB, 207 / 192 / 190; to 7,
     // 64 MiB 70 / 68 / 71, 500 MiB 712 / 646 / 642; to 15, 64 MiB 148 / 155 / -, 150 MiB 424 / 408 / -).
     const uint64_t cus = static_cast<uint64_t>(h->n_cu);
-    const uint32_t n_store = s.fused[0].stage.n_store;
     const bool copy_many = pl.n_load == 1 && n_store > 6;
     const uint64_t eighths = pl.n_load > 1 ? (pl.all ? 7 : 8)
                              : copy_many   ? (n_store > 8 ? 6 : 7) + (payload_bytes > 4 * kMemorySideCacheBytes ? 1 : 0)

@@ -123,11 +123,6 @@ constexpr int fold_copy_columns(unsigned n_store, bool in_cache) {
 //   stores sc1       16.2  47.4   96.5  164.7  291.9
 //   stores nt sc1    22.6  48.2   94.9  162.0  289.0
 //   stores nt        23.2  48.6   97.9  169.4  304.9
-enum FoldPolicy : int {
-    kFoldKeep = 0,    // results may stay in the memory-side cache: whoever reads them next finds them there
-    kFoldStream = 1,  // results stream past it
-    kFoldSpread = 2,  // one rank read, many written: loads by default policy, stores stream
-};
 template <int POLICY>
 struct FoldPolicyBits {
     static constexpr int kLoad = POLICY == kFoldSpread ? kPolicyDefault : kPolicyStream;

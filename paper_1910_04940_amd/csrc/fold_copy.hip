@@ -19,7 +19,7 @@ FoldFn fold_copy(int policy, int columns) {
         }
     }
     switch (columns) {   // to one rank
-        case 4: return policy == kFoldStream ? kCopy<kFoldStream, 4> : kCopy<kFoldKeep, 4>;
+        case 4: return policy == kFoldKeep ? kCopy<kFoldKeep, 4> : nullptr;   // (what fits the cache is kept)
         case 16: return policy == kFoldStream ? kCopy<kFoldStream, 16> : kCopy<kFoldKeep, 16>;
         default: return nullptr;
     }

@@ -183,6 +183,44 @@ inline uint64_t fold_levels(const std::vector<FoldFlow>& flows, uint32_t tile_el
 
 constexpr uint64_t kMemorySideCacheBytes = 256ull << 20;
 
+enum FoldPolicy : int {
+    kFoldKeep = 0,    // results may stay in the memory-side cache: whoever reads them next finds them there
+    kFoldStream = 1,  // results stream past it
+    kFoldSpread = 2,  // one rank read, many written: loads by default policy, stores stream
+};
+// How a call's results are written.  payload: bytes of all rank buffers; kernel_bytes: what the call reads and writes
+// (fold_bytes).
+//
+// Rank buffers that together fit the memory-side cache (256 MiB) are written so that results may stay there: whoever reads
+// them next (here: the next call) finds them.  Larger ones too where calls alternate their direction: a call then starts on
+// the last 256 MiB that the call before it wrote (repeated in place, 3 ranks x 98 MiB 98 -> 86 us, 8 x 256 MiB 701 -> 687).
+// Sums that all ranks get (the other operators have kernels that keep only) stream
+//   * in way 2 from twice the cache: 1 to 3 % faster where the next call works on other buffers (6 ranks x 98 MiB 196 -> 191);
+//   * in ways 1 and 3 from twelve times.  Kept / streamed, us, on three sets of buffers in turn, and repeated in place:
+//       caches   7.5  8 ranks x 240 MiB     693 / 690    672 / 700      9.5  8 ranks x 304 MiB    891 / 926    852 / 900
+//               10.5  8 ranks x 336 MiB     969 / 946    923 / 926     10.5  16 ranks x 168 MiB   923 / 908    900 / 890
+//                8.5  4 ranks x 544 MiB     750 / 757    735 / 775     10.3  6 ranks x 440 MiB    873 / 868    861 / 883
+//               12    8 ranks x 384 MiB    1056 / 1039  1032 / 1025    12    16 ranks x 192 MiB  1049 / 1008  1032 / 1024
+//               12.3  8 ranks x 392 MiB    1103 / 1072  1051 / 1034    13.7  5 ranks x 700 MiB   1208 / 1190  1161 / 1166
+//               14.1  4 ranks x 900 MiB    1197 / 1177  1183 / 1184    14.4  16 ranks x 230 MiB  1264 / 1204  1250 / 1224
+//     (in place, what a call finds of the one before it is worth up to 7 % at 7 to 10 caches; from twelve on streaming gains
+//     1 to 5 % on changing buffers and between -1 and 2 % in place.  On one card, at twelve exactly, in place 1063 / 1091
+//     and 1065 / 1128.)
+// A copy to one rank moves far less than the buffers hold, a gather of 8 x 400 MiB 350 MiB each way.  What it moves decides
+// whether it fits the cache (gather of 8 x 80 MiB, 140 MiB moved, kept / streamed 23.6 / 27.8, 4 x 140 MiB, 210 moved, 36.4 /
+// 37.9, 3 x 180 MiB, 240 moved, 41.7 / 41.6), and what it wrote is worth keeping at every size: way 1, in place, 8 x 400 MiB 108 /
+// 139, 4 x 800 MiB 180 / 215, 2 ranks x 1600 MiB 477 / 499, on changing buffers 132 / 136, 212 / 211, 500 / 499.  Way 2 streams,
+// from the same line as sums: on changing buffers 8 x 200 MiB 61.5 / 60.3, 4 x 400 MiB 100 / 98.
+inline FoldPolicy fold_policy(uint32_t n_load, uint32_t n_store, uint64_t payload, uint64_t kernel_bytes, bool has_deps, int way,
+                              bool alternates) {
+    if (n_load == 1 && n_store > 1) return kFoldSpread;
+    const bool copies = n_load == 1;
+    if ((copies ? kernel_bytes : payload) <= kMemorySideCacheBytes) return kFoldKeep;
+    if (has_deps || !alternates) return kFoldStream;
+    const bool streams = way == 2 ? payload >= 2 * kMemorySideCacheBytes : !copies && payload >= 12 * kMemorySideCacheBytes;
+    return streams ? kFoldStream : kFoldKeep;
+}
+
 // Which kernel serves a schedule.  Without dependencies the fold kernel: the other one
 // combines a stage's ranks in the order of load_rank, which is not that of a whole tree's
 // stack program, so a schedule the fold kernel cannot run is not run at all.  With

@@ -28,6 +28,7 @@ struct LaunchPlan {
     bool mid = false;              // partial sums are written on the way
     uint32_t n_load = 0;           // ranks a stage reads
     int copy_columns = 0;          // where it reads one: columns per wave
+    uint64_t kernel_bytes = 0;     // read and written per call (fold_bytes)
     uint32_t grid_shift = 0;       // the tile grid the levels were made for
 };
 

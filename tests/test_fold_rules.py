@@ -1,5 +1,5 @@
-"""The rules by which the launcher of the fold kernel chooses workgroups and counters.  No GPU:
-they are compiled here with the host compiler."""
+"""The rules by which the launcher of the fold kernel chooses workgroups, counters and how results are written.
+No GPU: they are compiled here with the host compiler."""
 import os
 import shutil
 import subprocess
@@ -48,3 +48,48 @@ def test_a_workgroup_for_every_ticket_draws_none(rule):
     assert rule("grid", 256, 200, 0, 57_344) == (200, 1, 0)
     assert rule("grid", 256, 256, 0, 57_344) == (256, 1, 0)
     assert rule("grid", 256, 257, 0, 57_344) == (256, 0, 1)
+
+
+MIB = 1 << 20
+KEEP, STREAM, SPREAD = 0, 1, 2
+
+
+def _policy(rule, k, mib, op, way=1, deps=0, alternates=1):
+    """Sums of k ranks of mib MiB that all get the result, or a gather of them."""
+    n_load, n_store = (k, k) if op == "sum" else (1, 1)
+    kernel = 2 * k * mib * MIB if op == "sum" else 2 * (mib * MIB - mib * MIB // k)
+    return rule("policy", n_load, n_store, k * mib * MIB, kernel, deps, way, alternates)[0]
+
+
+@pytest.mark.parametrize("way", [1, 3])
+def test_results_of_sums_stream_from_twelve_caches(rule, way):
+    for k, mib in ((8, 384), (16, 192), (4, 800)):
+        assert _policy(rule, k, mib, "sum", way) == STREAM
+        assert _policy(rule, k, mib // 2, "sum", way) == KEEP
+
+
+@pytest.mark.parametrize("k,mib", [(8, 80), (8, 400), (8, 4000), (4, 800), (2, 1600), (3, 1100)])
+def test_what_a_gather_wrote_stays_for_the_next_call(rule, k, mib):
+    """It writes one rank: of 8 x 400 MiB 350 MiB, not twelve times the cache."""
+    assert _policy(rule, k, mib, "gather", 1) == KEEP
+    assert _policy(rule, k, mib, "gather", 3) == KEEP
+
+
+def test_one_front_streams_what_does_not_fit(rule):
+    assert _policy(rule, 8, 64, "sum", 2) == STREAM and _policy(rule, 8, 63, "sum", 2) == KEEP
+    # a gather of 8 x 128 MiB reads 112 and writes 112: all of it fits the cache, though 1 GiB is set aside
+    assert _policy(rule, 8, 128, "gather", 2) == KEEP
+    assert _policy(rule, 4, 140, "gather", 2) == KEEP
+    assert _policy(rule, 2, 200, "gather", 2) == KEEP
+    assert _policy(rule, 8, 200, "gather", 2) == STREAM
+    assert _policy(rule, 4, 200, "gather", 2) == STREAM
+
+
+def test_calls_that_do_not_alternate_stream_past_a_cache_that_is_too_small(rule):
+    assert _policy(rule, 8, 32, "sum", alternates=0) == KEEP
+    assert _policy(rule, 8, 33, "sum", alternates=0) == STREAM
+    assert _policy(rule, 8, 33, "sum", deps=1) == STREAM
+    assert _policy(rule, 8, 146, "gather", alternates=0) == KEEP       # 255 MiB moved
+    assert _policy(rule, 8, 147, "gather", alternates=0) == STREAM     # 257
+    assert _policy(rule, 8, 147, "gather", deps=1) == STREAM
+    assert rule("policy", 1, 7, 64 * MIB, 64 * MIB, 0, 1, 1) == (SPREAD,)
