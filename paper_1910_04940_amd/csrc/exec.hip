@@ -211,8 +211,7 @@ void plan_fold(blink_schedule* h) {
     for (const FusedFlow& f : s.fused) pl.mid = pl.mid || f.mid_store != 0;
     pl.kernel_bytes = fold_bytes(s);
     const int n = static_cast<int>(pl.n_load);
-    const bool in_cache = s.traffic_bytes <= (n_store == 1 ? kMemorySideCacheBytes / 8 * 5 : kMemorySideCacheBytes);
-    pl.copy_columns = n == 1 ? fold_copy_columns(n_store, in_cache) : 0;
+    pl.copy_columns = n == 1 ? fold_copy_columns(s) : 0;
     const unsigned sub = fold_sub_elems(n == 1 ? pl.copy_columns : fold_columns(n, pl.all, FoldTile::kWhole));
     uint64_t tiles = 0;
     for (const FoldFlow& f : h->fold.flows) tiles += (f.len + sub - 1) / sub;

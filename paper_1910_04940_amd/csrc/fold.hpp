@@ -98,25 +98,6 @@ constexpr int fold_columns(int n, bool all, FoldTile tile) {
     return n == 2 ? 6 : n == 3 ? 4 : n <= 5 ? 3 : n <= 10 ? 2 : 1;
 }
 constexpr unsigned fold_sub_elems(int columns) { return static_cast<unsigned>(columns) * kFoldWaves * 256u; }
-// One rank read and copied to n_store of them: fewer columns the more stores follow each load, and
-// fewer while a payload has a workgroup for every tile.  us with 2 / 3 / 4 / 8 / 16 columns:
-//   Broadcast to 15, 64 MiB        148 / 158 / 164 / - / -
-//   to 7, 64 MiB                    73 /  68 /  69 / 76 / -      10 MiB  17.2 / 17.6 / 17.9 / - / -
-//   to 5, 85 MiB                     - /  73 /  69 / - / -       13 MiB  14.2 / 15.1 / 15.6 / - / -
-//   to 3, 300 MiB                    - /   - / 207 / 193 / 207   32 MiB  18.6 / 19.2 / 20.7 / 21.9 / 25.1
-//   to 2, 107 MiB                    - /   - /  57 / 50 / 54     43 MiB  17.3 / 17.4 / 17.5 / 18.8 / 19.5
-//   Gather of 4 ranks, 300 MiB       - /   - /  87 / 78 / 77     80 MiB     - /    - / 18.8 / 20.0 / 19.3
-// (to 2 to 4 ranks the line lies where the traffic no longer fits the memory-side cache, to one rank
-// where it takes 5/8 of it: Gather of 4 ranks, 100 MiB each, with 4 / 16 columns 22.9 / 23.9, of 5, 102 MiB, 34.2 / 25.7).
-constexpr int kCopyColumnsSmall = 2, kCopyColumnsMost = 2, kCopyColumnsMany = 3, kCopyColumns = 4, kCopyColumnsFew = 8,
-              kCopyColumnsOne = 16;
-constexpr int fold_copy_columns(unsigned n_store, bool in_cache) {
-    return n_store > 8 ? kCopyColumnsMost
-           : n_store > 6 ? kCopyColumnsMany
-           : n_store > 4 || in_cache ? kCopyColumns
-           : n_store > 1 ? kCopyColumnsFew : kCopyColumnsOne;
-}
-
 // Cache policies of the rank buffers' loads and stores.  Measured with the probe
 // (us; 8 ranks, three sets of buffers in turn; loads always nt):
 //   MiB per rank       7    16    35.5   64     114

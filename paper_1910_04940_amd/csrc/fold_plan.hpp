@@ -183,6 +183,41 @@ inline uint64_t fold_levels(const std::vector<FoldFlow>& flows, uint32_t tile_el
 
 constexpr uint64_t kMemorySideCacheBytes = 256ull << 20;
 
+// Bytes the fold kernel reads plus writes in rank buffers per call: every rank it takes from
+// once, every rank of the result once, and the sums written on the way.
+inline uint64_t fold_bytes(const Schedule& s) {
+    uint64_t bytes = 0;
+    for (const FusedFlow& f : s.fused)
+        bytes += (f.hi - f.lo) * 4u * (f.stage.n_load + f.stage.n_store + static_cast<unsigned>(__builtin_popcount(f.mid_store)));
+    return bytes;
+}
+
+// One rank read and copied to n_store of them: fewer columns the more stores follow each load, and
+// fewer while a payload has a workgroup for every tile.  us with 2 / 3 / 4 / 8 / 16 columns:
+//   Broadcast to 15, 64 MiB        148 / 158 / 164 / - / -
+//   to 7, 64 MiB                    73 /  68 /  69 / 76 / -      10 MiB  17.2 / 17.6 / 17.9 / - / -
+//   to 5, 85 MiB                     - /  73 /  69 / - / -       13 MiB  14.2 / 15.1 / 15.6 / - / -
+//   to 3, 300 MiB                    - /   - / 207 / 193 / 207   32 MiB  18.6 / 19.2 / 20.7 / 21.9 / 25.1
+//   to 2, 107 MiB                    - /   - /  57 / 50 / 54     43 MiB  17.3 / 17.4 / 17.5 / 18.8 / 19.5
+//   Gather of 4 ranks, 300 MiB       - /   - /  87 / 78 / 77     80 MiB     - /    - / 18.8 / 20.0 / 19.3
+// By what the call moves (fold_bytes; not by what the stages of a per-edge or per-node program would, which the kernel does
+// not): to up to three ranks the line lies at 5/8 of the memory-side cache, about where payloads cease to have a workgroup for
+// every tile, to four at twice the cache.  us with 4 / 8 columns by MiB moved, chains per node and whole-tree alike:
+//   to 2   163  25.5 / 25.1   210  31.9 / 31.3   250  37.9 / 37.1   300  50.4 / 46.3
+//   to 3   163  26.2 / 25.5   210  32.7 / 31.5   250  38.3 / 36.9   300  45.2 / 43.6
+//   to 4   163  25.5 / 25.8   210  31.7 / 32.0   425  61.1 / 61.4   512  81.7 / 79.5   1200  202 / 195
+//   Gather with 4 / 16 columns: of 4 ranks, 150 MiB moved, 22.9 / 23.9, of 5, 163, 34.2 / 25.7.
+constexpr int kCopyColumnsSmall = 2, kCopyColumnsMost = 2, kCopyColumnsMany = 3, kCopyColumns = 4, kCopyColumnsFew = 8,
+              kCopyColumnsOne = 16;
+inline int fold_copy_columns(const Schedule& s) {
+    const uint32_t n_store = s.fused[0].stage.n_store;
+    const bool large = fold_bytes(s) > (n_store < 4 ? kMemorySideCacheBytes / 8 * 5 : 2 * kMemorySideCacheBytes);
+    return n_store > 8 ? kCopyColumnsMost
+           : n_store > 6 ? kCopyColumnsMany
+           : n_store > 4 || !large ? kCopyColumns
+           : n_store > 1 ? kCopyColumnsFew : kCopyColumnsOne;
+}
+
 enum FoldPolicy : int {
     kFoldKeep = 0,    // results may stay in the memory-side cache: whoever reads them next finds them there
     kFoldStream = 1,  // results stream past it
@@ -242,15 +277,6 @@ inline Served served_by(const Schedule& s, bool fold_fits, bool hand_over) {
     if (hand_over || !fold_fits) return Served::kHandOver;
     const bool in_cache = static_cast<uint64_t>(s.k) * s.n * 4 <= kMemorySideCacheBytes;
     return s.fusion == BLINK_FUSE_NODE || in_cache ? Served::kFold : Served::kHandOver;
-}
-
-// Bytes the fold kernel reads plus writes in rank buffers per call: every rank it takes from
-// once, every rank of the result once, and the sums written on the way.
-inline uint64_t fold_bytes(const Schedule& s) {
-    uint64_t bytes = 0;
-    for (const FusedFlow& f : s.fused)
-        bytes += (f.hi - f.lo) * 4u * (f.stage.n_load + f.stage.n_store + static_cast<unsigned>(__builtin_popcount(f.mid_store)));
-    return bytes;
 }
 
 // Tile sizes a caller may ask for: powers of two.

@@ -1,6 +1,7 @@
 // What the launch rules of the fold kernel answer:
 //   fold_rules_check grid MOST N_ITEMS FOR_EVERY_TILE TICKET_BYTES      -> workgroups, dealt, two counters
 //   fold_rules_check policy N_LOAD N_STORE PAYLOAD KERNEL_BYTES HAS_DEPS WAY ALTERNATES   -> 0 keep, 1 stream, 2 spread
+//   fold_rules_check columns OP FUSION N CHUNK PARENT...       -> columns of a copy along one tree
 #include <cstdio>
 #include <cstdlib>
 #include <string>
@@ -18,6 +19,24 @@ int main(int argc, char** argv) {
     if (what == "policy") {
         std::printf("%d\n", blink::fold_policy(static_cast<uint32_t>(number(2)), static_cast<uint32_t>(number(3)), number(4), number(5),
                                                number(6) != 0, static_cast<int>(number(7)), number(8) != 0));
+        return 0;
+    }
+    if (what == "columns") {
+        blink::Trees trees;
+        trees.k = argc - 6;
+        trees.weight.push_back(1.0);
+        blink::ParentVec parent;
+        parent.fill(-2);
+        for (int v = 0; v < trees.k; ++v) {
+            parent[v] = static_cast<int8_t>(std::atoi(argv[6 + v]));
+            if (parent[v] < 0) trees.root.push_back(v);
+        }
+        trees.parent.push_back(parent);
+        blink::Schedule s;
+        if (blink::make_schedule(trees, static_cast<blink_op_t>(number(2)), number(4), number(5),
+                                 static_cast<blink_fusion_t>(number(3)), s) != BLINK_OK)
+            return 1;
+        std::printf("%d\n", blink::fold_copy_columns(s));
         return 0;
     }
     return 1;

@@ -1,4 +1,4 @@
-"""The rules by which the launcher of the fold kernel chooses workgroups, counters and how results are written.
+"""The rules by which the launcher of the fold kernel chooses workgroups, counters, a copy's columns and how results are written.
 No GPU: they are compiled here with the host compiler."""
 import os
 import shutil
@@ -6,7 +6,10 @@ import subprocess
 
 import pytest
 
+import paper_1910_04940_amd as bl
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1910_04940_amd", "csrc")
 
 
 @pytest.fixture(scope="module")
@@ -14,9 +17,9 @@ def rule(tmp_path_factory):
     cxx = shutil.which(os.environ.get("CXX", "g++"))
     assert cxx, "no host compiler"
     exe = str(tmp_path_factory.mktemp("rules") / "fold_rules_check")
-    subprocess.run([cxx, "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "include"), "-I",
-                    os.path.join(ROOT, "paper_1910_04940_amd", "csrc"), os.path.join(ROOT, "tests", "c", "fold_rules_check.cpp"),
-                    "-o", exe], check=True)
+    subprocess.run([cxx, "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                    os.path.join(ROOT, "tests", "c", "fold_rules_check.cpp"), os.path.join(CSRC, "schedule.cpp"),
+                    os.path.join(CSRC, "pack.cpp"), "-o", exe], check=True)
 
     def ask(*args):
         out = subprocess.run([exe] + [str(a) for a in args], check=True, capture_output=True, text=True).stdout
@@ -93,3 +96,22 @@ def test_calls_that_do_not_alternate_stream_past_a_cache_that_is_too_small(rule)
     assert _policy(rule, 8, 147, "gather", alternates=0) == STREAM     # 257
     assert _policy(rule, 8, 147, "gather", deps=1) == STREAM
     assert rule("policy", 1, 7, 64 * MIB, 64 * MIB, 0, 1, 1) == (SPREAD,)
+
+
+@pytest.mark.parametrize("k", [3, 4, 5])
+def test_a_copy_has_the_columns_of_what_it_moves(rule, k):
+    """Down a chain the stages of per-edge and per-node programs read what other stages wrote; the kernel that carries a tile
+    through all of them does not, so all three programs are the same copy."""
+    chain = list(range(-1, k - 1))
+    line = 512 if k == 5 else 160     # MiB in all rank buffers, each read or written once
+    for mib, columns in ((0.75 * line, 4), (0.98 * line, 4), (1.02 * line, 8)):
+        for fusion in (bl.BLINK_FUSE_EDGE, bl.BLINK_FUSE_NODE, bl.BLINK_FUSE_TREE):
+            n = int(mib * MIB) // 4 // k
+            assert rule("columns", bl.BLINK_OP_BROADCAST, fusion, n, 1 << 16, *chain) == (columns,), (mib, fusion)
+
+
+def test_a_copys_columns_by_ranks_written(rule):
+    def star(k, mib, op=bl.BLINK_OP_BROADCAST):
+        return rule("columns", op, bl.BLINK_FUSE_TREE, mib * MIB // 4 // k, 1 << 16, *([-1] + [0] * (k - 1)))[0]
+    assert [star(k, 1000) for k in (2, 3, 5, 6, 7, 8, 9, 10, 16)] == [16, 8, 8, 4, 4, 3, 3, 2, 2]
+    assert [star(k, 100) for k in (2, 3, 5, 6, 7, 8, 9, 10, 16)] == [4, 4, 4, 4, 4, 3, 3, 2, 2]
