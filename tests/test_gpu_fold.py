@@ -98,7 +98,7 @@ def test_sizes_where_the_launch_changes(n, fusion, op, dtype):
 
 
 # a copy's columns per wave follow the ranks written and the traffic: two (a workgroup per tile, or more
-# than eight ranks written), three (more than six), four, eight and sixteen (beyond the memory-side cache)
+# than eight ranks written), three (more than six), four, eight and sixteen (by what the copy moves)
 @pytest.mark.parametrize("k,sizes", [(2, (41_000_002, 43_000_002)), (3, (2_000_003, 12_000_001, 20_000_003, 23_000_003)),
                                      (8, (1_500_003, 6_000_001)), (10, (600_003, 4_500_003))])
 def test_copies_of_every_width(k, sizes):
@@ -336,3 +336,107 @@ def test_sums_and_other_operators_by_turns(k, n, n_trees):
             b.copy_(torch.from_numpy(a))
     assert untouched()
     assert sched.status()[0] == bl.BLINK_OK
+
+
+def _drawn_elems(traffic_per_elem):
+    """Elements per rank, ragged, of a payload just too large to have a workgroup for every tile."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return int(1.04 * 5 * 128 * 1024 * cus / traffic_per_elem) // 4 * 4 + 3
+
+
+def _random(k, n, dtype, rng):
+    """k rank buffers in one allocation with 64 guard elements behind each."""
+    step = (n + 64 + 255) // 256 * 256
+    slab = torch.zeros(k * step, dtype=torch.int32, device="cuda")
+    bufs = [slab[r * step:r * step + n].view(torch.float32 if dtype == "fp32" else torch.int32) for r in range(k)]
+    for b in bufs:
+        b.normal_(generator=rng) if dtype == "fp32" else b.random_(-2 ** 31, 2 ** 31, generator=rng)
+    return bufs, lambda: int(torch.count_nonzero(slab.view(k, step)[:, n:])) == 0
+
+
+def _in_tree_order(x, root, parent, op):
+    """The oracle's recursion along one tree, on the device, with a stretch of it checked against the oracle."""
+    combine = {"sum": torch.add, "max": torch.maximum}[op]
+
+    def total(v):
+        acc = x[v]
+        for c in range(len(parent)):
+            if parent[c] == v:
+                acc = combine(acc, total(c))
+        return acc
+    out = total(root)
+    at = out.numel() // 3
+    want = ox.tree_order_allreduce([b[at:at + 2000].cpu().numpy() for b in x], [root], [parent], [1.0], REDOPS[op][1])
+    assert out[at:at + 2000].cpu().numpy().tobytes() == want.tobytes()
+    return out
+
+
+def _same_bits(a, b):
+    return torch.equal(a.view(torch.int32), b.view(torch.int32))
+
+
+@pytest.mark.parametrize("fusion", ["node", "tree"])
+@pytest.mark.parametrize("k", range(2, 17))
+def test_drawn_tickets_with_every_number_of_ranks(k, fusion):
+    """AllReduce and Reduce, sums and maxima of both types by turns on one schedule, with results that may stay in the
+    memory-side cache; sums that stream past it (whole-tree programs of more than a cache, calls all forwards)."""
+    stream = _stream()
+    rng = torch.Generator(device="cuda")
+    rng.manual_seed(k)
+    root, parent = _tree(k, 1)
+    trees = bl.blink_trees_from_arrays(k, [root], [parent], [1.0])
+    cases = [("allreduce", _drawn_elems(8 * k), False), ("reduce", _drawn_elems(4 * (k + 1)), False)]
+    if fusion == "tree":
+        cases.append(("allreduce", (260 << 20) // (4 * k) + 1, True))
+    for which, n, streams in cases:
+        sched = bl.blink_make_schedule(trees, bl.BLINK_OP_REDUCE if which == "reduce" else bl.BLINK_OP_ALLREDUCE, n, 1 << 16,
+                                       FUSIONS[fusion])
+        if streams:
+            sched.set_sweep(False)
+        for op, dtype in (("sum", "fp32"), ("max", "int32"), ("sum", "int32"), ("max", "fp32")):
+            if streams and op == "max":
+                continue
+            bufs, untouched = _random(k, n, dtype, rng)
+            want = _in_tree_order([b.clone() for b in bufs], root, parent, op)
+            code = bl.BLINK_FP32 if dtype == "fp32" else bl.BLINK_INT32
+            if which == "reduce":
+                bl.blink_reduce(bufs, n, code, REDOPS[op][0], sched, stream)
+            else:
+                bl.blink_allreduce_op(bufs, n, code, REDOPS[op][0], sched, stream)
+            for r in [root] if which == "reduce" else range(k):
+                assert _same_bits(bufs[r], want), (which, n, op, dtype, r)
+            assert untouched()
+        assert sched.status()[0] == bl.BLINK_OK
+
+
+# MiB moved: where a payload ceases to have a workgroup for every tile, where it ceases to fit the memory-side cache and
+# at twice that a copy's columns and its way of writing change
+@pytest.mark.parametrize("moved", [150, 170, 240, 300, 530])
+@pytest.mark.parametrize("k", [2, 4, 5, 6])
+def test_copies_on_both_sides_of_their_lines(k, moved):
+    """Broadcast from, and Gather to, the middle of a star; forwards only, where results stream, and in way 2."""
+    stream = _stream()
+    trees = bl.blink_trees_from_arrays(k, [1], [[-1 if r == 1 else 1 for r in range(k)]], [1.0])
+    rng = torch.Generator(device="cuda")
+    rng.manual_seed(moved)
+    n = (moved << 20) // (4 * k) + 3
+    m = (moved << 20) // (8 * (k - 1)) * k
+    for way in (1, 2):
+        for op, size, sweep in ((bl.BLINK_OP_BROADCAST, n, True), (bl.BLINK_OP_GATHER, m, True), (bl.BLINK_OP_GATHER, m, False)):
+            sched = bl.blink_make_schedule(trees, op, size, 1 << 18)
+            sched.set_kernel(way)
+            sched.set_sweep(sweep)
+            bufs, untouched = _random(k, size, "int32", rng)
+            before = [b.clone() for b in bufs]
+            for _ in range(2):
+                if op == bl.BLINK_OP_BROADCAST:
+                    bl.blink_broadcast(bufs, size, bl.BLINK_INT32, sched, stream)
+                    assert all(torch.equal(b, before[1]) for b in bufs)
+                else:
+                    bl.blink_gather(bufs, size, bl.BLINK_INT32, sched, stream)
+                    piece = size // k
+                    for r in range(k):
+                        assert torch.equal(bufs[1][r * piece:(r + 1) * piece], before[r][r * piece:(r + 1) * piece]), r
+                    assert all(torch.equal(bufs[r], before[r]) for r in range(k) if r != 1)
+            assert untouched()
+            assert sched.status()[0] == bl.BLINK_OK
