@@ -267,8 +267,8 @@ blink_status_t blink_schedule_get_stages(const blink_schedule_t* s, blink_stage_
  * these very tickets in ascending order.  Where the order is free (no stage waits for
  * another) the tickets walk tile by tile across the
  * trees (section 4.2.2: trees sharing the machine take turns) unless a stage
- * reads more than 8 ranks.  There the list states the turns, not the very tiles: the
- * library may also serve such a schedule in another order where it measured that to
+ * reads more than 8 ranks.  There the list states the finest turns, not the very tiles: at streaming
+ * sizes the library gives a tree 128 KiB of every rank at a turn, it may also serve such a schedule in another order where it measured that to
  * be faster (blink_schedule_set_kernel), in alternating directions
  * (blink_schedule_set_sweep), it pays no heed to chunk boundaries inside a tree's
  * share, and tiles start on 1 KiB boundaries of the rank buffers where all of these

@@ -192,7 +192,8 @@ void plan_hand_over(blink_schedule* h) {
 // The plan where the fold kernel runs the schedule.  A drawn ticket is one sub-tile of the
 // kernel, or as many as make it move 56 KiB, which two counters keep up with (see fold_grid).
 // A payload of at most five tiles (of 128 KiB read and written) per CU gets a workgroup for
-// every tile: they are all resident at once or nearly so, and no ticket has to be drawn (probe, 8 ranks,
+// every tile, and no ticket has to be drawn.  Where ranks are combined they are all resident at once or nearly so; the
+// small tiles of a copy need not be (to two ranks a CU gets up to 27 workgroups and holds eight) (probe, 8 ranks,
 // workgroup per tile against 224 that draw: 2 MiB per rank 5.1 / 7.2 us, 4 MiB 9.6 /
 // 10.8, 7 MiB (3.5 tiles per CU) 14.4 / 16.2, 10.4 MiB (5.2) 25 / 25, 16 MiB 51 / 47).
 constexpr unsigned kFoldTicketBytes = 56 * 1024;
@@ -488,8 +489,10 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     // where one, two, five or six ranks are written, 7 on 8 CUs where three, four, seven or eight are, 6 on 8
     // with more; and one on eight CUs more than that from seven ranks and four times the memory-side cache on (us with
     // 192 / 224 / 256 workgroups: Gather of 3 ranks, 400 MiB, - / 89 / 90; Broadcast to 2, 400 MiB, 197 /
-    // 192 / 190; to 3, 300 MiB, 195 / 193 / 194; to 5, 85 MiB, 72 / 70 / 70, 200 MiB, 207 / 192 / 190; to 7,
-    // 64 MiB 70 / 68 / 71, 500 MiB 712 / 646 / 642; to 15, 64 MiB 148 / 155 / -, 150 MiB 424 / 408 / -).
+    // 192 / 190; to 3, 300 MiB, 195 / 193 / 194; to 5, 85 MiB, 72 / 70 / 70, 200 MiB, 207 / 192 / 190; to 15,
+    // 64 MiB 148 / 155 / -, 150 MiB 424 / 408 / -; to 7 by payload in times the cache, two - / 72.0 (AllGather 72.3) / 72.1
+    // (73.3), three - / 125.8 (127.8) / 123.8 (125.9), four and a half - / 184 (185) / 180 (180), six - / 262 / 255,
+    // nine - / 396 / 389, sixteen - / 653 / 642: to seven ranks the line could lie a little lower).
     const uint64_t cus = static_cast<uint64_t>(h->n_cu);
     const bool copy_many = pl.n_load == 1 && n_store > 6;
     const uint64_t eighths = pl.n_load > 1 ? (pl.all ? 7 : 8)
@@ -525,7 +528,10 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     // 351 / 388, 256 MiB 738 / 735; 6 ranks x 98 MiB 200 / 216).
     // Way 1 gives a tree 128 KiB of every rank at a turn: HBM serves a stretch like that best in one go
     // (8 ranks, us in turns of a tile / 64 / 128 / 256 KiB, on one set of buffers: 230 MiB 663 / 658 / 642 / 646,
-    // 256 MiB 675 / 671 / 658 / 668, on another 729 / 724 / 707 / 734, 400 MiB 1127 / 1116 / 1094 / 1098).
+    // 256 MiB 675 / 671 / 658 / 668, on another 729 / 724 / 707 / 734, 400 MiB 1127 / 1116 / 1094 / 1098; of a tile / 128 KiB,
+    // 7 ranks x 200 MiB 478 / 476, 6 x 98 MiB 201 / 196, 5 x 98 MiB 161 / 162, x 300 MiB 504 / 522, 4 x 98 MiB 130 / 130,
+    // 4 x 300 MiB 405 / 410, 3 x 98 MiB 95 / 95, AllGather 8 x 64 MiB 74 / 75, 8 x 256 MiB 455 / 418, Broadcast 333 / 333:
+    // it helps where there are many trees, and what it costs to five ranks and less a schedule's timed choice avoids).
     const uint32_t run_turn = pl.small ? 1u : std::max(1u, kFoldRunElems / pl.tile_elems);
     p.turn = way == 2 || s.has_deps ? kTurnPayload : (way == 3 || !by_tile) ? chunk_turn : run_turn;
     p.tile_elems = pl.tile_elems;

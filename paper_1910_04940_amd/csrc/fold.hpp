@@ -10,7 +10,7 @@
 //
 //   * Four waves share one tile; a wave owns U columns of 1 KiB per rank, so a
 //     tile is 4 * U KiB of every rank.  U falls with the number of ranks (fold_columns): where
-//     all ranks are written 40 to 72 KiB of loads per workgroup are in flight.  More in flight than HBM
+//     all ranks are written 44 to 80 KiB of loads per workgroup are in flight (half tiles: from 28).  More in flight than HBM
 //     needs to be busy only spreads the requests out (probe, 8 ranks x 64 MiB, 208 / 224 / 256 / 320 / 448
 //     workgroups 160 / 160 / 168 / 178 / 188 us): one workgroup on seven of eight CUs.
 //   * The number of ranks a stage reads, and whether it writes them all, are
@@ -25,12 +25,12 @@
 //     arrived; its answer travels while the ranks are combined and the results stored.  Measured
 //     against a ticket drawn a tile ahead and loads in front of the stores (us, three sets of
 //     buffers in turn): 8 ranks x 64 MiB 166.5 -> 164.4, x 256 MiB 709 -> 681, x 20 MB 56.9 -> 55.8,
-//     16 ranks x 1 GiB 5585 -> 5178, 3 ranks x 98 MiB 98.8 -> 97.4, Broadcast to 7 ranks, 64 MiB,
+//     16 ranks x 1 GiB 5600 -> 5310, 3 ranks x 98 MiB 98.8 -> 97.4, Broadcast to 7 ranks, 64 MiB,
 //     72.6 -> 69.7, largest value (fp32) 8 x 64 MiB 181 -> 171.  For the same reason a workgroup
 //     that takes two neighbouring tiles one after the other is 10 % slower (168 -> 185) though it
 //     draws half the tickets, and loads issued one by one as registers become free, which keeps
 //     more in flight, are slower as well (probe, 8 x 64 MiB: 170 against 161).
-//   * Tiles are dealt out by two counters (see fold_class; large ones by one); a small payload has
+//   * Tickets come from two counters, or from one where that keeps up (see fold_grid); a small payload has
 //     a workgroup for every tile and no counter (see the launcher).
 #pragma once
 #include "fold_plan.hpp"

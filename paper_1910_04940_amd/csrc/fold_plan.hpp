@@ -228,9 +228,12 @@ enum FoldPolicy : int {
 //
 // Rank buffers that together fit the memory-side cache (256 MiB) are written so that results may stay there: whoever reads
 // them next (here: the next call) finds them.  Larger ones too where calls alternate their direction: a call then starts on
-// the last 256 MiB that the call before it wrote (repeated in place, 3 ranks x 98 MiB 98 -> 86 us, 8 x 256 MiB 701 -> 687).
+// the last 256 MiB that the call before it wrote (way 1, on changing buffers / repeated in place: 3 ranks x 98 MiB 95 / 83 us,
+// 8 x 256 MiB 659 / 646).
 // Sums that all ranks get (the other operators have kernels that keep only) stream
-//   * in way 2 from twice the cache: 1 to 3 % faster where the next call works on other buffers (6 ranks x 98 MiB 196 -> 191);
+//   * in way 2 from twice the cache: kept / streamed, on changing buffers 6 ranks x 98 MiB 192.1 / 190.6, 8 x 64 MiB 172.3 / 170.8,
+//     8 x 230 MiB 606 / 603, 5 x 150 MiB 250 / 245, 16 x 24 MiB 132 / 128; in place 177 / 188, 159 / 173, 593 / 620, 238 / 246, 115 /
+//     129 (there ways 1 and 3, which keep, are to be had);
 //   * in ways 1 and 3 from twelve times.  Kept / streamed, us, on three sets of buffers in turn, and repeated in place:
 //       caches   7.5  8 ranks x 240 MiB     693 / 690    672 / 700      9.5  8 ranks x 304 MiB    891 / 926    852 / 900
 //               10.5  8 ranks x 336 MiB     969 / 946    923 / 926     10.5  16 ranks x 168 MiB   923 / 908    900 / 890
@@ -264,8 +267,8 @@ inline FoldPolicy fold_policy(uint32_t n_load, uint32_t n_store, uint64_t payloa
 // through counters and memory.  Measured on 8 ranks, fp32 sums, three sets of buffers in turn,
 // us, handed over (the best of 16 KiB to 4 MiB chunks) / in one wave:
 //   MiB per rank      8           16          32           64          128         256
-//   per-node      58 / 24     88 / 53    162 / 93    309 / 176   588 / 350   1132 / 719
-//   per-edge      61 / 26     96 / 54    173 / 95    325 / 179   603 / 354   1169 / 725
+//   per-node      57 / 26     87 / 50    168 / 92    316 / 180   599 / 355   1161 / 714
+//   per-edge      60 / 29     99 / 54    179 / 101   333 / 196   635 / 384   1243 / 769
 // One wave is about twice as fast at every size.  Per-edge payloads larger than the memory-side
 // cache are handed over all the same, not for speed: they are the paper's pipeline of chunks,
 // and its pace is what callers who tune the chunk size (section 4.2.1, blink_miad_*) measure

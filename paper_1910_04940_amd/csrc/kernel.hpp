@@ -14,8 +14,9 @@
 // A tile (256..65536 elements, chosen per schedule) is cut into sub-tiles of up to U
 // 128-bit columns per lane and rank; a stage reads its ranks in order, combines them one
 // after the other and writes the result to its ranks.  A sub-tile's loads are issued
-// before the stores of the one in front of it, whose registers are free by then: vector
-// memory operations complete in order, so loads behind stores would wait for them.
+// before the stores of the one in front of it, whose registers are free by then, so that
+// they need not wait for those.  (fold.hpp has it the other way round, measured there; here the other
+// order has not been measured.)
 //
 // Chunk-granular hand-over (the paper's per-chunk event): a stage instance has
 // a 64-bit counter of finished tiles.  Counters are never reset; call number e

@@ -126,8 +126,8 @@ BLINK_HOST_DEVICE inline void ticket_to_tile(unsigned long long t, unsigned grou
 }
 
 // `group` of the published list.  Without dependencies the order of tiles is free: the
-// trees are interleaved tile by tile, all of them while a stage reads at most 8
-// ranks.  With more ranks per stage that makes too many request streams at a
+// list interleaves the trees tile by tile, the finest form of taking turns, all of them while a stage reads at most 8
+// ranks (the one-pass kernel gives a tree a longer turn, see the launcher).  With more ranks per stage that makes too many request streams at a
 // time (16 ranks x 16 one-hop trees = 256): there the trees take turns chunk by
 // chunk (16 x 1 GiB: 5.5 -> 5.9 TB/s; two servers of 8: 5.7 -> 5.9).  With
 // dependencies the tickets follow the execution order itself.

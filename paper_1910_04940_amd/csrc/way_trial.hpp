@@ -5,11 +5,16 @@
 //      reads more than 8 ranks: 16 x 16 streams at a time are too many)
 //   2  one front through the payload, one tree's share after the other
 //   3  chunk by chunk across the trees (several trees, at most 8 ranks)
-// Which is fastest depends on where the buffers lie in HBM and how far apart the
-// trees' shares are, in ways addresses do not reveal.  With a standalone probe
-// (8 ranks, 4 trees, buffers in allocations of their own, three sets in turn; us for
-// ways 1 / 2): 64 MiB per rank 182 / 163, 114 MiB 324 / 294, 400 MiB 1119 / 1042, but
-// 256 MiB, where the shares are a power of two apart, 658 / 691.  So the first calls on
+// Which is fastest depends on where the buffers lie in HBM, how far apart the trees' shares are and whether a call finds
+// its buffers where the one before it left them, in ways addresses do not reveal.  us for ways 1 / 2 / 3, three sets of
+// buffers in turn, and repeated in place:
+//   8 ranks x  40 MiB   114 / 109 / 111    94 /  94 /  94      6 ranks x  98 MiB   205 / 191 / 199   187 / 189 / 182
+//              64 MiB   180 / 167 / 173   161 / 169 / 162                400 MiB   791 / 770 / 783   769 / 763 / 764
+//             114 MiB   318 / 298 / 313   303 / 305 / 299      5 ranks x  98 MiB   168 / 163 / 167   147 / 145 / 147
+//             230 MiB   648 / 607 / 634   630 / 604 / 607                400 MiB   713 / 662 / 700   683 / 675 / 684
+//             256 MiB   673 / 747 / 879   665 / 695 / 722      4 ranks x 500 MiB   679 / 639 / 667   655 / 640 / 652
+//             400 MiB  1084 /1071 /1102  1147 /1093 /1178      two servers of 8, 64 MiB  347 / 336 / -   331 / 338 / -
+// (256 MiB: the shares are a power of two apart.)  So the first calls on
 // such a schedule go round the candidates, kTrialSamples times each, each call timed
 // with a pair of events on the caller's stream; the next call waits for the last of
 // them (the one time a call waits for the device, besides a schedule's first) and
@@ -17,11 +22,11 @@
 // bits.
 //
 // Only like calls are compared: sums, whose time does not depend on the element type (8 x
-// 64 MiB, way 1, fp32 / int32: 184.1 / 184.3 us), and the other operators on either type
-// (largest value: 189.3 / 182.8) each have a round of their own, and the first round that is
+// 64 MiB, way 1, fp32 / int32: 176 / 178 us), and the other operators on either type, which have kernels of their
+// own (largest value: 177 / 177), each have a round of their own, and the first round that is
 // complete decides for all.  Timed calls go to and fro like all others, so each starts on what
 // the call before it left in the memory-side cache; that call was of another way.  (Timed
-// all forwards, on cold data, 8 x 256 MiB in allocations of their own chose way 2: repeated in
+// all forwards, on cold data, 8 x 256 MiB in allocations of their own chose way 2 with the kernel before this one: repeated in
 // place 748 us a call, against 705 with way 1, which gains by what the call before it left.)
 // No HIP in here.
 #pragma once
@@ -59,10 +64,9 @@ inline int timed_way(const WayTrial& t, const Ways& w, int cls) {
 }
 
 // Way 2, or way 1 where there is none, gets the schedule unless another beats it by more
-// than the 2 % by which such minima scatter from one trial to the next: it is the fastest
-// or within 1 % of it on most shapes (three sets of buffers in turn, us for ways 1 / 2 / 3:
-// two servers of 8 x 64 MiB 344 / 336 / -, 6 ranks x 97.6 MiB 209 / 196 / 204, 8 x 230 MiB
-// 664 / 614 / 634; the other way round 8 x 256 MiB 717 / 735 / 786).
+// than the 2 % by which such minima scatter from one trial to the next: on changing buffers it is 1 to 8 % ahead
+// on all shapes above but the one of shares a power of two apart; in place it is the fastest or level on half of them and
+// 2 to 5 % behind on the others, which the timed calls show.
 // ms: the times of a class's calls in the order of their launch.  Each candidate's first is
 // left out: it carries what happens once (the code's first launch, tables not yet in any
 // cache).  Kernels of a tenth of a millisecond differ by a few percent, which is also

@@ -1,4 +1,4 @@
-"""The ways in which a whole-tree program can be served at streaming size (tile by tile
+"""The ways in which a whole-tree program can be served at streaming size (in short turns
 across the trees, one front through the payload, chunk by chunk across the trees), each
 forced in turn, and the automatic choice among them: all against the oracle, bit for bit.
 Sizes are large enough that the schedules stream (smaller payloads get a workgroup for
