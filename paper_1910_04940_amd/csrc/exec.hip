@@ -1,7 +1,7 @@
 // The launcher of the two kernels (kernel.hpp: stages that wait for one another;
 // fold.hpp: the others): the device block of a schedule (status record, progress
 // counters, tables), the launch plan, the launch and its bookkeeping.
-#include "fold.hpp"
+#include "fold_once.hpp"
 
 #include <atomic>
 #include <mutex>
@@ -199,6 +199,7 @@ void plan_hand_over(blink_schedule* h) {
 constexpr unsigned kFoldTicketBytes = 56 * 1024;
 constexpr unsigned kFoldRunElems = 32 * 1024;
 constexpr uint64_t kFoldSmallBytesPerCu = 5 * 128 * 1024;
+constexpr uint64_t kOnceHalfBytesPerCu = 3 * 128 * 1024;   // up to here half tiles in the kernel that does nothing else (see kLdsOfFew)
 constexpr unsigned kFoldHalfTilesPerCu = 2;   // up to here half tiles are faster (see fold_columns)
 
 FoldTile fold_tile(const LaunchPlan& pl) { return pl.half ? FoldTile::kHalf : pl.small ? FoldTile::kWhole : FoldTile::kDrawn; }
@@ -229,6 +230,8 @@ void plan_fold(blink_schedule* h) {
     pl.tile_elems = tile;
     pl.grid_shift = 0;
     pl.n_items = fold_levels(h->fold.flows, tile, 0, !words_inline(*h), &h->fold.levels);
+    pl.once = pl.small && pl.all && !pl.mid && h->tile_override == 0 && h->fold.flows.size() <= kOnceMostFlows && once_fits(s.n, h->fold.flows);
+    pl.once_half = pl.kernel_bytes <= kOnceHalfBytesPerCu * cus;
 }
 
 blink_status_t make_plan(blink_schedule* h) {
@@ -394,7 +397,7 @@ namespace {
 // launch that failed must not consume a call number or move the ticket bases
 // (the next call would wait for tiles that nobody ever counted).  timed: the events to
 // record around it.
-blink_status_t launch(blink_schedule* h, const void* fn, unsigned grid, unsigned threads, void* params, hipStream_t stream,
+blink_status_t launch(blink_schedule* h, const void* fn, dim3 grid, unsigned threads, void* params, hipStream_t stream,
                       Timed timed) {
     if (timed.index >= 0 && hipEventRecord(trial_event(h, timed, 0), stream) != hipSuccess) {
         (void)hipGetLastError();  // e.g. a capturing stream: give the trial up
@@ -402,7 +405,7 @@ blink_status_t launch(blink_schedule* h, const void* fn, unsigned grid, unsigned
         timed = Timed();
     }
     void* args[] = {params};
-    const hipError_t launched = hipLaunchKernel(fn, dim3(grid), dim3(threads), args, 0, stream);
+    const hipError_t launched = hipLaunchKernel(fn, grid, dim3(threads), args, 0, stream);
     if (launched != hipSuccess) {
         std::fprintf(stderr, "blink: kernel launch failed: %s\n", hipGetErrorString(launched));
         (void)hipGetLastError();  // the failed launch's error is reported here, not left for later calls
@@ -416,7 +419,7 @@ blink_status_t launch(blink_schedule* h, const void* fn, unsigned grid, unsigned
             pick(h, 1);
         }
     }
-    h->last_grid = grid;
+    h->last_grid = grid.x * grid.y;
     return BLINK_OK;
 }
 
@@ -445,6 +448,28 @@ FoldFn pick_fold(blink_dtype_t dtype, bool sum, const LaunchPlan& pl, int policy
     return sum ? fold_i32_sum(n, pl.all, tile, stream) : fold_i32_other(n, pl.all, tile);
 }
 
+// A call on the fold kernel for a workgroup per tile.
+blink_status_t run_once(blink_schedule* h, void* const* bufs, blink_dtype_t dtype, blink_redop_t redop, hipStream_t stream,
+                        uint32_t grid_shift) {
+    LaunchPlan& pl = h->plan;
+    const std::vector<FoldFlow>& flows = h->fold.flows;
+    const int n = static_cast<int>(pl.n_load);
+    if (pl.once_shift != grid_shift) {
+        const unsigned most = fold_sub_elems(fold_columns(n, true, pl.once_half ? FoldTile::kHalf : FoldTile::kWhole));
+        pl.once_grid = once_grid(flows, most, grid_shift, static_cast<uint32_t>(h->n_cu));
+        pl.once_shift = grid_shift;
+    }
+    const OnceGrid& g = pl.once_grid;
+    const bool many = flows.size() > kInlineFlows;
+    const auto pick = dtype == BLINK_FP32 ? (redop == BLINK_SUM ? once_f32_sum : once_f32_other)
+                                          : (redop == BLINK_SUM ? once_i32_sum : once_i32_other);
+    const OnceKernel kernel = pick(n, pl.once_half, many);
+    if (!kernel.fn) return BLINK_EINVAL;
+    alignas(16) unsigned char params[kOnceParamsBytes];
+    kernel.fill({flows.data(), static_cast<unsigned>(flows.size()), grid_shift, g.tiles, g.tile_elems, static_cast<unsigned>(redop), bufs}, params);
+    return launch(h, kernel.fn, dim3(g.columns, static_cast<unsigned>(flows.size())), kFoldThreads, params, stream, Timed());
+}
+
 // A call on the fold kernel.  block: the static block, or null for the schedule's own, which is only made where tickets are drawn or the tables
 // do not travel with the launch.
 blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtype, blink_redop_t redop, hipStream_t stream,
@@ -462,6 +487,14 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     for (int i = 1; i < s.k; ++i) common = common && (reinterpret_cast<uintptr_t>(bufs[i]) & 1023u) == past;
     if (common) grid_shift = static_cast<uint32_t>(past / 4);
     const FoldTables& t = h->fold;
+    if (pl.once && h->wg_per_cu == 0) {
+        if (static_block) h->static_record = false;
+        if (blink_status_t st = run_once(h, bufs, dtype, redop, stream, grid_shift)) return st;
+        h->last_kernel = 1;
+        h->handed_over = 0;
+        if (!static_block) h->epoch += 1;
+        return BLINK_OK;
+    }
     if (words_inline(*h) && grid_shift != pl.grid_shift) {
         pl.n_items = fold_levels(t.flows, pl.tile_elems, grid_shift, false, &h->fold.levels);
         pl.grid_shift = grid_shift;
@@ -544,7 +577,7 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     p.two = two;
     p.width = two ? grid / 2 : grid;
     p.call = static_block ? 1 : static_cast<unsigned>(h->epoch + 1);
-    if (blink_status_t st = launch(h, reinterpret_cast<const void*>(fn), grid, kFoldThreads, &p, stream, timed)) return st;
+    if (blink_status_t st = launch(h, reinterpret_cast<const void*>(fn), dim3(grid), kFoldThreads, &p, stream, timed)) return st;
     h->last_kernel = way;
     h->handed_over = 0;
     if (static_block) return BLINK_OK;
@@ -610,7 +643,7 @@ blink_status_t run_hand_over(blink_schedule* h, void* const* bufs, blink_dtype_t
         h->static_record = true;
         if (blink_status_t st = launch_clear(block, l.counters_end, stream)) return st;
     }
-    if (blink_status_t st = launch(h, reinterpret_cast<const void*>(fn), static_cast<unsigned>(grid), kLanes, &p, stream, Timed())) return st;
+    if (blink_status_t st = launch(h, reinterpret_cast<const void*>(fn), dim3(static_cast<unsigned>(grid)), kLanes, &p, stream, Timed())) return st;
     h->last_kernel = 1;
     h->handed_over = 1;
     if (static_block) return BLINK_OK;

@@ -1,0 +1,8 @@
+// Instantiations of the fold kernel for a workgroup per tile: products, minima and maxima of fp32 elements.  See fold_once.hpp.
+#include "fold_once.hpp"
+
+namespace blink {
+
+OnceKernel once_f32_other(int n, bool half, bool many) { return pick_once<float, false>(n, half, many); }
+
+}  // namespace blink

@@ -1,0 +1,8 @@
+// Instantiations of the fold kernel for a workgroup per tile: sums of fp32 elements.  See fold_once.hpp.
+#include "fold_once.hpp"
+
+namespace blink {
+
+OnceKernel once_f32_sum(int n, bool half, bool many) { return pick_once<float, true>(n, half, many); }
+
+}  // namespace blink

@@ -131,6 +131,71 @@ inline uint32_t fold_tiles(uint64_t off, uint64_t len, uint32_t tile_elems, uint
     return static_cast<uint32_t>((((off + grid_shift) & 255u) + len + tile_elems - 1) / tile_elems);
 }
 
+// The grid of the kernel that has a workgroup for every tile and does nothing else (fold_once.hpp): a row per flow, a
+// column per tile of the longest, and one more column where some flow begins or ends within a 16-byte column of memory.
+struct OnceGrid {
+    uint32_t tile_elems, tiles, columns;
+};
+// Tiles are as small as they can be without a workgroup more on any CU than tiles of `most` elements would give it (a CU
+// that has one tile more than the others decides when the call ends): 3 ranks x 3.2 MiB, 270 tiles of 12 KiB, 4.45 us, 512
+// of 6.3 KiB 3.97; 6 ranks x 2.1 MiB 5.46 / 4.75; 4 ranks x 4.7 MiB 7.05 / 6.45; 8 ranks x 2.4 MiB 7.28 / 6.47.  In steps of
+// 256 bytes (steps of 1 KiB: 6.47 -> 7.25, steps of less split what a channel holds together).
+constexpr uint32_t kOnceTileStep = 64;   // elements
+inline OnceGrid once_grid(const std::vector<FoldFlow>& flows, uint32_t most, uint32_t grid_shift, uint32_t cus) {
+    const auto count = [&](uint32_t tile) {
+        uint64_t c = 0;
+        for (const FoldFlow& f : flows) c += fold_tiles(f.off, f.len, tile, grid_shift);
+        return c;
+    };
+    const uint64_t budget = (count(most) + cus - 1) / cus * cus;
+    uint32_t low = 1, high = most / kOnceTileStep;   // in steps: the smallest that keeps the budget
+    while (low < high) {
+        const uint32_t mid = (low + high) / 2;
+        if (count(mid * kOnceTileStep) <= budget) high = mid; else low = mid + 1;
+    }
+    OnceGrid g{high * kOnceTileStep, 0, 0};
+    bool ragged = false;
+    for (const FoldFlow& f : flows) {
+        g.tiles = std::max(g.tiles, fold_tiles(f.off, f.len, g.tile_elems, grid_shift));
+        ragged = ragged || (f.off & 3u) || ((f.off + f.len) & 3u);
+    }
+    g.columns = g.tiles + (ragged ? 1u : 0u);
+    return g;
+}
+// What a workgroup of that kernel has: byte offsets from the start of every rank buffer.
+struct OnceRange {
+    int32_t origin;        // where the flow's tile 0 starts on the tile grid (see fold_range): a multiple of 16
+    int32_t first, last;   // the flow's whole 16-byte columns (none where first >= last)
+    int32_t begin, end;    // all of it
+};
+inline OnceRange once_range(uint64_t off, uint64_t len, uint32_t grid_shift) {
+    const uint32_t o = static_cast<uint32_t>(off), e = o + static_cast<uint32_t>(len);
+    return {static_cast<int32_t>((o - ((o + grid_shift) & 255u)) * 4u), static_cast<int32_t>(((o + 3) & ~3u) * 4u),
+            static_cast<int32_t>((e & ~3u) * 4u), static_cast<int32_t>(o * 4u), static_cast<int32_t>(e * 4u)};
+}
+// The columns of tile x, [*from, *to); none where *from >= *to.
+BLINK_HOST_DEVICE inline void once_tile(const OnceRange& r, uint32_t x, int32_t tile_bytes, int32_t* from, int32_t* to) {
+    const int32_t tile = r.origin + static_cast<int32_t>(x) * tile_bytes;
+    *from = tile > r.first ? tile : r.first;
+    *to = tile + tile_bytes < r.last ? tile + tile_bytes : r.last;
+}
+// The element outside the whole columns that lane 0 to 7 moves (up to three at either end of a flow), or an offset
+// outside every window.
+constexpr int32_t kOnceNowhere = 0x7ffffff0;
+BLINK_HOST_DEVICE inline int32_t once_edge(const OnceRange& r, int32_t lane) {
+    const int32_t head_end = r.first < r.end ? r.first : r.end, tail = r.last > head_end ? r.last : head_end;
+    const int32_t e = lane < 4 ? r.begin + lane * 4 : tail + (lane - 4) * 4;
+    return lane < 8 && e < (lane < 4 ? head_end : r.end) ? e : kOnceNowhere;
+}
+// It can run a payload whose byte offsets, tile grid included, fit 31 bits.  Flows may differ in length: columns that
+// only the longest has are empty workgroups elsewhere, which end at once; where they would outnumber the others the
+// general kernel is used.
+inline bool once_fits(uint64_t n, const std::vector<FoldFlow>& flows) {
+    uint64_t longest = 0;
+    for (const FoldFlow& f : flows) longest = std::max(longest, f.len);
+    return n < (1ull << 29) - 65536 && longest * flows.size() <= 2 * n;
+}
+
 // The flows of a schedule, longest first.  False where the fold kernel cannot run them
 // (no program is like that): flows that read different numbers of ranks, that read
 // several and write neither one nor as many, or whose stack program is missing or

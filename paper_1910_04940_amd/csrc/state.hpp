@@ -24,6 +24,10 @@ struct LaunchPlan {
     bool fold = false;
     bool small = false;            // a workgroup for every tile
     bool half = false;             // tiles of half the size (where small)
+    bool once = false;             // by the kernel that does nothing else (fold_once.hpp)
+    bool once_half = false;        // there: tiles of half the size
+    OnceGrid once_grid{};          // made for once_shift
+    uint32_t once_shift = ~0u;
     bool all = false;              // every stage writes all the ranks it reads
     bool mid = false;              // partial sums are written on the way
     uint32_t n_load = 0;           // ranks a stage reads

@@ -1,0 +1,72 @@
+"""The kernel with a workgroup for every tile: payloads around the lines where its tiles change (half and
+whole ones, a few elements, a workgroup more on some compute unit), shares of different length, up to
+four flows, up to sixteen and more, buffers off the 1 KiB grid, every operator.  Bit for bit against
+the oracle, nothing written beside the buffers."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+from oracle import execute as ox
+
+from test_gpu_fold import REDOPS, _slab, _stream, _tree
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_1910_04940_amd as bl  # noqa: E402
+
+CODES = {"fp32": bl.BLINK_FP32, "int32": bl.BLINK_INT32}
+
+
+def _forest(k, weights):
+    forest = [_tree(k, s) for s in range(len(weights))]
+    roots, parents = [r for r, _ in forest], [p for _, p in forest]
+    return bl.blink_trees_from_arrays(k, roots, parents, weights), roots, parents
+
+
+# equal and unequal shares in the small and in the large arguments, one flow more than these hold, and
+# shares so unequal that the general kernel serves
+@pytest.mark.parametrize("weights", [[1.0], [1.0, 2.0, 3.0], [1.0] * 4, [1.0] * 5, [1.0 + t for t in range(16)], [1.0] * 17,
+                                     [1.0, 1.0, 1.0, 40.0]], ids=lambda w: f"{len(w)} trees, {w[-1]:g}")
+@pytest.mark.parametrize("k,op,dtype", [(2, "sum", "fp32"), (3, "max", "fp32"), (4, "sum", "fp32"), (5, "min", "int32"),
+                                        (8, "sum", "int32"), (9, "prod", "fp32"), (16, "sum", "fp32")])
+def test_shares(k, op, dtype, weights):
+    stream = _stream()
+    trees, roots, parents = _forest(k, weights)
+    code, oracle_op = REDOPS[op]
+    # traffic of 96 and 160 MiB is where half tiles, and a workgroup per tile, end on 256 compute units
+    half, small = 96 * 2**20 // (8 * k), 160 * 2**20 // (8 * k)
+    for n in (7, 1_027, 65_539, half - 5, half + 4_099, small - 2_047):
+        x = [si.hash_payload(83, r, 0, n, dtype) for r in range(k)]
+        want = ox.tree_order_allreduce(x, roots, parents, weights, oracle_op)
+        bufs, untouched = _slab(x)
+        sched = bl.blink_make_schedule(trees, bl.BLINK_OP_ALLREDUCE, n, 1 << 16, bl.BLINK_FUSE_TREE)
+        bl.blink_allreduce_op(bufs, n, CODES[dtype], code, sched, stream)
+        torch.cuda.synchronize()
+        for r in {0, k // 2, k - 1}:
+            assert bufs[r].cpu().numpy().tobytes() == want.tobytes(), (n, r)
+        assert untouched()
+
+
+@pytest.mark.parametrize("past", [(16,) * 5, (528,) * 5, (1008,) * 5, (0, 16, 512, 1008, 64)])
+def test_buffers_off_the_grid(past):
+    """One schedule, called on buffers at different distances from a 1 KiB boundary."""
+    stream = _stream()
+    k, n = 5, 300_007
+    trees, roots, parents = _forest(k, [1.0, 1.0])
+    x = [si.hash_payload(89, r, 0, n, "int32") for r in range(k)]
+    want = ox.allreduce_int32_definition(x)
+    sched = bl.blink_make_schedule(trees, bl.BLINK_OP_ALLREDUCE, n, 1 << 16, bl.BLINK_FUSE_TREE)
+    for at in ((0,) * k, past, (0,) * k):
+        step = (n + 1024) // 256 * 256 + 256
+        whole = torch.zeros(k * step + 512, dtype=torch.int32, device="cuda")
+        slab = whole[-whole.data_ptr() // 4 % 256:]
+        bufs = [slab[r * step + at[r] // 4:][:n] for r in range(k)]
+        for b, a in zip(bufs, x):
+            b.copy_(torch.from_numpy(a))
+        bl.blink_allreduce(bufs, n, bl.BLINK_INT32, sched, stream)
+        torch.cuda.synchronize()
+        assert all(np.array_equal(b.cpu().numpy(), want) for b in bufs)
+        for b in bufs:
+            b.zero_()
+        assert int(torch.count_nonzero(whole)) == 0
