@@ -230,7 +230,7 @@ void plan_fold(blink_schedule* h) {
     pl.tile_elems = tile;
     pl.grid_shift = 0;
     pl.n_items = fold_levels(h->fold.flows, tile, 0, !words_inline(*h), &h->fold.levels);
-    pl.once = pl.small && pl.all && !pl.mid && h->tile_override == 0 && h->fold.flows.size() <= kOnceMostFlows && once_fits(s.n, h->fold.flows);
+    pl.once = pl.small && pl.all && !pl.mid && h->tile_override == 0 && !h->fold.once.empty();
     pl.once_half = pl.kernel_bytes <= kOnceHalfBytesPerCu * cus;
 }
 
@@ -452,7 +452,7 @@ FoldFn pick_fold(blink_dtype_t dtype, bool sum, const LaunchPlan& pl, int policy
 blink_status_t run_once(blink_schedule* h, void* const* bufs, blink_dtype_t dtype, blink_redop_t redop, hipStream_t stream,
                         uint32_t grid_shift) {
     LaunchPlan& pl = h->plan;
-    const std::vector<FoldFlow>& flows = h->fold.flows;
+    const std::vector<FoldFlow>& flows = h->fold.once;
     const int n = static_cast<int>(pl.n_load);
     if (pl.once_shift != grid_shift) {
         const unsigned most = fold_sub_elems(fold_columns(n, true, pl.once_half ? FoldTile::kHalf : FoldTile::kWhole));
@@ -460,13 +460,14 @@ blink_status_t run_once(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
         pl.once_shift = grid_shift;
     }
     const OnceGrid& g = pl.once_grid;
-    const bool many = flows.size() > kInlineFlows;
+    const bool many = flows.size() > kOnceFewFlows;
     const auto pick = dtype == BLINK_FP32 ? (redop == BLINK_SUM ? once_f32_sum : once_f32_other)
                                           : (redop == BLINK_SUM ? once_i32_sum : once_i32_other);
     const OnceKernel kernel = pick(n, pl.once_half, many);
     if (!kernel.fn) return BLINK_EINVAL;
     alignas(16) unsigned char params[kOnceParamsBytes];
-    kernel.fill({flows.data(), static_cast<unsigned>(flows.size()), grid_shift, g.tiles, g.tile_elems, static_cast<unsigned>(redop), bufs}, params);
+    const uint32_t call = once_call(g.tile_elems, grid_shift, static_cast<uint32_t>(redop), g.tiles);
+    kernel.fill({flows.data(), static_cast<unsigned>(flows.size()), static_cast<unsigned>(h->s.n), call, bufs}, params);
     return launch(h, kernel.fn, dim3(g.columns, static_cast<unsigned>(flows.size())), kFoldThreads, params, stream, Timed());
 }
 

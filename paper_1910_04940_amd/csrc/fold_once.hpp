@@ -4,9 +4,8 @@
 // Such a call is bound by the latency of one pass: arguments, rank data, stores.  What lies in
 // front of the loads counts in full, and so does the length of the code, which every call
 // fetches anew (1.5 to 3 KB here, 5 to 9 KB in fold.hpp).  So the place in the grid says which flow (y) and
-// which of its tiles (x) a workgroup has, the arguments hold each flow's buffers in the order in
-// which its stack program consumes them, and one round of scalar loads stands between a wave's
-// start and its rank loads: no tickets, no levels, no loop.
+// which of its tiles (x) a workgroup has, two rounds of scalar loads, the second from
+// lines that the first has fetched, stand between a wave's start and its rank loads: no tickets, no levels, no loop.
 //
 // us per call, one after the other in a graph on three sets of buffers in turn, blink_fold / this kernel
 // (sums, int32): 8 ranks x 16 KiB 2.84 / 2.2, 64 KiB and a ragged end 3.48 / 2.5, 1 MiB 3.97 / 3.2, 2 MiB
@@ -21,38 +20,36 @@
 
 namespace blink {
 
-// At most this many flows travel in the arguments of the larger of two variants (those of the
-// other hold kInlineFlows); copying them takes the host 0.04 us per 100 bytes.
-constexpr int kOnceMostFlows = 16;
-
 // Where whole tiles are handed out (the upper two fifths of the range) two workgroups at a time run on a CU, by the LDS
 // they ask for: more loads in flight spread the requests out.  Against as many as fit, us: 8 ranks x 9.5 MiB 24.9 / 22.9,
 // 8.8 MiB 20.8 / 19.2, 4 ranks x 16 MiB 20.3 / 18.3; half tiles there 24.1, 19.5, 17.9.
 constexpr int kLdsOfFew = 56 * 1024;
 
-// A flow as a workgroup needs it.
-template <int N>
-struct OnceFlow {
-    OnceRange range;
-    unsigned code[(N + 7) / 8];  // a nibble per rank in the order of consumption: push | folds << 1
-    void* buf[N];                // the ranks' buffers in that order
-};
+// The arguments are short: a launch with at most 112 bytes of them takes the host less time (C call on one host, 3 to 7
+// ranks 3.0 us, 8 ranks with 120 bytes 3.7, with 370 or more 3.8 to 4; on another host 2.24 up to 112 bytes, 2.30 beyond).
+// So a buffer's address is one more scalar load away, from a line that is there by then, a flow's program is packed as tightly as
+// that takes for 8 ranks, and there are two variants, for few flows and for many (kOnceMostFlows).
+constexpr int kOnceFewFlows = 4;
+// Flow f's program: the ranks in the order of consumption, and for each push | folds << 1.  Up to 4 ranks: word f, four
+// bits per rank, the codes from bit 16 on.  Up to 8: word f, three bits per rank, the low byte of the codes from bit 24
+// on; the other two, three bits per code, are a half of word F + f / 2.  More: words 4 f and 4 f + 1, four bits per rank, and
+// the codes in the next two.
+constexpr int once_words(int n, int flows) { return n <= 4 ? flows : n <= 8 ? flows + (flows + 1) / 2 : 4 * flows; }
 template <int N, int F>
 struct OnceParams {
-    OnceFlow<N> flow[F];
-    unsigned edge_column;    // the column of the grid (x) that moves what fills no 16-byte column of memory
-    unsigned redop;          // blink_redop_t
-    int tile_bytes;          // of a rank: at most what the workgroup's columns hold
+    void* buf[N];
+    unsigned begin[F + 1];    // flow f: elements [begin[f], begin[f + 1])
+    unsigned word[once_words(N, F)];
+    unsigned call;            // see once_call
 };
+static_assert(sizeof(OnceParams<8, kOnceFewFlows>) <= 112, "see above");
 
-// What the host passes on (see fill_once): the same, before the number of ranks is a constant.
+// What the host passes on (see fill_once), before the number of ranks is a constant.
 struct OnceCall {
-    const FoldFlow* flows;
+    const FoldFlow* flows;   // in payload order, each beginning where the one before it ends
     unsigned n_flows;
-    unsigned grid_shift;     // see fold_range
-    unsigned tiles;          // of the longest flow
-    unsigned tile_elems;
-    unsigned redop;
+    unsigned n;              // elements
+    unsigned call;           // see once_call
     void* const* bufs;
 };
 
@@ -64,26 +61,33 @@ __global__ __launch_bounds__(kFoldThreads) void blink_once(const OnceParams<N, F
     constexpr int kLdsBytes = FEW ? std::max(kParkedBytes, kLdsOfFew) : std::max(kParkedBytes, 16);
     __shared__ U4 parked[kLdsBytes / 16];
     const BLINK_CONST OnceParams<N, F>* p = (const BLINK_CONST OnceParams<N, F>*)__builtin_amdgcn_kernarg_segment_ptr();
-    const BLINK_CONST OnceFlow<N>* fl = p->flow + blockIdx.y;
+    const unsigned f = blockIdx.y, call = p->call;
     if constexpr (FEW && kParked == 0) asm volatile("" ::"v"(parked));   // (otherwise nothing uses the LDS)
-    const int tile_bytes = p->tile_bytes;
-    const unsigned edge_column = p->edge_column, redop = SUM ? static_cast<unsigned>(BLINK_SUM) : p->redop;
-    const OnceRange range = {fl->range.origin, fl->range.first, fl->range.last, fl->range.begin, fl->range.end};
-    unsigned code[(N + 7) / 8];
+    unsigned order[(N + 7) / 8], codes[(N + 7) / 8];
+    if constexpr (N <= 4) {
+        order[0] = p->word[f];
+    } else if constexpr (N <= 8) {
+        order[0] = p->word[f], codes[0] = p->word[F + f / 2];
+    } else {
+        order[0] = p->word[4 * f], order[1] = p->word[4 * f + 1], codes[0] = p->word[4 * f + 2], codes[1] = p->word[4 * f + 3];
+    }
+    const unsigned begin = p->begin[f], end = p->begin[f + 1];
+    asm volatile("" ::"s"(begin), "s"(end), "s"(order[0]), "s"(call), "s"(p->buf[0]), "s"(p->buf[N - 1]));   // all of them with one wait
+    constexpr int kBits = N > 4 && N <= 8 ? 3 : 4;
+    if constexpr (N <= 4) codes[0] = order[0] >> 16;
+    else if constexpr (N <= 8) codes[0] = order[0] >> 24 | (codes[0] >> (f & 1) * 16 & 0xffffu) << 8;
+    auto rank = [&](int i) { return order[i / 8] >> (i % 8 * kBits) & ((1u << kBits) - 1); };
+    auto push = [&](int i) { return codes[i / 8] >> (i % 8 * kBits) & 1u; };
+    auto folds = [&](int i) { return codes[i / 8] >> (i % 8 * kBits + 1) & ((1u << (kBits - 1)) - 1); };
     char* buf[N];
 #pragma unroll
-    for (int q = 0; q < (N + 7) / 8; ++q) code[q] = fl->code[q];
-#pragma unroll
-    for (int i = 0; i < N; ++i) buf[i] = static_cast<char*>(fl->buf[i]);
-    // all of them with one wait
-    asm volatile("" ::"s"(edge_column), "s"(tile_bytes), "s"(redop), "s"(range.origin), "s"(range.first),
-                 "s"(range.last), "s"(code[0]), "s"(buf[0]), "s"(buf[N - 1]));
-    auto push = [&](int i) { return (code[i / 8] >> (i % 8 * 4)) & 1u; };
-    auto folds = [&](int i) { return (code[i / 8] >> (i % 8 * 4 + 1)) & 7u; };
+    for (int i = 0; i < N; ++i) buf[i] = static_cast<char*>(p->buf[rank(i)]);
+    const unsigned redop = SUM ? static_cast<unsigned>(BLINK_SUM) : once_redop(call);
+    const OnceRange range = once_range(begin, end - begin, once_shift(call));
     const int lane = threadIdx.x & (kLanes - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
 
-    if (blockIdx.x == edge_column) {
+    if (blockIdx.x == once_edges(call)) {
         // up to three elements at either end of the flow, one per lane of one wave
         if (wave != 0) return;
         const int at = once_edge(range, lane);   // (past the window: nothing happens)
@@ -114,7 +118,7 @@ __global__ __launch_bounds__(kFoldThreads) void blink_once(const OnceParams<N, F
     }
 
     int from, to;
-    once_tile(range, blockIdx.x, tile_bytes, &from, &to);
+    once_tile(range, blockIdx.x, static_cast<int>(once_tile_elems(call) * 4), &from, &to);
     if (from >= to) return;   // flows need not be equally long
     const int column = from + (wave * U * kLanes + lane) * 16;   // columns past `to` fall outside the windows
     U4 r[N][U];
@@ -161,19 +165,31 @@ __global__ __launch_bounds__(kFoldThreads) void blink_once(const OnceParams<N, F
 template <int N, int F>
 void fill_once(const OnceCall& c, void* to) {
     OnceParams<N, F>& p = *static_cast<OnceParams<N, F>*>(to);
+    constexpr int kBits = N > 4 && N <= 8 ? 3 : 4;
+    for (int i = 0; i < N; ++i) p.buf[i] = c.bufs[i];
+    for (unsigned& w : p.word) w = 0;
     for (unsigned f = 0; f < c.n_flows; ++f) {
         const FoldFlow& fl = c.flows[f];
-        OnceFlow<N>& o = p.flow[f];
-        o.range = once_range(fl.off, fl.len, c.grid_shift);
-        for (unsigned& q : o.code) q = 0;
+        p.begin[f] = static_cast<unsigned>(fl.off);
+        uint64_t order = 0, codes = 0;
         for (int i = 0; i < N; ++i) {
-            o.code[i / 8] |= static_cast<unsigned>(fl.seq[i] >> 4) << (i % 8 * 4);
-            o.buf[i] = c.bufs[fl.seq[i] & 15];
+            order |= static_cast<uint64_t>(fl.seq[i] & 15u) << (i * kBits);
+            codes |= static_cast<uint64_t>(fl.seq[i] >> 4) << (i * kBits);
+        }
+        if (N <= 4) {
+            p.word[f] = static_cast<unsigned>(order | codes << 16);
+        } else if (N <= 8) {
+            p.word[f] = static_cast<unsigned>(order | codes << 24);
+            p.word[F + f / 2] |= static_cast<unsigned>(codes >> 8 << (f & 1) * 16);
+        } else {
+            for (int q = 0; q < 2; ++q) {
+                p.word[4 * f + q] = static_cast<unsigned>(order >> 32 * q);
+                p.word[4 * f + 2 + q] = static_cast<unsigned>(codes >> 32 * q);
+            }
         }
     }
-    p.edge_column = c.tiles;
-    p.redop = c.redop;
-    p.tile_bytes = static_cast<int>(c.tile_elems * 4);
+    p.begin[c.n_flows] = c.n;
+    p.call = c.call;
 }
 
 // A kernel and what fills its arguments.
@@ -184,13 +200,16 @@ struct OnceKernel {
 constexpr size_t kOnceParamsBytes = sizeof(OnceParams<BLINK_MAX_RANKS, kOnceMostFlows>);
 static_assert(kOnceParamsBytes <= 4096, "kernel arguments");
 
-template <typename T, bool SUM, FoldTile TILE, int F>
+template <typename T, bool SUM, FoldTile TILE, bool MANY>
 OnceKernel pick_once(int n) {
     switch (n) {
-#define BLINK_CASE(N)                                                                                                          \
-    case N:                                                                                                                    \
-        return {reinterpret_cast<const void*>(blink_once<T, N, F, SUM, fold_columns(N, true, TILE), TILE == FoldTile::kWhole>), \
-                fill_once<N, F>};
+#define BLINK_CASE(N)                                                                                                              \
+    case N: {                                                                                                                      \
+        constexpr int kFlows = MANY ? kOnceMostFlows : kOnceFewFlows;                                                          \
+        return {reinterpret_cast<const void*>(                                                                                     \
+                    blink_once<T, N, kFlows, SUM, fold_columns(N, true, TILE), TILE == FoldTile::kWhole>),                         \
+                fill_once<N, kFlows>};                                                                                             \
+    }
         BLINK_FOLD_CASES
 #undef BLINK_CASE
         default: return {};
@@ -198,10 +217,10 @@ OnceKernel pick_once(int n) {
 }
 template <typename T, bool SUM>
 OnceKernel pick_once(int n, bool half, bool many) {
-    if (half) return many ? pick_once<T, SUM, FoldTile::kHalf, kOnceMostFlows>(n) : pick_once<T, SUM, FoldTile::kHalf, kInlineFlows>(n);
-    return many ? pick_once<T, SUM, FoldTile::kWhole, kOnceMostFlows>(n) : pick_once<T, SUM, FoldTile::kWhole, kInlineFlows>(n);
+    if (half) return many ? pick_once<T, SUM, FoldTile::kHalf, true>(n) : pick_once<T, SUM, FoldTile::kHalf, false>(n);
+    return many ? pick_once<T, SUM, FoldTile::kWhole, true>(n) : pick_once<T, SUM, FoldTile::kWhole, false>(n);
 }
-// Stages that read n ranks and write them all; half: tiles of half the size; many: more than kInlineFlows flows.
+// Stages that read n ranks and write them all; half: tiles of half the size; many: more than kOnceFewFlows flows.
 OnceKernel once_f32_sum(int n, bool half, bool many);
 OnceKernel once_f32_other(int n, bool half, bool many);
 OnceKernel once_i32_sum(int n, bool half, bool many);

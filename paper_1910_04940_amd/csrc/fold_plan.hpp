@@ -141,6 +141,7 @@ struct OnceGrid {
 // of 6.3 KiB 3.97; 6 ranks x 2.1 MiB 5.46 / 4.75; 4 ranks x 4.7 MiB 7.05 / 6.45; 8 ranks x 2.4 MiB 7.28 / 6.47.  In steps of
 // 256 bytes (steps of 1 KiB: 6.47 -> 7.25, steps of less split what a channel holds together).
 constexpr uint32_t kOnceTileStep = 64;   // elements
+constexpr size_t kOnceMostFlows = 16;
 inline OnceGrid once_grid(const std::vector<FoldFlow>& flows, uint32_t most, uint32_t grid_shift, uint32_t cus) {
     const auto count = [&](uint32_t tile) {
         uint64_t c = 0;
@@ -168,8 +169,8 @@ struct OnceRange {
     int32_t first, last;   // the flow's whole 16-byte columns (none where first >= last)
     int32_t begin, end;    // all of it
 };
-inline OnceRange once_range(uint64_t off, uint64_t len, uint32_t grid_shift) {
-    const uint32_t o = static_cast<uint32_t>(off), e = o + static_cast<uint32_t>(len);
+BLINK_HOST_DEVICE inline OnceRange once_range(uint32_t o, uint32_t len, uint32_t grid_shift) {
+    const uint32_t e = o + len;
     return {static_cast<int32_t>((o - ((o + grid_shift) & 255u)) * 4u), static_cast<int32_t>(((o + 3) & ~3u) * 4u),
             static_cast<int32_t>((e & ~3u) * 4u), static_cast<int32_t>(o * 4u), static_cast<int32_t>(e * 4u)};
 }
@@ -187,13 +188,31 @@ BLINK_HOST_DEVICE inline int32_t once_edge(const OnceRange& r, int32_t lane) {
     const int32_t e = lane < 4 ? r.begin + lane * 4 : tail + (lane - 4) * 4;
     return lane < 8 && e < (lane < 4 ? head_end : r.end) ? e : kOnceNowhere;
 }
-// It can run a payload whose byte offsets, tile grid included, fit 31 bits.  Flows may differ in length: columns that
-// only the longest has are empty workgroups elsewhere, which end at once; where they would outnumber the others the
-// general kernel is used.
-inline bool once_fits(uint64_t n, const std::vector<FoldFlow>& flows) {
-    uint64_t longest = 0;
-    for (const FoldFlow& f : flows) longest = std::max(longest, f.len);
-    return n < (1ull << 29) - 65536 && longest * flows.size() <= 2 * n;
+// The rest of its arguments in one word: tile (in steps), grid_shift (in columns of 16 bytes), operator, and the column
+// of the grid that moves the elements outside whole columns (none: one past the grid).
+BLINK_HOST_DEVICE inline uint32_t once_call(uint32_t tile_elems, uint32_t grid_shift, uint32_t redop, uint32_t edges) {
+    return tile_elems / kOnceTileStep | grid_shift / 4u << 8 | redop << 14 | edges << 16;
+}
+BLINK_HOST_DEVICE inline uint32_t once_tile_elems(uint32_t call) { return (call & 255u) * kOnceTileStep; }
+BLINK_HOST_DEVICE inline uint32_t once_shift(uint32_t call) { return (call >> 8 & 63u) * 4u; }
+BLINK_HOST_DEVICE inline uint32_t once_redop(uint32_t call) { return call >> 14 & 3u; }
+BLINK_HOST_DEVICE inline uint32_t once_edges(uint32_t call) { return call >> 16; }
+
+// The flows as that kernel is given them, in payload order; none where it cannot run them: there are more than `most`, they
+// leave something out or overlap, a byte offset (tile grid included) does not fit 31 bits, or they
+// differ so much in length that workgroups without a tile (those beyond a shorter flow's end, which end at once) would
+// outnumber the others.
+constexpr uint64_t kOnceMostElems = (1ull << 29) - 65536;
+inline std::vector<FoldFlow> once_flows(std::vector<FoldFlow> flows, uint64_t n, size_t most) {
+    std::sort(flows.begin(), flows.end(), [](const FoldFlow& a, const FoldFlow& b) { return a.off < b.off; });
+    uint64_t at = 0, longest = 0;
+    for (const FoldFlow& f : flows) {
+        if (f.off != at) return {};
+        at += f.len;
+        longest = std::max(longest, f.len);
+    }
+    if (at != n || n >= kOnceMostElems || flows.size() > most || longest * flows.size() > 2 * n) return {};
+    return flows;
 }
 
 // The flows of a schedule, longest first.  False where the fold kernel cannot run them
@@ -365,6 +384,7 @@ static_assert((kLeastTileOverride << (kLevelSets - 2)) == kMostTileOverride, "a 
 struct FoldTables {
     bool fits = false;               // the kernel can run the schedule
     std::vector<FoldFlow> flows;
+    std::vector<FoldFlow> once;      // see once_flows
     std::vector<FoldLevel> levels;   // room for one per flow; filled by the launch plan
     // Tables on the device, copied as they are: fold_words with the number of flows as stride,
     // then the sets of levels, room for one level per flow in each.
@@ -383,6 +403,7 @@ struct FoldTables {
 inline void fold_tables(const Schedule& s, FoldTables* out) {
     out->fits = fold_flows(s, &out->flows);
     if (!out->fits) out->flows.clear();
+    out->once = once_flows(out->flows, s.n, kOnceMostFlows);
     out->levels.reserve(out->flows.size());
     out->tables.assign(FoldTables::words_per_flow() * out->flows.size(), 0);
     fold_words(out->flows, static_cast<uint32_t>(out->flows.size()), out->tables.data());

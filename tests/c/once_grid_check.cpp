@@ -25,8 +25,12 @@ int main(int argc, char** argv) {
         whole += blink::fold_tiles(f.off, f.len, most, shift);
     }
     std::printf("%u %u %u\n", g.tile_elems, busy, whole);
+    const uint32_t call = blink::once_call(g.tile_elems, shift, 3, g.tiles);
+    if (blink::once_tile_elems(call) != g.tile_elems || blink::once_shift(call) != shift || blink::once_redop(call) != 3 ||
+        blink::once_edges(call) != g.tiles)
+        return 5;
     for (size_t f = 0; f < flows.size(); ++f) {
-        const blink::OnceRange r = blink::once_range(flows[f].off, flows[f].len, shift);
+        const blink::OnceRange r = blink::once_range(static_cast<uint32_t>(flows[f].off), static_cast<uint32_t>(flows[f].len), shift);
         if (r.origin % 16) return 2;
         for (uint32_t x = 0; x < g.columns; ++x) {
             if (x == g.tiles) {
