@@ -4,6 +4,7 @@
 #include "fold_once.hpp"
 
 #include <atomic>
+#include <cstring>
 #include <mutex>
 
 namespace blink {
@@ -230,7 +231,9 @@ void plan_fold(blink_schedule* h) {
     pl.tile_elems = tile;
     pl.grid_shift = 0;
     pl.n_items = fold_levels(h->fold.flows, tile, 0, !words_inline(*h), &h->fold.levels);
-    pl.once = pl.small && pl.all && !pl.mid && h->tile_override == 0 && !h->fold.once.empty();
+    pl.once = pl.small && (pl.all || n == 1) && !pl.mid && h->tile_override == 0 && !h->fold.once.empty();
+    if (n == 1)
+        for (const FoldFlow& f : h->fold.once) pl.once_stores = std::max(pl.once_stores, __builtin_popcount(f.stores & 0xffffu));
     pl.once_half = pl.kernel_bytes <= kOnceHalfBytesPerCu * cus;
 }
 
@@ -455,20 +458,25 @@ blink_status_t run_once(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     const std::vector<FoldFlow>& flows = h->fold.once;
     const int n = static_cast<int>(pl.n_load);
     if (pl.once_shift != grid_shift) {
-        const unsigned most = fold_sub_elems(fold_columns(n, true, pl.once_half ? FoldTile::kHalf : FoldTile::kWhole));
-        pl.once_grid = once_grid(flows, most, grid_shift, static_cast<uint32_t>(h->n_cu));
+        const int columns = n == 1 ? once_copy_columns(pl.once_stores) : fold_columns(n, true, pl.once_half ? FoldTile::kHalf : FoldTile::kWhole);
+        pl.once_grid = once_grid(flows, fold_sub_elems(columns), grid_shift, static_cast<uint32_t>(h->n_cu));
         pl.once_shift = grid_shift;
     }
     const OnceGrid& g = pl.once_grid;
     const bool many = flows.size() > kOnceFewFlows;
     const auto pick = dtype == BLINK_FP32 ? (redop == BLINK_SUM ? once_f32_sum : once_f32_other)
                                           : (redop == BLINK_SUM ? once_i32_sum : once_i32_other);
-    const OnceKernel kernel = pick(n, pl.once_half, many);
+    const OnceKernel kernel = n == 1 ? once_copy(h->s.k, pl.once_stores, many) : pick(n, pl.once_half, many);
     if (!kernel.fn) return BLINK_EINVAL;
-    alignas(16) unsigned char params[kOnceParamsBytes];
+    if (!pl.once_filled) {
+        kernel.fill(flows, pl.once_params);   // the same for all element types and operators
+        pl.once_filled = true;
+    }
+    void** const buf = reinterpret_cast<void**>(pl.once_params);
+    for (int i = 0; i < kernel.bufs; ++i) buf[i] = bufs[std::min(i, h->s.k - 1)];
     const uint32_t call = once_call(g.tile_elems, grid_shift, static_cast<uint32_t>(redop), g.tiles);
-    kernel.fill({flows.data(), static_cast<unsigned>(flows.size()), static_cast<unsigned>(h->s.n), call, bufs}, params);
-    return launch(h, kernel.fn, dim3(g.columns, static_cast<unsigned>(flows.size())), kFoldThreads, params, stream, Timed());
+    std::memcpy(pl.once_params + kernel.call_at, &call, sizeof call);
+    return launch(h, kernel.fn, dim3(g.columns, static_cast<unsigned>(flows.size())), kFoldThreads, pl.once_params, stream, Timed());
 }
 
 // A call on the fold kernel.  block: the static block, or null for the schedule's own, which is only made where tickets are drawn or the tables

@@ -44,15 +44,6 @@ struct OnceParams {
 };
 static_assert(sizeof(OnceParams<8, kOnceFewFlows>) <= 112, "see above");
 
-// What the host passes on (see fill_once), before the number of ranks is a constant.
-struct OnceCall {
-    const FoldFlow* flows;   // in payload order, each beginning where the one before it ends
-    unsigned n_flows;
-    unsigned n;              // elements
-    unsigned call;           // see once_call
-    void* const* bufs;
-};
-
 // FEW: at most two workgroups at a time on a CU.
 template <typename T, int N, int F, bool SUM, int U, bool FEW>
 __global__ __launch_bounds__(kFoldThreads) void blink_once(const OnceParams<N, F>) {
@@ -162,14 +153,14 @@ __global__ __launch_bounds__(kFoldThreads) void blink_once(const OnceParams<N, F
     }
 }
 
+// What of the arguments is the same for all calls on a schedule: all but the buffers and `call`.
 template <int N, int F>
-void fill_once(const OnceCall& c, void* to) {
+void fill_once(const std::vector<FoldFlow>& flows, void* to) {
     OnceParams<N, F>& p = *static_cast<OnceParams<N, F>*>(to);
     constexpr int kBits = N > 4 && N <= 8 ? 3 : 4;
-    for (int i = 0; i < N; ++i) p.buf[i] = c.bufs[i];
     for (unsigned& w : p.word) w = 0;
-    for (unsigned f = 0; f < c.n_flows; ++f) {
-        const FoldFlow& fl = c.flows[f];
+    for (size_t f = 0; f < flows.size(); ++f) {
+        const FoldFlow& fl = flows[f];
         p.begin[f] = static_cast<unsigned>(fl.off);
         uint64_t order = 0, codes = 0;
         for (int i = 0; i < N; ++i) {
@@ -188,17 +179,93 @@ void fill_once(const OnceCall& c, void* to) {
             }
         }
     }
-    p.begin[c.n_flows] = c.n;
-    p.call = c.call;
+    p.begin[flows.size()] = static_cast<unsigned>(flows.back().off + flows.back().len);
 }
 
-// A kernel and what fills its arguments.
+// The same where one rank is read and copied to others, up to M of them; K: ranks whose buffers are in the arguments.
+// Flow f's program: four bits per rank, the source and then M destinations, the source again in the place of those it
+// does not have.
+template <int K, int F>
+struct OnceCopyParams {
+    void* buf[K];
+    unsigned begin[F + 1];
+    unsigned word[F * K / 8];
+    unsigned call;
+};
+static_assert(sizeof(OnceCopyParams<8, kOnceFewFlows>) <= 112, "see OnceParams");
+
+template <int K, int M, int F, int U>
+__global__ __launch_bounds__(kFoldThreads) void blink_once_copy(const OnceCopyParams<K, F>) {
+    // one load and M stores per column: what was read stays in the caches for its next reader, what is written streams;
+    // a copy to one rank like a sum (see FoldPolicyBits)
+    constexpr int kPolicy = M == 1 ? kFoldKeep : kFoldSpread;
+    constexpr int LD = FoldPolicyBits<kPolicy>::kLoad, ST = FoldPolicyBits<kPolicy>::kStore;
+    const BLINK_CONST OnceCopyParams<K, F>* p = (const BLINK_CONST OnceCopyParams<K, F>*)__builtin_amdgcn_kernarg_segment_ptr();
+    const unsigned f = blockIdx.y, call = p->call;
+    unsigned ranks[K / 8];
+#pragma unroll
+    for (int q = 0; q < K / 8; ++q) ranks[q] = p->word[f * (K / 8) + q];
+    const unsigned begin = p->begin[f], end = p->begin[f + 1];
+    asm volatile("" ::"s"(begin), "s"(end), "s"(ranks[0]), "s"(call), "s"(p->buf[0]), "s"(p->buf[K - 1]));   // all of them with one wait
+    auto rank = [&](int i) { return ranks[i / 8] >> (i % 8 * 4) & 15u; };
+    char* buf[M + 1];
+#pragma unroll
+    for (int i = 0; i <= M; ++i) buf[i] = static_cast<char*>(p->buf[rank(i)]);
+    if (rank(1) == rank(0)) return;   // nothing of this flow moves
+    const OnceRange range = once_range(begin, end - begin, once_shift(call));
+    const int lane = threadIdx.x & (kLanes - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+    if (blockIdx.x == once_edges(call)) {
+        if (wave != 0) return;
+        const int at = once_edge(range, lane);
+        const unsigned x = __builtin_amdgcn_raw_buffer_load_b32(__builtin_amdgcn_make_buffer_rsrc(buf[0], 0, range.end, kRawDword3), at, 0, LD);
+#pragma unroll
+        for (int i = 1; i <= M; ++i)
+            if (i == 1 || rank(i) != rank(0))
+                __builtin_amdgcn_raw_buffer_store_b32(x, __builtin_amdgcn_make_buffer_rsrc(buf[i], 0, range.end, kRawDword3), at, 0, ST);
+        return;
+    }
+    int from, to;
+    once_tile(range, blockIdx.x, static_cast<int>(once_tile_elems(call) * 4), &from, &to);
+    if (from >= to) return;
+    const int column = from + (wave * U * kLanes + lane) * 16;
+    U4 r[U];
+    const __amdgpu_buffer_rsrc_t source = __builtin_amdgcn_make_buffer_rsrc(buf[0], 0, to, kRawDword3);
+#pragma unroll
+    for (int u = 0; u < U; ++u) r[u] = __builtin_amdgcn_raw_buffer_load_b128(source, column + u * kLanes * 16, 0, LD);
+#pragma unroll
+    for (int i = 1; i <= M; ++i) {
+        if (i > 1 && rank(i) == rank(0)) continue;
+        const __amdgpu_buffer_rsrc_t win = __builtin_amdgcn_make_buffer_rsrc(buf[i], 0, to, kRawDword3);
+#pragma unroll
+        for (int u = 0; u < U; ++u) __builtin_amdgcn_raw_buffer_store_b128(r[u], win, column + u * kLanes * 16, 0, ST);
+    }
+}
+
+template <int K, int F>
+void fill_once_copy(const std::vector<FoldFlow>& flows, void* to) {
+    OnceCopyParams<K, F>& p = *static_cast<OnceCopyParams<K, F>*>(to);
+    for (size_t f = 0; f < flows.size(); ++f) {
+        const FoldFlow& fl = flows[f];
+        const unsigned source = fl.seq[0] & 15u;
+        p.begin[f] = static_cast<unsigned>(fl.off);
+        uint64_t ranks = 0x1111111111111111ull * source;
+        int i = 1;
+        for (unsigned left = fl.stores & 0xffffu; left; left &= left - 1, ++i)
+            ranks ^= static_cast<uint64_t>(static_cast<unsigned>(__builtin_ctz(left)) ^ source) << (i * 4);
+        for (int q = 0; q < K / 8; ++q) p.word[f * (K / 8) + q] = static_cast<unsigned>(ranks >> 32 * q);
+    }
+    p.begin[flows.size()] = static_cast<unsigned>(flows.back().off + flows.back().len);
+}
+
+// A kernel, what fills its arguments and where the call's own are: the buffers at the start, so many, and one word.
 struct OnceKernel {
     const void* fn = nullptr;
-    void (*fill)(const OnceCall&, void*) = nullptr;
+    void (*fill)(const std::vector<FoldFlow>&, void*) = nullptr;
+    int bufs = 0;
+    size_t call_at = 0;
 };
-constexpr size_t kOnceParamsBytes = sizeof(OnceParams<BLINK_MAX_RANKS, kOnceMostFlows>);
-static_assert(kOnceParamsBytes <= 4096, "kernel arguments");
+static_assert(sizeof(OnceParams<BLINK_MAX_RANKS, kOnceMostFlows>) <= kOnceParamsBytes, "the largest");
 
 template <typename T, bool SUM, FoldTile TILE, bool MANY>
 OnceKernel pick_once(int n) {
@@ -208,7 +275,7 @@ OnceKernel pick_once(int n) {
         constexpr int kFlows = MANY ? kOnceMostFlows : kOnceFewFlows;                                                          \
         return {reinterpret_cast<const void*>(                                                                                     \
                     blink_once<T, N, kFlows, SUM, fold_columns(N, true, TILE), TILE == FoldTile::kWhole>),                         \
-                fill_once<N, kFlows>};                                                                                             \
+                fill_once<N, kFlows>, N, sizeof(void*) * N + 4 * (kFlows + 1 + once_words(N, kFlows))};                                                  \
     }
         BLINK_FOLD_CASES
 #undef BLINK_CASE
@@ -225,5 +292,13 @@ OnceKernel once_f32_sum(int n, bool half, bool many);
 OnceKernel once_f32_other(int n, bool half, bool many);
 OnceKernel once_i32_sum(int n, bool half, bool many);
 OnceKernel once_i32_other(int n, bool half, bool many);
+
+// Copies to up to m ranks among k; many: more than kOnceFewFlows flows.
+OnceKernel once_copy(int k, int m, bool many);
+// Columns per wave.  Against blink_fold, geometric means over random sizes with 1 / 2 / 4 columns, up to 7, and 7 to 10 tenths of the
+// sizes that have a workgroup per tile: Broadcast to 7 1.13 / 1.13 / 1.12, 1.01 / 1.09 / 1.07, AllGather of 8 1.06 / 1.09 / 1.04,
+// 1.00 / 1.06 / 1.02, of 5 1.07 / 1.09 / 1.07, 1.01 / 1.05 / 1.02, Broadcast to 2 1.04 / 1.06 / 1.05, 1.03 / 1.04 / 1.02,
+// AllGather of 16 1.38 / 1.33 / 1.27, 1.30 / 1.25 / 1.24; Gather of 8 with 2 / 4 / 8 1.10 / 1.08 / 1.06, 1.07 / 1.06 / 1.07.
+constexpr int once_copy_columns(int m) { return m > 8 ? 1 : 2; }
 
 }  // namespace blink

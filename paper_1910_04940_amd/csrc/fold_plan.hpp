@@ -142,6 +142,7 @@ struct OnceGrid {
 // 256 bytes (steps of 1 KiB: 6.47 -> 7.25, steps of less split what a channel holds together).
 constexpr uint32_t kOnceTileStep = 64;   // elements
 constexpr size_t kOnceMostFlows = 16;
+constexpr size_t kOnceParamsBytes = 464;   // room for its arguments
 inline OnceGrid once_grid(const std::vector<FoldFlow>& flows, uint32_t most, uint32_t grid_shift, uint32_t cus) {
     const auto count = [&](uint32_t tile) {
         uint64_t c = 0;
@@ -198,21 +199,41 @@ BLINK_HOST_DEVICE inline uint32_t once_shift(uint32_t call) { return (call >> 8 
 BLINK_HOST_DEVICE inline uint32_t once_redop(uint32_t call) { return call >> 14 & 3u; }
 BLINK_HOST_DEVICE inline uint32_t once_edges(uint32_t call) { return call >> 16; }
 
-// The flows as that kernel is given them, in payload order; none where it cannot run them: there are more than `most`, they
-// leave something out or overlap, a byte offset (tile grid included) does not fit 31 bits, or they
-// differ so much in length that workgroups without a tile (those beyond a shorter flow's end, which end at once) would
-// outnumber the others.
+// The flows as that kernel is given them, in payload order; none where it cannot run them: there are more than
+// kOnceMostFlows, they leave something out or overlap, a byte offset (tile grid included) does not fit 31 bits, or they differ
+// so much in length that workgroups without a tile (those beyond a shorter flow's end, which end at once) would outnumber the
+// others.  Copies: what goes from one rank to the same others all along is one flow, whatever trees it was split among (a
+// Broadcast has one, an AllGather one per piece), and a stretch that does not move (a Gather's root's own piece) is one
+// without stores.
 constexpr uint64_t kOnceMostElems = (1ull << 29) - 65536;
-inline std::vector<FoldFlow> once_flows(std::vector<FoldFlow> flows, uint64_t n, size_t most) {
+inline std::vector<FoldFlow> once_flows(std::vector<FoldFlow> flows, uint64_t n, bool copies) {
+    if (flows.empty() || n >= kOnceMostElems) return {};
     std::sort(flows.begin(), flows.end(), [](const FoldFlow& a, const FoldFlow& b) { return a.off < b.off; });
+    std::vector<FoldFlow> out;
     uint64_t at = 0, longest = 0;
-    for (const FoldFlow& f : flows) {
-        if (f.off != at) return {};
+    auto put = [&](const FoldFlow& f) {
+        const bool joins = copies && !out.empty() && out.back().seq[0] == f.seq[0] && out.back().stores == f.stores;
+        if (joins)
+            out.back().len += f.len;
+        else
+            out.push_back(f);
         at += f.len;
-        longest = std::max(longest, f.len);
+        longest = std::max(longest, out.back().len);
+    };
+    auto hole = [&](uint64_t until) {
+        FoldFlow f{};
+        f.off = at, f.len = until - at;
+        put(f);
+    };
+    for (const FoldFlow& f : flows) {
+        if (f.off < at || (f.off > at && !copies)) return {};
+        if (f.off > at) hole(f.off);
+        put(f);
     }
-    if (at != n || n >= kOnceMostElems || flows.size() > most || longest * flows.size() > 2 * n) return {};
-    return flows;
+    if (at > n || (at < n && !copies)) return {};
+    if (at < n) hole(n);
+    if (out.size() > kOnceMostFlows || longest * out.size() > 2 * n) return {};
+    return out;
 }
 
 // The flows of a schedule, longest first.  False where the fold kernel cannot run them
@@ -403,7 +424,7 @@ struct FoldTables {
 inline void fold_tables(const Schedule& s, FoldTables* out) {
     out->fits = fold_flows(s, &out->flows);
     if (!out->fits) out->flows.clear();
-    out->once = once_flows(out->flows, s.n, kOnceMostFlows);
+    out->once = once_flows(out->flows, s.n, s.fused.empty() || s.fused[0].stage.n_load == 1);
     out->levels.reserve(out->flows.size());
     out->tables.assign(FoldTables::words_per_flow() * out->flows.size(), 0);
     fold_words(out->flows, static_cast<uint32_t>(out->flows.size()), out->tables.data());

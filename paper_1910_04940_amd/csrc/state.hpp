@@ -26,8 +26,11 @@ struct LaunchPlan {
     bool half = false;             // tiles of half the size (where small)
     bool once = false;             // by the kernel that does nothing else (fold_once.hpp)
     bool once_half = false;        // there: tiles of half the size
+    int once_stores = 0;           // copies there: the most ranks a flow is copied to
     OnceGrid once_grid{};          // made for once_shift
     uint32_t once_shift = ~0u;
+    bool once_filled = false;
+    alignas(16) unsigned char once_params[kOnceParamsBytes] = {};   // the launch copies them
     bool all = false;              // every stage writes all the ranks it reads
     bool mid = false;              // partial sums are written on the way
     uint32_t n_load = 0;           // ranks a stage reads

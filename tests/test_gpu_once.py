@@ -70,3 +70,49 @@ def test_buffers_off_the_grid(past):
         for b in bufs:
             b.zero_()
         assert int(torch.count_nonzero(whole)) == 0
+
+
+@pytest.mark.parametrize("fusion", [bl.BLINK_FUSE_TREE, bl.BLINK_FUSE_EDGE])
+@pytest.mark.parametrize("k", [2, 3, 5, 8, 9, 16])
+def test_copies(k, fusion):
+    """One rank read and copied to one, several or all others, to another number of them per piece (a
+    per-edge Gather), pieces that begin and end anywhere, a root that keeps its own."""
+    stream = _stream()
+    trees, roots, _ = _forest(k, [1.0])
+    root = roots[0]
+    for m in (1, 3, 1_021, 30_011, 20 * 2**20 // (4 * k * k)):
+        n = k * m
+        x = [si.hash_payload(97, r, 0, n, "int32") for r in range(k)]
+        gathered = ox.allgather_definition(x)
+        for op, call, want in ((bl.BLINK_OP_BROADCAST, bl.blink_broadcast, [x[root]] * k),
+                               (bl.BLINK_OP_ALLGATHER, bl.blink_allgather, [gathered] * k),
+                               (bl.BLINK_OP_GATHER, bl.blink_gather, {root: gathered})):
+            bufs, untouched = _slab(x)
+            sched = bl.blink_make_schedule(trees, op, n, 1 << 12, fusion)
+            call(bufs, n, bl.BLINK_INT32, sched, stream)
+            torch.cuda.synchronize()
+            for r in range(k):
+                if not isinstance(want, dict) or r in want:
+                    assert np.array_equal(bufs[r].cpu().numpy(), want[r]), (op, n, r)
+                elif fusion == bl.BLINK_FUSE_TREE:      # a piece goes to the root alone
+                    assert np.array_equal(bufs[r].cpu().numpy(), x[r]), (op, n, r)
+            assert untouched()
+
+
+def test_copies_along_trees_with_different_roots():
+    """A Gather whose pieces go to a root per tree, some of which stay where they are."""
+    stream = _stream()
+    k, n = 3, 3 * 5_003
+    trees = bl.blink_trees_from_arrays(k, [0, 1], [[-1, 0, 0], [1, -1, 1]], [1.0, 2.0])
+    x = [si.hash_payload(101, r, 0, n, "int32") for r in range(k)]
+    sched = bl.blink_make_schedule(trees, bl.BLINK_OP_GATHER, n, 1 << 12, bl.BLINK_FUSE_TREE)
+    b = sched.bounds()
+    bufs, untouched = _slab(x)
+    bl.blink_gather(bufs, n, bl.BLINK_INT32, sched, stream)
+    torch.cuda.synchronize()
+    want = [a.copy() for a in x]
+    for t, root in enumerate((0, 1)):
+        for j in range(k):
+            lo, hi = j * (n // k) + b[t], j * (n // k) + b[t + 1]
+            want[root][lo:hi] = x[j][lo:hi]
+    assert all(np.array_equal(a.cpu().numpy(), w) for a, w in zip(bufs, want)) and untouched()
