@@ -16,7 +16,7 @@ LIB = os.path.join(HERE, "libblink.so")
 SOURCES = ["kernel_f32.hip", "kernel_i32.hip",
            "fold_f32_sum.hip", "fold_i32_sum.hip", "fold_f32_other.hip", "fold_i32_other.hip",
            "fold_once_f32_sum.hip", "fold_once_i32_sum.hip", "fold_once_f32_other.hip", "fold_once_i32_other.hip",
-           "fold_once_copy.hip",
+           "fold_once_f32_mid.hip", "fold_once_i32_mid.hip", "fold_once_copy.hip",
            "fold_f32_mid.hip", "fold_i32_mid.hip", "fold_copy.hip", "exec.hip",
            "api.cpp", "pack.cpp", "schedule.cpp", "miad.cpp"]
 FLAGS = [

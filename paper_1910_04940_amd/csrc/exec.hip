@@ -231,7 +231,7 @@ void plan_fold(blink_schedule* h) {
     pl.tile_elems = tile;
     pl.grid_shift = 0;
     pl.n_items = fold_levels(h->fold.flows, tile, 0, !words_inline(*h), &h->fold.levels);
-    pl.once = pl.small && (pl.all || n == 1) && !pl.mid && h->tile_override == 0 && !h->fold.once.empty();
+    pl.once = pl.small && h->tile_override == 0 && !h->fold.once.empty();
     if (n == 1)
         for (const FoldFlow& f : h->fold.once) pl.once_stores = std::max(pl.once_stores, __builtin_popcount(f.stores & 0xffffu));
     pl.once_half = pl.kernel_bytes <= kOnceHalfBytesPerCu * cus;
@@ -458,15 +458,17 @@ blink_status_t run_once(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     const std::vector<FoldFlow>& flows = h->fold.once;
     const int n = static_cast<int>(pl.n_load);
     if (pl.once_shift != grid_shift) {
-        const int columns = n == 1 ? once_copy_columns(pl.once_stores) : fold_columns(n, true, pl.once_half ? FoldTile::kHalf : FoldTile::kWhole);
+        const int columns = n == 1 ? once_copy_columns(pl.once_stores) : fold_columns(n, pl.all, pl.once_half && pl.all ? FoldTile::kHalf : FoldTile::kWhole);
         pl.once_grid = once_grid(flows, fold_sub_elems(columns), grid_shift, static_cast<uint32_t>(h->n_cu));
         pl.once_shift = grid_shift;
     }
     const OnceGrid& g = pl.once_grid;
     const bool many = flows.size() > kOnceFewFlows;
-    const auto pick = dtype == BLINK_FP32 ? (redop == BLINK_SUM ? once_f32_sum : once_f32_other)
-                                          : (redop == BLINK_SUM ? once_i32_sum : once_i32_other);
-    const OnceKernel kernel = n == 1 ? once_copy(h->s.k, pl.once_stores, many) : pick(n, pl.once_half, many);
+    const bool fp32 = dtype == BLINK_FP32, sum = redop == BLINK_SUM;
+    const OnceKernel kernel = n == 1   ? once_copy(h->s.k, pl.once_stores, many)
+                              : pl.mid ? (fp32 ? once_f32_mid : once_i32_mid)(n, pl.all, pl.once_half, many, sum)
+                              : sum    ? (fp32 ? once_f32_sum : once_i32_sum)(n, pl.all, pl.once_half, many)
+                                       : (fp32 ? once_f32_other : once_i32_other)(n, pl.all, pl.once_half, many);
     if (!kernel.fn) return BLINK_EINVAL;
     if (!pl.once_filled) {
         kernel.fill(flows, pl.once_params);   // the same for all element types and operators

@@ -33,25 +33,28 @@ constexpr int kOnceFewFlows = 4;
 // Flow f's program: the ranks in the order of consumption, and for each push | folds << 1.  Up to 4 ranks: word f, four
 // bits per rank, the codes from bit 16 on.  Up to 8: word f, three bits per rank, the low byte of the codes from bit 24
 // on; the other two, three bits per code, are a half of word F + f / 2.  More: words 4 f and 4 f + 1, four bits per rank, and
-// the codes in the next two.
+// the codes in the next two.  Where one rank is written it stands in the place of the first code, which says nothing.
 constexpr int once_words(int n, int flows) { return n <= 4 ? flows : n <= 8 ? flows + (flows + 1) / 2 : 4 * flows; }
-template <int N, int F>
+// Where partial sums are written on the way (FusedFlow::mid_store and mid_rank), flow f's: up to 8 ranks in word f, which additions' in
+// the low byte, then three bits per addition for the rank; more ranks in words 3 f (which) and 3 f + 1, 3 f + 2 (four bits).
+constexpr int once_mid_words(int n, int flows, bool mid) { return !mid ? 0 : n <= 8 ? flows : 3 * flows; }
+template <int N, int F, bool MID>
 struct OnceParams {
     void* buf[N];
     unsigned begin[F + 1];    // flow f: elements [begin[f], begin[f + 1])
-    unsigned word[once_words(N, F)];
+    unsigned word[once_words(N, F) + once_mid_words(N, F, MID)];
     unsigned call;            // see once_call
 };
-static_assert(sizeof(OnceParams<8, kOnceFewFlows>) <= 112, "see above");
+static_assert(sizeof(OnceParams<8, kOnceFewFlows, false>) <= 112, "see above");
 
-// FEW: at most two workgroups at a time on a CU.
-template <typename T, int N, int F, bool SUM, int U, bool FEW>
-__global__ __launch_bounds__(kFoldThreads) void blink_once(const OnceParams<N, F>) {
+// ALL: the ranks read are written, else one.  SUM, U, MID: see blink_fold.  FEW: at most two workgroups at a time on a CU.
+template <typename T, int N, int F, bool ALL, bool SUM, bool MID, int U, bool FEW>
+__global__ __launch_bounds__(kFoldThreads) void blink_once(const OnceParams<N, F, MID>) {
     constexpr int kParked = N < 4 ? 0 : N / 2 - 1;   // accumulators in LDS (see blink_fold)
     constexpr int kParkedBytes = kParked * U * kFoldThreads * 16;
     constexpr int kLdsBytes = FEW ? std::max(kParkedBytes, kLdsOfFew) : std::max(kParkedBytes, 16);
     __shared__ U4 parked[kLdsBytes / 16];
-    const BLINK_CONST OnceParams<N, F>* p = (const BLINK_CONST OnceParams<N, F>*)__builtin_amdgcn_kernarg_segment_ptr();
+    const BLINK_CONST OnceParams<N, F, MID>* p = (const BLINK_CONST OnceParams<N, F, MID>*)__builtin_amdgcn_kernarg_segment_ptr();
     const unsigned f = blockIdx.y, call = p->call;
     if constexpr (FEW && kParked == 0) asm volatile("" ::"v"(parked));   // (otherwise nothing uses the LDS)
     unsigned order[(N + 7) / 8], codes[(N + 7) / 8];
@@ -63,7 +66,18 @@ __global__ __launch_bounds__(kFoldThreads) void blink_once(const OnceParams<N, F
         order[0] = p->word[4 * f], order[1] = p->word[4 * f + 1], codes[0] = p->word[4 * f + 2], codes[1] = p->word[4 * f + 3];
     }
     const unsigned begin = p->begin[f], end = p->begin[f + 1];
-    asm volatile("" ::"s"(begin), "s"(end), "s"(order[0]), "s"(call), "s"(p->buf[0]), "s"(p->buf[N - 1]));   // all of them with one wait
+    unsigned which = 0;                // additions whose sum is written on the way, the next one's in bit 0
+    unsigned long long sums = 0;       // their ranks, likewise
+    if constexpr (MID) {
+        const BLINK_CONST unsigned* mid = p->word + once_words(N, F);
+        if constexpr (N <= 8) {
+            which = mid[f] & 255u, sums = mid[f] >> 8;
+        } else {
+            which = mid[3 * f], sums = static_cast<unsigned long long>(mid[3 * f + 2]) << 32 | mid[3 * f + 1];
+        }
+    }
+    constexpr int kSumBits = N <= 8 ? 3 : 4;
+    asm volatile("" ::"s"(begin), "s"(end), "s"(order[0]), "s"(call), "s"(p->buf[0]), "s"(p->buf[N - 1]), "s"(which));   // all of them with one wait
     constexpr int kBits = N > 4 && N <= 8 ? 3 : 4;
     if constexpr (N <= 4) codes[0] = order[0] >> 16;
     else if constexpr (N <= 8) codes[0] = order[0] >> 24 | (codes[0] >> (f & 1) * 16 & 0xffffu) << 8;
@@ -77,6 +91,16 @@ __global__ __launch_bounds__(kFoldThreads) void blink_once(const OnceParams<N, F
     const OnceRange range = once_range(begin, end - begin, once_shift(call));
     const int lane = threadIdx.x & (kLanes - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+    RankTable ranks{};
+    if constexpr (MID) {   // lane r: rank r's buffer
+        const unsigned long long mine = reinterpret_cast<unsigned long long>(p->buf[lane < N ? lane : 0]);
+        ranks = {static_cast<unsigned>(mine), static_cast<unsigned>(mine >> 32)};
+    }
+    const int one = static_cast<int>(codes[0] & ((1u << kBits) - 1));   // the rank written where that is one
+    auto destination = [&](int j, int limit) {
+        return __builtin_amdgcn_make_buffer_rsrc(ALL ? buf[j] : static_cast<char*>(p->buf[one]), 0, limit, kRawDword3);
+    };
+    constexpr int kStores = ALL ? N : 1;
 
     if (blockIdx.x == once_edges(call)) {
         // up to three elements at either end of the flow, one per lane of one wave
@@ -90,21 +114,28 @@ __global__ __launch_bounds__(kFoldThreads) void blink_once(const OnceParams<N, F
             x[i] = __builtin_amdgcn_raw_buffer_load_b32(__builtin_amdgcn_make_buffer_rsrc(buf[i], 0, end, kRawDword3), at, 0, kPolicyDefault);
         unsigned acc = x[0];
         int depth = 0;
+        auto add = [&](unsigned x) {
+            acc = combine1<T>(redop, acc, x);
+            if constexpr (MID) {
+                if (which & 1u)
+                    __builtin_amdgcn_raw_buffer_store_b32(acc, rank_window(ranks, sums & ((1u << kSumBits) - 1), 0, end), at, 0, kPolicyThrough);
+                which >>= 1, sums >>= kSumBits;
+            }
+        };
 #pragma unroll
         for (int i = 1; i < N; ++i) {
             if (N >= 4 && push(i)) {
                 park[depth++ * kLanes + lane] = acc;
                 acc = x[i];
             } else {
-                acc = combine1<T>(redop, acc, x[i]);
+                add(x[i]);
             }
             if (N >= 4)
 #pragma unroll 1
-                for (unsigned f = folds(i); f; --f) acc = combine1<T>(redop, acc, park[--depth * kLanes + lane]);
+                for (unsigned f = folds(i); f; --f) add(park[--depth * kLanes + lane]);
         }
 #pragma unroll
-        for (int i = 0; i < N; ++i)
-            __builtin_amdgcn_raw_buffer_store_b32(acc, __builtin_amdgcn_make_buffer_rsrc(buf[i], 0, end, kRawDword3), at, 0, kPolicyThrough);
+        for (int j = 0; j < kStores; ++j) __builtin_amdgcn_raw_buffer_store_b32(acc, destination(j, end), at, 0, kPolicyThrough);
         return;
     }
 
@@ -119,21 +150,41 @@ __global__ __launch_bounds__(kFoldThreads) void blink_once(const OnceParams<N, F
 #pragma unroll
         for (int u = 0; u < U; ++u) r[i][u] = __builtin_amdgcn_raw_buffer_load_b128(win, column + u * kLanes * 16, 0, kPolicyStream);
     }
-    asm volatile("" ::: "memory");   // all of them before anything is combined
-    U4 acc[U];
+    asm volatile("" ::: "memory");   // all of them, in this order, before anything is combined
+    if constexpr (MID) __builtin_amdgcn_sched_barrier(0);
+    // Where sums are written on the way a new accumulator has registers of its own: if it shares those of a load the
+    // compiler waits for all memory operations, those stores among them, at every loop that it enters (per node, 16
+    // ranks x 0.9 MiB 9.5 us, 8.3 so).
+    auto take = [&](U4 (&acc)[U], const U4 (&x)[U]) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) acc[u] = r[0][u];
+        for (int u = 0; u < U; ++u) {
+            acc[u] = x[u];
+            if constexpr (MID) asm volatile("" : "+v"(acc[u]));
+        }
+    };
+    U4 acc[U];
+    take(acc, r[0]);
     int depth = 0;
+    auto add = [&](const U4 (&x)[U]) {
+        combine_columns<T, SUM, U>(redop, acc, x);
+        if constexpr (MID) {
+            if (which & 1u) {
+                const __amdgpu_buffer_rsrc_t win = rank_window(ranks, sums & ((1u << kSumBits) - 1), 0, to);
+#pragma unroll
+                for (int u = 0; u < U; ++u) __builtin_amdgcn_raw_buffer_store_b128(acc[u], win, column + u * kLanes * 16, 0, kPolicyThrough);
+            }
+            which >>= 1, sums >>= kSumBits;
+        }
+    };
 #pragma unroll
     for (int i = 1; i < N; ++i) {
         if (N >= 4 && push(i)) {
 #pragma unroll
             for (int u = 0; u < U; ++u) parked[(depth * U + u) * kFoldThreads + threadIdx.x] = acc[u];
             ++depth;
-#pragma unroll
-            for (int u = 0; u < U; ++u) acc[u] = r[i][u];
+            take(acc, r[i]);
         } else {
-            combine_columns<T, SUM, U>(redop, acc, r[i]);
+            add(r[i]);
         }
         if (N >= 4)
 #pragma unroll 1
@@ -142,21 +193,21 @@ __global__ __launch_bounds__(kFoldThreads) void blink_once(const OnceParams<N, F
                 U4 below[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) below[u] = parked[(depth * U + u) * kFoldThreads + threadIdx.x];
-                combine_columns<T, SUM, U>(redop, acc, below);
+                add(below);
             }
     }
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-        const __amdgpu_buffer_rsrc_t win = __builtin_amdgcn_make_buffer_rsrc(buf[i], 0, to, kRawDword3);
+    for (int j = 0; j < kStores; ++j) {
+        const __amdgpu_buffer_rsrc_t win = destination(j, to);
 #pragma unroll
         for (int u = 0; u < U; ++u) __builtin_amdgcn_raw_buffer_store_b128(acc[u], win, column + u * kLanes * 16, 0, kPolicyThrough);
     }
 }
 
 // What of the arguments is the same for all calls on a schedule: all but the buffers and `call`.
-template <int N, int F>
+template <int N, int F, bool MID>
 void fill_once(const std::vector<FoldFlow>& flows, void* to) {
-    OnceParams<N, F>& p = *static_cast<OnceParams<N, F>*>(to);
+    OnceParams<N, F, MID>& p = *static_cast<OnceParams<N, F, MID>*>(to);
     constexpr int kBits = N > 4 && N <= 8 ? 3 : 4;
     for (unsigned& w : p.word) w = 0;
     for (size_t f = 0; f < flows.size(); ++f) {
@@ -166,6 +217,17 @@ void fill_once(const std::vector<FoldFlow>& flows, void* to) {
         for (int i = 0; i < N; ++i) {
             order |= static_cast<uint64_t>(fl.seq[i] & 15u) << (i * kBits);
             codes |= static_cast<uint64_t>(fl.seq[i] >> 4) << (i * kBits);
+        }
+        const uint32_t stores = fl.stores & 0xffffu;
+        if (!(stores & (stores - 1))) codes = (codes & ~static_cast<uint64_t>((1u << kBits) - 1)) | static_cast<unsigned>(__builtin_ctz(stores));
+        if (MID) {
+            unsigned* const mid = p.word + once_words(N, F);
+            if (N <= 8) {
+                mid[f] = fl.stores >> 16;
+                for (int i = 0; i < N - 1; ++i) mid[f] |= static_cast<unsigned>(fl.mid_rank >> 4 * i & 7u) << (8 + 3 * i);
+            } else {
+                mid[3 * f] = fl.stores >> 16, mid[3 * f + 1] = static_cast<unsigned>(fl.mid_rank), mid[3 * f + 2] = static_cast<unsigned>(fl.mid_rank >> 32);
+            }
         }
         if (N <= 4) {
             p.word[f] = static_cast<unsigned>(order | codes << 16);
@@ -265,34 +327,39 @@ struct OnceKernel {
     int bufs = 0;
     size_t call_at = 0;
 };
-static_assert(sizeof(OnceParams<BLINK_MAX_RANKS, kOnceMostFlows>) <= kOnceParamsBytes, "the largest");
+static_assert(sizeof(OnceParams<BLINK_MAX_RANKS, kOnceMostFlows, true>) <= kOnceParamsBytes, "the largest");
 
-template <typename T, bool SUM, FoldTile TILE, bool MANY>
+template <typename T, bool ALL, bool SUM, bool MID, FoldTile TILE, bool MANY>
 OnceKernel pick_once(int n) {
     switch (n) {
-#define BLINK_CASE(N)                                                                                                              \
-    case N: {                                                                                                                      \
-        constexpr int kFlows = MANY ? kOnceMostFlows : kOnceFewFlows;                                                          \
-        return {reinterpret_cast<const void*>(                                                                                     \
-                    blink_once<T, N, kFlows, SUM, fold_columns(N, true, TILE), TILE == FoldTile::kWhole>),                         \
-                fill_once<N, kFlows>, N, sizeof(void*) * N + 4 * (kFlows + 1 + once_words(N, kFlows))};                                                  \
+#define BLINK_CASE(N)                                                                                                                  \
+    case N: {                                                                                                                          \
+        constexpr int kFlows = MANY ? kOnceMostFlows : kOnceFewFlows;                                                                  \
+        return {reinterpret_cast<const void*>(                                                                                         \
+                    blink_once<T, N, kFlows, ALL, SUM, MID, fold_columns(N, ALL, TILE), ALL && TILE == FoldTile::kWhole>),             \
+                fill_once<N, kFlows, MID>, N,                                                                                          \
+                sizeof(void*) * N + 4 * (kFlows + 1 + once_words(N, kFlows) + once_mid_words(N, kFlows, MID))};                        \
     }
         BLINK_FOLD_CASES
 #undef BLINK_CASE
         default: return {};
     }
 }
-template <typename T, bool SUM>
-OnceKernel pick_once(int n, bool half, bool many) {
-    if (half) return many ? pick_once<T, SUM, FoldTile::kHalf, true>(n) : pick_once<T, SUM, FoldTile::kHalf, false>(n);
-    return many ? pick_once<T, SUM, FoldTile::kWhole, true>(n) : pick_once<T, SUM, FoldTile::kWhole, false>(n);
+template <typename T, bool SUM, bool MID>
+OnceKernel pick_once(int n, bool all, bool half, bool many) {
+    constexpr FoldTile kHalf = FoldTile::kHalf, kWhole = FoldTile::kWhole;
+    if (!all) return many ? pick_once<T, false, SUM, MID, kWhole, true>(n) : pick_once<T, false, SUM, MID, kWhole, false>(n);
+    if (half) return many ? pick_once<T, true, SUM, MID, kHalf, true>(n) : pick_once<T, true, SUM, MID, kHalf, false>(n);
+    return many ? pick_once<T, true, SUM, MID, kWhole, true>(n) : pick_once<T, true, SUM, MID, kWhole, false>(n);
 }
-// Stages that read n ranks and write them all; half: tiles of half the size; many: more than kOnceFewFlows flows.
-OnceKernel once_f32_sum(int n, bool half, bool many);
-OnceKernel once_f32_other(int n, bool half, bool many);
-OnceKernel once_i32_sum(int n, bool half, bool many);
-OnceKernel once_i32_other(int n, bool half, bool many);
-
+// Stages that read n ranks; all: and write them all, else one; half: tiles of half the size; many: more than kOnceFewFlows
+// flows; mid: with partial sums written on the way.
+OnceKernel once_f32_sum(int n, bool all, bool half, bool many);
+OnceKernel once_f32_other(int n, bool all, bool half, bool many);
+OnceKernel once_f32_mid(int n, bool all, bool half, bool many, bool sum);
+OnceKernel once_i32_sum(int n, bool all, bool half, bool many);
+OnceKernel once_i32_other(int n, bool all, bool half, bool many);
+OnceKernel once_i32_mid(int n, bool all, bool half, bool many, bool sum);
 // Copies to up to m ranks among k; many: more than kOnceFewFlows flows.
 OnceKernel once_copy(int k, int m, bool many);
 // Columns per wave.  Against blink_fold, geometric means over random sizes with 1 / 2 / 4 columns, up to 7, and 7 to 10 tenths of the

@@ -3,6 +3,6 @@
 
 namespace blink {
 
-OnceKernel once_f32_other(int n, bool half, bool many) { return pick_once<float, false>(n, half, many); }
+OnceKernel once_f32_other(int n, bool all, bool half, bool many) { return pick_once<float, false, false>(n, all, half, many); }
 
 }  // namespace blink

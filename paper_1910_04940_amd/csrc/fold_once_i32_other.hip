@@ -3,6 +3,6 @@
 
 namespace blink {
 
-OnceKernel once_i32_other(int n, bool half, bool many) { return pick_once<unsigned, false>(n, half, many); }
+OnceKernel once_i32_other(int n, bool all, bool half, bool many) { return pick_once<unsigned, false, false>(n, all, half, many); }
 
 }  // namespace blink

@@ -3,6 +3,6 @@
 
 namespace blink {
 
-OnceKernel once_i32_sum(int n, bool half, bool many) { return pick_once<unsigned, true>(n, half, many); }
+OnceKernel once_i32_sum(int n, bool all, bool half, bool many) { return pick_once<unsigned, true, false>(n, all, half, many); }
 
 }  // namespace blink

@@ -142,7 +142,7 @@ struct OnceGrid {
 // 256 bytes (steps of 1 KiB: 6.47 -> 7.25, steps of less split what a channel holds together).
 constexpr uint32_t kOnceTileStep = 64;   // elements
 constexpr size_t kOnceMostFlows = 16;
-constexpr size_t kOnceParamsBytes = 464;   // room for its arguments
+constexpr size_t kOnceParamsBytes = 656;   // room for its arguments
 inline OnceGrid once_grid(const std::vector<FoldFlow>& flows, uint32_t most, uint32_t grid_shift, uint32_t cus) {
     const auto count = [&](uint32_t tile) {
         uint64_t c = 0;

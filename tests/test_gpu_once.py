@@ -7,6 +7,7 @@ import pytest
 
 import synth_inputs as si
 from oracle import execute as ox
+from oracle import schedule as osch
 
 from test_gpu_fold import REDOPS, _slab, _stream, _tree
 
@@ -46,6 +47,44 @@ def test_shares(k, op, dtype, weights):
         for r in {0, k // 2, k - 1}:
             assert bufs[r].cpu().numpy().tobytes() == want.tobytes(), (n, r)
         assert untouched()
+
+
+# sums written on the way, of every addition or of a node's last, and one rank written: where they lie in the arguments
+# changes with the number of ranks (4, 8) and of flows
+@pytest.mark.parametrize("n_trees", [1, 4, 16])
+@pytest.mark.parametrize("k", [3, 4, 5, 8, 9, 16])
+def test_sums_on_the_way_and_at_one_rank(k, n_trees):
+    stream = _stream()
+    trees, roots, parents = _forest(k, [1.0] * n_trees)
+    w = [1.0] * n_trees
+    for n in (5, 4_099, 16 * 2**20 // (8 * k), 100 * 2**20 // (8 * k) + 3):
+        x = [si.hash_payload(103, r, 0, n, "int32") for r in range(k)]
+        want = ox.allreduce_int32_definition(x)
+        steps = osch.make_steps(roots, parents, w, osch.REDUCE_TO_ROOT, n, 1 << 16)
+        left = [a.copy() for a in x]
+        ox.run_steps(left, steps)
+        for fusion in (bl.BLINK_FUSE_EDGE, bl.BLINK_FUSE_NODE, bl.BLINK_FUSE_TREE):
+            bufs, untouched = _slab(x)
+            sched = bl.blink_make_schedule(trees, bl.BLINK_OP_ALLREDUCE, n, 1 << 16, fusion)
+            bl.blink_allreduce(bufs, n, bl.BLINK_INT32, sched, stream)
+            torch.cuda.synchronize()
+            assert all(np.array_equal(b.cpu().numpy(), want) for b in bufs) and untouched(), (n, fusion)
+            bufs, untouched = _slab(x)
+            sched = bl.blink_make_schedule(trees, bl.BLINK_OP_REDUCE, n, 1 << 16, fusion)
+            bl.blink_reduce(bufs, n, bl.BLINK_INT32, bl.BLINK_SUM, sched, stream)
+            torch.cuda.synchronize()
+            b = sched.bounds()
+            for r, got in enumerate(bufs):
+                got = got.cpu().numpy()
+                if fusion == bl.BLINK_FUSE_TREE:        # only the roots are written, each on its share
+                    keep = x[r].copy()
+                    for t, root in enumerate(roots):
+                        if root == r:
+                            keep[b[t]:b[t + 1]] = want[b[t]:b[t + 1]]
+                    assert np.array_equal(got, keep), (n, r)
+                else:                                   # a reduce leaves what the step list leaves
+                    assert np.array_equal(got, left[r]), (n, fusion, r)
+            assert untouched()
 
 
 @pytest.mark.parametrize("past", [(16,) * 5, (528,) * 5, (1008,) * 5, (0, 16, 512, 1008, 64)])
