@@ -66,6 +66,10 @@ class BlinkError(RuntimeError):
 
 _lib = None
 _hip = None
+# _blinkcall.call (see csrc/call.c) once the library is loaded, and the addresses of its collectives.
+_call = lambda *arguments: None
+_at = dict.fromkeys(("blink_allreduce", "blink_allreduce_noalloc", "blink_broadcast", "blink_allgather", "blink_gather",
+                     "blink_allreduce_op", "blink_reduce"), 0)
 
 
 def _load_hip_runtime() -> None:
@@ -94,7 +98,7 @@ def _load_hip_runtime() -> None:
 
 
 def lib() -> C.CDLL:
-    global _lib
+    global _lib, _call
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -158,6 +162,10 @@ def lib() -> C.CDLL:
     L.blink_miad_free.restype = None
     L.blink_strerror.argtypes = [C.c_int]
     L.blink_strerror.restype = C.c_char_p
+    from . import _blinkcall
+    for name in _at:
+        _at[name] = C.cast(getattr(L, name), vp).value
+    _call = _blinkcall.call
     _lib = L
     return L
 
@@ -248,12 +256,13 @@ class Schedule:
 
     def __init__(self, handle: int, k: int, n: int, op: int):
         self._h = C.c_void_p(handle)
+        self._address = handle
         self.k, self.n, self.op = k, n, op
 
     def __del__(self):
         if getattr(self, "_h", None) and _lib is not None:
             _lib.blink_schedule_free(self._h)
-            self._h = None
+            self._h = self._address = None
 
     @property
     def num_steps(self) -> int:
@@ -397,51 +406,63 @@ def _pointers(bufs: Sequence) -> "C.Array":
         return array(*[int(b.data_ptr()) if hasattr(b, "data_ptr") else int(b) for b in bufs])
 
 
-# A collective on a small payload takes the GPU 3 to 5 us, less than a wasteful call
-# takes here: the library's functions are looked up once (attributes of the loaded
-# library object) and a tensor is asked for its pointer only (8 ranks: 0.5 us a call).
+# A collective on a small payload takes the GPU 2 to 4 us, less than a wasteful call takes here: a list of
+# tensors and plain integers go to the library through _blinkcall, anything else (and the first call,
+# which loads the library) through ctypes.
 def blink_allreduce(bufs: Sequence, n_elems: int, dtype: int, schedule: Schedule, stream: int = 0) -> None:
     """bufs: k device pointers (ints) or objects with .data_ptr(); stream: hipStream_t as int."""
-    status = (_lib or lib()).blink_allreduce(_pointers(bufs), len(bufs), n_elems, dtype, schedule._h, C.c_void_p(stream))
+    status = _call(_at["blink_allreduce"], bufs, n_elems, dtype, schedule, stream)
+    if status is None:
+        status = (_lib or lib()).blink_allreduce(_pointers(bufs), len(bufs), n_elems, dtype, schedule._h, C.c_void_p(stream))
     if status:
         _check(status, "blink_allreduce")
 
 
 def blink_allreduce_noalloc(bufs: Sequence, n_elems: int, dtype: int, schedule: Schedule, stream: int = 0) -> None:
     """blink_allreduce on the library's static device block: the call allocates nothing."""
-    status = (_lib or lib()).blink_allreduce_noalloc(_pointers(bufs), len(bufs), n_elems, dtype, schedule._h, C.c_void_p(stream))
+    status = _call(_at["blink_allreduce_noalloc"], bufs, n_elems, dtype, schedule, stream)
+    if status is None:
+        status = (_lib or lib()).blink_allreduce_noalloc(_pointers(bufs), len(bufs), n_elems, dtype, schedule._h, C.c_void_p(stream))
     if status:
         _check(status, "blink_allreduce_noalloc")
 
 
 def blink_broadcast(bufs: Sequence, n_elems: int, dtype: int, schedule: Schedule, stream: int = 0) -> None:
-    status = (_lib or lib()).blink_broadcast(_pointers(bufs), len(bufs), n_elems, dtype, schedule._h, C.c_void_p(stream))
+    status = _call(_at["blink_broadcast"], bufs, n_elems, dtype, schedule, stream)
+    if status is None:
+        status = (_lib or lib()).blink_broadcast(_pointers(bufs), len(bufs), n_elems, dtype, schedule._h, C.c_void_p(stream))
     if status:
         _check(status, "blink_broadcast")
 
 
 def blink_allgather(bufs: Sequence, n_elems: int, dtype: int, schedule: Schedule, stream: int = 0) -> None:
-    status = (_lib or lib()).blink_allgather(_pointers(bufs), len(bufs), n_elems, dtype, schedule._h, C.c_void_p(stream))
+    status = _call(_at["blink_allgather"], bufs, n_elems, dtype, schedule, stream)
+    if status is None:
+        status = (_lib or lib()).blink_allgather(_pointers(bufs), len(bufs), n_elems, dtype, schedule._h, C.c_void_p(stream))
     if status:
         _check(status, "blink_allgather")
 
 
 def blink_gather(bufs: Sequence, n_elems: int, dtype: int, schedule: Schedule, stream: int = 0) -> None:
-    status = (_lib or lib()).blink_gather(_pointers(bufs), len(bufs), n_elems, dtype, schedule._h, C.c_void_p(stream))
+    status = _call(_at["blink_gather"], bufs, n_elems, dtype, schedule, stream)
+    if status is None:
+        status = (_lib or lib()).blink_gather(_pointers(bufs), len(bufs), n_elems, dtype, schedule._h, C.c_void_p(stream))
     if status:
         _check(status, "blink_gather")
 
 
-def blink_allreduce_op(bufs: Sequence, n_elems: int, dtype: int, redop: int, schedule: Schedule,
-                       stream: int = 0) -> None:
-    status = (_lib or lib()).blink_allreduce_op(_pointers(bufs), len(bufs), n_elems, dtype, redop, schedule._h, C.c_void_p(stream))
+def blink_allreduce_op(bufs: Sequence, n_elems: int, dtype: int, redop: int, schedule: Schedule, stream: int = 0) -> None:
+    status = _call(_at["blink_allreduce_op"], bufs, n_elems, dtype, schedule, stream, redop)
+    if status is None:
+        status = (_lib or lib()).blink_allreduce_op(_pointers(bufs), len(bufs), n_elems, dtype, redop, schedule._h, C.c_void_p(stream))
     if status:
         _check(status, "blink_allreduce_op")
 
 
-def blink_reduce(bufs: Sequence, n_elems: int, dtype: int, redop: int, schedule: Schedule,
-                 stream: int = 0) -> None:
-    status = (_lib or lib()).blink_reduce(_pointers(bufs), len(bufs), n_elems, dtype, redop, schedule._h, C.c_void_p(stream))
+def blink_reduce(bufs: Sequence, n_elems: int, dtype: int, redop: int, schedule: Schedule, stream: int = 0) -> None:
+    status = _call(_at["blink_reduce"], bufs, n_elems, dtype, schedule, stream, redop)
+    if status is None:
+        status = (_lib or lib()).blink_reduce(_pointers(bufs), len(bufs), n_elems, dtype, redop, schedule._h, C.c_void_p(stream))
     if status:
         _check(status, "blink_reduce")
 

@@ -1,4 +1,5 @@
-"""Compile the HIP library in-tree: csrc/* -> libblink.so (gfx950 only).
+"""Compile the HIP library in-tree: csrc/* -> libblink.so (gfx950 only), and the Python
+module that calls it (_blinkcall.so).
 
 The objects are linked WITHOUT a dependency on a particular libamdhip64: a
 process must hold exactly one HIP runtime, and a PyTorch wheel brings its own.
@@ -8,11 +9,13 @@ C++ program simply links its own libamdhip64)."""
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libblink.so")
+CALL = os.path.join(HERE, "_blinkcall.so")   # call.c: a Python module, host code only
 SOURCES = ["kernel_f32.hip", "kernel_i32.hip",
            "fold_f32_sum.hip", "fold_i32_sum.hip", "fold_f32_other.hip", "fold_i32_other.hip",
            "fold_once_f32_sum.hip", "fold_once_i32_sum.hip", "fold_once_f32_other.hip", "fold_once_i32_other.hip",
@@ -53,6 +56,11 @@ def build(verbose: bool = False) -> str:
     if verbose:
         print(" ".join(link), flush=True)
     subprocess.run(link, check=True)
+    call = [os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
+            os.path.join(CSRC, "call.c"), "-o", CALL]
+    if verbose:
+        print(" ".join(call), flush=True)
+    subprocess.run(call, check=True)
     return LIB
 
 
