@@ -98,7 +98,8 @@ typedef enum { BLINK_STEP_REDUCE = 0, BLINK_STEP_COPY = 1 } blink_step_kind_t;
  * another.  A wavefront either carries a tile through all of them in turn (NODE; EDGE
  * payloads that fit the GPU's 256 MiB memory-side cache), or the stages of one chunk
  * hand over to one another through device-side completion counters (larger EDGE
- * payloads; any where blink_schedule_set_hand_over asks for it). */
+ * payloads; any where blink_schedule_set_hand_over asks for it), chunks of 512 KiB
+ * and more in pieces of 256 KiB. */
 typedef enum { BLINK_FUSE_EDGE = 0, BLINK_FUSE_NODE = 1, BLINK_FUSE_TREE = 2 } blink_fusion_t;
 
 typedef struct blink_trees blink_trees_t;

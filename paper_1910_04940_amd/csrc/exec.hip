@@ -18,6 +18,8 @@ namespace blink {
 // (the array's name in host code is a host-side stand-in, not a device address).
 // All calls of blink_allreduce_noalloc on one GPU share that GPU's block.
 constexpr size_t kStaticBlockBytes = 4u << 20;
+// A block of a schedule's own has room for more counters (see hand_over_pieces).
+constexpr size_t kMostCounterBytes = 32u << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticBlockBytes];
 
 namespace {
@@ -56,12 +58,13 @@ KernelFn pick_kernel(blink_dtype_t dtype) { return dtype == BLINK_FP32 ? kernel_
 
 size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-BlockLayout layout_of(const Schedule& s) {
+BlockLayout layout_of(const Schedule& s, bool static_block) {
     constexpr size_t kLine = static_cast<size_t>(kCounterStride) * sizeof(unsigned long long);
     BlockLayout l;
     l.ticket = static_cast<size_t>(kStatusWords) * sizeof(unsigned long long);   // the fold kernel relies on it
     l.done = l.ticket + kMaxQueues * kLine;
-    l.counters_end = l.done + s.inst.size() * kLine;
+    l.pieces = hand_over_pieces(s, kLine, static_block ? kStaticBlockBytes / 2 : kMostCounterBytes);   // (half: the tables fit as well)
+    l.counters_end = l.done + s.inst.size() * l.pieces * kLine;
     l.tmpl = round_up(l.counters_end, 256);
     l.inst = round_up(l.tmpl + s.tmpl.size() * sizeof(StageTmpl), 256);
     l.bytes = round_up(l.inst + s.inst.size() * sizeof(StageInst), 256);
@@ -277,7 +280,7 @@ blink_status_t reset_progress(blink_schedule* h) {
     BLINK_HIP(hipDeviceSynchronize());
     if (!h->d_block) return BLINK_OK;
     // the next call's tables go in with it (see upload); the status record is read before
-    BLINK_HIP(hipMemset(h->d_block, 0, layout_of(h->s).counters_end));
+    BLINK_HIP(hipMemset(h->d_block, 0, layout_of(h->s, false).counters_end));
     BLINK_HIP(hipDeviceSynchronize());
     return BLINK_OK;
 }
@@ -648,6 +651,7 @@ blink_status_t run_hand_over(blink_schedule* h, void* const* bufs, blink_dtype_t
     p.tile_shift = pl.tile_shift;
     p.redop = static_cast<unsigned>(redop);
     p.n_inst = static_cast<unsigned>(s.inst.size());
+    p.pieces = l.pieces;
     p.max_naps = 4;   // looks at a dependency back off to ~0.8 us apart
 
     if (static_block) {
@@ -685,7 +689,7 @@ blink_status_t execute(blink_schedule* h, void* const* bufs, int k, size_t n, bl
     }
     if (s.inst.empty()) return BLINK_OK;
     if (blink_status_t st = make_plan(h)) return st;
-    const BlockLayout l = layout_of(s);
+    const BlockLayout l = layout_of(s, static_block);
     char* block = nullptr;   // the static block, or null: the schedule's own
     if (static_block) {
         if (blink_status_t st = claim_static_block(h, l, static_cast<hipStream_t>(stream), &block)) return st;

@@ -19,7 +19,8 @@
 // order has not been measured.)
 //
 // Chunk-granular hand-over (the paper's per-chunk event): a stage instance has
-// a 64-bit counter of finished tiles.  Counters are never reset; call number e
+// a 64-bit counter of finished tiles, and a chunk of 512 KiB or more is handed on in pieces, each
+// with a counter of its own (see hand_over_pieces).  Counters are never reset; call number e
 // on a schedule waits for e * tiles.  Data handed from stage to stage travels
 // with system-scope cache policy (see blink_consume), the counters with
 // agent-scope atomics.
@@ -88,6 +89,7 @@ struct KParams {
     unsigned redop;       // blink_redop_t
     unsigned max_naps;  // longest pause between two looks at a dependency, in units of ~0.2 us
     unsigned n_inst;    // stage instances
+    unsigned pieces;    // counters per instance (see hand_over_pieces)
 };
 
 // Address spaces: the kernel arguments and the schedule tables are never
@@ -329,7 +331,7 @@ __global__ __launch_bounds__(kLanes, 1) void blink_consume(const KParams) {
     const unsigned tiles_per_chunk = p->tiles_per_chunk;
     const unsigned tile_shift = p->tile_shift;
     const unsigned tile_elems = 1u << tile_shift;
-    const unsigned n_inst = p->n_inst;
+    const unsigned n_inst = p->n_inst, pieces = p->pieces;
 
     // Lane-dependent regions.  readfirstlane needs lane 0 present, so the
     // compiler must never get the chance to let some lanes run ahead of lane 0
@@ -361,7 +363,7 @@ __global__ __launch_bounds__(kLanes, 1) void blink_consume(const KParams) {
     unsigned long long* const status = p->status;
     if (__hip_atomic_load(status + kStatusState, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
     unsigned queue = blockIdx.x % n_queues, empty_queues = 0;
-    long long pending = -1;  // instance whose finished tile still has to be counted
+    long long pending = -1;  // counter in which a finished tile still has to be counted
     for (;;) {
         unsigned long long raw = 0;
         if (lane == 0) {
@@ -397,13 +399,22 @@ __global__ __launch_bounds__(kLanes, 1) void blink_consume(const KParams) {
             const unsigned tlen = static_cast<unsigned>(hi_e - lo_e);
             ConstTmpl st = tmpl + in->tmpl;
 
+            // the tile's piece of the instance: its counter and its ends
+            unsigned long long piece = 0, piece_lo = off, piece_hi = end;
+            if (pieces > 1) {
+                const unsigned long long block = block_lo >> kPieceShift;
+                piece = block - (off >> kPieceShift);
+                piece_lo = max(off, block << kPieceShift);
+                piece_hi = min(end, (block + 1) << kPieceShift);
+            }
             const int n_dep = in->n_dep;
             if (n_dep) {
                 bool gave_up = false;
                 if (lane < n_dep) {
                     const unsigned long long want =
-                        epoch * (((end + tile_elems - 1) >> tile_shift) - (off >> tile_shift));
-                    const unsigned long long* f = done + static_cast<long long>(in->dep[lane]) * kCounterStride;
+                        epoch * (((piece_hi + tile_elems - 1) >> tile_shift) - (piece_lo >> tile_shift));
+                    const unsigned long long* f =
+                        done + (static_cast<unsigned long long>(in->dep[lane]) * pieces + piece) * kCounterStride;
                     // poll, backing off (up to ~0.8 us between looks for large
                     // schedules) so that waiting waves leave the memory system
                     // to the working ones.  Every 64th look also checks the
@@ -464,7 +475,7 @@ __global__ __launch_bounds__(kLanes, 1) void blink_consume(const KParams) {
                 // every store of this wave has reached memory before the counter moves
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                 __builtin_amdgcn_s_waitcnt(0);
-                pending = ii;
+                pending = static_cast<long long>(static_cast<unsigned long long>(ii) * pieces + piece);
             }
         }
     }

@@ -2,6 +2,7 @@
 // 4.2.1, 4.2.2): per-tree shares, chunks, the tree-edge step list, and the
 // "stages" (one or several steps carried out in a single pass over a tile).
 #pragma once
+#include <algorithm>
 #include <cstdint>
 #include <vector>
 
@@ -159,6 +160,29 @@ inline uint64_t ticket_count(const Schedule& s, unsigned group, unsigned tile_sh
     uint64_t last_most = 1;
     for (uint64_t i = first; i < n_inst; ++i) last_most = last_most > tiles_of(s.inst[i]) ? last_most : tiles_of(s.inst[i]);
     return first * most + (n_inst - first) * last_most;
+}
+
+// Where stages wait for one another a chunk of two pieces or more is handed on piece by piece: blocks of 2^kPieceShift
+// elements of the payload (256 KiB), whatever the tile size (tiles are no larger, and lie on the same grid).  A stage and
+// the ones it waits for are of one chunk, so a piece waits for the same piece.  With one event per chunk of 1 MiB
+// a wave that had drawn a chunk's first tile waited for all 32 tiles of the stage before, and while the pipeline fills and
+// drains there is little else to do.  us, per edge, an event per chunk / per piece, three sets of buffers in turn:
+//   chunks of            1 MiB       2 MiB       4 MiB      16 MiB
+//   8 ranks x  64 MiB  348 / 320   343 / 304   321 / 291   327 / 296
+//           x 128 MiB  645 / 621   633 / 599   603 / 572   599 / 595
+//   16 ranks x 32 MiB  363 / 338   417 / 332   416 / 333   415 / 332
+//   5 ranks x  98 MiB  300 / 288   324 / 289   364 / 290   322 / 313
+//   3 ranks x  98 MiB  154 / 150   168 / 149   187 / 150   300 / 155
+//   4 ranks x 256 MiB  554 / 555   690 / 552   587 / 548   556 / 569
+// Pieces of 128 and 64 KiB: within 1 % (16 ranks x 32 MiB 340 / 330 / 326).  Smaller chunks are one piece: what a
+// caller who tunes the chunk size measures there is the chunk.
+// block_bytes: room for counters, counter_bytes apart, and instances; where the pieces' do not fit chunks have one each.
+constexpr unsigned kPieceShift = 16;
+inline uint32_t hand_over_pieces(const Schedule& s, uint64_t counter_bytes, uint64_t block_bytes) {
+    if (!s.has_deps || s.chunk < (2ull << kPieceShift)) return 1;
+    uint64_t most = 1;
+    for (const StageInst& in : s.inst) most = std::max<uint64_t>(most, ((in.off + in.len - 1) >> kPieceShift) - (in.off >> kPieceShift) + 1);
+    return s.inst.size() * (most * counter_bytes + sizeof(StageInst)) <= block_bytes ? static_cast<uint32_t>(most) : 1u;
 }
 
 // Exact floor(n * (w_0+..+w_{t-1}) / (w_0+..+w_{T-1})) rounded down to a multiple of

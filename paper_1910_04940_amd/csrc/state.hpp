@@ -40,14 +40,15 @@ struct LaunchPlan {
 };
 
 // Layout of the device block of a schedule, in bytes from its start:
-//   status record (kStatusWords 64-bit words), ticket counters, one counter of
-//   finished tiles per stage instance (counters kCounterStride words apart),
+//   status record (kStatusWords 64-bit words), ticket counters, a counter of
+//   finished tiles per stage instance, or per piece of it (counters kCounterStride words apart),
 //   stage templates, stage instances.  The fold kernel counts no finished tiles and
 //   knows neither templates nor instances: its
 //   tables, where they do not travel in the kernel's arguments, lie where the counters
 //   of finished tiles would (they need 204 of every 256 bytes there).
 struct BlockLayout {
     size_t ticket = 0, done = 0, tmpl = 0, inst = 0, bytes = 0;
+    uint32_t pieces = 1;      // counters per stage instance (see hand_over_pieces)
     size_t counters_end = 0;  // status record and counters are [0, counters_end)
     size_t words = 0;         // FoldTables::tables
 };

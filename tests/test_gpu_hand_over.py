@@ -180,3 +180,50 @@ def test_what_the_switch_takes():
     assert edge.kernel_bytes < edge.traffic_bytes
     edge.set_hand_over(True)
     assert edge.kernel_bytes == edge.traffic_bytes
+
+
+# chunks that are handed on in pieces of 65,536 elements: whole and odd numbers of them, tiles as large as a
+# piece and as small as they get, more counters than the shared block has room for (then a chunk has one)
+@pytest.mark.parametrize("n,chunk", [(300_007, 131_072), (1_000_003, 200_001), (1_000_003, 1 << 20), (500_001, 131_071)])
+@pytest.mark.parametrize("tile", [0, 256, 65_536])
+def test_chunks_in_pieces(n, chunk, tile):
+    stream = _stream()
+    k = 5
+    trees, _, _, _ = _forest(k, 2)
+    x = [si.hash_payload(107, r, 0, n, "int32") for r in range(k)]
+    want = ox.allreduce_int32_definition(x)
+    sched = _schedule(trees, bl.BLINK_OP_ALLREDUCE, n, chunk, "edge")
+    sched.set_launch(0, tile)
+    for call in (bl.blink_allreduce, bl.blink_allreduce, bl.blink_allreduce_noalloc, bl.blink_allreduce):
+        bufs, untouched = _slab(x)
+        call(bufs, n, bl.BLINK_INT32, sched, stream)
+        assert sched.status()[0] == bl.BLINK_OK and sched.handed_over == 1
+        assert all(np.array_equal(b.cpu().numpy(), want) for b in bufs) and untouched()
+
+
+def test_an_abandoned_wait_names_the_chunks_stages():
+    """Counters of pieces, reported as those of the stage; a reset clears them all."""
+    stream = _stream()
+    k, n, chunk = 6, 700_001, 262_144
+    trees, _, _, _ = _forest(k, 2)
+    x = [si.hash_payload(109, r, 0, n, "int32") for r in range(k)]
+    want = ox.allreduce_int32_definition(x)
+    sched = _schedule(trees, bl.BLINK_OP_ALLREDUCE, n, chunk, "edge")
+    bufs, _ = _slab(x)
+    bl.blink_allreduce(bufs, n, bl.BLINK_INT32, sched, stream)
+    assert sched.status()[0] == bl.BLINK_OK
+    sched.set_wait_limit(2000)
+    sched.test_skip_call()
+    bl.blink_allreduce(bufs, n, bl.BLINK_INT32, sched, stream)
+    st, rec = sched.status()
+    stages = sched.stages()
+    assert st == bl.BLINK_ESTUCK and rec["call"] == 3
+    assert rec["awaited_stage"] in [int(d) for d in stages[rec["stage"]]["deps"][:stages[rec["stage"]]["n_dep"]]]
+    assert rec["wanted"] % 3 == 0 and rec["seen"] <= rec["wanted"] // 3 * 2
+    sched.reset()
+    sched.set_wait_limit(0)
+    for _ in range(2):
+        bufs, _ = _slab(x)
+        bl.blink_allreduce(bufs, n, bl.BLINK_INT32, sched, stream)
+        assert sched.status()[0] == bl.BLINK_OK
+        assert all(np.array_equal(b.cpu().numpy(), want) for b in bufs)
