@@ -117,7 +117,7 @@ def kernel_sources_digest():
     sources and of the launcher."""
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_1910_04940_amd", "csrc")
-    for name in ("kernel.hpp", "fold.hpp", "fold_plan.hpp", "way_trial.hpp", "exec.hip", "schedule.hpp"):
+    for name in ("kernel.hpp", "fold.hpp", "fold_once.hpp", "fold_plan.hpp", "way_trial.hpp", "exec.hip", "schedule.hpp"):
         with open(os.path.join(csrc, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

@@ -195,8 +195,8 @@ void plan_hand_over(blink_schedule* h) {
 
 // The plan where the fold kernel runs the schedule.  A drawn ticket is one sub-tile of the
 // kernel, or as many as make it move 56 KiB, which two counters keep up with (see fold_grid).
-// A payload of at most five tiles (of 128 KiB read and written) per CU gets a workgroup for
-// every tile, and no ticket has to be drawn.  Where ranks are combined they are all resident at once or nearly so; the
+// A payload that blink_once serves (see once_bytes_per_cu), or one it cannot of at most five tiles (of 128 KiB read
+// and written) per CU, gets a workgroup for every tile, and no ticket has to be drawn.  Where ranks are combined they are all resident at once or nearly so; the
 // small tiles of a copy need not be (to two ranks a CU gets up to 27 workgroups and holds eight) (probe, 8 ranks,
 // workgroup per tile against 224 that draw: 2 MiB per rank 5.1 / 7.2 us, 4 MiB 9.6 /
 // 10.8, 7 MiB (3.5 tiles per CU) 14.4 / 16.2, 10.4 MiB (5.2) 25 / 25, 16 MiB 51 / 47).
@@ -222,7 +222,13 @@ void plan_fold(blink_schedule* h) {
     uint64_t tiles = 0;
     for (const FoldFlow& f : h->fold.flows) tiles += (f.len + sub - 1) / sub;
     const uint64_t cus = static_cast<uint64_t>(h->n_cu);
-    pl.small = tiles * sub * 4 * (pl.n_load + n_store) <= kFoldSmallBytesPerCu * cus;
+    if (n == 1)
+        for (const FoldFlow& f : h->fold.once) pl.once_stores = std::max(pl.once_stores, __builtin_popcount(f.stores & 0xffffu));
+    const bool once_can = h->tile_override == 0 && !h->fold.once.empty();
+    const uint64_t line = once_bytes_per_cu(pl.n_load, pl.all, n == 1 ? pl.once_stores : n_store, h->fold.once.size() > 1);
+    pl.once = once_can && pl.kernel_bytes <= line * cus;
+    pl.once_half = pl.kernel_bytes <= kOnceHalfBytesPerCu * cus;
+    pl.small = pl.once || (!once_can && tiles * sub * 4 * (pl.n_load + n_store) <= kFoldSmallBytesPerCu * cus);
     // a tile per flow more than that: shares need not be whole tiles
     pl.half = pl.small && pl.all && tiles <= kFoldHalfTilesPerCu * cus + h->fold.flows.size();
     if (pl.small && n == 1 && n_store > 1 && tiles > cus) pl.copy_columns = kCopyColumnsSmall;   // (one tile per CU at most: no difference)
@@ -234,10 +240,6 @@ void plan_fold(blink_schedule* h) {
     pl.tile_elems = tile;
     pl.grid_shift = 0;
     pl.n_items = fold_levels(h->fold.flows, tile, 0, !words_inline(*h), &h->fold.levels);
-    pl.once = pl.small && h->tile_override == 0 && !h->fold.once.empty();
-    if (n == 1)
-        for (const FoldFlow& f : h->fold.once) pl.once_stores = std::max(pl.once_stores, __builtin_popcount(f.stores & 0xffffu));
-    pl.once_half = pl.kernel_bytes <= kOnceHalfBytesPerCu * cus;
 }
 
 blink_status_t make_plan(blink_schedule* h) {
@@ -477,11 +479,13 @@ blink_status_t run_once(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
         kernel.fill(flows, pl.once_params);   // the same for all element types and operators
         pl.once_filled = true;
     }
-    void** const buf = reinterpret_cast<void**>(pl.once_params);
+    alignas(16) unsigned char params[kOnceParamsBytes];
+    std::memcpy(params, pl.once_params, kernel.call_at);
+    void** const buf = reinterpret_cast<void**>(params);
     for (int i = 0; i < kernel.bufs; ++i) buf[i] = bufs[std::min(i, h->s.k - 1)];
     const uint32_t call = once_call(g.tile_elems, grid_shift, static_cast<uint32_t>(redop), g.tiles);
-    std::memcpy(pl.once_params + kernel.call_at, &call, sizeof call);
-    return launch(h, kernel.fn, dim3(g.columns, static_cast<unsigned>(flows.size())), kFoldThreads, pl.once_params, stream, Timed());
+    std::memcpy(params + kernel.call_at, &call, sizeof call);
+    return launch(h, kernel.fn, dim3(g.columns, static_cast<unsigned>(flows.size())), kFoldThreads, params, stream, Timed());
 }
 
 // A call on the fold kernel.  block: the static block, or null for the schedule's own, which is only made where tickets are drawn or the tables

@@ -164,6 +164,36 @@ inline OnceGrid once_grid(const std::vector<FoldFlow>& flows, uint32_t most, uin
     g.columns = g.tiles + (ragged ? 1u : 0u);
     return g;
 }
+// Up to how much traffic per CU that kernel serves a payload (10 units: 160 MiB on 256 CUs).  Its speed relative to drawn
+// tickets, on three sets of buffers in turn / on so many that none is in any cache, by units:
+//                             5 to 6     6 to 7     7 to 8     8 to 9     9 to 10   10 to 13   13 to 16   16 to 20   20 to 24
+//   sums to all, 2 ranks     .99 / .99  .99 / .97  .99 / .95  .98 / .94  .93 / .93
+//     3 ranks                .98 / .99  .98 / .96  .97 / .95  .97 / .94  .95 / .94  .89 / .93
+//     4 ranks                          1.02 / .98 1.00 / .98 1.03 / .96 1.00 / .96  .92 / .93
+//     6 ranks                          1.05 / .97 1.04 / .96 1.03 / .95 1.04 / .95  .91 / .93
+//     8 ranks                          1.10 /1.02 1.09 /1.01 1.07 /1.00 1.06 / .99  .96 / .98
+//   to one, 3 ranks                                                                1.00 / .99 1.00 / .98 1.00 / .95  .99 / .95
+//     4 ranks                                                                      1.08 /1.05 1.07 /1.04 1.06 /1.05 1.05 /1.02
+//     8 ranks                                                                      1.06 /1.09 1.04 /1.05 1.03 /1.02 1.01 /1.00
+//     10 and 16 ranks                                                              1.03 /1.00 1.00 /1.00  .99 / .98  .96 / .96
+//   copies to one, of 8                                                            1.02 /1.05 1.05 /1.05 1.09 /1.07 1.12 /1.10
+//     (further on, to 30 and 40 units: of 8 1.04 /1.02 and 1.03 /1.04, of 5 1.05 /1.04 and 1.01 /1.01, of 4 1.07 /1.06 and .99 /1.01)
+//     of one to 2                      1.07 /1.10 1.05 /1.09 1.04 /1.08 1.03 /1.07 1.01 / .98
+//     of one to 3                      1.10 /1.10 1.10 /1.09 1.06 /1.11 1.04 /1.08 1.02 /1.02 1.01
+//     of one to 7                      1.08 /1.10 1.04 /1.04  .97 /1.02  .95 / .99  .94 / .96
+//     of pieces to 7                   1.12 /1.17 1.08 /1.09 1.05 /1.07 1.04 /1.08 1.01 /1.03  .98
+//     of pieces to 9 and 15                                                        1.21 /1.24 1.11 /1.15 1.00 /1.03  .99 /1.00
+// (in between on a line of a number of ranks not listed: its neighbours'.)
+constexpr uint64_t kOnceLineUnit = 64 * 1024;
+inline uint64_t once_bytes_per_cu(uint32_t n_load, bool all, uint32_t n_store, bool pieces) {
+    const uint64_t units = n_load > 1 && all  ? (n_load < 4 ? 5 : n_load == 4 ? 9 : 10)
+                           : n_load > 1       ? (n_load < 4 ? 10 : n_load <= 8 ? 20 : 12)
+                           : n_store == 1     ? 24
+                           : pieces           ? (n_store > 8 ? 16 : 12)
+                           : n_store == 7 || n_store == 8 ? 8 : 10;
+    return units * kOnceLineUnit;
+}
+
 // What a workgroup of that kernel has: byte offsets from the start of every rank buffer.
 struct OnceRange {
     int32_t origin;        // where the flow's tile 0 starts on the tile grid (see fold_range): a multiple of 16

@@ -30,7 +30,7 @@ struct LaunchPlan {
     OnceGrid once_grid{};          // made for once_shift
     uint32_t once_shift = ~0u;
     bool once_filled = false;
-    alignas(16) unsigned char once_params[kOnceParamsBytes] = {};   // the launch copies them
+    alignas(16) unsigned char once_params[kOnceParamsBytes] = {};   // what of them all calls share
     bool all = false;              // every stage writes all the ranks it reads
     bool mid = false;              // partial sums are written on the way
     uint32_t n_load = 0;           // ranks a stage reads

@@ -37,7 +37,8 @@ def test_shares(k, op, dtype, weights):
     code, oracle_op = REDOPS[op]
     # traffic of 96 and 160 MiB is where half tiles, and a workgroup per tile, end on 256 compute units
     half, small = 96 * 2**20 // (8 * k), 160 * 2**20 // (8 * k)
-    for n in (7, 1_027, 65_539, half - 5, half + 4_099, small - 2_047):
+    large = (half - 5, half + 4_099, small - 2_047) if len(weights) in (1, 3, 5) else (half + 4_099,) if len(weights) == 4 else ()
+    for n in (7, 1_027, 65_539) + large:
         x = [si.hash_payload(83, r, 0, n, dtype) for r in range(k)]
         want = ox.tree_order_allreduce(x, roots, parents, weights, oracle_op)
         bufs, untouched = _slab(x)
@@ -155,3 +156,36 @@ def test_copies_along_trees_with_different_roots():
             lo, hi = j * (n // k) + b[t], j * (n // k) + b[t + 1]
             want[root][lo:hi] = x[j][lo:hi]
     assert all(np.array_equal(a.cpu().numpy(), w) for a, w in zip(bufs, want)) and untouched()
+
+
+# traffic on either side of where drawn tickets take over, on 256 compute units: (ranks, collective, MiB of traffic there)
+@pytest.mark.parametrize("k,op,mib", [(2, "allreduce", 80), (3, "allreduce", 80), (4, "allreduce", 144), (8, "allreduce", 160),
+                                      (3, "reduce", 160), (8, "reduce", 320), (9, "reduce", 192), (3, "gather", 384),
+                                      (4, "broadcast", 160), (8, "broadcast", 128), (4, "allgather", 192), (10, "allgather", 256)])
+def test_both_sides_of_the_line(k, op, mib):
+    stream = _stream()
+    trees, roots, _ = _forest(k, [1.0])
+    root = roots[0]
+    code = {"allreduce": bl.BLINK_OP_ALLREDUCE, "reduce": bl.BLINK_OP_REDUCE, "gather": bl.BLINK_OP_GATHER,
+            "broadcast": bl.BLINK_OP_BROADCAST, "allgather": bl.BLINK_OP_ALLGATHER}[op]
+    per = {"allreduce": 8 * k, "reduce": 4 * (k + 1), "gather": 8 * (k - 1) / k}.get(op, 4 * k)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(k)
+    for n in (int(mib * 2**20 / per) - 4_099, int(mib * 2**20 / per) + 4_099):
+        n -= n % k
+        bufs = [torch.randint(-2**31, 2**31, (n,), dtype=torch.int32, device="cuda", generator=gen) for _ in range(k)]
+        m = n // k
+        if op in ("allreduce", "reduce"):
+            want = bufs[0].clone()
+            for b in bufs[1:]:
+                want += b
+        else:
+            want = bufs[root].clone() if op == "broadcast" else torch.cat([b[r * m:(r + 1) * m] for r, b in enumerate(bufs)])
+        sched = bl.blink_make_schedule(trees, code, n, 1 << 18, bl.BLINK_FUSE_TREE)
+        if op == "reduce":
+            bl.blink_reduce(bufs, n, bl.BLINK_INT32, bl.BLINK_SUM, sched, stream)
+        else:
+            getattr(bl, "blink_" + op)(bufs, n, bl.BLINK_INT32, sched, stream)
+        torch.cuda.synchronize()
+        for r in ([root] if op in ("reduce", "gather") else range(k)):
+            assert torch.equal(bufs[r], want), (n, r)
