@@ -1,5 +1,5 @@
-// The launcher of the two kernels (kernel.hpp: stages that wait for one another;
-// fold.hpp: the others): the device block of a schedule (status record, progress
+// The launcher of the kernels (kernel.hpp: stages that wait for one another;
+// fold.hpp: the others, fold_once.hpp: small payloads of those): the device block of a schedule (status record, progress
 // counters, tables), the launch plan, the launch and its bookkeeping.
 #include "fold_once.hpp"
 
@@ -225,7 +225,7 @@ void plan_fold(blink_schedule* h) {
     if (n == 1)
         for (const FoldFlow& f : h->fold.once) pl.once_stores = std::max(pl.once_stores, __builtin_popcount(f.stores & 0xffffu));
     const bool once_can = h->tile_override == 0 && !h->fold.once.empty();
-    const uint64_t line = once_bytes_per_cu(pl.n_load, pl.all, n == 1 ? pl.once_stores : n_store, h->fold.once.size() > 1);
+    const uint64_t line = once_bytes_per_cu(pl.n_load, pl.all, n == 1 ? pl.once_stores : n_store, h->fold.once.size());
     pl.once = once_can && pl.kernel_bytes <= line * cus;
     pl.once_half = pl.kernel_bytes <= kOnceHalfBytesPerCu * cus;
     pl.small = pl.once || (!once_can && tiles * sub * 4 * (pl.n_load + n_store) <= kFoldSmallBytesPerCu * cus);

@@ -30,8 +30,9 @@
 //     that takes two neighbouring tiles one after the other is 10 % slower (168 -> 185) though it
 //     draws half the tickets, and loads issued one by one as registers become free, which keeps
 //     more in flight, are slower as well (probe, 8 x 64 MiB: 170 against 161).
-//   * Tickets come from two counters, or from one where that keeps up (see fold_grid); a small payload has
-//     a workgroup for every tile and no counter (see the launcher).
+//   * Tickets come from two counters, or from one where that keeps up (see fold_grid).  A payload small enough for
+//     a workgroup per tile is served by fold_once.hpp; this kernel takes it, without a counter, where that one cannot: more
+//     flows, shares too unequal, a tile size or a grid that the caller asks for.
 #pragma once
 #include "fold_plan.hpp"
 #include "kernel.hpp"

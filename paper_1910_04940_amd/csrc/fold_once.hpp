@@ -3,14 +3,14 @@
 //
 // Such a call is bound by the latency of one pass: arguments, rank data, stores.  What lies in
 // front of the loads counts in full, and so does the length of the code, which every call
-// fetches anew (1.5 to 3 KB here, 5 to 9 KB in fold.hpp).  So the place in the grid says which flow (y) and
+// fetches anew (sums of 4 ranks 1.9 KB, of 8 3.4, against 6.8 and 8.7 in fold.hpp).  So the place in the grid says which flow (y) and
 // which of its tiles (x) a workgroup has, two rounds of scalar loads, the second from
 // lines that the first has fetched, stand between a wave's start and its rank loads: no tickets, no levels, no loop.
 //
 // us per call, one after the other in a graph on three sets of buffers in turn, blink_fold / this kernel
-// (sums, int32): 8 ranks x 16 KiB 2.84 / 2.2, 64 KiB and a ragged end 3.48 / 2.5, 1 MiB 3.97 / 3.2, 2 MiB
-// 6.6 / 5.4, 4 MiB 10 to 11 / 9.5, 8 MiB 23 / 17.5 (shares a power of two apart; at 7.3 MiB 18.5 / 16.1),
-// 4 ranks x 1 MiB 3.3 / 2.7, 4 MiB 6.75 / 6.2, 3 ranks x 3.2 MiB 4.9 / 4.0.
+// (sums, int32): 8 ranks x 16 KiB 2.84 / 2.28, 64 KiB and a ragged end 3.45 / 2.36, 0.4 MiB 3.8 / 2.7, 1 MiB 3.97 / 3.56,
+// 1.5 MiB 6.1 / 4.4, 4 MiB 11.1 / 9.7, 8 MiB 23 / 17.5 (shares a power of two apart; at 6.1 MiB 16.3 / 13.5),
+// 4 ranks x 0.8 MiB 3.3 / 2.6, 4 MiB 6.75 / 5.5, 16 ranks x 0.8 MiB 6.5 / 5.6; 3 ranks x 3.2 MiB 4.9 / 4.0.
 //
 // The tiles of one flow go out one after the other, one flow after the other: in turns across the flows the
 // shares of a payload of 2^n elements, a power of two apart, kept asking the same channels (8 ranks x 8
@@ -20,7 +20,7 @@
 
 namespace blink {
 
-// Where whole tiles are handed out (the upper two fifths of the range) two workgroups at a time run on a CU, by the LDS
+// Where whole tiles are handed out (from 96 MiB of traffic on 256 CUs) two workgroups at a time run on a CU, by the LDS
 // they ask for: more loads in flight spread the requests out.  Against as many as fit, us: 8 ranks x 9.5 MiB 24.9 / 22.9,
 // 8.8 MiB 20.8 / 19.2, 4 ranks x 16 MiB 20.3 / 18.3; half tiles there 24.1, 19.5, 17.9.
 constexpr int kLdsOfFew = 56 * 1024;

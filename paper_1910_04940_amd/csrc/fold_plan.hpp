@@ -183,14 +183,18 @@ inline OnceGrid once_grid(const std::vector<FoldFlow>& flows, uint32_t most, uin
 //     of one to 7                      1.08 /1.10 1.04 /1.04  .97 /1.02  .95 / .99  .94 / .96
 //     of pieces to 7                   1.12 /1.17 1.08 /1.09 1.05 /1.07 1.04 /1.08 1.01 /1.03  .98
 //     of pieces to 9 and 15                                                        1.21 /1.24 1.11 /1.15 1.00 /1.03  .99 /1.00
-// (in between on a line of a number of ranks not listed: its neighbours'.)
+// Sums that all ranks get, and copies of one rank, keep the line at 10: the 3 to 6 % that drawn tickets gain there in the
+// steady state (two to four ranks) cost a schedule's first call its device block (30 to 60 us) and the next ones the timed choice, and a
+// call on the shared block a kernel that clears it (2 us).  Repeated on one set of buffers (where drawn tickets meet what the call
+// before left in the cache, and so do these), by the same units: sums to one of 8 ranks 1.15 1.09 1.03, of 4 1.16 1.10 1.07, of 16
+// 1.08 up to 12; copies to one of 8 1.06 1.04 1.04 1.02, of 4 1.04 1.02 1.02 1.01, of 3 1.01 1.00 .99 .98 (so two sources
+// stop at 16); pieces to 7 1.01 up to 12, to 15 1.14 up to 13 and .87 to 1.1 up to 16 (so 13).
 constexpr uint64_t kOnceLineUnit = 64 * 1024;
-inline uint64_t once_bytes_per_cu(uint32_t n_load, bool all, uint32_t n_store, bool pieces) {
-    const uint64_t units = n_load > 1 && all  ? (n_load < 4 ? 5 : n_load == 4 ? 9 : 10)
-                           : n_load > 1       ? (n_load < 4 ? 10 : n_load <= 8 ? 20 : 12)
-                           : n_store == 1     ? 24
-                           : pieces           ? (n_store > 8 ? 16 : 12)
-                           : n_store == 7 || n_store == 8 ? 8 : 10;
+inline uint64_t once_bytes_per_cu(uint32_t n_load, bool all, uint32_t n_store, size_t sources) {
+    const uint64_t units = n_load > 1 && !all           ? (n_load < 4 ? 10 : n_load <= 8 ? 20 : 12)
+                           : n_load == 1 && n_store == 1 ? (sources > 2 ? 24 : sources == 2 ? 16 : 10)
+                           : n_load == 1 && sources > 1  ? (n_store > 8 ? 13 : 12)
+                                                         : 10;
     return units * kOnceLineUnit;
 }
 
