@@ -222,11 +222,9 @@ void plan_fold(blink_schedule* h) {
     uint64_t tiles = 0;
     for (const FoldFlow& f : h->fold.flows) tiles += (f.len + sub - 1) / sub;
     const uint64_t cus = static_cast<uint64_t>(h->n_cu);
-    if (n == 1)
-        for (const FoldFlow& f : h->fold.once) pl.once_stores = std::max(pl.once_stores, __builtin_popcount(f.stores & 0xffffu));
+    if (n == 1) pl.once_stores = static_cast<int>(once_stores(h->fold.once));
     const bool once_can = h->tile_override == 0 && !h->fold.once.empty();
-    const uint64_t line = once_bytes_per_cu(pl.n_load, pl.all, n == 1 ? pl.once_stores : n_store, h->fold.once.size());
-    pl.once = once_can && pl.kernel_bytes <= line * cus;
+    pl.once = once_can && once_serves(s, h->fold.once, cus);
     pl.once_half = pl.kernel_bytes <= kOnceHalfBytesPerCu * cus;
     pl.small = pl.once || (!once_can && tiles * sub * 4 * (pl.n_load + n_store) <= kFoldSmallBytesPerCu * cus);
     // a tile per flow more than that: shares need not be whole tiles

@@ -131,6 +131,15 @@ inline uint32_t fold_tiles(uint64_t off, uint64_t len, uint32_t tile_elems, uint
     return static_cast<uint32_t>((((off + grid_shift) & 255u) + len + tile_elems - 1) / tile_elems);
 }
 
+// Bytes the fold kernel reads plus writes in rank buffers per call: every rank it takes from
+// once, every rank of the result once, and the sums written on the way.
+inline uint64_t fold_bytes(const Schedule& s) {
+    uint64_t bytes = 0;
+    for (const FusedFlow& f : s.fused)
+        bytes += (f.hi - f.lo) * 4u * (f.stage.n_load + f.stage.n_store + static_cast<unsigned>(__builtin_popcount(f.mid_store)));
+    return bytes;
+}
+
 // The grid of the kernel that has a workgroup for every tile and does nothing else (fold_once.hpp): a row per flow, a
 // column per tile of the longest, and one more column where some flow begins or ends within a 16-byte column of memory.
 struct OnceGrid {
@@ -189,13 +198,31 @@ inline OnceGrid once_grid(const std::vector<FoldFlow>& flows, uint32_t most, uin
 // before left in the cache, and so do these), by the same units: sums to one of 8 ranks 1.15 1.09 1.03, of 4 1.16 1.10 1.07, of 16
 // 1.08 up to 12; copies to one of 8 1.06 1.04 1.04 1.02, of 4 1.04 1.02 1.02 1.01, of 3 1.01 1.00 .99 .98 (so two sources
 // stop at 16); pieces to 7 1.01 up to 12, to 15 1.14 up to 13 and .87 to 1.1 up to 16 (so 13).
+// (sources: ranks that something is copied from.  A Gather's root is none: its own piece stays where it is.)
 constexpr uint64_t kOnceLineUnit = 64 * 1024;
-inline uint64_t once_bytes_per_cu(uint32_t n_load, bool all, uint32_t n_store, size_t sources) {
+inline uint64_t once_bytes_per_cu(uint32_t n_load, bool all, uint32_t n_store, uint32_t sources) {
     const uint64_t units = n_load > 1 && !all           ? (n_load < 4 ? 10 : n_load <= 8 ? 20 : 12)
                            : n_load == 1 && n_store == 1 ? (sources > 2 ? 24 : sources == 2 ? 16 : 10)
                            : n_load == 1 && sources > 1  ? (n_store > 8 ? 13 : 12)
                                                          : 10;
     return units * kOnceLineUnit;
+}
+// The most ranks that one of the flows is copied to.
+inline uint32_t once_stores(const std::vector<FoldFlow>& once) {
+    int most = 0;
+    for (const FoldFlow& f : once) most = std::max(most, __builtin_popcount(f.stores & 0xffffu));
+    return static_cast<uint32_t>(most);
+}
+// Whether that kernel serves a schedule on `cus` compute units; once: its flows (see once_flows).
+inline bool once_serves(const Schedule& s, const std::vector<FoldFlow>& once, uint64_t cus) {
+    if (once.empty()) return false;
+    const StageTmpl& st = s.fused[0].stage;
+    const bool copies = st.n_load == 1;
+    uint32_t from = 0;
+    for (const FoldFlow& f : once)
+        if (f.stores & 0xffffu) from |= 1u << (f.seq[0] & 15u);
+    return fold_bytes(s) <= cus * once_bytes_per_cu(st.n_load, !copies && st.n_store == st.n_load, copies ? once_stores(once) : st.n_store,
+                                                    static_cast<uint32_t>(__builtin_popcount(from)));
 }
 
 // What a workgroup of that kernel has: byte offsets from the start of every rank buffer.
@@ -321,15 +348,6 @@ inline uint64_t fold_levels(const std::vector<FoldFlow>& flows, uint32_t tile_el
 }
 
 constexpr uint64_t kMemorySideCacheBytes = 256ull << 20;
-
-// Bytes the fold kernel reads plus writes in rank buffers per call: every rank it takes from
-// once, every rank of the result once, and the sums written on the way.
-inline uint64_t fold_bytes(const Schedule& s) {
-    uint64_t bytes = 0;
-    for (const FusedFlow& f : s.fused)
-        bytes += (f.hi - f.lo) * 4u * (f.stage.n_load + f.stage.n_store + static_cast<unsigned>(__builtin_popcount(f.mid_store)));
-    return bytes;
-}
 
 // One rank read and copied to n_store of them: fewer columns the more stores follow each load, and
 // fewer while a payload has a workgroup for every tile.  us with 2 / 3 / 4 / 8 / 16 columns:

@@ -2,6 +2,7 @@
 //   fold_rules_check grid MOST N_ITEMS FOR_EVERY_TILE TICKET_BYTES      -> workgroups, dealt, two counters
 //   fold_rules_check policy N_LOAD N_STORE PAYLOAD KERNEL_BYTES HAS_DEPS WAY ALTERNATES   -> 0 keep, 1 stream, 2 spread
 //   fold_rules_check columns OP FUSION N CHUNK PARENT...       -> columns of a copy along one tree
+//   fold_rules_check once OP FUSION N CHUNK PARENT...          -> a workgroup per tile on 256 compute units (along one tree)
 #include <cstdio>
 #include <cstdlib>
 #include <string>
@@ -21,7 +22,7 @@ int main(int argc, char** argv) {
                                                number(6) != 0, static_cast<int>(number(7)), number(8) != 0));
         return 0;
     }
-    if (what == "columns") {
+    if (what == "columns" || what == "once") {
         blink::Trees trees;
         trees.k = argc - 6;
         trees.weight.push_back(1.0);
@@ -36,7 +37,13 @@ int main(int argc, char** argv) {
         if (blink::make_schedule(trees, static_cast<blink_op_t>(number(2)), number(4), number(5),
                                  static_cast<blink_fusion_t>(number(3)), s) != BLINK_OK)
             return 1;
-        std::printf("%d\n", blink::fold_copy_columns(s));
+        if (what == "columns") {
+            std::printf("%d\n", blink::fold_copy_columns(s));
+        } else {
+            blink::FoldTables t;
+            blink::fold_tables(s, &t);
+            std::printf("%d\n", blink::once_serves(s, t.once, 256));
+        }
         return 0;
     }
     return 1;

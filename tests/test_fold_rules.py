@@ -115,3 +115,26 @@ def test_a_copys_columns_by_ranks_written(rule):
         return rule("columns", op, bl.BLINK_FUSE_TREE, mib * MIB // 4 // k, 1 << 16, *([-1] + [0] * (k - 1)))[0]
     assert [star(k, 1000) for k in (2, 3, 5, 6, 7, 8, 9, 10, 16)] == [16, 8, 8, 4, 4, 3, 3, 2, 2]
     assert [star(k, 100) for k in (2, 3, 5, 6, 7, 8, 9, 10, 16)] == [4, 4, 4, 4, 4, 3, 3, 2, 2]
+
+
+# Up to how many MiB read and written on 256 compute units a whole-tree payload has a workgroup per tile: (ranks, collective,
+# MiB).  tests/test_gpu_once.py runs both sides of them.
+ONCE_LINES = [(2, "allreduce", 160), (3, "allreduce", 160), (8, "allreduce", 160), (16, "allreduce", 160),
+              (3, "reduce", 160), (4, "reduce", 320), (8, "reduce", 320), (9, "reduce", 192),
+              (2, "gather", 160), (3, "gather", 256), (4, "gather", 384), (8, "gather", 384),
+              (2, "broadcast", 160), (4, "broadcast", 160), (8, "broadcast", 160),
+              (2, "allgather", 256), (4, "allgather", 192), (8, "allgather", 192), (10, "allgather", 208)]
+# bytes that a collective reads and writes per element of k ranks' payload
+MOVED = {"allreduce": lambda k: 8 * k, "reduce": lambda k: 4 * (k + 1), "gather": lambda k: 8 * (k - 1) / k,
+         "broadcast": lambda k: 4 * k, "allgather": lambda k: 4 * k}
+OPS = {"allreduce": bl.BLINK_OP_ALLREDUCE, "reduce": bl.BLINK_OP_REDUCE, "gather": bl.BLINK_OP_GATHER,
+       "broadcast": bl.BLINK_OP_BROADCAST, "allgather": bl.BLINK_OP_ALLGATHER}
+
+
+@pytest.mark.parametrize("k,op,mib", ONCE_LINES)
+def test_how_far_a_payload_has_a_workgroup_per_tile(rule, k, op, mib):
+    """Whichever rank is the root: the piece that a Gather's root keeps is not one that is copied."""
+    for root in {0, k // 2, k - 1}:
+        star = [-1 if v == root else root for v in range(k)]
+        for n, served in ((int(mib * MIB / MOVED[op](k)) - 4_099, 1), (int(mib * MIB / MOVED[op](k)) + 4_099, 0)):
+            assert rule("once", OPS[op], bl.BLINK_FUSE_TREE, n - n % k, 1 << 16, *star) == (served,), (root, n)

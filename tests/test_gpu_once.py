@@ -9,6 +9,7 @@ import synth_inputs as si
 from oracle import execute as ox
 from oracle import schedule as osch
 
+from test_fold_rules import MOVED, ONCE_LINES, OPS
 from test_gpu_fold import REDOPS, _slab, _stream, _tree
 
 pytestmark = pytest.mark.gpu
@@ -158,17 +159,13 @@ def test_copies_along_trees_with_different_roots():
     assert all(np.array_equal(a.cpu().numpy(), w) for a, w in zip(bufs, want)) and untouched()
 
 
-# traffic on either side of where drawn tickets take over, on 256 compute units: (ranks, collective, MiB of traffic there)
-@pytest.mark.parametrize("k,op,mib", [(2, "allreduce", 160), (3, "allreduce", 160), (8, "allreduce", 160),
-                                      (3, "reduce", 160), (8, "reduce", 320), (9, "reduce", 192), (3, "gather", 256), (4, "gather", 384),
-                                      (4, "broadcast", 160), (8, "broadcast", 160), (4, "allgather", 192), (10, "allgather", 208)])
+# traffic on either side of where drawn tickets take over, on 256 compute units
+@pytest.mark.parametrize("k,op,mib", ONCE_LINES)
 def test_both_sides_of_the_line(k, op, mib):
     stream = _stream()
     trees, roots, _ = _forest(k, [1.0])
     root = roots[0]
-    code = {"allreduce": bl.BLINK_OP_ALLREDUCE, "reduce": bl.BLINK_OP_REDUCE, "gather": bl.BLINK_OP_GATHER,
-            "broadcast": bl.BLINK_OP_BROADCAST, "allgather": bl.BLINK_OP_ALLGATHER}[op]
-    per = {"allreduce": 8 * k, "reduce": 4 * (k + 1), "gather": 8 * (k - 1) / k}.get(op, 4 * k)
+    code, per = OPS[op], MOVED[op](k)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(k)
     for n in (int(mib * 2**20 / per) - 4_099, int(mib * 2**20 / per) + 4_099):
