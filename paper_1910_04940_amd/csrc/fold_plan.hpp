@@ -265,13 +265,14 @@ BLINK_HOST_DEVICE inline uint32_t once_edges(uint32_t call) { return call >> 16;
 // so much in length that workgroups without a tile (those beyond a shorter flow's end, which end at once) would outnumber the
 // others.  Copies: what goes from one rank to the same others all along is one flow, whatever trees it was split among (a
 // Broadcast has one, an AllGather one per piece), and a stretch that does not move (a Gather's root's own piece) is one
-// without stores.
+// without stores, unless it lies at either end of the payload: there it is left out.  (Its workgroups end at once, but where it came
+// first they were in front of all others: Gather of 2 ranks, 130 to 160 MiB moved, 24.7 us, 23.0 without them, of 3 24.0 / 23.2.)
 constexpr uint64_t kOnceMostElems = (1ull << 29) - 65536;
 inline std::vector<FoldFlow> once_flows(std::vector<FoldFlow> flows, uint64_t n, bool copies) {
     if (flows.empty() || n >= kOnceMostElems) return {};
     std::sort(flows.begin(), flows.end(), [](const FoldFlow& a, const FoldFlow& b) { return a.off < b.off; });
     std::vector<FoldFlow> out;
-    uint64_t at = 0, longest = 0;
+    uint64_t at = copies ? flows.front().off : 0, longest = 0;
     auto put = [&](const FoldFlow& f) {
         const bool joins = copies && !out.empty() && out.back().seq[0] == f.seq[0] && out.back().stores == f.stores;
         if (joins)
@@ -281,18 +282,16 @@ inline std::vector<FoldFlow> once_flows(std::vector<FoldFlow> flows, uint64_t n,
         at += f.len;
         longest = std::max(longest, out.back().len);
     };
-    auto hole = [&](uint64_t until) {
-        FoldFlow f{};
-        f.off = at, f.len = until - at;
-        put(f);
-    };
     for (const FoldFlow& f : flows) {
         if (f.off < at || (f.off > at && !copies)) return {};
-        if (f.off > at) hole(f.off);
+        if (f.off > at) {
+            FoldFlow hole{};
+            hole.off = at, hole.len = f.off - at;
+            put(hole);
+        }
         put(f);
     }
     if (at > n || (at < n && !copies)) return {};
-    if (at < n) hole(n);
     if (out.size() > kOnceMostFlows || longest * out.size() > 2 * n) return {};
     return out;
 }

@@ -3,6 +3,7 @@
 //   fold_rules_check policy N_LOAD N_STORE PAYLOAD KERNEL_BYTES HAS_DEPS WAY ALTERNATES   -> 0 keep, 1 stream, 2 spread
 //   fold_rules_check columns OP FUSION N CHUNK PARENT...       -> columns of a copy along one tree
 //   fold_rules_check once OP FUSION N CHUNK PARENT...          -> a workgroup per tile on 256 compute units (along one tree)
+//   fold_rules_check flows OP FUSION N CHUNK PARENT...         -> that kernel's flows: first element, elements, ranks written
 #include <cstdio>
 #include <cstdlib>
 #include <string>
@@ -22,7 +23,7 @@ int main(int argc, char** argv) {
                                                number(6) != 0, static_cast<int>(number(7)), number(8) != 0));
         return 0;
     }
-    if (what == "columns" || what == "once") {
+    if (what == "columns" || what == "once" || what == "flows") {
         blink::Trees trees;
         trees.k = argc - 6;
         trees.weight.push_back(1.0);
@@ -42,7 +43,11 @@ int main(int argc, char** argv) {
         } else {
             blink::FoldTables t;
             blink::fold_tables(s, &t);
-            std::printf("%d\n", blink::once_serves(s, t.once, 256));
+            if (what == "once") std::printf("%d\n", blink::once_serves(s, t.once, 256));
+            if (what == "flows")
+                for (const blink::FoldFlow& f : t.once)
+                    std::printf("%llu %llu %d\n", static_cast<unsigned long long>(f.off), static_cast<unsigned long long>(f.len),
+                                __builtin_popcount(f.stores & 0xffffu));
         }
         return 0;
     }

@@ -138,3 +138,15 @@ def test_how_far_a_payload_has_a_workgroup_per_tile(rule, k, op, mib):
         star = [-1 if v == root else root for v in range(k)]
         for n, served in ((int(mib * MIB / MOVED[op](k)) - 4_099, 1), (int(mib * MIB / MOVED[op](k)) + 4_099, 0)):
             assert rule("once", OPS[op], bl.BLINK_FUSE_TREE, n - n % k, 1 << 16, *star) == (served,), (root, n)
+
+
+@pytest.mark.parametrize("k", [2, 3, 5, 8])
+def test_the_piece_that_a_gathers_root_keeps(rule, k):
+    """No workgroups for it, unless it lies between pieces that move."""
+    for m in (1, 5_003):
+        for root in range(k):
+            star = [-1 if v == root else root for v in range(k)]
+            got = rule("flows", OPS["gather"], bl.BLINK_FUSE_TREE, k * m, 1 << 16, *star)
+            want = [(v * m, m, int(v != root)) for v in range(k)]
+            want = want[1:] if root == 0 else want[:-1] if root == k - 1 else want
+            assert got == tuple(x for w in want for x in w), (m, root)
