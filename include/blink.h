@@ -383,7 +383,11 @@ blink_status_t blink_schedule_set_launch(blink_schedule_t* s, int wg_per_cu, int
  * them waits for them, and the fastest way serves from then on, whatever the operator.  Sums, and the other operators on either element type, go
  * round by themselves; whichever is done first decides.  blink_allreduce_noalloc takes no
  * part in the timing: it uses way 1 until there is a pick, then that.  Payloads of a few
- * tiles per compute unit use way 1.  blink_schedule_reset, blink_schedule_set_sweep to
+ * tiles per compute unit use way 1, whatever is asked for.  So do, unless a way, a sweep that
+ * does not alternate or a launch shape is asked for, larger ones that have a workgroup per tile all
+ * the same (on a whole card a Reduce of 4 to 8 ranks that reads and writes up to 320 MiB, of
+ * more ranks 192, a Gather to one root 256 to 384, an AllGather 192 to 256).
+ * blink_schedule_reset, blink_schedule_set_sweep to
  * another mode and blink_schedule_set_launch to another tile size start the timing afresh;
  * 1, 2, 3 = that way, or way 1 where the schedule does not have it.
  * blink_schedule_last_kernel: the way the latest call ran (0 before the first
@@ -401,9 +405,10 @@ int blink_schedule_last_kernel(const blink_schedule_t* s);
  * copies to one rank that move more than it holds, from the same line; and data that one rank
  * sends to several always streams.  alternate = 0: every call goes forwards and
  * streams its stores past the cache (sums whose buffers, and copies to one rank whose
- * traffic, do not fit it).  Same bits either
- * way; schedules with
- * dependencies and blink_allreduce_noalloc always go forwards. */
+ * traffic, do not fit it).  Same bits either way.  Schedules with dependencies and
+ * blink_allreduce_noalloc always go forwards; payloads that have a workgroup per tile (see
+ * blink_schedule_set_kernel) have no direction, and their results may stay in the cache (data
+ * that one rank sends to several streams). */
 blink_status_t blink_schedule_set_sweep(blink_schedule_t* s, int alternate);
 
 /* always = 1: the stages of an EDGE or NODE program hand their chunks over to one another
@@ -424,7 +429,7 @@ int blink_schedule_handed_over(const blink_schedule_t* s);
  * blink_schedule_reset.  The rank buffers of an abandoned call hold partial
  * results.  Nothing but a bug (or two calls overlapping on one schedule) makes
  * a wait that long.
- * Payloads of more than a few tiles per compute unit that are served in one pass have their
+ * Payloads that are served in one pass and have no workgroup per tile (see blink_schedule_set_kernel) have their
  * tiles dealt out by a counter.  There a call that overlaps with another call on the schedule is
  * noticed by the counter's answers: the record is set, with no stage in it, both calls' results
  * are partial, and later calls do nothing until blink_schedule_reset. */

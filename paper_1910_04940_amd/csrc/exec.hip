@@ -195,11 +195,13 @@ void plan_hand_over(blink_schedule* h) {
 
 // The plan where the fold kernel runs the schedule.  A drawn ticket is one sub-tile of the
 // kernel, or as many as make it move 56 KiB, which two counters keep up with (see fold_grid).
-// A payload that blink_once serves (see once_bytes_per_cu), or one it cannot of at most five tiles (of 128 KiB read
-// and written) per CU, gets a workgroup for every tile, and no ticket has to be drawn.  Where ranks are combined they are all resident at once or nearly so; the
+// A payload of at most five tiles (of 128 KiB read and written) per CU gets a workgroup for every tile, and no ticket has to
+// be drawn, unless blink_once can serve such schedules and no longer does at this size (see once_bytes_per_cu).  Where ranks are
+// combined they are all resident at once or nearly so; the
 // small tiles of a copy need not be (to two ranks a CU gets up to 27 workgroups and holds eight) (probe, 8 ranks,
 // workgroup per tile against 224 that draw: 2 MiB per rank 5.1 / 7.2 us, 4 MiB 9.6 /
-// 10.8, 7 MiB (3.5 tiles per CU) 14.4 / 16.2, 10.4 MiB (5.2) 25 / 25, 16 MiB 51 / 47).
+// 10.8, 7 MiB (3.5 tiles per CU) 14.4 / 16.2, 10.4 MiB (5.2) 25 / 25, 16 MiB 51 / 47).  Larger ones that blink_once
+// serves draw tickets where a caller's wish takes them to this kernel (see once_call_serves).
 constexpr unsigned kFoldTicketBytes = 56 * 1024;
 constexpr unsigned kFoldRunElems = 32 * 1024;
 constexpr uint64_t kFoldSmallBytesPerCu = 5 * 128 * 1024;
@@ -226,7 +228,7 @@ void plan_fold(blink_schedule* h) {
     const bool once_can = h->tile_override == 0 && !h->fold.once.empty();
     pl.once = once_can && once_serves(s, h->fold.once, cus);
     pl.once_half = pl.kernel_bytes <= kOnceHalfBytesPerCu * cus;
-    pl.small = pl.once || (!once_can && tiles * sub * 4 * (pl.n_load + n_store) <= kFoldSmallBytesPerCu * cus);
+    pl.small = (pl.once || !once_can) && tiles * sub * 4 * (pl.n_load + n_store) <= kFoldSmallBytesPerCu * cus;
     // a tile per flow more than that: shares need not be whole tiles
     pl.half = pl.small && pl.all && tiles <= kFoldHalfTilesPerCu * cus + h->fold.flows.size();
     if (pl.small && n == 1 && n_store > 1 && tiles > cus) pl.copy_columns = kCopyColumnsSmall;   // (one tile per CU at most: no difference)
@@ -503,7 +505,7 @@ blink_status_t run_fold(blink_schedule* h, void* const* bufs, blink_dtype_t dtyp
     for (int i = 1; i < s.k; ++i) common = common && (reinterpret_cast<uintptr_t>(bufs[i]) & 1023u) == past;
     if (common) grid_shift = static_cast<uint32_t>(past / 4);
     const FoldTables& t = h->fold;
-    if (pl.once && h->wg_per_cu == 0) {
+    if (pl.once && once_call_serves(pl.small, s.has_deps, h->wg_per_cu, h->kernel_choice, h->sweep_alternates)) {
         if (static_block) h->static_record = false;
         if (blink_status_t st = run_once(h, bufs, dtype, redop, stream, grid_shift)) return st;
         h->last_kernel = 1;

@@ -225,6 +225,14 @@ inline bool once_serves(const Schedule& s, const std::vector<FoldFlow>& once, ui
                                                     static_cast<uint32_t>(__builtin_popcount(from)));
 }
 
+// Whether it serves a call on a schedule that it serves.  It has one order and one policy of stores, and as many workgroups as
+// tiles: a caller who asks for a grid, for a way, or for sweeps that do not alternate gets them from the other kernel.  Except
+// for the way and the sweep of a few tiles per CU (small: the other kernel has a workgroup for each there too, and all of them
+// fit the memory-side cache) and of programs with dependencies, which have neither.
+inline bool once_call_serves(bool small, bool has_deps, int wg_per_cu, int kernel_choice, bool alternates) {
+    return wg_per_cu == 0 && (small || has_deps || (kernel_choice == 0 && alternates));
+}
+
 // What a workgroup of that kernel has: byte offsets from the start of every rank buffer.
 struct OnceRange {
     int32_t origin;        // where the flow's tile 0 starts on the tile grid (see fold_range): a multiple of 16

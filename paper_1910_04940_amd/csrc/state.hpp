@@ -22,9 +22,9 @@ struct LaunchPlan {
     uint64_t n_items = 0;          // tickets per call
     // what the fold kernel runs (fold.hpp)
     bool fold = false;
-    bool small = false;            // a workgroup for every tile
+    bool small = false;            // a few tiles per CU: a workgroup for every one
     bool half = false;             // tiles of half the size (where small)
-    bool once = false;             // by the kernel that does nothing else (fold_once.hpp)
+    bool once = false;             // served by the kernel that does nothing else (fold_once.hpp), see once_call_serves
     bool once_half = false;        // there: tiles of half the size
     int once_stores = 0;           // copies there: the most ranks a flow is copied to
     OnceGrid once_grid{};          // made for once_shift

@@ -4,6 +4,7 @@
 //   fold_rules_check columns OP FUSION N CHUNK PARENT...       -> columns of a copy along one tree
 //   fold_rules_check once OP FUSION N CHUNK PARENT...          -> a workgroup per tile on 256 compute units (along one tree)
 //   fold_rules_check flows OP FUSION N CHUNK PARENT...         -> that kernel's flows: first element, elements, ranks written
+//   fold_rules_check call SMALL HAS_DEPS WG_PER_CU KERNEL ALTERNATES   -> a call by that kernel
 #include <cstdio>
 #include <cstdlib>
 #include <string>
@@ -21,6 +22,11 @@ int main(int argc, char** argv) {
     if (what == "policy") {
         std::printf("%d\n", blink::fold_policy(static_cast<uint32_t>(number(2)), static_cast<uint32_t>(number(3)), number(4), number(5),
                                                number(6) != 0, static_cast<int>(number(7)), number(8) != 0));
+        return 0;
+    }
+    if (what == "call") {
+        std::printf("%d\n", blink::once_call_serves(number(2) != 0, number(3) != 0, static_cast<int>(number(4)), static_cast<int>(number(5)),
+                                                    number(6) != 0));
         return 0;
     }
     if (what == "columns" || what == "once" || what == "flows") {

@@ -150,3 +150,14 @@ def test_the_piece_that_a_gathers_root_keeps(rule, k):
             want = [(v * m, m, int(v != root)) for v in range(k)]
             want = want[1:] if root == 0 else want[:-1] if root == k - 1 else want
             assert got == tuple(x for w in want for x in w), (m, root)
+
+
+def test_what_a_caller_asks_for_comes_from_the_kernel_that_has_it(rule):
+    """Beyond a few tiles per compute unit a way, a sweep that does not alternate and a grid are the drawing kernel's."""
+    for small in (0, 1):
+        for deps in (0, 1):
+            assert rule("call", small, deps, 0, 0, 1) == (1,)
+            for wg in (1, 4):
+                assert rule("call", small, deps, wg, 0, 1) == (0,)
+            for kernel, alternates in ((1, 1), (2, 1), (3, 1), (0, 0), (2, 0)):
+                assert rule("call", small, deps, 0, kernel, alternates) == (int(small or deps),)

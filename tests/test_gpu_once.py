@@ -186,3 +186,51 @@ def test_both_sides_of_the_line(k, op, mib):
         torch.cuda.synchronize()
         for r in ([root] if op in ("reduce", "gather") else range(k)):
             assert torch.equal(bufs[r], want), (n, r)
+
+
+# payloads with a workgroup per tile that are more than a few tiles per compute unit: (ranks, collective, MiB of traffic)
+@pytest.mark.parametrize("k,op,mib", [(8, "reduce", 180), (4, "reduce", 310), (8, "reduce", 318), (9, "reduce", 185), (3, "gather", 240),
+                                      (4, "gather", 370), (8, "gather", 200), (4, "allgather", 185), (10, "allgather", 200)])
+def test_wishes_beyond_a_few_tiles(k, op, mib):
+    """A way, a sweep or a grid that a caller asks for is served with it, and right, then the usual call again."""
+    stream = _stream()
+    trees = bl.blink_trees_from_arrays(k, [0, 0], [[-1] + [0] * (k - 1), list(range(-1, k - 1))], [1.0, 1.0])   # a star and a chain
+    n = int(mib * 2**20 / MOVED[op](k))
+    n -= n % k
+    m = n // k
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(k)
+    x = [torch.randint(-2**31, 2**31, (n,), dtype=torch.int32, device="cuda", generator=gen) for _ in range(k)]
+    if op == "reduce":
+        want = x[0].clone()
+        for b in x[1:]:
+            want += b
+    else:
+        want = torch.cat([b[r * m:(r + 1) * m] for r, b in enumerate(x)])
+    sched = bl.blink_make_schedule(trees, OPS[op], n, 1 << 18, bl.BLINK_FUSE_TREE)
+
+    def call(way):
+        bufs = [b.clone() for b in x]
+        for _ in range(1 if op == "reduce" else 2):        # (a second gather finds what the first one left)
+            if op == "reduce":
+                bl.blink_reduce(bufs, n, bl.BLINK_INT32, bl.BLINK_SUM, sched, stream)
+            else:
+                getattr(bl, "blink_" + op)(bufs, n, bl.BLINK_INT32, sched, stream)
+        assert sched.status()[0] == bl.BLINK_OK
+        if way:
+            assert sched.last_kernel == way
+        for r in (range(k) if op == "allgather" else [0]):
+            assert torch.equal(bufs[r], want), (way, r)
+
+    call(1)
+    for kernel, way in ((2, 2), (3, 1 if op == "reduce" and k > 8 else 3), (1, 1), (0, 1)):
+        sched.set_kernel(kernel)
+        call(way)
+    sched.set_sweep(False)
+    call(0)
+    sched.set_sweep(True)
+    sched.set_launch(2, 0)
+    call(0)
+    sched.set_launch(0, 0)
+    sched.reset()
+    call(1)
