@@ -66,7 +66,7 @@ class BlinkError(RuntimeError):
 
 _lib = None
 _hip = None
-# _blinkcall.call (see csrc/call.c) once the library is loaded, and the addresses of its collectives.
+# _blinkcall.call (see csrc/call.c) once the library is loaded, where that module is built, and the addresses of its collectives.
 _call = lambda *arguments: None
 _at = dict.fromkeys(("blink_allreduce", "blink_allreduce_noalloc", "blink_broadcast", "blink_allgather", "blink_gather",
                      "blink_allreduce_op", "blink_reduce"), 0)
@@ -162,10 +162,14 @@ def lib() -> C.CDLL:
     L.blink_miad_free.restype = None
     L.blink_strerror.argtypes = [C.c_int]
     L.blink_strerror.restype = C.c_char_p
-    from . import _blinkcall
-    for name in _at:
-        _at[name] = C.cast(getattr(L, name), vp).value
-    _call = _blinkcall.call
+    try:
+        from . import _blinkcall
+    except ImportError:   # not built, or for another interpreter: ctypes does as well
+        pass
+    else:
+        for name in _at:
+            _at[name] = C.cast(getattr(L, name), vp).value
+        _call = _blinkcall.call
     _lib = L
     return L
 

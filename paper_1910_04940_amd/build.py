@@ -1,5 +1,5 @@
 """Compile the HIP library in-tree: csrc/* -> libblink.so (gfx950 only), and the Python
-module that calls it (_blinkcall.so).
+module that calls it (_blinkcall, without which calls go through ctypes).
 
 The objects are linked WITHOUT a dependency on a particular libamdhip64: a
 process must hold exactly one HIP runtime, and a PyTorch wheel brings its own.
@@ -15,7 +15,8 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libblink.so")
-CALL = os.path.join(HERE, "_blinkcall.so")   # call.c: a Python module, host code only
+# call.c: a Python module, host code only.  Its name carries the interpreter it is for: another one does not load it.
+CALL = os.path.join(HERE, "_blinkcall" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 SOURCES = ["kernel_f32.hip", "kernel_i32.hip",
            "fold_f32_sum.hip", "fold_i32_sum.hip", "fold_f32_other.hip", "fold_i32_other.hip",
            "fold_once_f32_sum.hip", "fold_once_i32_sum.hip", "fold_once_f32_other.hip", "fold_once_i32_other.hip",
@@ -56,12 +57,25 @@ def build(verbose: bool = False) -> str:
     if verbose:
         print(" ".join(link), flush=True)
     subprocess.run(link, check=True)
-    call = [os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
-            os.path.join(CSRC, "call.c"), "-o", CALL]
-    if verbose:
-        print(" ".join(call), flush=True)
-    subprocess.run(call, check=True)
+    build_call(CALL, verbose)
     return LIB
+
+
+def build_call(to: str, verbose: bool = False) -> bool:
+    """The module of call.c.  It saves a call a microsecond of host time and nothing depends on it: where there is no C
+    compiler or no Python headers none is left behind, and the caller is told."""
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "call.c"), "-o", to]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    try:
+        subprocess.run(cmd, check=True)
+        return True
+    except (OSError, subprocess.CalledProcessError) as e:
+        if os.path.exists(to):
+            os.remove(to)
+        print(f"{os.path.basename(to)} was not built, calls go through ctypes: {e}", file=sys.stderr, flush=True)
+        return False
 
 
 if __name__ == "__main__":

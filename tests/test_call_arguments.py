@@ -2,13 +2,16 @@
 through the native module, and everything else through ctypes, with the same outcome.  Calls on
 an empty payload look at no buffer.  No GPU."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
 
 import paper_1910_04940_amd as bl
 import synth_inputs as si
-from paper_1910_04940_amd import binding
+from paper_1910_04940_amd import binding, build
 
 torch = pytest.importorskip("torch")
 
@@ -100,3 +103,32 @@ def test_the_usual_call_is_native(monkeypatch):
     monkeypatch.setattr(binding, "_pointers", lambda bufs: pytest.fail("through ctypes"))
     bl.blink_allreduce([torch.zeros(8) for _ in range(4)], 0, bl.BLINK_FP32, s, 0)
     bl.blink_reduce([16, 32, 48, 64], 0, bl.BLINK_FP32, bl.BLINK_SUM, _schedule(op=bl.BLINK_OP_REDUCE))
+
+
+def test_without_the_native_module():
+    """Packing, scheduling and calls work on the library alone."""
+    code = """
+import sys
+sys.modules["paper_1910_04940_amd._blinkcall"] = None     # what importing it then raises is an ImportError
+import paper_1910_04940_amd as bl
+import synth_inputs as si
+t = si.complete_graph(4)
+s = bl.blink_make_schedule(bl.blink_pack_trees(t.k, t.src, t.dst, t.cap, 0), bl.BLINK_OP_ALLREDUCE, 0, 16)
+bl.blink_allreduce([16, 32, 48, 64], 0, bl.BLINK_FP32, s)
+try:
+    bl.blink_allreduce([16, 32, 48], 0, bl.BLINK_FP32, s)
+except bl.BlinkError as e:
+    print("status", e.status == bl.BLINK_EMISMATCH)
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", code], cwd=root, check=True, capture_output=True, text=True).stdout
+    assert out.split() == ["status", "True"]
+
+
+def test_a_module_that_cannot_be_built_is_said_and_left_out(tmp_path, monkeypatch, capfd):
+    to = str(tmp_path / "_blinkcall.so")
+    assert build.build_call(to) and os.path.exists(to)
+    for compiler in ("false", str(tmp_path / "no such compiler")):
+        monkeypatch.setenv("CC", compiler)
+        assert not build.build_call(to) and not os.path.exists(to)
+        assert "ctypes" in capfd.readouterr().err
