@@ -314,7 +314,8 @@ void blink_schedule_free(blink_schedule_t* s);
  * (BLINK_EMISMATCH otherwise).  With n_elems == 0 the call does nothing and
  * does not look at the entries of bufs (they may be null).  The first call
  * on a schedule that needs them also allocates and fills its small device-side tables
- * (synchronously). */
+ * (synchronously); so does the first after blink_schedule_set_hand_over where chunks handed on in
+ * pieces need larger ones. */
 blink_status_t blink_allreduce(void* const* bufs, int k, size_t n_elems, blink_dtype_t dtype,
                                blink_schedule_t* s, void* stream);
 blink_status_t blink_broadcast(void* const* bufs, int k, size_t n_elems, blink_dtype_t dtype,

@@ -17,9 +17,6 @@ namespace blink {
 // it only through the address hipGetSymbolAddress returns with that GPU current
 // (the array's name in host code is a host-side stand-in, not a device address).
 // All calls of blink_allreduce_noalloc on one GPU share that GPU's block.
-constexpr size_t kStaticBlockBytes = 4u << 20;
-// A block of a schedule's own has room for more counters (see hand_over_pieces).
-constexpr size_t kMostCounterBytes = 32u << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticBlockBytes];
 
 namespace {
@@ -58,12 +55,16 @@ KernelFn pick_kernel(blink_dtype_t dtype) { return dtype == BLINK_FP32 ? kernel_
 
 size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-BlockLayout layout_of(const Schedule& s, bool static_block) {
-    constexpr size_t kLine = static_cast<size_t>(kCounterStride) * sizeof(unsigned long long);
+// The status record and the ticket counters, at the head of a block whatever follows.
+constexpr size_t kLine = static_cast<size_t>(kCounterStride) * sizeof(unsigned long long);
+constexpr size_t kTicketAt = static_cast<size_t>(kStatusWords) * sizeof(unsigned long long);   // the fold kernel relies on it
+constexpr size_t kHeadBytes = kTicketAt + kMaxQueues * kLine;
+
+BlockLayout layout_of(const Schedule& s, Served served, bool static_block) {
     BlockLayout l;
-    l.ticket = static_cast<size_t>(kStatusWords) * sizeof(unsigned long long);   // the fold kernel relies on it
-    l.done = l.ticket + kMaxQueues * kLine;
-    l.pieces = hand_over_pieces(s, kLine, static_block ? kStaticBlockBytes / 2 : kMostCounterBytes);   // (half: the tables fit as well)
+    l.ticket = kTicketAt;
+    l.done = kHeadBytes;
+    l.pieces = counters_per_stage(s, served, kLine, static_block);
     l.counters_end = l.done + s.inst.size() * l.pieces * kLine;
     l.tmpl = round_up(l.counters_end, 256);
     l.inst = round_up(l.tmpl + s.tmpl.size() * sizeof(StageTmpl), 256);
@@ -104,16 +105,16 @@ blink_status_t bind_device(blink_schedule* h) {
     return BLINK_OK;
 }
 
-// The schedule's own block: one allocation, made at the first call that needs it.
+// The schedule's own block: one allocation, made at the first call that needs it and
+// made anew where a plan needs a larger one (chunks that are handed on in pieces, on a caller's request).
 // Synchronously zeroed and filled, then and when a new plan needs other tables.
 // Nothing is left behind when a step fails.
 blink_status_t upload(blink_schedule* h, const BlockLayout& l) {
     if (h->d_block && !h->tables_stale) return BLINK_OK;
     void* block = h->d_block;
-    if (block)
-        BLINK_HIP(hipDeviceSynchronize());   // calls under the old plan
-    else
-        BLINK_HIP(hipMalloc(&block, l.bytes));
+    if (block) BLINK_HIP(hipDeviceSynchronize());   // calls under the old plan
+    const bool anew = h->block_bytes < l.bytes;
+    if (anew) BLINK_HIP(hipMalloc(&block, l.bytes));
     blink_status_t st = BLINK_OK;
     const hipError_t zeroed = hipMemset(block, 0, cleared_bytes(h->plan, l));
     if (zeroed != hipSuccess) {
@@ -122,11 +123,15 @@ blink_status_t upload(blink_schedule* h, const BlockLayout& l) {
     }
     if (st == BLINK_OK) st = copy_tables(*h, l, static_cast<char*>(block));
     if (st != BLINK_OK) {
-        if (!h->d_block) (void)hipFree(block);
+        if (anew) (void)hipFree(block);
         return st;
     }
+    if (anew) {
+        if (h->d_block) (void)hipFree(h->d_block);
+        h->d_block = block;
+        h->block_bytes = l.bytes;
+    }
     BLINK_HIP(hipDeviceSynchronize());
-    h->d_block = block;
     h->tables_stale = false;
     return BLINK_OK;
 }
@@ -259,6 +264,8 @@ blink_status_t make_plan(blink_schedule* h) {
         plan_fold(h);
     else
         plan_hand_over(h);
+    pl.own = layout_of(h->s, served, false);
+    pl.shared = layout_of(h->s, served, true);
     pl.made = true;
     return BLINK_OK;
 }
@@ -281,8 +288,8 @@ blink_status_t reset_progress(blink_schedule* h) {
     if (h->device < 0) return BLINK_OK;
     BLINK_HIP(hipDeviceSynchronize());
     if (!h->d_block) return BLINK_OK;
-    // the next call's tables go in with it (see upload); the status record is read before
-    BLINK_HIP(hipMemset(h->d_block, 0, layout_of(h->s, false).counters_end));
+    // the next call's counters and tables go in with it (see upload); the status record is read before
+    BLINK_HIP(hipMemset(h->d_block, 0, kHeadBytes));
     BLINK_HIP(hipDeviceSynchronize());
     return BLINK_OK;
 }
@@ -395,6 +402,7 @@ void release_device_state(blink_schedule* h) {
     drop_trial_events(h);
     if (h->d_block) (void)hipFree(h->d_block);
     h->d_block = nullptr;
+    h->block_bytes = 0;
     h->device = -1;
 }
 
@@ -693,7 +701,7 @@ blink_status_t execute(blink_schedule* h, void* const* bufs, int k, size_t n, bl
     }
     if (s.inst.empty()) return BLINK_OK;
     if (blink_status_t st = make_plan(h)) return st;
-    const BlockLayout l = layout_of(s, static_block);
+    const BlockLayout& l = static_block ? h->plan.shared : h->plan.own;
     char* block = nullptr;   // the static block, or null: the schedule's own
     if (static_block) {
         if (blink_status_t st = claim_static_block(h, l, static_cast<hipStream_t>(stream), &block)) return st;

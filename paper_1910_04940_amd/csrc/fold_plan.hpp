@@ -446,6 +446,13 @@ inline Served served_by(const Schedule& s, bool fold_fits, bool hand_over) {
     return s.fusion == BLINK_FUSE_NODE || in_cache ? Served::kFold : Served::kHandOver;
 }
 
+// Counters of finished tiles per stage instance in a block: pieces' only where chunks are handed over, the other kernels count no
+// tiles.  The static block's pieces leave half of it for the tables; a schedule's own has room for more counters.
+constexpr size_t kStaticBlockBytes = 4u << 20, kMostCounterBytes = 32u << 20;
+inline uint32_t counters_per_stage(const Schedule& s, Served served, uint64_t counter_bytes, bool static_block) {
+    return served == Served::kHandOver ? hand_over_pieces(s, counter_bytes, static_block ? kStaticBlockBytes / 2 : kMostCounterBytes) : 1u;
+}
+
 // Tile sizes a caller may ask for: powers of two.
 constexpr uint32_t kLeastTileOverride = 256, kMostTileOverride = 65536;
 // Sets of levels that lie on the device where a schedule's tables do: one per such tile

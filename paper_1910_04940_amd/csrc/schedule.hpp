@@ -177,6 +177,7 @@ inline uint64_t ticket_count(const Schedule& s, unsigned group, unsigned tile_sh
 // Pieces of 128 and 64 KiB: within 1 % (16 ranks x 32 MiB 340 / 330 / 326).  Smaller chunks are one piece: what a
 // caller who tunes the chunk size measures there is the chunk.
 // block_bytes: room for counters, counter_bytes apart, and instances; where the pieces' do not fit chunks have one each.
+// Looks at every instance.
 constexpr unsigned kPieceShift = 16;
 inline uint32_t hand_over_pieces(const Schedule& s, uint64_t counter_bytes, uint64_t block_bytes) {
     if (!s.has_deps || s.chunk < (2ull << kPieceShift)) return 1;

@@ -9,6 +9,20 @@
 
 namespace blink {
 
+// Layout of the device block of a schedule, in bytes from its start:
+//   status record (kStatusWords 64-bit words), ticket counters, a counter of
+//   finished tiles per stage instance, or per piece of it (counters kCounterStride words apart),
+//   stage templates, stage instances.  The fold kernel counts no finished tiles and
+//   knows neither templates nor instances: its
+//   tables, where they do not travel in the kernel's arguments, lie where the counters
+//   of finished tiles would (they need 204 of every 256 bytes there).
+struct BlockLayout {
+    size_t ticket = 0, done = 0, tmpl = 0, inst = 0, bytes = 0;
+    uint32_t pieces = 1;      // counters per stage instance (see counters_per_stage)
+    size_t counters_end = 0;  // status record and counters are [0, counters_end)
+    size_t words = 0;         // FoldTables::tables
+};
+
 // What a launch needs besides the schedule itself.  It depends only on the
 // schedule, the device and the caller's overrides, so it is worked out once, at
 // the first call, and kept until an override changes (the progress counters
@@ -16,6 +30,7 @@ namespace blink {
 struct LaunchPlan {
     bool made = false;
     unsigned tile_elems = 0;       // elements per tile (ticket)
+    BlockLayout own, shared;       // of the schedule's own block and of a device's static one
     // stages that wait for one another (kernel.hpp)
     unsigned tile_shift = 0;       // log2 of tile_elems
     uint32_t tiles_per_chunk = 1;  // most tiles any stage instance has
@@ -39,20 +54,6 @@ struct LaunchPlan {
     uint32_t grid_shift = 0;       // the tile grid the levels were made for
 };
 
-// Layout of the device block of a schedule, in bytes from its start:
-//   status record (kStatusWords 64-bit words), ticket counters, a counter of
-//   finished tiles per stage instance, or per piece of it (counters kCounterStride words apart),
-//   stage templates, stage instances.  The fold kernel counts no finished tiles and
-//   knows neither templates nor instances: its
-//   tables, where they do not travel in the kernel's arguments, lie where the counters
-//   of finished tiles would (they need 204 of every 256 bytes there).
-struct BlockLayout {
-    size_t ticket = 0, done = 0, tmpl = 0, inst = 0, bytes = 0;
-    uint32_t pieces = 1;      // counters per stage instance (see hand_over_pieces)
-    size_t counters_end = 0;  // status record and counters are [0, counters_end)
-    size_t words = 0;         // FoldTables::tables
-};
-
 }  // namespace blink
 
 struct blink_schedule {
@@ -61,6 +62,7 @@ struct blink_schedule {
     blink::LaunchPlan plan;
     int device = -1;              // HIP device the schedule has run on; -1 = none yet
     void* d_block = nullptr;      // its block there (see BlockLayout); null = not needed so far
+    size_t block_bytes = 0;       // of that block
     bool tables_stale = true;     // the block's tables are not those of the plan
     uint64_t id = 0;              // names, with the kernel the tables are for, the owner of a device's static block
     uint64_t epoch = 0;           // calls made so far on d_block; its counters hold epoch * tiles

@@ -4,6 +4,8 @@
 //   fold_rules_check columns OP FUSION N CHUNK PARENT...       -> columns of a copy along one tree
 //   fold_rules_check once OP FUSION N CHUNK PARENT...          -> a workgroup per tile on 256 compute units (along one tree)
 //   fold_rules_check flows OP FUSION N CHUNK PARENT...         -> that kernel's flows: first element, elements, ranks written
+//   fold_rules_check counters OP FUSION N CHUNK PARENT...      -> counters per stage instance in an own and a shared block, as it is
+//                                                                 served and where waiting stages are asked for
 //   fold_rules_check call SMALL HAS_DEPS WG_PER_CU KERNEL ALTERNATES   -> a call by that kernel
 #include <cstdio>
 #include <cstdlib>
@@ -29,7 +31,7 @@ int main(int argc, char** argv) {
                                                     number(6) != 0));
         return 0;
     }
-    if (what == "columns" || what == "once" || what == "flows") {
+    if (what == "columns" || what == "once" || what == "flows" || what == "counters") {
         blink::Trees trees;
         trees.k = argc - 6;
         trees.weight.push_back(1.0);
@@ -50,6 +52,10 @@ int main(int argc, char** argv) {
             blink::FoldTables t;
             blink::fold_tables(s, &t);
             if (what == "once") std::printf("%d\n", blink::once_serves(s, t.once, 256));
+            if (what == "counters")
+                for (bool hand_over : {false, true})
+                    for (bool shared : {false, true})
+                        std::printf("%u\n", blink::counters_per_stage(s, blink::served_by(s, t.fits, hand_over), 256, shared));
             if (what == "flows")
                 for (const blink::FoldFlow& f : t.once)
                     std::printf("%llu %llu %d\n", static_cast<unsigned long long>(f.off), static_cast<unsigned long long>(f.len),

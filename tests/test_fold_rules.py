@@ -161,3 +161,16 @@ def test_what_a_caller_asks_for_comes_from_the_kernel_that_has_it(rule):
                 assert rule("call", small, deps, wg, 0, 1) == (0,)
             for kernel, alternates in ((1, 1), (2, 1), (3, 1), (0, 0), (2, 0)):
                 assert rule("call", small, deps, 0, kernel, alternates) == (int(small or deps),)
+
+
+@pytest.mark.parametrize("n,chunk,own,shared", [(3_000_000, 1 << 16, 1, 1), (3_000_000, 1 << 17, 2, 2), (3_000_000, 1 << 20, 16, 16),
+                                                (20_000_000, 1 << 17, 2, 1), (20_000_000, 1 << 22, 64, 1)])
+def test_only_stages_that_hand_over_have_counters_for_pieces(rule, n, chunk, own, shared):
+    """The kernels that carry a tile through all stages count none of them, so their blocks have no room for pieces; in the
+    shared block chunks have one counter each where those of pieces do not fit (the last two)."""
+    chain = list(range(-1, 15))
+    in_cache = 16 * 4 * n <= 256 * MIB
+    for fusion in (bl.BLINK_FUSE_EDGE, bl.BLINK_FUSE_NODE, bl.BLINK_FUSE_TREE):
+        waits = [own, shared] if fusion != bl.BLINK_FUSE_TREE else [1, 1]
+        as_served = waits if fusion == bl.BLINK_FUSE_EDGE and not in_cache else [1, 1]
+        assert rule("counters", OPS["allreduce"], fusion, n, chunk, *chain) == tuple(as_served + waits), fusion

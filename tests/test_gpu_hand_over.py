@@ -183,7 +183,7 @@ def test_what_the_switch_takes():
 
 
 # chunks that are handed on in pieces of 65,536 elements: whole and odd numbers of them, tiles as large as a
-# piece and as small as they get, more counters than the shared block has room for (then a chunk has one)
+# piece and as small as they get
 @pytest.mark.parametrize("n,chunk", [(300_007, 131_072), (1_000_003, 200_001), (1_000_003, 1 << 20), (500_001, 131_071)])
 @pytest.mark.parametrize("tile", [0, 256, 65_536])
 def test_chunks_in_pieces(n, chunk, tile):
@@ -199,6 +199,48 @@ def test_chunks_in_pieces(n, chunk, tile):
         call(bufs, n, bl.BLINK_INT32, sched, stream)
         assert sched.status()[0] == bl.BLINK_OK and sched.handed_over == 1
         assert all(np.array_equal(b.cpu().numpy(), want) for b in bufs) and untouched()
+
+
+def _in_place(sched, k, n, calls):
+    """Calls on device data, each against torch's sum."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(k)
+    x = [torch.randint(-2**31, 2**31, (n,), dtype=torch.int32, device="cuda", generator=gen) for _ in range(k)]
+    want = x[0].clone()
+    for b in x[1:]:
+        want += b
+    bufs = [torch.empty_like(b) for b in x]
+    for call in calls:
+        for b, a in zip(bufs, x):
+            b.copy_(a)
+        call(bufs, n, bl.BLINK_INT32, sched, _stream())
+        assert sched.status()[0] == bl.BLINK_OK
+        assert all(torch.equal(b, want) for b in bufs)
+        yield
+
+
+def test_more_pieces_than_the_shared_block_has_counters_for():
+    """A chunk has one counter there and a counter per piece in the schedule's own block."""
+    k, n, chunk = 16, 17_000_003, 131_072
+    trees = bl.blink_trees_from_arrays(k, [0], [list(range(-1, k - 1))], [1.0])
+    sched = _schedule(trees, bl.BLINK_OP_ALLREDUCE, n, chunk, "edge")
+    assert sched.num_stages * (2 * 256 + 56) > 2 << 20      # two counters and the stage itself
+    for _ in _in_place(sched, k, n, [bl.blink_allreduce_noalloc, bl.blink_allreduce, bl.blink_allreduce_noalloc, bl.blink_allreduce,
+                                     bl.blink_allreduce]):
+        assert sched.handed_over == 1
+
+
+def test_a_block_grows_with_the_pieces():
+    """Tickets are drawn from a block without counters of pieces; where waiting stages are asked for later it is made anew."""
+    k, n, chunk = 6, 6_000_007, 1 << 20
+    trees, _, _, _ = _forest(k, 2)
+    sched = _schedule(trees, bl.BLINK_OP_ALLREDUCE, n, chunk, "node")
+    served = [0, 0, 1, 1, 1, 0, 1, 1]
+    calls = _in_place(sched, k, n, [bl.blink_allreduce] * 4 + [bl.blink_allreduce_noalloc] + [bl.blink_allreduce] * 3)
+    for handed_over in served:
+        sched.set_hand_over(bool(handed_over))
+        next(calls)
+        assert sched.handed_over == handed_over
 
 
 def test_an_abandoned_wait_names_the_chunks_stages():
