@@ -329,21 +329,24 @@ struct OnceKernel {
 };
 static_assert(sizeof(OnceParams<BLINK_MAX_RANKS, kOnceMostFlows, true>) <= kOnceParamsBytes, "the largest");
 
+// (Two ranks form one sum, the result: no program writes it on the way.)
 template <typename T, bool ALL, bool SUM, bool MID, FoldTile TILE, bool MANY>
 OnceKernel pick_once(int n) {
     switch (n) {
 #define BLINK_CASE(N)                                                                                                                  \
-    case N: {                                                                                                                          \
-        constexpr int kFlows = MANY ? kOnceMostFlows : kOnceFewFlows;                                                                  \
-        return {reinterpret_cast<const void*>(                                                                                         \
-                    blink_once<T, N, kFlows, ALL, SUM, MID, fold_columns(N, ALL, TILE), ALL && TILE == FoldTile::kWhole>),             \
-                fill_once<N, kFlows, MID>, N,                                                                                          \
-                sizeof(void*) * N + 4 * (kFlows + 1 + once_words(N, kFlows) + once_mid_words(N, kFlows, MID))};                        \
-    }
+    case N:                                                                                                                            \
+        if constexpr (N > 2 || !MID) {                                                                                                 \
+            constexpr int kFlows = MANY ? kOnceMostFlows : kOnceFewFlows;                                                              \
+            return {reinterpret_cast<const void*>(                                                                                     \
+                        blink_once<T, N, kFlows, ALL, SUM, MID, fold_columns(N, ALL, TILE), ALL && TILE == FoldTile::kWhole>),         \
+                    fill_once<N, kFlows, MID>, N,                                                                                      \
+                    sizeof(void*) * N + 4 * (kFlows + 1 + once_words(N, kFlows) + once_mid_words(N, kFlows, MID))};                    \
+        }                                                                                                                              \
+        break;
         BLINK_FOLD_CASES
 #undef BLINK_CASE
-        default: return {};
     }
+    return {};
 }
 template <typename T, bool SUM, bool MID>
 OnceKernel pick_once(int n, bool all, bool half, bool many) {

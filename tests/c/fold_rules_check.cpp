@@ -6,6 +6,7 @@
 //   fold_rules_check flows OP FUSION N CHUNK PARENT...         -> that kernel's flows: first element, elements, ranks written
 //   fold_rules_check counters OP FUSION N CHUNK PARENT...      -> counters per stage instance in an own and a shared block, as it is
 //                                                                 served and where waiting stages are asked for
+//   fold_rules_check sums OP FUSION N CHUNK PARENT...          -> additions whose sum is written on the way
 //   fold_rules_check call SMALL HAS_DEPS WG_PER_CU KERNEL ALTERNATES   -> a call by that kernel
 #include <cstdio>
 #include <cstdlib>
@@ -31,7 +32,7 @@ int main(int argc, char** argv) {
                                                     number(6) != 0));
         return 0;
     }
-    if (what == "columns" || what == "once" || what == "flows" || what == "counters") {
+    if (what == "columns" || what == "once" || what == "flows" || what == "counters" || what == "sums") {
         blink::Trees trees;
         trees.k = argc - 6;
         trees.weight.push_back(1.0);
@@ -52,6 +53,8 @@ int main(int argc, char** argv) {
             blink::FoldTables t;
             blink::fold_tables(s, &t);
             if (what == "once") std::printf("%d\n", blink::once_serves(s, t.once, 256));
+            if (what == "sums")
+                for (const blink::FusedFlow& f : s.fused) std::printf("%d\n", __builtin_popcount(f.mid_store));
             if (what == "counters")
                 for (bool hand_over : {false, true})
                     for (bool shared : {false, true})

@@ -174,3 +174,12 @@ def test_only_stages_that_hand_over_have_counters_for_pieces(rule, n, chunk, own
         waits = [own, shared] if fusion != bl.BLINK_FUSE_TREE else [1, 1]
         as_served = waits if fusion == bl.BLINK_FUSE_EDGE and not in_cache else [1, 1]
         assert rule("counters", OPS["allreduce"], fusion, n, chunk, *chain) == tuple(as_served + waits), fusion
+
+
+def test_sums_written_on_the_way(rule):
+    """Of k ranks in a chain: per edge and per node all but the last, which is the result.  Two ranks have none."""
+    for k in (2, 3, 8):
+        chain = list(range(-1, k - 1))
+        for op in ("allreduce", "reduce"):
+            for fusion, sums in ((bl.BLINK_FUSE_EDGE, k - 2), (bl.BLINK_FUSE_NODE, k - 2), (bl.BLINK_FUSE_TREE, 0)):
+                assert rule("sums", OPS[op], fusion, 1_003, 1 << 16, *chain) == (sums,), (k, op, fusion)
