@@ -132,11 +132,11 @@ inline uint32_t fold_tiles(uint64_t off, uint64_t len, uint32_t tile_elems, uint
 }
 
 // Bytes the fold kernel reads plus writes in rank buffers per call: every rank it takes from
-// once, every rank of the result once, and the sums written on the way.
-inline uint64_t fold_bytes(const Schedule& s) {
+// once, every rank of the result once, and (sums) the sums written on the way.
+inline uint64_t fold_bytes(const Schedule& s, bool sums = true) {
     uint64_t bytes = 0;
     for (const FusedFlow& f : s.fused)
-        bytes += (f.hi - f.lo) * 4u * (f.stage.n_load + f.stage.n_store + static_cast<unsigned>(__builtin_popcount(f.mid_store)));
+        bytes += (f.hi - f.lo) * 4u * (f.stage.n_load + f.stage.n_store + (sums ? static_cast<unsigned>(__builtin_popcount(f.mid_store)) : 0u));
     return bytes;
 }
 
@@ -199,6 +199,14 @@ inline OnceGrid once_grid(const std::vector<FoldFlow>& flows, uint32_t most, uin
 // 1.08 up to 12; copies to one of 8 1.06 1.04 1.04 1.02, of 4 1.04 1.02 1.02 1.01, of 3 1.01 1.00 .99 .98 (so two sources
 // stop at 16); pieces to 7 1.01 up to 12, to 15 1.14 up to 13 and .87 to 1.1 up to 16 (so 13).
 // (sources: ranks that something is copied from.  A Gather's root is none: its own piece stays where it is.)
+//
+// Sums written on the way count up to 7 ranks, and in a Reduce of 4 to 8; with more ranks, and in a Reduce of 3, they do not:
+// between the two lines that makes, a workgroup per tile / drawn tickets, us by MiB without the sums:
+//   per edge, all ranks   8  117  22.98 / 24.15   130  23.65 / 25.97   150  27.82 / 28.63    16  121  24.76 / 26.30   141  27.31 / 29.41
+//   per node              8  137  22.08 / 23.31   150  24.40 / 25.10   159  26.35 / 27.30    16  137  23.44 / 24.98   159  28.26 / 29.82
+//   per edge, to one      3  140  23.57 / 24.50   155  25.89 / 26.51                         16  120  32.43 / 34.40   155  40.17 / 43.21
+// 12 ranks per edge 0.995, per node 0.996, to one 1.04 and 1.02 times as fast on average; drawn tickets faster: all ranks, 3 to 6
+// of them 1 to 3 %, 7 the same, to one, 4 to 8 per node 4 to 8 %, per edge -2 to 3 %.
 constexpr uint64_t kOnceLineUnit = 64 * 1024;
 inline uint64_t once_bytes_per_cu(uint32_t n_load, bool all, uint32_t n_store, uint32_t sources) {
     const uint64_t units = n_load > 1 && !all           ? (n_load < 4 ? 10 : n_load <= 8 ? 20 : 12)
@@ -221,8 +229,10 @@ inline bool once_serves(const Schedule& s, const std::vector<FoldFlow>& once, ui
     uint32_t from = 0;
     for (const FoldFlow& f : once)
         if (f.stores & 0xffffu) from |= 1u << (f.seq[0] & 15u);
-    return fold_bytes(s) <= cus * once_bytes_per_cu(st.n_load, !copies && st.n_store == st.n_load, copies ? once_stores(once) : st.n_store,
-                                                    static_cast<uint32_t>(__builtin_popcount(from)));
+    const bool all = !copies && st.n_store == st.n_load;
+    const bool sums = all ? st.n_load < 8 : st.n_load >= 4 && st.n_load <= 8;
+    return fold_bytes(s, sums) <= cus * once_bytes_per_cu(st.n_load, all, copies ? once_stores(once) : st.n_store,
+                                                          static_cast<uint32_t>(__builtin_popcount(from)));
 }
 
 // Whether it serves a call on a schedule that it serves.  It has one order and one policy of stores, and as many workgroups as

@@ -124,6 +124,9 @@ ONCE_LINES = [(2, "allreduce", 160), (3, "allreduce", 160), (8, "allreduce", 160
               (2, "gather", 160), (3, "gather", 256), (4, "gather", 384), (8, "gather", 384),
               (2, "broadcast", 160), (4, "broadcast", 160), (8, "broadcast", 160),
               (2, "allgather", 256), (4, "allgather", 192), (8, "allgather", 192), (10, "allgather", 208)]
+# The same for programs that write sums on the way: k - 2 of them per edge in a chain, of 4 bytes, where they count.
+ONCE_SUMS = [(3, "allreduce", 160, 1), (7, "allreduce", 160, 5), (8, "allreduce", 160, 0), (16, "allreduce", 160, 0),
+             (3, "reduce", 160, 0), (4, "reduce", 320, 2), (8, "reduce", 320, 6), (9, "reduce", 192, 0), (16, "reduce", 192, 0)]
 # bytes that a collective reads and writes per element of k ranks' payload
 MOVED = {"allreduce": lambda k: 8 * k, "reduce": lambda k: 4 * (k + 1), "gather": lambda k: 8 * (k - 1) / k,
          "broadcast": lambda k: 4 * k, "allgather": lambda k: 4 * k}
@@ -138,6 +141,15 @@ def test_how_far_a_payload_has_a_workgroup_per_tile(rule, k, op, mib):
         star = [-1 if v == root else root for v in range(k)]
         for n, served in ((int(mib * MIB / MOVED[op](k)) - 4_099, 1), (int(mib * MIB / MOVED[op](k)) + 4_099, 0)):
             assert rule("once", OPS[op], bl.BLINK_FUSE_TREE, n - n % k, 1 << 16, *star) == (served,), (root, n)
+
+
+@pytest.mark.parametrize("k,op,mib,sums", ONCE_SUMS)
+def test_how_far_programs_with_sums_on_the_way_have_one(rule, k, op, mib, sums):
+    chain = list(range(-1, k - 1))
+    line = int(mib * MIB / (MOVED[op](k) + 4 * sums))
+    for fusion in (bl.BLINK_FUSE_EDGE, bl.BLINK_FUSE_NODE):
+        for n, served in ((line - 4_099, 1), (line + 4_099, 0)):
+            assert rule("once", OPS[op], fusion, n, 1 << 16, *chain) == (served,), (fusion, n)
 
 
 @pytest.mark.parametrize("k", [2, 3, 5, 8])

@@ -9,7 +9,7 @@ import synth_inputs as si
 from oracle import execute as ox
 from oracle import schedule as osch
 
-from test_fold_rules import MOVED, ONCE_LINES, OPS
+from test_fold_rules import MOVED, ONCE_LINES, ONCE_SUMS, OPS
 from test_gpu_fold import REDOPS, _slab, _stream, _tree
 
 pytestmark = pytest.mark.gpu
@@ -159,13 +159,16 @@ def test_copies_along_trees_with_different_roots():
     assert all(np.array_equal(a.cpu().numpy(), w) for a, w in zip(bufs, want)) and untouched()
 
 
-# traffic on either side of where drawn tickets take over, on 256 compute units
-@pytest.mark.parametrize("k,op,mib", ONCE_LINES)
-def test_both_sides_of_the_line(k, op, mib):
+# traffic on either side of where drawn tickets take over, on 256 compute units; with sums written on the way along a chain
+@pytest.mark.parametrize("k,op,mib,sums", [line + (None,) for line in ONCE_LINES] + ONCE_SUMS)
+def test_both_sides_of_the_line(k, op, mib, sums):
     stream = _stream()
+    fusion = bl.BLINK_FUSE_TREE if sums is None else bl.BLINK_FUSE_EDGE
     trees, roots, _ = _forest(k, [1.0])
+    if sums is not None:
+        trees, roots = bl.blink_trees_from_arrays(k, [0], [list(range(-1, k - 1))], [1.0]), [0]
     root = roots[0]
-    code, per = OPS[op], MOVED[op](k)
+    code, per = OPS[op], MOVED[op](k) + 4 * (sums or 0)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(k)
     for n in (int(mib * 2**20 / per) - 4_099, int(mib * 2**20 / per) + 4_099):
@@ -178,7 +181,7 @@ def test_both_sides_of_the_line(k, op, mib):
                 want += b
         else:
             want = bufs[root].clone() if op == "broadcast" else torch.cat([b[r * m:(r + 1) * m] for r, b in enumerate(bufs)])
-        sched = bl.blink_make_schedule(trees, code, n, 1 << 18, bl.BLINK_FUSE_TREE)
+        sched = bl.blink_make_schedule(trees, code, n, 1 << 18, fusion)
         if op == "reduce":
             bl.blink_reduce(bufs, n, bl.BLINK_INT32, bl.BLINK_SUM, sched, stream)
         else:
