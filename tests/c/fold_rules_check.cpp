@@ -7,6 +7,7 @@
 //   fold_rules_check counters OP FUSION N CHUNK PARENT...      -> counters per stage instance in an own and a shared block, as it is
 //                                                                 served and where waiting stages are asked for
 //   fold_rules_check sums OP FUSION N CHUNK PARENT...          -> additions whose sum is written on the way
+//   fold_rules_check shares OP N WEIGHT...                    -> the flows of four ranks in so many stars, one per weight, root 0
 //   fold_rules_check call SMALL HAS_DEPS WG_PER_CU KERNEL ALTERNATES   -> a call by that kernel
 #include <cstdio>
 #include <cstdlib>
@@ -30,6 +31,24 @@ int main(int argc, char** argv) {
     if (what == "call") {
         std::printf("%d\n", blink::once_call_serves(number(2) != 0, number(3) != 0, static_cast<int>(number(4)), static_cast<int>(number(5)),
                                                     number(6) != 0));
+        return 0;
+    }
+    if (what == "shares") {
+        blink::Trees trees;
+        trees.k = 4;
+        for (int i = 4; i < argc; ++i) {
+            blink::ParentVec parent;
+            parent.fill(-2);
+            for (int v = 0; v < 4; ++v) parent[v] = v ? 0 : -1;
+            trees.parent.push_back(parent);
+            trees.root.push_back(0);
+            trees.weight.push_back(std::atof(argv[i]));
+        }
+        blink::Schedule s;
+        if (blink::make_schedule(trees, static_cast<blink_op_t>(number(2)), number(3), 1 << 16, BLINK_FUSE_TREE, s) != BLINK_OK) return 1;
+        blink::FoldTables t;
+        blink::fold_tables(s, &t);
+        std::printf("%zu %d\n", t.once.size(), blink::once_serves(s, t.once, 256));
         return 0;
     }
     if (what == "columns" || what == "once" || what == "flows" || what == "counters" || what == "sums") {

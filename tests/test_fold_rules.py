@@ -143,6 +143,20 @@ def test_how_far_a_payload_has_a_workgroup_per_tile(rule, k, op, mib):
             assert rule("once", OPS[op], bl.BLINK_FUSE_TREE, n - n % k, 1 << 16, *star) == (served,), (root, n)
 
 
+# Shares of a payload, flows of the kernel with a workgroup per tile (0: it cannot run them).  tests/test_gpu_once.py runs them.
+ONCE_SHARES = [([1.0], 1), ([1.0, 2.0, 3.0], 3), ([1.0] * 4, 4), ([1.0] * 5, 5), ([1.0 + t for t in range(16)], 16), ([1.0] * 17, 0),
+               ([1.0, 1.0, 1.0, 40.0], 0)]
+
+
+@pytest.mark.parametrize("weights,flows", ONCE_SHARES)
+def test_which_shares_have_a_workgroup_per_tile(rule, weights, flows):
+    assert rule("shares", OPS["allreduce"], 1_000_003, *weights) == (flows, int(flows > 0))
+    # what goes from one rank to the same others is one flow, whatever trees it was split among
+    assert rule("shares", OPS["broadcast"], 1_000_003, *weights) == (1, 1)
+    assert rule("shares", OPS["gather"], 1_000_000, *weights) == (3, 1)
+    assert rule("shares", OPS["allgather"], 1_000_000, *weights) == (4, 1)
+
+
 @pytest.mark.parametrize("k,op,mib,sums", ONCE_SUMS)
 def test_how_far_programs_with_sums_on_the_way_have_one(rule, k, op, mib, sums):
     chain = list(range(-1, k - 1))

@@ -9,7 +9,7 @@ import synth_inputs as si
 from oracle import execute as ox
 from oracle import schedule as osch
 
-from test_fold_rules import MOVED, ONCE_LINES, ONCE_SUMS, OPS
+from test_fold_rules import MOVED, ONCE_LINES, ONCE_SHARES, ONCE_SUMS, OPS
 from test_gpu_fold import REDOPS, _slab, _stream, _tree
 
 pytestmark = pytest.mark.gpu
@@ -28,8 +28,7 @@ def _forest(k, weights):
 
 # equal and unequal shares in the small and in the large arguments, one flow more than these hold, and
 # shares so unequal that the general kernel serves
-@pytest.mark.parametrize("weights", [[1.0], [1.0, 2.0, 3.0], [1.0] * 4, [1.0] * 5, [1.0 + t for t in range(16)], [1.0] * 17,
-                                     [1.0, 1.0, 1.0, 40.0]], ids=lambda w: f"{len(w)} trees, {w[-1]:g}")
+@pytest.mark.parametrize("weights", [w for w, _ in ONCE_SHARES], ids=lambda w: f"{len(w)} trees, {w[-1]:g}")
 @pytest.mark.parametrize("k,op,dtype", [(2, "sum", "fp32"), (3, "max", "fp32"), (4, "sum", "fp32"), (5, "min", "int32"),
                                         (8, "sum", "int32"), (9, "prod", "fp32"), (16, "sum", "fp32")])
 def test_shares(k, op, dtype, weights):
