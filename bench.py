@@ -407,7 +407,7 @@ def main():
                                        "node's partial sum written",
                                "tree": "staged minimum: every rank buffer read once and written once, 8k B/elt "
                                        "(broadcast: the root read once, the others written once, 4k)"}[args.fusion],
-                "kernel": "blink_fold / blink_consume", "avg_kernel_ms": avg_kernel_ms,
+                "kernel": "blink_fold / blink_once / blink_consume", "avg_kernel_ms": avg_kernel_ms,
                 "median_kernel_ms": sorted(kernel_ms)[len(kernel_ms) // 2],
                 "min_kernel_ms": min(kernel_ms)}
     if traffic is not None:   # the counters' bytes over this run's kernel time

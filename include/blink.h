@@ -273,8 +273,9 @@ blink_status_t blink_schedule_get_stages(const blink_schedule_t* s, blink_stage_
  * be faster (blink_schedule_set_kernel), in alternating directions
  * (blink_schedule_set_sweep), it pays no heed to chunk boundaries inside a tree's
  * share, and tiles start on 1 KiB boundaries of the rank buffers where all of these
- * start the same distance past one.  EDGE and NODE programs whose tiles are carried through
- * all stages at once do not follow the list: there the trees take no turns, one tree's share
+ * start the same distance past one.  Payloads that have a workgroup per tile (see
+ * blink_schedule_set_kernel), and EDGE and NODE programs whose tiles are carried through
+ * all stages at once, do not follow the list: there the trees take no turns, one tree's share
  * comes after the other.
  * *n_tickets receives the count; stage and tile (host, caller-allocated, that
  * many entries) may both be null to ask for the count. */
@@ -439,8 +440,9 @@ typedef struct {
     int32_t stage;          /* index (blink_schedule_get_stages order) of the stage that gave up; -1 if none */
     int32_t awaited_stage;  /* the stage it waited for; -1 if none */
     int32_t reserved;
-    uint64_t seen;          /* finished tiles the awaited stage had counted, over all calls; without a stage: the
-                               tickets the counter had dealt out */
+    uint64_t seen;          /* finished tiles the awaited stage (where chunks are handed on in pieces: the awaited
+                               piece of it) had counted, over all calls; without a stage: the tickets the counter
+                               had dealt out */
     uint64_t wanted;        /* the count it had to reach; without a stage: dealt out when the call starts */
     uint64_t call;          /* number of the call on this schedule (1 = first) */
 } blink_progress_t;

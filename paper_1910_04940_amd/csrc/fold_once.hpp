@@ -28,7 +28,8 @@ constexpr int kLdsOfFew = 56 * 1024;
 // The arguments are short: a launch with at most 112 bytes of them takes the host less time (C call on one host, 3 to 7
 // ranks 3.0 us, 8 ranks with 120 bytes 3.7, with 370 or more 3.8 to 4; on another host 2.24 up to 112 bytes, 2.30 beyond).
 // So a buffer's address is one more scalar load away, from a line that is there by then, a flow's program is packed as tightly as
-// that takes for 8 ranks, and there are two variants, for few flows and for many (kOnceMostFlows).
+// that takes for 8 ranks, and there are two variants, for few flows and for many (kOnceMostFlows).  With sums written on the way
+// the few flows take 112 bytes up to 6 ranks, 120 for 7 and 128 for 8.
 constexpr int kOnceFewFlows = 4;
 // Flow f's program: the ranks in the order of consumption, and for each push | folds << 1.  Up to 4 ranks: word f, four
 // bits per rank, the codes from bit 16 on.  Up to 8: word f, three bits per rank, the low byte of the codes from bit 24
@@ -45,7 +46,7 @@ struct OnceParams {
     unsigned word[once_words(N, F) + once_mid_words(N, F, MID)];
     unsigned call;            // see once_call
 };
-static_assert(sizeof(OnceParams<8, kOnceFewFlows, false>) <= 112, "see above");
+static_assert(sizeof(OnceParams<8, kOnceFewFlows, false>) <= 112 && sizeof(OnceParams<6, kOnceFewFlows, true>) <= 112, "see above");
 
 // ALL: the ranks read are written, else one.  SUM, U, MID: see blink_fold.  FEW: at most two workgroups at a time on a CU.
 template <typename T, int N, int F, bool ALL, bool SUM, bool MID, int U, bool FEW>
